@@ -179,44 +179,62 @@ size_t gemm_splitk_bytes(int T, int d_in, int d_out, bool bf16) {
     return S == 0 ? 0 : (size_t)(S + 1) * T * d_out * sizeof(float);   // +1: the expand extension
 }
 
-template <int MI, int NI>
-static hipError_t launch_mfma(GemmArgs a, hipStream_t stream) {
-    constexpr int BM = MI * 64, BN = NI * 64;
-    constexpr int smem = gemm_lds_bytes<MI, NI>();
-    hipError_t e0 = ensure_lds_limit(reinterpret_cast<const void*>(&gemm_mfma_kernel<MI, NI>), smem);
-    if (e0 != hipSuccess) return e0;
-    e0 = ensure_lds_limit(reinterpret_cast<const void*>(&gemm_mfma_dma_kernel<MI, NI>), smem);
-    if (e0 != hipSuccess) return e0;
-    a.tiles_m = ceil_div(a.T, BM);
-    a.tiles_n = ceil_div(a.d_out, BN);
-    // the pipelined kernel needs whole K tiles and byte offsets inside x and W that fit 32 bits
+// The pipelined kernels need whole K tiles, byte offsets inside x, W and the extension operands that fit 32 bits, and
+// for their staged epilogue an output tile (256 rows at most, fp32 at the widest) whose offsets do too.
+static bool dma_ok(const GemmArgs& a, int BM, int BN) {
     const uint64_t widest = (uint64_t)(a.d_in > a.ext_stride ? a.d_in : a.ext_stride) * 2;
-    const bool dma_ok = a.d_in % kGemmBK == 0 && ((uint64_t)a.T + BM) * widest < (1ull << 32) &&
-                        ((uint64_t)a.d_out + BN) * widest < (1ull << 32);
-    if (dma_ok && a.partial != nullptr) {
+    return a.d_in % kGemmBK == 0 && ((uint64_t)a.T + BM) * widest < (1ull << 32) &&
+           ((uint64_t)a.d_out + BN) * widest < (1ull << 32) && (uint64_t)a.d_out * 4 * 256 < (1ull << 32);
+}
+
+template <typename K>
+static hipError_t launch_w3(K kern, const GemmArgs& a, int lds_bytes, int splits, hipStream_t stream) {
+    const hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(kern), lds_bytes);
+    if (e != hipSuccess) return e;
+    kern<<<dim3(a.tiles_m * a.tiles_n, splits), 256, lds_bytes, stream>>>(a);
+    return hipGetLastError();
+}
+
+// One workgroup per (MI*64) x (NI*64) output tile; the output is written, or added to, by the kernel itself.
+template <int MI, int NI>
+static hipError_t launch_tiles(GemmArgs a, hipStream_t stream) {
+    a.tiles_m = ceil_div(a.T, MI * 64);
+    a.tiles_n = ceil_div(a.d_out, NI * 64);
+    if (dma_ok(a, MI * 64, NI * 64)) {
+        constexpr int smem = gemm_w3_lds_bytes<MI, NI>();
+        return a.accumulate ? launch_w3(&gemm_mfma_w3_kernel<MI, NI, kEpiAccumulate>, a, smem, 1, stream)
+                            : launch_w3(&gemm_mfma_w3_kernel<MI, NI, kEpiStore>, a, smem, 1, stream);
+    }
+    constexpr int MF = MI < NI ? MI : NI, smem = gemm_lds_bytes<MF, MF>();   // any d_in, any size
+    const hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(&gemm_mfma_kernel<MF, MF>), smem);
+    if (e != hipSuccess) return e;
+    a.tiles_m = ceil_div(a.T, MF * 64);
+    a.tiles_n = ceil_div(a.d_out, MF * 64);
+    gemm_mfma_kernel<MF, MF><<<a.tiles_m * a.tiles_n, 256, smem, stream>>>(a);
+    return hipGetLastError();
+}
+
+// At most 64 tokens: 64 x 64 tiles, split along K where the caller has room for the fp32 tiles (a.partial).
+static hipError_t launch_skinny(GemmArgs a, hipStream_t stream) {
+    constexpr int smem = gemm_lds_bytes<1, 1>();
+    hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(&gemm_mfma_kernel<1, 1>), smem);
+    if (e == hipSuccess) e = ensure_lds_limit(reinterpret_cast<const void*>(&gemm_mfma_dma_kernel<1, 1>), smem);
+    if (e != hipSuccess) return e;
+    a.tiles_m = ceil_div(a.T, 64);
+    a.tiles_n = ceil_div(a.d_out, 64);
+    const bool dma = dma_ok(a, 64, 64);
+    if (dma && a.partial != nullptr) {
         const int nsplit = a.splits + (a.ext_k > 0 ? 1 : 0);
-        gemm_mfma_dma_kernel<MI, NI><<<dim3(a.tiles_m * a.tiles_n, nsplit), 256, smem, stream>>>(a);
-        hipError_t e = hipGetLastError();
+        gemm_mfma_dma_kernel<1, 1><<<dim3(a.tiles_m * a.tiles_n, nsplit), 256, smem, stream>>>(a);
+        e = hipGetLastError();
         if (e != hipSuccess) return e;
         const size_t n8 = (size_t)a.T * a.d_out / 8;
         gemm_splitk_reduce_kernel<<<(unsigned)((n8 + 255) / 256), 256, 0, stream>>>(a.partial, nsplit, a.T, a.d_out,
                                                                                    a.out, a.accumulate);
-    } else if (dma_ok && ((MI == 4 && NI == 4) || (MI == 2 && NI == 2))) {
-        constexpr int M3 = MI == 4 ? 4 : 2;   // the instantiations of the three-deep-ring kernel that exist
-        // the epilogue form is a compile-time parameter of this kernel: plain store (the layer's GEMM) or accumulate
-        auto go = [&](auto kern) -> hipError_t {
-            const hipError_t e1 = ensure_lds_limit(reinterpret_cast<const void*>(kern), gemm_w3_lds_bytes<M3, M3>());
-            if (e1 != hipSuccess) return e1;
-            kern<<<a.tiles_m * a.tiles_n, 256, gemm_w3_lds_bytes<M3, M3>(), stream>>>(a);
-            return hipSuccess;
-        };
-        const hipError_t e1 = a.accumulate ? go(&gemm_mfma_w3_kernel<M3, M3, kEpiAccumulate>)
-                                           : go(&gemm_mfma_w3_kernel<M3, M3, kEpiStore>);
-        if (e1 != hipSuccess) return e1;
-    } else if (dma_ok) {
-        gemm_mfma_dma_kernel<MI, NI><<<a.tiles_m * a.tiles_n, 256, smem, stream>>>(a);
+    } else if (dma) {
+        gemm_mfma_dma_kernel<1, 1><<<a.tiles_m * a.tiles_n, 256, smem, stream>>>(a);
     } else {
-        gemm_mfma_kernel<MI, NI><<<a.tiles_m * a.tiles_n, 256, smem, stream>>>(a);
+        gemm_mfma_kernel<1, 1><<<a.tiles_m * a.tiles_n, 256, smem, stream>>>(a);
     }
     return hipGetLastError();
 }
@@ -233,7 +251,7 @@ static bool dense_small_tiles(int T) { return T <= 4096; }
 bool gemm_dense_splitk_ok(int T, int d_in, int rows) {
     const uint64_t widest = (uint64_t)d_in * 2;
     return d_in % kGemmBK == 0 && rows % 8 == 0 && ((uint64_t)T + 2 * 64) * widest < (1ull << 32) &&
-           ((uint64_t)rows + 5 * 64) * widest < (1ull << 32);
+           ((uint64_t)rows + 5 * 64) * widest < (1ull << 32) && (uint64_t)rows * 4 * 256 < (1ull << 32);
 }
 
 int gemm_dense_splits(int T, int d_in, int rows) {
@@ -247,14 +265,9 @@ int gemm_dense_splits(int T, int d_in, int rows) {
 
 template <int MI, int NI>
 static hipError_t launch_dense(GemmArgs a, hipStream_t stream) {   // three-deep W ring, fp32 split-K tiles
-    constexpr int smem = gemm_w3_lds_bytes<MI, NI>();
-    auto kern = &gemm_mfma_w3_kernel<MI, NI, kEpiPartial>;
-    const hipError_t ea = ensure_lds_limit(reinterpret_cast<const void*>(kern), smem);
-    if (ea != hipSuccess) return ea;
     a.tiles_m = ceil_div(a.T, MI * 64);
     a.tiles_n = ceil_div(a.d_out, NI * 64);
-    kern<<<dim3(a.tiles_m * a.tiles_n, a.splits), 256, smem, stream>>>(a);
-    return hipGetLastError();
+    return launch_w3(&gemm_mfma_w3_kernel<MI, NI, kEpiPartial>, a, gemm_w3_lds_bytes<MI, NI>(), a.splits, stream);
 }
 
 hipError_t launch_gemm_dense_splitk(const void* x, const void* Wcat, int T, int d_in, int rows, float* partial,
@@ -298,19 +311,11 @@ hipError_t launch_gemm_dense_splitk_multi(const void* x, const DenseOperand* ops
     a.tiles_n = tile0;
     if (gemm_multi_big_rows(T)) {
         if (((uint64_t)T + 256) * ((uint64_t)d_in * 2) >= (1ull << 32)) return hipErrorInvalidValue;
-        constexpr int smem = gemm_w3_lds_bytes<4, 2>();
-        const hipError_t ea = ensure_lds_limit(reinterpret_cast<const void*>(&gemm_mfma_w3_kernel<4, 2, kEpiPartial>), smem);
-        if (ea != hipSuccess) return ea;
         a.tiles_m = ceil_div(T, 256);
-        gemm_mfma_w3_kernel<4, 2, kEpiPartial><<<dim3(a.tiles_m * a.tiles_n, S), 256, smem, stream>>>(a);
-        return hipGetLastError();
+        return launch_w3(&gemm_mfma_w3_kernel<4, 2, kEpiPartial>, a, gemm_w3_lds_bytes<4, 2>(), S, stream);
     }
-    constexpr int smem = gemm_w3_lds_bytes<2, 2>();
-    const hipError_t ea = ensure_lds_limit(reinterpret_cast<const void*>(&gemm_mfma_w3_kernel<2, 2, kEpiPartial>), smem);
-    if (ea != hipSuccess) return ea;
     a.tiles_m = ceil_div(T, 128);
-    gemm_mfma_w3_kernel<2, 2, kEpiPartial><<<dim3(a.tiles_m * a.tiles_n, S), 256, smem, stream>>>(a);
-    return hipGetLastError();
+    return launch_w3(&gemm_mfma_w3_kernel<2, 2, kEpiPartial>, a, gemm_w3_lds_bytes<2, 2>(), S, stream);
 }
 
 // Decode in two launches: (1) the main K splits of x * W^T with the rows of Wcat as extra column
@@ -373,21 +378,16 @@ hipError_t launch_gemm_decode_finish(const DecodeMember* mem, int G, int S, int 
 
 bool gemm_fuses_expand(bool bf16) { return bf16; }
 
-template <int MI, int NI>
-static hipError_t init_tile_kernels() {
-    hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(&gemm_mfma_kernel<MI, NI>), gemm_lds_bytes<MI, NI>());
-    if (e != hipSuccess) return e;
-    return ensure_lds_limit(reinterpret_cast<const void*>(&gemm_mfma_dma_kernel<MI, NI>), gemm_lds_bytes<MI, NI>());
-}
-
 // every kernel of this file that a launcher above may start with more than the default dynamic LDS
 hipError_t gemm_init_kernels() {
-    hipError_t e = init_tile_kernels<4, 4>();
-    if (e == hipSuccess) e = init_tile_kernels<2, 2>();
-    if (e == hipSuccess) e = init_tile_kernels<1, 1>();
+    hipError_t e = hipSuccess;
     auto lim = [&](auto kern, int bytes) {
         if (e == hipSuccess) e = ensure_lds_limit(reinterpret_cast<const void*>(kern), bytes);
     };
+    lim(&gemm_mfma_kernel<4, 4>, gemm_lds_bytes<4, 4>());
+    lim(&gemm_mfma_kernel<2, 2>, gemm_lds_bytes<2, 2>());
+    lim(&gemm_mfma_kernel<1, 1>, gemm_lds_bytes<1, 1>());
+    lim(&gemm_mfma_dma_kernel<1, 1>, gemm_lds_bytes<1, 1>());
     lim(&gemm_mfma_w3_kernel<4, 4, kEpiStore>, gemm_w3_lds_bytes<4, 4>());
     lim(&gemm_mfma_w3_kernel<4, 4, kEpiAccumulate>, gemm_w3_lds_bytes<4, 4>());
     lim(&gemm_mfma_w3_kernel<4, 2, kEpiStore>, gemm_w3_lds_bytes<4, 2>());
@@ -414,7 +414,7 @@ hipError_t launch_gemm(const void* x, const void* W, int T, int d_in, int d_out,
             a.partial = splitk_ws;
             a.splits = S;
             a.tiles_per_split = ceil_div(d_in / kGemmBK, S);
-            return launch_mfma<1, 1>(a, stream);
+            return launch_skinny(a, stream);
         }
         const int64_t big_tiles = (int64_t)ceil_div(T, 256) * ceil_div(d_out, 256);
         // 256 x 256 tiles once they fill most of the 256 CUs; below that 128 x 128 tiles keep more CUs busy
@@ -423,28 +423,16 @@ hipError_t launch_gemm(const void* x, const void* W, int T, int d_in, int d_out,
         // 256 x 256 tiles costs more than the smaller tiles' lower efficiency (4096 -> 4096: T = 4608, 288 tiles, 174
         // us against 155 with 128 x 128 tiles; T = 5120 176 against 163; 336 tiles and more: the big tiles win again,
         // and with two rounds or more they always do: 544 tiles 275 against 279)
-        if (T > 128 && big_tiles >= 160 && !(big_tiles > 256 && big_tiles <= 328)) return launch_mfma<4, 4>(a, stream);
+        if (T > 128 && big_tiles >= 160 && !(big_tiles > 256 && big_tiles <= 328)) return launch_tiles<4, 4>(a, stream);
         // between the two: 256 x 128 tiles where 160 to 256 of them cover the output, one per CU (a wavefront's
         // 128 x 64 piece needs 0.75 fragment reads per MFMA against 1.0 at 128 x 128).  Measured against 128 x 128
         // tiles: T = 1280 at 4096 -> 4096 (160 tiles) 50.2 against 55.2 us, T = 2048 (256 tiles) 62.3 against 66.0,
         // T = 512 at 4096 -> 14336 59.2 against 63.6, T = 2048 at 14336 -> 4096 199 against 219; with 128 tiles
         // (T = 1024) 47.0 against 39.1, so not below 160
         const int64_t mid_tiles = (int64_t)ceil_div(T, 256) * ceil_div(d_out, 128);
-        const uint64_t widest = (uint64_t)(d_in > ext_stride ? d_in : ext_stride) * 2;
-        if (T > 128 && mid_tiles >= 160 && mid_tiles <= 256 && d_in % kGemmBK == 0 &&
-            ((uint64_t)T + 256) * widest < (1ull << 32) && ((uint64_t)d_out + 128) * widest < (1ull << 32)) {
-            a.tiles_m = ceil_div(T, 256);
-            a.tiles_n = ceil_div(d_out, 128);
-            auto go = [&](auto kern) -> hipError_t {
-                const hipError_t e1 = ensure_lds_limit(reinterpret_cast<const void*>(kern), gemm_w3_lds_bytes<4, 2>());
-                if (e1 != hipSuccess) return e1;
-                kern<<<a.tiles_m * a.tiles_n, 256, gemm_w3_lds_bytes<4, 2>(), stream>>>(a);
-                return hipGetLastError();
-            };
-            return a.accumulate ? go(&gemm_mfma_w3_kernel<4, 2, kEpiAccumulate>) : go(&gemm_mfma_w3_kernel<4, 2, kEpiStore>);
-        }
-        if (T > 64) return launch_mfma<2, 2>(a, stream);
-        return launch_mfma<1, 1>(a, stream);
+        if (T > 128 && mid_tiles >= 160 && mid_tiles <= 256 && dma_ok(a, 256, 128)) return launch_tiles<4, 2>(a, stream);
+        if (T > 64) return launch_tiles<2, 2>(a, stream);
+        return launch_skinny(a, stream);
     }
     dim3 grid(ceil_div(d_out, 64), ceil_div(T, 64));
     gemm_fma_kernel<float><<<grid, 256, 0, stream>>>((const float*)x, (const float*)W, T, d_in, d_out,

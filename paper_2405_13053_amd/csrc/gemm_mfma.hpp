@@ -358,10 +358,8 @@ __device__ __forceinline__ void tile_of_workgroup(int wg, int tiles_m, int tiles
     tile_n = in_group / gm;
 }
 
-// Epilogue shared by the pipelined kernels: store a workgroup's accumulators.
-// EPI fixes at compile time which of the three forms a kernel carries (kEpiAny: decided at run time).  With one form
-// the accumulators leave their registers block row by block row as they are converted; with all three behind
-// run-time branches the compiler first copies every accumulator out (and spills) before it branches.
+// Epilogue of the two-slot kernel: store a workgroup's 32 x 32 accumulators.
+// EPI fixes at compile time which of the three forms a kernel carries (kEpiAny: decided at run time).
 constexpr int kEpiAny = -1, kEpiStore = 0, kEpiAccumulate = 1, kEpiPartial = 2;
 template <int MI, int NI, int EPI = kEpiAny>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[MI][NI], unsigned char* smem_raw, int m0,
@@ -633,20 +631,27 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(const GemmArgs a_in)
 // ------------------------------------------------------------------------------------------
 // The same pipeline with a three-deep ring for the W operand (2 x-slots + 3 W-slots: the whole 160 KB of
 // LDS for the 256 x 256 tile).  A global->LDS load occupies the CU's address unit for ~16 cycles, so the
-// four wavefronts can sustain one load per two MFMAs each; issued as one per MFMA (all pieces of a tile in
+// four wavefronts can sustain one load per two 32-cycle MFMAs each; issued in one burst (all pieces of a tile in
 // the last phase, the only time a two-slot ring has a free slot) they stall the MFMAs queued behind them.
-// Here tile it+2's W pieces go out during the first three phases of tile it, into the W-slot that no
+// Here tile it+2's W pieces go out during the first k-step of tile it, into the W-slot that no
 // wavefront has read since the previous barrier, and only its x pieces wait for the barrier, spread over
-// the MFMAs of the last phase.  Loads complete in order, so the barrier of tile it waits for everything
+// the MFMAs of the second.  Loads complete in order, so the barrier of tile it waits for everything
 // but the newest W pieces (vmcnt = W pieces per wavefront).
+//
+// The contraction runs on v_mfma_f32_16x16x32_bf16: on the layer's data the chip is power-limited, and per multiply
+// this shape reads and writes half as many accumulator registers as 32x32x16.  Measured against the same kernel with
+// 32x32x16 (256 x 256 tiles, extension of 256, back to back): 95.1 against 104-106 us at 4096 x 4096 x 4096, 666
+// against 725 us at 8192 x 4096 x 14336; inside the layer 101.2 against 111.2 us.  The instruction is written in assembly with the accumulator tied in an AGPR: from the builtin
+// the compiler lets the result land in other registers than the accumulator and moves about 100 of them per K tile.
+// The compiler does not know that the statement is an MFMA, so (1) the source states the order of MFMAs, LDS reads
+// and loads itself, group by group between scheduling barriers; (2) nothing but MFMAs touches an accumulator inside
+// the K loop, and mfma_drain() stands between the last MFMA and the first read of a result.
 // ------------------------------------------------------------------------------------------
 template <int MI, int NI>
 __host__ __device__ constexpr int gemm_w3_lds_bytes() {
     constexpr int ring = (2 * MI * 64 + 3 * NI * 64) * kGemmBK * 2;
-    constexpr int stage = 4 * (MI * 32) * gemm_epilogue_stride<NI>();
-    constexpr int pstage = 4 * 32 * gemm_partial_stride<NI>();
-    constexpr int m = ring > stage ? ring : stage;
-    return m > pstage ? m : pstage;
+    constexpr int stage = 4 * 32 * gemm_partial_stride<NI>();   // the widest epilogue: 32 fp32 rows per wavefront
+    return ring > stage ? ring : stage;
 }
 
 // how many of NPC pieces go out right after the i-th of NR fragment reads (evenly spread, the last read included)
@@ -654,29 +659,144 @@ __host__ __device__ constexpr int pieces_after_read(int i, int NPC, int NR) {
     return (i + 1) * NPC / NR - i * NPC / NR;
 }
 
-template <int N>
-__device__ __forceinline__ void sgb_vmem() {
-    if constexpr (N > 0) METEORA_SGB(0x020, N);
-}
-template <int N>
-__device__ __forceinline__ void sgb_mfma() {
-    if constexpr (N > 0) METEORA_SGB(0x008, N);
+// Epilogue of the three-deep-ring kernel.  EPI fixes at compile time which form a kernel carries: with one form the
+// accumulators leave their registers as they are converted (with all three behind run-time branches the compiler
+// copies every accumulator out, and spills, before it branches).  A lane holds 4 consecutive output columns of token
+// row l & 15 per block; the tile is staged in this wavefront's own LDS region, RS rows at a time, and leaves as
+// 16-byte pieces that cover whole rows (the direct 8-byte stores touch 16 rows per instruction; with accumulate the
+// old output comes in by the same pieces: 24.6 against 36.4 us for 3000 x 5120 outputs and K = 224).
+template <int MB, int NB, int EPI>
+__device__ __forceinline__ void gemm_epilogue16(const GemmArgs& a, f32x4 (&acc)[MB][NB], unsigned char* smem_raw, int m0,
+                                                int n0, int wm, int wn, int wave, int lane) {
+    constexpr bool F32 = EPI == kEpiPartial;
+    constexpr int RS = 32;                                     // staged rows
+    constexpr int EB = F32 ? 4 : 2;                            // bytes per staged value
+    constexpr int EST = NB * 16 * EB + 16;                     // bytes per staged row
+    constexpr int PPR = NB * 16 * EB / 16;                     // 16-byte pieces per staged row
+    constexpr int NP = RS * PPR / 64;                          // pieces per lane
+    static_assert(RS * PPR % 64 == 0, "whole wavefronts of pieces");
+    const int l15 = lane & 15, kq = lane >> 4;
+    __syncthreads();                                           // every wavefront is done with the operand tiles
+    unsigned char* ep = smem_raw + wave * RS * EST;            // this wavefront's own; its LDS accesses stay in order
+    // The workgroup's rows of the output as a buffer: pieces past its last row or column are dropped by the hardware.
+    // The whole offset of a piece is in the per-lane operand, which the bounds check covers.
+    constexpr int BM = MB * 32;
+    void* base = F32 ? (void*)(a.partial + ((size_t)blockIdx.y * a.T + m0) * a.d_out) : (void*)(a.out + (size_t)m0 * a.d_out);
+    const uint32_t row_bytes = (uint32_t)a.d_out * EB;
+    const __amdgpu_buffer_rsrc_t out =
+        __builtin_amdgcn_make_buffer_rsrc(base, 0, (uint32_t)min(a.T - m0, BM) * row_bytes, 0x00020000);
+    const uint32_t kOutside = 0xffffffffu;
+    uint32_t voff[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        const int p = i * 64 + lane, col = n0 + wn + (p % PPR) * (16 / EB);   // d_out % 8 == 0: all in or all out
+        voff[i] = col < a.d_out ? (uint32_t)(wm + p / PPR) * row_bytes + (uint32_t)col * EB : kOutside;
+    }
+    auto offset = [&](int i, int mb) {
+        return voff[i] == kOutside ? kOutside : voff[i] + (uint32_t)(mb * 16) * row_bytes;
+    };
+    auto sync = [] {   // orders this wavefront's own LDS accesses
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+#pragma unroll
+    for (int mb = 0; mb < MB; mb += RS / 16) {
+        if constexpr (EPI == kEpiAccumulate) {   // the old output comes in the way the new one leaves
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                const int p = i * 64 + lane;
+                *reinterpret_cast<u32x4*>(ep + (p / PPR) * EST + (p % PPR) * 16) =
+                    __builtin_amdgcn_raw_buffer_load_b128(out, offset(i, mb), 0, 0);
+            }
+            sync();
+        }
+#pragma unroll
+        for (int h = 0; h < RS / 16; ++h)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                f32x4 v = acc[mb + h][nb];
+                unsigned char* dst = ep + (h * 16 + l15) * EST + (nb * 16 + kq * 4) * EB;
+                if constexpr (F32) {
+                    *reinterpret_cast<f32x4*>(dst) = v;
+                } else {
+                    if constexpr (EPI == kEpiAccumulate) {
+                        const uint2 old = *reinterpret_cast<const uint2*>(dst);
+                        v[0] += bf16_bits_to_float(old.x & 0xffffu);
+                        v[1] += bf16_bits_to_float(old.x >> 16);
+                        v[2] += bf16_bits_to_float(old.y & 0xffffu);
+                        v[3] += bf16_bits_to_float(old.y >> 16);
+                    }
+                    uint2 pk;
+                    pk.x = pack_bf16x2(v[0], v[1]);
+                    pk.y = pack_bf16x2(v[2], v[3]);
+                    *reinterpret_cast<uint2*>(dst) = pk;
+                }
+            }
+        sync();
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const int p = i * 64 + lane;
+            const u32x4 v = *reinterpret_cast<const u32x4*>(ep + (p / PPR) * EST + (p % PPR) * 16);
+            __builtin_amdgcn_raw_buffer_store_b128(v, out, offset(i, mb), 0, 0);
+        }
+        sync();
+        __builtin_amdgcn_sched_barrier(0);   // accumulators leave their registers 32 rows at a time
+    }
 }
 
-// Order of one phase: per fragment read, one MFMA, the read, MPR-1 more MFMAs, then the read's share of NPC loads.
-template <int MPR, int NPC, int NR, int... I>
-__device__ __forceinline__ void sgb_reads(std::integer_sequence<int, I...>) {
-    ((METEORA_SGB(0x008, 1), METEORA_SGB(0x100, 1), sgb_mfma<MPR - 1>(), sgb_vmem<pieces_after_read(I, NPC, NR)>()), ...);
+// Fragments of one k-step of 32 for a wavefront's MB x NB blocks of 16 x 16: lane l holds row (l & 15), k chunk l >> 4.
+template <int MB, int NB>
+struct Frags16 {
+    bf16x8 x[MB];
+    bf16x8 w[NB];
+};
+
+__device__ __forceinline__ void mfma16(f32x4& acc, const bf16x8& w, const bf16x8& x) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(x));
+}
+// The wait states between an MFMA and another instruction's read of its result (the compiler inserts them for the
+// builtin only; 16x16x32 is 8 passes: at most 11 are required).
+__device__ __forceinline__ void mfma_drain() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int MI, int NI, int EPI = kEpiAny>
+// Order of the MB x NB products of a k-step: 2 x 2 micro-blocks, each a cycle, walked as a snake, so that one operand
+// register changes from one MFMA to the next (0.5% less time than sweeping whole rows).
+template <int NB>
+__host__ __device__ constexpr int order_mi(int k) { return (k / (2 * NB)) * 2 + ((k >> 1) & 1); }
+template <int NB>
+__host__ __device__ constexpr int order_ni(int k) {
+    const int col = (k >> 2) % (NB / 2), in = k & 3;
+    return (((k / (2 * NB)) & 1) ? NB / 2 - 1 - col : col) * 2 + ((in == 1 || in == 2) ? 1 : 0);
+}
+
+// Fragment number i in the order the MFMAs need them: x 0, x 1, every W fragment, the other x fragments.
+template <int MB, int NB>
+__device__ __forceinline__ void load_frag16(Frags16<MB, NB>& f, const bf16_t* xs, const bf16_t* wsm, int wm, int wn, int l15,
+                                            int kq, int ks, int i) {
+    if (i >= 2 && i < 2 + NB) {
+        const int n = i - 2, row = wn + n * 16 + l15;
+        f.w[n] = *reinterpret_cast<const bf16x8*>(wsm + row * kGemmBK + swz(row, ks * 4 + kq) * 8);
+    } else {
+        const int m = i < 2 ? i : i - NB, row = wm + m * 16 + l15;
+        f.x[m] = *reinterpret_cast<const bf16x8*>(xs + row * kGemmBK + swz(row, ks * 4 + kq) * 8);
+    }
+}
+
+template <int MI, int NI, int EPI>
 __global__ __launch_bounds__(256) void gemm_mfma_w3_kernel(const GemmArgs a_in) {
     GemmArgs a = a_in;
     constexpr int BM = MI * 64, BN = NI * 64;
+    constexpr int MB = MI * 2, NB = NI * 2;     // 16 x 16 blocks of a wavefront
     constexpr int PX = BM / 32, PW = BN / 32;   // pieces per wavefront per tile
-    constexpr int NR = MI + NI;                 // fragment reads per k-step
-    static_assert(MI * NI >= NR, "a phase needs one MFMA per fragment read");
-    constexpr int PW1 = (PW + 2) / 3, PW2 = (PW - PW1 + 1) / 2, PW3 = PW - PW1 - PW2;   // W pieces per phase
+    constexpr int NR = MB + NB, NM = MB * NB;   // fragment reads and MFMAs per k-step
+    // MFMAs per fragment read: k-step 0's reads (of k-step 1) end early, since the barrier waits for them; k-step 1's
+    // (of the next tile) are spread over all of it
+    constexpr int RA = NM * 3 / 4 / NR > 0 ? NM * 3 / 4 / NR : 1, RB = NM / NR;
+    static_assert(RB >= 1, "a k-step needs one MFMA per fragment read");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     bf16_t* smem = reinterpret_cast<bf16_t*>(smem_raw);
     constexpr int kXElems = BM * kGemmBK, kWElems = BN * kGemmBK;
@@ -684,7 +804,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_w3_kernel(const GemmArgs a_in) 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = (wave >> 1) * (BM / 2), wn = (wave & 1) * (BN / 2);
-    const int lrow = lane & 31, khalf = lane >> 5;
+    const int l15 = lane & 15, kq = lane >> 4;
     int tile_m, tile_n;
     tile_of_workgroup(blockIdx.x, a.tiles_m, a.tiles_n, tile_m, tile_n);
     const int m0 = tile_m * BM;
@@ -699,13 +819,11 @@ __global__ __launch_bounds__(256) void gemm_mfma_w3_kernel(const GemmArgs a_in) 
         a.partial = a_in.seg[e].partial;
     }
 
-    f32x16 acc[MI][NI];
+    f32x4 acc[MB][NB];
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
+    for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.f;
+        for (int ni = 0; ni < NB; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // this workgroup's share of the contraction: main K tiles [kt0, kt0 + nk_main) and/or the extension
     int kt0 = 0, nk_main = a.d_in / kGemmBK;
@@ -752,27 +870,33 @@ __global__ __launch_bounds__(256) void gemm_mfma_w3_kernel(const GemmArgs a_in) 
         }
     };
 
-    Frags<MI, NI> f0, f1;
+    Frags16<MB, NB> f0, f1;
     if (nk > 1) {
         request_tile(0);
         request_tile(1);
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PX + PW) : "memory");
         __syncthreads();
-        load_frags<MI, NI>(f0, xslot(0), wslot(0), wm, wn, lrow, khalf, 0);
     } else if (nk > 0) {
         request_tile(0);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        load_frags<MI, NI>(f0, xslot(0), wslot(0), wm, wn, lrow, khalf, 0);
+    }
+    if (nk > 0) {
+#pragma unroll
+        for (int i = 0; i < NR; ++i) load_frag16<MB, NB>(f0, xslot(0), wslot(0), wm, wn, l15, kq, 0, i);
     }
 
+    // MFMAs [K0, K1) of a k-step
+    auto mfmas = [&](const Frags16<MB, NB>& f, int k0, int k1) {
+#pragma unroll
+        for (int k = k0; k < k1; ++k)
+            mfma16(acc[order_mi<NB>(k)][order_ni<NB>(k)], f.w[order_ni<NB>(k)], f.x[order_mi<NB>(k)]);
+    };
     // REQ: 0 = tile it+2 is a main tile, 1 = it is an extension tile, 2 = there is none (last two tiles)
     // PH: it % 6 when it is known at compile time (the unrolled main loop: every slot address is then a
     // constant and no address arithmetic sits between two tiles), -1 otherwise
-    // first: the tile's first k-step starts the accumulators (tile 0 of the unrolled form)
-    auto tile_step = [&](int it, auto req, auto ph, auto first) {
+    auto tile_step = [&](int it, auto req, auto ph) {
         constexpr int REQ = decltype(req)::value, PH = decltype(ph)::value;
-        constexpr bool FIRST = decltype(first)::value;
         using IsExt = std::integral_constant<bool, REQ == 1>;
         auto xsl = [&](int d) {   // x-slot / W-slot of tile it + d
             if constexpr (PH >= 0) return smem + ((PH + d) & 1) * kXElems;
@@ -786,29 +910,20 @@ __global__ __launch_bounds__(256) void gemm_mfma_w3_kernel(const GemmArgs a_in) 
         const bf16_t* ws = wsl(0);
         bf16_t* const xreq = xsl(2);
         bf16_t* const wreq = wsl(2);
-        // phases 1-3: MI*NI MFMAs of k-step ks-1, the fragment reads of k-step ks one per MFMA from the start of
-        // the phase, and W pieces [P0, P0 + NPC) of tile it+2 spread between the reads (program order = the
-        // order the LDS accesses keep)
-        auto phase = [&](Frags<MI, NI>& fnext, const Frags<MI, NI>& fcur, int ks, auto p0, auto npc, auto start) {
-            constexpr int P0 = decltype(p0)::value, NPC = REQ < 2 ? decltype(npc)::value : 0;
-            int issued = 0;
+        // k-step 0: its MFMAs, the fragment reads of k-step 1 and the W pieces of tile it+2
+        int issued = 0;
 #pragma unroll
-            for (int i = 0; i < NR; ++i) {
-                load_frag1<MI, NI>(fnext, xs, ws, wm, wn, lrow, khalf, ks, i);
-                if constexpr (NPC > 0) {
+        for (int i = 0; i < NR; ++i) {
+            mfmas(f0, i * RA, (i + 1) * RA);
+            load_frag16<MB, NB>(f1, xs, ws, wm, wn, l15, kq, 1, i);
+            if constexpr (REQ < 2) {
 #pragma unroll
-                    for (int c = 0; c < pieces_after_read(i, NPC, NR); ++c) request_w(wreq, it + 2, P0 + issued++, IsExt{});
-                }
+                for (int c = 0; c < pieces_after_read(i, PW, NR); ++c) request_w(wreq, it + 2, issued++, IsExt{});
             }
-            if constexpr (decltype(start)::value) mma_frags_first<MI, NI>(acc, fcur);
-            else mma_frags<MI, NI>(acc, fcur);
-            sgb_reads<1, NPC, NR>(std::make_integer_sequence<int, NR>{});
-            sgb_mfma<MI * NI - NR>();
             __builtin_amdgcn_sched_barrier(0);
-        };
-        phase(f1, f0, 1, std::integral_constant<int, 0>{}, std::integral_constant<int, PW1>{}, std::bool_constant<FIRST>{});
-        phase(f0, f1, 2, std::integral_constant<int, PW1>{}, std::integral_constant<int, PW2>{}, std::false_type{});
-        phase(f1, f0, 3, std::integral_constant<int, PW1 + PW2>{}, std::integral_constant<int, PW3>{}, std::false_type{});
+        }
+        mfmas(f0, NR * RA, NM);
+        __builtin_amdgcn_sched_barrier(0);
         // tile it+1 (x requested one tile ago, W before that) must have landed, and every wavefront's reads of
         // tile it must be complete; the W pieces of tile it+2 just issued may still be in flight
         // (a plain s_barrier: __syncthreads() carries a fence, for which the compiler waits for every load)
@@ -818,37 +933,35 @@ __global__ __launch_bounds__(256) void gemm_mfma_w3_kernel(const GemmArgs a_in) 
             __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
         }
+        // k-step 1: its MFMAs, the first fragments of tile it+1 and the x pieces of tile it+2 into the x-slot just
+        // drained
         const bf16_t* xn = xsl(1);
         const bf16_t* wnx = wsl(1);
         if constexpr (REQ < 2) {
-            // first fragments of tile it+1, and the x pieces of tile it+2 into the x-slot just drained, spread
-            // over the phase: MPR MFMAs per read, a read's pieces after them
-            constexpr int MPR = MI * NI / NR;
-            int issued = 0;
-            // read order: the next phase's first MFMAs use x block 0 with every W block, then x blocks 1..
+            issued = 0;
 #pragma unroll
             for (int i = 0; i < NR; ++i) {
-                const int fi = i == 0 ? 0 : (i <= NI ? MI + i - 1 : i - NI);
-                load_frag1<MI, NI>(f0, xn, wnx, wm, wn, lrow, khalf, 0, fi);
+                mfmas(f1, i * RB, (i + 1) * RB);
+                load_frag16<MB, NB>(f0, xn, wnx, wm, wn, l15, kq, 0, i);
 #pragma unroll
                 for (int c = 0; c < pieces_after_read(i, PX, NR); ++c) request_x(xreq, it + 2, issued++, IsExt{});
+                __builtin_amdgcn_sched_barrier(0);
             }
-            mma_frags<MI, NI>(acc, f1);
-            sgb_reads<MPR, PX, NR>(std::make_integer_sequence<int, NR>{});
-            sgb_mfma<MI * NI - NR * MPR>();
+            mfmas(f1, NR * RB, NM);
         } else {
-            if (it + 1 < nk) load_frags<MI, NI>(f0, xn, wnx, wm, wn, lrow, khalf, 0);
-            mma_frags<MI, NI>(acc, f1);
-            sgb_reads<1, 0, NR>(std::make_integer_sequence<int, NR>{});
-            sgb_mfma<MI * NI - NR>();
+            if (it + 1 < nk) {   // reads only: MFMAs in both arms of a branch make the compiler copy accumulators
+#pragma unroll
+                for (int i = 0; i < NR; ++i) load_frag16<MB, NB>(f0, xn, wnx, wm, wn, l15, kq, 0, i);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            mfmas(f1, 0, NM);
         }
         __builtin_amdgcn_sched_barrier(0);
     };
     using Req0 = std::integral_constant<int, 0>;
     using Rt = std::integral_constant<int, -1>;
-    using No = std::false_type;
-    // the last extension tile may hold data in its first two k-steps only (28 adapters of rank 8: 224 of 256 columns;
-    // the rest is zero padding): those two k-steps are all it gets
+    // the last extension tile may hold data in its first k-step only (28 adapters of rank 8: 224 of 256 columns;
+    // the rest is zero padding): that k-step is all it gets
     const bool half_last = nk_ext > 0 && ((a.ext_k - 1) % kGemmBK) < kGemmBK / 2;
     // A wavefront whose whole piece of the tile lies past the matrix (ragged last tile row or column: the third
     // 128-column tile of the 320 routing products is half empty) moves its share of the operand tiles and keeps the
@@ -877,30 +990,24 @@ __global__ __launch_bounds__(256) void gemm_mfma_w3_kernel(const GemmArgs a_in) 
         }
         it = nk;
     }
-    if constexpr (MI == 4 && NI == 4) {   // six tiles per trip: the period of the 2-slot and 3-slot rings
-        if (nk_main > 8 && !idle) {
-            // tile 0 on its own: its first k-step starts the accumulators; the trips then begin at tile 1
-            tile_step(0, Req0{}, std::integral_constant<int, 0>{}, std::true_type{});
-            for (it = 1; it + 7 < nk_main; it += 6) {
-                tile_step(it, Req0{}, std::integral_constant<int, 1>{}, No{});
-                tile_step(it + 1, Req0{}, std::integral_constant<int, 2>{}, No{});
-                tile_step(it + 2, Req0{}, std::integral_constant<int, 3>{}, No{});
-                tile_step(it + 3, Req0{}, std::integral_constant<int, 4>{}, No{});
-                tile_step(it + 4, Req0{}, std::integral_constant<int, 5>{}, No{});
-                tile_step(it + 5, Req0{}, std::integral_constant<int, 0>{}, No{});
-            }
+    // six tiles per trip in the 256 x 256 kernel: the period of the 2-slot and 3-slot rings
+    if constexpr (MI == 4 && NI == 4) {
+        for (; it + 7 < nk_main; it += 6) {
+            tile_step(it, Req0{}, std::integral_constant<int, 0>{});
+            tile_step(it + 1, Req0{}, std::integral_constant<int, 1>{});
+            tile_step(it + 2, Req0{}, std::integral_constant<int, 2>{});
+            tile_step(it + 3, Req0{}, std::integral_constant<int, 3>{});
+            tile_step(it + 4, Req0{}, std::integral_constant<int, 4>{});
+            tile_step(it + 5, Req0{}, std::integral_constant<int, 5>{});
         }
     }
-    for (; it + 2 < nk_main; ++it) tile_step(it, Req0{}, Rt{}, No{});
-    for (; it + 2 < nk; ++it) tile_step(it, std::integral_constant<int, 1>{}, Rt{}, No{});
-    for (; it < nk - (half_last ? 1 : 0); ++it) tile_step(it, std::integral_constant<int, 2>{}, Rt{}, No{});
-    if (half_last && !idle) {   // uniform; its first fragments were read, behind the barrier, in the previous step's last phase
-        load_frags<MI, NI>(f1, xslot(it), wslot(it), wm, wn, lrow, khalf, 1);
-        mma_frags<MI, NI>(acc, f0);
-        mma_frags<MI, NI>(acc, f1);
-    }
+    for (; it + 2 < nk_main; ++it) tile_step(it, Req0{}, Rt{});
+    for (; it + 2 < nk; ++it) tile_step(it, std::integral_constant<int, 1>{}, Rt{});
+    for (; it < nk - (half_last ? 1 : 0); ++it) tile_step(it, std::integral_constant<int, 2>{}, Rt{});
+    if (half_last && !idle) mfmas(f0, 0, NM);   // read, behind the barrier, in the previous step's last phase
+    mfma_drain();
 
-    gemm_epilogue<MI, NI, EPI>(a, acc, smem_raw, m0, n0, wm, wn, wave, lane);
+    gemm_epilogue16<MB, NB, EPI>(a, acc, smem_raw, m0, n0, wm, wn, wave, lane);
 }
 
 }  // namespace meteora

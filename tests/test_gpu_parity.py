@@ -160,6 +160,33 @@ def test_base_gemm_matches_oracle(T, d_in, d_out, dtype):
     assert util.rel_max_err(out, oracle.base(ops["x"], ops["W"])) <= util.tol(shape)
 
 
+# The 16x16x32 kernel at the edges of its K loop (1, 2 and 3 K tiles, one short of and one past an unrolled trip of six,
+# a trip and a remainder) in each of its tile shapes, ragged in both directions.
+@pytest.mark.parametrize("d_in", [64, 128, 192, 448, 512, 1088])
+@pytest.mark.parametrize("T,d_out", [(2600, 4104), (1300, 4104), (300, 264)], ids=["256x256", "256x128", "128x128"])
+def test_base_gemm_k_loop_edges(T, d_out, d_in):
+    shape = LS(T, d_in, d_out, 2, 2, 1, 1.0, "bf16")
+    _, dev = util.make_case(shape, seed=32, condition=False)
+    out = m.base_gemm(dev["x"], dev["W"])
+    ref = dev["x"].double() @ dev["W"].double().t().contiguous()
+    # one bf16 rounding of an fp32 sum: half an ulp (2^-9 of the value), fp32 summation error far below it
+    assert float(((out.double() - ref).abs() - 2.0 ** -8 * ref.abs()).max()) <= 1e-4
+
+
+# accumulate = 1 in each tile shape: the old output is read, added in fp32 and rounded once; ranks whose last
+# extension K tile is a half (N*r % 64 <= 32) and a whole one
+@pytest.mark.parametrize("N,r", [(28, 8), (7, 8)], ids=["half-tile", "whole-tile"])
+@pytest.mark.parametrize("T,d_out", [(2600, 4104), (1300, 4104), (300, 264)], ids=["256x256", "256x128", "128x128"])
+def test_lora_accumulate_in_each_tile_shape(T, d_out, N, r):
+    shape = LS(T, 64, d_out, N, r, 2, 2.0, "bf16")
+    ops, dev = util.make_case(shape, seed=33, condition=False)
+    idx, w, _ = m.gate_topk(dev["x"], dev["W_gate"], None, 2)
+    old = torch.randn((T, d_out), device="cuda", generator=torch.Generator(device="cuda").manual_seed(3)).bfloat16()
+    out = m.lora_forward(dev["x"], dev["A"], dev["B"], idx, w, 2.0, out=old.clone(), accumulate=True)
+    ref = oracle.lora_delta(ops["x"], ops["A"], ops["B"], _np(idx), _np(w).astype(np.float64), 2.0)
+    assert util.rel_max_err(out, old.double().cpu().numpy() + ref) <= util.tol(shape)
+
+
 # --------------------------------------------------------------------------------- whole layer
 LAYER_SHAPES = [
     LS(64, 256, 256, 4, 8, 2, 2.0, "f32", "uniform", "cfg1"),
