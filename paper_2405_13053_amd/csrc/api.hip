@@ -72,17 +72,20 @@ WsLayout ws_layout(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
     L.hdense = take((size_t)T * L.ext_stride * sizeof(uint16_t));
     L.apack = take(shrink_apack_bytes(d_in, N, r, bf16));
     L.hpart = take(shrink_hpart_bytes(T, d_in, r, k, bf16));
-    L.splitk = take(gemm_splitk_bytes(T, d_in, d_out, bf16));
+    const bool decode3 = decode_fused_applies(T, d_in, d_out, N, r, bf16);
+    const int S_decode = decode3 ? gemm_decode_plan(d_in, &d_out, 1, prep_wcat_rows(N, r)).S : 0;
+    size_t splitk = gemm_splitk_bytes(T, d_in, d_out, bf16);   // lora_forward at such a size splits in its own way
+    if ((size_t)S_decode * T * d_out * sizeof(float) > splitk) splitk = (size_t)S_decode * T * d_out * sizeof(float);
+    L.splitk = take(splitk);
     L.btrans = take(prep_btrans_bytes(d_out, N, r, bf16));
     const bool dense = route_dense_applies(T, d_in, N, r, bf16);
-    const bool decode3 = decode_fused_applies(T, d_in, d_out, N, r, bf16);
     L.wcat = take(dense || decode3 ? prep_wcat_bytes(d_in, N, r, bf16) : 0);
     // the routing products come in the K splits of the launch that writes them: the products launch's own count, or
     // that of the split base projection when both share one launch (which may be the larger of the two)
     const int S_mid = dense_midsplit_splits(T, d_in, d_out, N, r, bf16);
     L.dpart = take(S_mid > 0 ? (size_t)S_mid * T * prep_wcat_rows(N, r) * sizeof(float)
                              : route_dense_part_bytes(T, d_in, N, r, bf16));
-    L.gpart = take(decode3 ? (size_t)gemm_splitk_splits(T, d_in, d_out, bf16) * T * prep_wcat_rows(N, r) * sizeof(float) : 0);
+    L.gpart = take((size_t)S_decode * T * prep_wcat_rows(N, r) * sizeof(float));
     L.spart = take((size_t)S_mid * T * d_out * sizeof(float));
     L.total = off;
     return L;
@@ -258,7 +261,7 @@ int meteora_workspace_regions(int T, int d_in, int d_out, int N, int r, int k, m
         if (dense || decode3) wr("wcat", prep_wcat_bytes(d_in, N, r, bf16));
     }
     if (decode3) {
-        const int S = gemm_group_splits(T, d_in, &d_out, 1, CR);
+        const int S = gemm_decode_plan(d_in, &d_out, 1, CR).S;
         wr("splitk", (size_t)S * T * d_out * sizeof(float));
         wr("gpart", (size_t)S * T * CR * sizeof(float));
     } else if (dense) {
@@ -528,14 +531,14 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
         const DecodeMember mem{W, pk.wcat, gate_bias, A, B, d_out, at<float>(ws, L.splitk), at<float>(ws, L.gpart),
                                at<float>(ws, L.h32), idx, w, out};
         const int gate_rows = prep_wcat_rows(N, r);   // the gate terms and every adapter's shrink columns
-        const int S = gemm_group_splits(T, d_in, &d_out, 1, gate_rows);
+        const SplitPlan plan = gemm_decode_plan(d_in, &d_out, 1, gate_rows);
         {
             StageScope sc(ST_GEMM, st, tslot);
-            METEORA_HIP(launch_gemm_decode_main(x, &mem, 1, gate_rows, S, T, d_in, st));
+            METEORA_HIP(launch_gemm_decode_main(x, &mem, 1, gate_rows, plan, T, d_in, st));
         }
         // top-k, softmax, then the split-K reduction with the expand from the selected adapters' shrink tiles: one launch
         StageScope sc(ST_SHRINK, st, tslot);
-        METEORA_HIP(launch_decode_tail_group(&mem, 1, S, T, N, r, k, gate_rows, inv_temperature, scale, st));
+        METEORA_HIP(launch_decode_tail_group(&mem, 1, plan, T, N, r, k, gate_rows, inv_temperature, scale, st));
         return METEORA_OK;
     }
     if (dense) {
@@ -552,7 +555,8 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
             }
             if (decode_tail_applies(r)) {   // selection, reduction and expand in one launch, as for decode
                 StageScope sc(ST_SHRINK, st, tslot);
-                METEORA_HIP(launch_decode_tail_group(&mem, 1, S, T, N, r, k, prep_wcat_rows(N, r), inv_temperature, scale, st));
+                METEORA_HIP(launch_decode_tail_group(&mem, 1, SplitPlan{S, 0, 0}, T, N, r, k, prep_wcat_rows(N, r), inv_temperature,
+                                                     scale, st));
                 return METEORA_OK;
             }
             {
@@ -675,7 +679,7 @@ extern "C" size_t meteora_group_workspace_bytes(const int* d_out, int G, int T, 
     }
     if (fused) {
         const int gate_rows = prep_wcat_rows(N, r);
-        const size_t f = group_layout(d_out, G, T, d_in, N, r, k, gemm_group_splits(T, d_in, d_out, G, gate_rows),
+        const size_t f = group_layout(d_out, G, T, d_in, N, r, k, gemm_decode_plan(d_in, d_out, G, gate_rows).S,
                                       gate_rows).total + 256;
         need = f > need ? f : need;
     }
@@ -738,7 +742,7 @@ extern "C" meteora_status meteora_linear_forward_group(const void* x, const mete
         }
         if (decode_tail_applies(r)) {
             StageScope sc(ST_SHRINK, st, tslot);
-            METEORA_HIP(launch_decode_tail_group(mem, G, S, T, N, r, k, cat_rows, inv_temperature, scale, st));
+            METEORA_HIP(launch_decode_tail_group(mem, G, SplitPlan{S, 0, 0}, T, N, r, k, cat_rows, inv_temperature, scale, st));
             return METEORA_OK;
         }
         {
@@ -761,8 +765,8 @@ extern "C" meteora_status meteora_linear_forward_group(const void* x, const mete
         return METEORA_OK;
     }
     const int gate_rows = prep_wcat_rows(N, r);
-    const GroupLayout L = group_layout(d_outs, G, T, d_in, N, r, k, gemm_group_splits(T, d_in, d_outs, G, gate_rows),
-                                       gate_rows);
+    const SplitPlan plan = gemm_decode_plan(d_in, d_outs, G, gate_rows);
+    const GroupLayout L = group_layout(d_outs, G, T, d_in, N, r, k, plan.S, gate_rows);
     DecodeMember mem[kMaxDecodeGroup];
     for (int g = 0; g < G; ++g) {
         const meteora_group_member& m = members[g];
@@ -775,10 +779,10 @@ extern "C" meteora_status meteora_linear_forward_group(const void* x, const mete
     const int tslot = timing_begin_call(st);
     {
         StageScope sc(ST_GEMM, st, tslot);
-        METEORA_HIP(launch_gemm_decode_main(x, mem, G, gate_rows, L.S, T, d_in, st));
+        METEORA_HIP(launch_gemm_decode_main(x, mem, G, gate_rows, plan, T, d_in, st));
     }
     StageScope sc(ST_SHRINK, st, tslot);
-    METEORA_HIP(launch_decode_tail_group(mem, G, L.S, T, N, r, k, gate_rows, inv_temperature, scale, st));
+    METEORA_HIP(launch_decode_tail_group(mem, G, plan, T, N, r, k, gate_rows, inv_temperature, scale, st));
     return METEORA_OK;
 }
 

@@ -318,49 +318,6 @@ hipError_t launch_gemm_dense_splitk_multi(const void* x, const DenseOperand* ops
     return launch_w3(&gemm_mfma_w3_kernel<2, 2, kEpiPartial>, a, gemm_w3_lds_bytes<2, 2>(), S, stream);
 }
 
-// Decode in two launches: (1) the main K splits of x * W^T with the rows of Wcat as extra column
-// tiles (fp32 tiles into `partial` and `gpartial`), (2) routing on the gate tiles, then the reduction with the
-// expand from the shrink tiles (route_small.hip).  A group of G layers that share x runs through the same two
-// launches: the column tiles of all their W and Wcat form one grid, all with the same number S of K splits.
-int gemm_group_splits(int T, int d_in, const int* d_out, int G, int gate_rows) {
-    if (T < 1 || T > 64 || d_in % kGemmBK != 0) return 0;
-    const int nk = d_in / kGemmBK;
-    if (nk < 8) return 0;
-    int tiles = 0;
-    for (int g = 0; g < G; ++g) tiles += ceil_div(d_out[g], 64) + ceil_div(gate_rows, 64);
-    if (G == 1) return gemm_splitk_splits(T, d_in, d_out[0], true);   // same split as the single-layer call
-    int S = ceil_div(512, tiles);   // about two workgroups per CU (measured: 384 to 1536 tried)
-    if (S > nk / 4) S = nk / 4;
-    return S < 1 ? 1 : S;
-}
-
-hipError_t launch_gemm_decode_main(const void* x, const DecodeMember* mem, int G, int gate_rows, int S, int T,
-                                   int d_in, hipStream_t stream) {
-    if (S <= 0 || gate_rows % 8 != 0 || G < 1 || 2 * G > GemmArgs::kMaxSegments) return hipErrorInvalidValue;
-    GemmArgs a{};
-    a.x = (const bf16_t*)x; a.T = T; a.d_in = d_in;
-    a.splits = S; a.tiles_per_split = ceil_div(d_in / kGemmBK, S);
-    const uint64_t widest = (uint64_t)d_in * 2;
-    if (d_in % kGemmBK != 0 || ((uint64_t)T + 64) * widest >= (1ull << 32)) return hipErrorInvalidValue;
-    int tile0 = 0;
-    for (int g = 0; g < G; ++g) {
-        if (((uint64_t)mem[g].d_out + 64) * widest >= (1ull << 32)) return hipErrorInvalidValue;
-        a.seg[2 * g] = {(const bf16_t*)mem[g].W, mem[g].partial, mem[g].d_out, tile0};
-        tile0 += ceil_div(mem[g].d_out, 64);
-        a.seg[2 * g + 1] = {(const bf16_t*)mem[g].wg3, mem[g].gpartial, gate_rows, tile0};
-        tile0 += ceil_div(gate_rows, 64);
-    }
-    a.nseg = 2 * G;
-    a.W = a.seg[0].W; a.d_out = a.seg[0].rows; a.partial = a.seg[0].partial;   // replaced per workgroup
-    constexpr int smem = gemm_lds_bytes<1, 1>();
-    const hipError_t ea = ensure_lds_limit(reinterpret_cast<const void*>(&gemm_mfma_dma_kernel<1, 1>), smem);
-    if (ea != hipSuccess) return ea;
-    a.tiles_m = ceil_div(T, 64);
-    a.tiles_n = tile0;
-    gemm_mfma_dma_kernel<1, 1><<<dim3(a.tiles_m * a.tiles_n, S), 256, smem, stream>>>(a);
-    return hipGetLastError();
-}
-
 hipError_t launch_gemm_decode_finish(const DecodeMember* mem, int G, int S, int T, int k, int r,
                                      hipStream_t stream) {
     if (S <= 0 || r % 8 != 0 || G < 1 || G > kMaxDecodeGroup) return hipErrorInvalidValue;

@@ -58,9 +58,9 @@ struct GemmArgs {
     // split == splits (only if ext_k > 0) takes the expand extension; fp32 tiles go to partial[split][T][d_out]
     float* partial;       // nullptr: no split, the kernel writes `out` itself
     int splits, tiles_per_split;
-    // decode (two-slot split-K kernel only): the column tiles of one launch may belong to several row-major
-    // matrices that share x (the base weights of the layers of a group, and for each layer the gate-term rows of
-    // its Wcat, so the gate logits ride in the launch that streams W).  Segment e owns column tiles
+    // few-tile batches (fp32 tiles of the three-deep-ring kernel only): the column tiles of one launch may belong to
+    // several row-major matrices that share x (the base weights of the layers of a group, and for each layer its
+    // Wcat, so the routing products ride in the launch that reads W).  Segment e owns column tiles
     // [seg[e].tile0, seg[e+1].tile0) and writes fp32 tiles seg[e].partial[split][T][seg[e].rows].  nseg = 0: off.
     struct Segment {
         const bf16_t* W;   // [rows, d_in]
@@ -470,8 +470,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[M
 }
 
 template <int MI, int NI>
-__global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(const GemmArgs a_in) {
-    GemmArgs a = a_in;
+__global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(const GemmArgs a) {
     constexpr int BM = MI * 64, BN = NI * 64;
     constexpr int PX = BM / 32, PW = BN / 32;   // pieces per wavefront per tile
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -484,17 +483,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(const GemmArgs a_in)
     const int lrow = lane & 31, khalf = lane >> 5;
     int tile_m, tile_n;
     tile_of_workgroup(blockIdx.x, a.tiles_m, a.tiles_n, tile_m, tile_n);
-    const int m0 = tile_m * BM;
-    int n0 = tile_n * BN;
-    if (a.nseg > 0) {   // uniform: the tile is an ordinary tile of its segment's matrix
-        int e = 0;
-        for (int i = 1; i < a.nseg; ++i)
-            if (tile_n >= a_in.seg[i].tile0) e = i;
-        n0 = (tile_n - a_in.seg[e].tile0) * BN;
-        a.W = a_in.seg[e].W;
-        a.d_out = a_in.seg[e].rows;
-        a.partial = a_in.seg[e].partial;
-    }
+    const int m0 = tile_m * BM, n0 = tile_n * BN;
 
     f32x16 acc[MI][NI];
 #pragma unroll

@@ -13,6 +13,7 @@ namespace meteora {
 hipError_t ensure_lds_limit(const void* kernel, int bytes);
 hipError_t init_kernels();
 hipError_t gemm_init_kernels();
+hipError_t gemm_decode_init_kernels();
 hipError_t gate_init_kernels();
 hipError_t shrink_init_kernels();
 hipError_t bucket_init_scratch();
@@ -123,7 +124,7 @@ hipError_t launch_expand(const float* h32, const void* B, const int32_t* topk_id
 // group of up to kMaxDecodeGroup layers that share x (q/k/v, gate/up):
 // launch_gemm_decode_main: the main K splits of x * W_g^T as fp32 tiles partial_g[S][T][d_out_g], and in the same
 //   launch x * Wcat_g^T (gate_rows = prep_wcat_rows(N, r): the gate terms and every adapter's shrink columns) as
-//   gpartial_g[S][T][gate_rows]; S = gemm_group_splits(...) for every member;
+//   gpartial_g[S][T][gate_rows]; S and the splits of every row tile follow from gemm_decode_plan(...);
 // launch_decode_tail_group (route_small.hip): top-k, softmax -> idx_g, w_g, and
 //   out_g = bf16(sum of the S tiles in order + sum_slot (scale * w * h from the shrink tiles) * B_g[idx_g]).
 // launch_gemm_decode_finish: the reduction with the expand alone, from hs_g[T,k,r] = scale * w * h (the few-tile
@@ -144,12 +145,19 @@ struct DecodeMember {
     void* out;            // [T,d_out]
 };
 int gemm_splitk_splits(int T, int d_in, int d_out, bool bf16);
-int gemm_group_splits(int T, int d_in, const int* d_out, int G, int gate_rows);   // 0: the shapes are not split
-hipError_t launch_gemm_decode_main(const void* x, const DecodeMember* mem, int G, int gate_rows, int S, int T,
-                                   int d_in, hipStream_t stream);
+// How the K splits of a launch's row tiles (kSplitRows rows each, nk K steps) are cut.  per_wg = 0: every tile has S
+// splits.  Otherwise the K steps of tile g are the units [g * nk, (g + 1) * nk) of the launch, cut into runs of per_wg
+// units; the runs that touch a tile are its splits, at most S.
+constexpr int kSplitRows = 128;
+struct SplitPlan {
+    int S, nk, per_wg;
+};
+SplitPlan gemm_decode_plan(int d_in, const int* d_out, int G, int gate_rows);
+hipError_t launch_gemm_decode_main(const void* x, const DecodeMember* mem, int G, int gate_rows, const SplitPlan& plan,
+                                   int T, int d_in, hipStream_t stream);
 hipError_t launch_gemm_decode_finish(const DecodeMember* mem, int G, int S, int T, int k, int r, hipStream_t stream);
 bool decode_tail_applies(int r);   // ranks the tail's kernel is built for
-hipError_t launch_decode_tail_group(const DecodeMember* mem, int G, int S, int T, int N, int r, int k, int gate_rows,
+hipError_t launch_decode_tail_group(const DecodeMember* mem, int G, const SplitPlan& plan, int T, int N, int r, int k, int gate_rows,
                                     float inv_temperature, float scale, hipStream_t stream);
 // The same three launches for batches of a few hundred tokens with few output tiles: launch_gemm_dense_splitk_multi over
 // every W_g and Wcat_g (gpartial_g then holds [S][T][prep_wcat_rows]), this selection for all members, the finish above.

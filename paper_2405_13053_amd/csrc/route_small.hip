@@ -159,9 +159,18 @@ struct FinishGroup {
         const bf16_t* B;        // [N, r, d_out]
         bf16_t* out;            // [T, d_out]
         int d_out;
+        int tile0, gate_tile0;  // first row tile of its W and of its Wcat in the launch that wrote the K splits
     } m[kMaxDecodeGroup];
-    int nsplit, chunks;         // K splits; stretches of kTailThreads * 8 columns per row of the widest member
+    SplitPlan plan;
+    int chunks;                 // stretches of kTailThreads * 8 columns per row of the widest member
 };
+
+// K splits of row tile g of the launch (see SplitPlan)
+__device__ __forceinline__ int split_count(const SplitPlan& p, int g) {
+    if (p.per_wg == 0) return p.S;   // uniform
+    const uint32_t first = (uint32_t)(g * p.nk) / (uint32_t)p.per_wg;
+    return (int)((uint32_t)(g * p.nk + p.nk - 1) / (uint32_t)p.per_wg - first) + 1;
+}
 
 // ------------------------------------------------------------------------------------------------------------
 // Decode tail: everything of a decode-sized layer call after the one launch that streams W.  That launch computes,
@@ -188,7 +197,7 @@ __global__ __launch_bounds__(kTailThreads) void decode_tail_kernel(int T, int N,
     int t = blockIdx.x / fg.chunks;
     const int member = t / T;
     t -= member * T;
-    const int d_out = fg.m[member].d_out, c8 = d_out / 8, nsplit = fg.nsplit;
+    const int d_out = fg.m[member].d_out, c8 = d_out / 8, S = fg.plan.S;
     if (chunk * kTailThreads >= c8) return;   // a narrower member of the group: nothing in this stretch
     const int gi = chunk * kTailThreads + threadIdx.x;
     const bool active = gi < c8;              // lanes past the row's end work on its last columns and do not store
@@ -197,6 +206,8 @@ __global__ __launch_bounds__(kTailThreads) void decode_tail_kernel(int T, int N,
     const bf16_t* __restrict__ B = fg.m[member].B;
     const float* partial = fg.m[member].partial + (size_t)t * d_out + c;
     const size_t pstride = (size_t)T * d_out;
+
+    const int tile = c / kSplitRows, nsplit = split_count(fg.plan, fg.m[member].tile0 + tile);
 
     // the projection's split tiles do not depend on the routing: the first 8 go out first
     f32x4 pre0[8], pre1[8];
@@ -208,7 +219,9 @@ __global__ __launch_bounds__(kTailThreads) void decode_tail_kernel(int T, int N,
     }
     float g[1];
     const int lt[1] = {0};
-    dense_logits<NP, 1, 8>(gpart, nsplit, CR, rg.m[member].bias, T, N, t, lt, lane & (NP - 1), g);
+    static_assert(3 * NP <= kSplitRows, "the gate terms are rows of Wcat's first row tile");
+    const int gate_tile0 = fg.m[member].gate_tile0;
+    dense_logits<NP, 1, 8>(gpart, split_count(fg.plan, gate_tile0), CR, rg.m[member].bias, T, N, t, lt, lane & (NP - 1), g);
     int sel_i[1];
     float sel_w[1];
     wave_topk_softmax<NP, 1>(g, lane, N, k, inv_temperature, sel_i, sel_w);   // lane s < k: the s-th choice
@@ -220,7 +233,7 @@ __global__ __launch_bounds__(kTailThreads) void decode_tail_kernel(int T, int N,
 #pragma unroll
     for (int u = 0; u < 8; ++u)
         if (u < nsplit) { lo += pre0[u]; hi += pre1[u]; }
-    for (int s0 = 8; s0 < nsplit; s0 += 8) {   // tiles in order, 8 tiles' loads in flight
+    for (int s0 = 8; s0 < S; s0 += 8) {   // tiles in order, 8 tiles' loads in flight
         f32x4 v0[8], v1[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
@@ -246,23 +259,25 @@ __global__ __launch_bounds__(kTailThreads) void decode_tail_kernel(int T, int N,
         const int my_slot = min(s0 + lane / r, k - 1);
         const int a_e = __shfl(sel_i[0], my_slot);
         const float w_e = __shfl(sel_w[0], my_slot);
-        const float* hsrc = gpart + (size_t)t * CR + 3 * NP + a_e * r + (lane & (r - 1));
+        const int hcol = 3 * NP + a_e * r + (lane & (r - 1));
+        const float* hsrc = gpart + (size_t)t * CR + hcol;
+        const int hsplit = split_count(fg.plan, gate_tile0 + hcol / kSplitRows);
         float hv8[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) hv8[u] = hsrc[(size_t)min(u, nsplit - 1) * T * CR];
+        for (int u = 0; u < 8; ++u) hv8[u] = hsrc[(size_t)min(u, hsplit - 1) * T * CR];
         u32x4 bcur[8];
         load_rows(s0, 0, bcur);   // the first rows of B are under way while the shrink tiles arrive
         float h = 0.f;
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-            if (u < nsplit) h += hv8[u];
-        for (int p0 = 8; p0 < nsplit; p0 += 8) {
+            if (u < hsplit) h += hv8[u];
+        for (int p0 = 8; p0 < S; p0 += 8) {
             float v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = hsrc[(size_t)min(p0 + u, nsplit - 1) * T * CR];
+            for (int u = 0; u < 8; ++u) v[u] = hsrc[(size_t)min(p0 + u, hsplit - 1) * T * CR];
 #pragma unroll
             for (int u = 0; u < 8; ++u)
-                if (p0 + u < nsplit) h += v[u];
+                if (p0 + u < hsplit) h += v[u];
         }
         const float hv = scale * w_e * h;
         const int ngroups = ns * R8;
@@ -300,20 +315,22 @@ __global__ __launch_bounds__(kTailThreads) void decode_tail_kernel(int T, int N,
 bool decode_tail_applies(int r) { return r == 8 || r == 16 || r == 32; }
 
 // gate_rows = every row of Wcat: the split tiles mem[g].gpartial hold the gate terms and all adapters' shrink.
-hipError_t launch_decode_tail_group(const DecodeMember* mem, int G, int S, int T, int N, int r, int k, int gate_rows,
+hipError_t launch_decode_tail_group(const DecodeMember* mem, int G, const SplitPlan& plan, int T, int N, int r, int k, int gate_rows,
                                     float inv_temperature, float scale, hipStream_t stream) {
-    if (G < 1 || G > kMaxDecodeGroup || S < 1 || padded_adapters(N) != 32 || gate_rows != prep_wcat_rows(N, r))
+    if (G < 1 || G > kMaxDecodeGroup || plan.S < 1 || padded_adapters(N) != 32 || gate_rows != prep_wcat_rows(N, r))
         return hipErrorInvalidValue;
     RouteGroup rg{};
     FinishGroup fg{};
-    int widest = 0;
+    int widest = 0, tiles = 0;
     for (int g = 0; g < G; ++g) {
         if (mem[g].d_out % 8 != 0 || mem[g].d_out < 8) return hipErrorInvalidValue;
         rg.m[g] = {mem[g].gpartial, mem[g].bias, mem[g].idx, mem[g].w};
-        fg.m[g] = {mem[g].partial, (const bf16_t*)mem[g].B, (bf16_t*)mem[g].out, mem[g].d_out};
+        fg.m[g] = {mem[g].partial, (const bf16_t*)mem[g].B, (bf16_t*)mem[g].out, mem[g].d_out, tiles,
+                   tiles + ceil_div(mem[g].d_out, kSplitRows)};
+        tiles += ceil_div(mem[g].d_out, kSplitRows) + ceil_div(gate_rows, kSplitRows);
         widest = mem[g].d_out > widest ? mem[g].d_out : widest;
     }
-    fg.nsplit = S;
+    fg.plan = plan;
     fg.chunks = ceil_div(widest / 8, kTailThreads);
     const unsigned grid = (unsigned)G * T * fg.chunks;
     auto go = [&](auto kern) {

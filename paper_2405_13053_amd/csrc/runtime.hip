@@ -43,6 +43,8 @@ hipError_t ensure_lds_limit(const void* kernel, int bytes) {
 hipError_t init_kernels() {
     hipError_t e = gemm_init_kernels();
     if (e != hipSuccess) return e;
+    e = gemm_decode_init_kernels();
+    if (e != hipSuccess) return e;
     e = gate_init_kernels();
     if (e != hipSuccess) return e;
     e = shrink_init_kernels();

@@ -279,6 +279,13 @@ SMALL_BATCH_SHAPES = [
     LS(50, 1024, 776, 16, 32, 8, 0.5, "bf16", "zipf", "T=50-N16-r32-k8-tail"),
     LS(9, 1024, 4104, 28, 8, 8, 1.0, "bf16", "uniform", "T=9-k8-ragged-stretch"),
     LS(64, 2048, 1544, 28, 8, 1, 2.0, "bf16", "zipf", "T=64-top1-tail"),
+    # the launch that streams W: a half-empty last K step, token blocks of 16 at their edges, a ragged row tile
+    LS(16, 576, 264, 28, 8, 2, 2.0, "bf16", "uniform", "T=16-half-K-step"),
+    LS(17, 1088, 136, 28, 16, 2, 2.0, "bf16", "zipf", "T=17-half-K-step"),
+    LS(32, 1600, 1288, 28, 8, 2, 2.0, "bf16", "uniform", "T=32-half-K-step"),
+    # 131 row tiles: runs that cut row tiles at any K step; 258: runs that are longer than a row tile
+    LS(33, 512, 16384, 28, 8, 2, 2.0, "bf16", "uniform", "T=33-runs"),
+    LS(5, 512, 32640, 28, 8, 2, 2.0, "bf16", "zipf", "T=5-long-runs"),
 ]
 
 
