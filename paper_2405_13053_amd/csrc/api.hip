@@ -273,7 +273,7 @@ int meteora_workspace_regions(int T, int d_in, int d_out, int N, int r, int k, m
             wr("dpart", (size_t)gemm_dense_splits(T, d_in, CR) * T * CR * sizeof(float));
             wr("hdense", (size_t)T * L.ext_stride * sizeof(uint16_t));
         }
-    } else {
+    } else if (bf16) {   // fp32 storage needs no more
         wr("partials", (size_t)gate_kslices(d_in, bf16) * T * NP * sizeof(float));
         const bool fused = gemm_fuses_expand(bf16);
         if (fused) wr("hdense", (size_t)T * L.ext_stride * sizeof(uint16_t));
@@ -378,7 +378,7 @@ static meteora_status check_lora_args(const void* x, const void* A, const void* 
     return METEORA_OK;
 }
 
-// bucketing + shrink + (base projection if W != NULL) + expand on a given routing;
+// bucketing + shrink + (base projection if W != NULL: bf16 only) + expand on a given routing;
 // shared by lora_forward (W == NULL) and linear_forward
 static meteora_status run_lora(const void* x, const void* W, const void* A, const void* B, const int32_t* topk_idx,
                                const float* topk_w, int T, int d_in, int d_out, int N, int r, int k, float scale,
@@ -409,13 +409,9 @@ static meteora_status run_lora(const void* x, const void* W, const void* A, cons
                                 pk.btrans, N * r, out, accumulate,
                                 gemm_splitk_bytes(T, d_in, d_out, bf16) > 0 ? at<float>(ws, L.splitk) : nullptr, st));
     } else {
-        if (W) {
-            StageScope sc(ST_GEMM, st, tslot);
-            METEORA_HIP(launch_gemm(x, W, T, d_in, d_out, bf16, nullptr, 0, nullptr, 0, out, accumulate, nullptr, st));
-        }
         StageScope sc(ST_EXPAND, st, tslot);
         METEORA_HIP(launch_expand(h32, B, topk_idx, topk_w, T, d_out, N, r, k, scale, bf16, out,
-                                  W ? 1 : accumulate, st));
+                                  accumulate, st));
     }
     return METEORA_OK;
 }
@@ -580,6 +576,16 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
         StageScope sc(ST_GEMM, st, tslot);
         METEORA_HIP(launch_gemm(x, W, T, d_in, d_out, bf16, at<void>(ws, L.hdense), L.ext_stride, pk.btrans, N * r,
                                 out, 0, nullptr, st));
+        return METEORA_OK;
+    }
+    if (!bf16) {
+        {
+            StageScope sc(ST_GEMM, st, tslot);
+            METEORA_HIP(launch_gemm(x, W, T, d_in, d_out, false, nullptr, 0, nullptr, 0, out, 0, nullptr, st));
+        }
+        StageScope sc(ST_EXPAND, st, tslot);
+        METEORA_HIP(launch_route_lora_f32((const float*)x, W_gate, gate_bias, (const float*)A, (const float*)B, T, d_in,
+                                          d_out, N, r, k, inv_temperature, scale, idx, w, (float*)out, st));
         return METEORA_OK;
     }
     {

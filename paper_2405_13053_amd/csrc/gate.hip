@@ -9,34 +9,20 @@
 #include "kernels.hpp"
 #include "topk_key.hpp"
 #include "prep.hpp"
+#include "gate_row.hpp"
 
 namespace meteora {
 
 // ------------------------------------------------------------------------------------------
-// Stage 1, plain-FMA version (fp32 inputs, or shapes the MFMA version does not take).
-// One workgroup per token; wave w sums the w-th quarter of d_in; lane j owns adapter j.
+// Stage 1 for fp32 inputs: one workgroup per token (see gate_row).
 // ------------------------------------------------------------------------------------------
-template <typename TX>
-__global__ __launch_bounds__(256) void gate_logits_fma_kernel(const TX* __restrict__ x,
-                                                              const float* __restrict__ W_gate,
-                                                              int T, int d_in, int N, int NP,
-                                                              float* __restrict__ partials) {
+__global__ __launch_bounds__(kRowThreads) void gate_logits_f32_kernel(const float* __restrict__ x,
+                                                                      const float* __restrict__ W_gate, int d_in, int N,
+                                                                      int cols, int NP, float* __restrict__ partials) {
     __shared__ float red[4][kMaxAdapters];
-    const int t = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int per = ceil_div(d_in, 4);
-    const int i0 = wave * per, i1 = min(d_in, i0 + per);
-    const TX* xt = x + (size_t)t * d_in;
-    float acc = 0.f;
-    if (lane < N) {
-        for (int i = i0; i < i1; ++i) acc = fmaf(to_float(xt[i]), W_gate[(size_t)i * N + lane], acc);
-    }
-    red[wave][lane] = acc;
-    __syncthreads();
-    if (wave == 0 && lane < NP) {
-        float s = (lane < N) ? ((red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane])) : 0.f;
-        partials[(size_t)t * NP + lane] = s;
-    }
+    const int t = blockIdx.x, j = threadIdx.x;
+    gate_row(x + (size_t)t * d_in, W_gate, d_in, N, cols, red);
+    if (j < NP) partials[(size_t)t * NP + j] = j < N ? (red[0][j] + red[1][j]) + (red[2][j] + red[3][j]) : 0.f;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -250,7 +236,8 @@ hipError_t launch_gate_logits(const void* x, const float* W_gate, int T, int d_i
                               void* wsplit, float* partials, hipStream_t stream) {
     const int NP = padded_adapters(N);
     if (!bf16) {
-        gate_logits_fma_kernel<float><<<T, 256, 0, stream>>>((const float*)x, W_gate, T, d_in, N, NP, partials);
+        gate_logits_f32_kernel<<<T, kRowThreads, 0, stream>>>((const float*)x, W_gate, d_in, N, pow2_at_least(N), NP,
+                                                              partials);
         return hipGetLastError();
     }
     const int KS = gate_kslices(d_in, true), NCB = NP / 32;

@@ -129,6 +129,12 @@ hipError_t launch_expand(const float* h32, const void* B, const int32_t* topk_id
 //   out_g = bf16(sum of the S tiles in order + sum_slot (scale * w * h from the shrink tiles) * B_g[idx_g]).
 // launch_gemm_decode_finish: the reduction with the expand alone, from hs_g[T,k,r] = scale * w * h (the few-tile
 //   form of mid-sized batches below).
+// ---- fp32 storage (layer_f32.hip): the base projection, and the rest of the layer onto it
+hipError_t launch_gemm_f32(const float* x, const float* W, int T, int d_in, int d_out, float* out, hipStream_t stream);
+hipError_t launch_route_lora_f32(const float* x, const float* W_gate, const float* bias, const float* A, const float* B,
+                                 int T, int d_in, int d_out, int N, int r, int k, float inv_temperature, float scale,
+                                 int32_t* topk_idx, float* topk_w, float* out, hipStream_t stream);
+
 constexpr int kMaxDecodeGroup = 4;
 struct DecodeMember {
     const void* W;        // [d_out, d_in]

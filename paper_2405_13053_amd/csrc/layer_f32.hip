@@ -1,0 +1,205 @@
+// The layer with fp32 storage: the base projection on fp32 MFMAs, and everything else of Eq. 2 per token.
+#include "common.hpp"
+#include "gate_row.hpp"
+#include "kernels.hpp"
+#include "topk_key.hpp"
+
+namespace meteora {
+
+// ------------------------------------------------------------------------------------------
+// out[T, d_out] = x[T, d_in] * W[d_out, d_in]^T in fp32.
+//
+// v_mfma_f32_16x16x4_f32 takes one K value per lane, 16 rows x 4 K values per operand.  A lane loads 16 bytes, the K
+// values 4c..4c+3 of its row (c = lane / 16), and feeds them to four MFMAs: the j-th multiplies K values 4c + j of
+// both operands, which is the same set.  The matrix cores take 32 cycles for what two such loads of 1 KB feed to one
+// block, so operands come straight from L2 into registers, one step of 16 K values ahead, without LDS.
+// A wavefront owns MB x NB blocks of 16 x 16; the four of a workgroup either share one such tile, each taking a
+// quarter of K (small outputs: latency counts, and tiles are few), or are 2 x 2 tiles next to each other.
+// Rows of all three matrices are whole 32-byte pieces.
+//
+// Measured against 64 x 64 tiles of plain FMAs through LDS, call by call: 64 x 256 -> 256 29.7 -> 9.7 us, 1024 x 768 ->
+// 768 84 -> 27, 4096 x 4096 -> 4096 3.57 -> 1.36 ms.
+// ------------------------------------------------------------------------------------------
+template <int MB, int NB, bool SPLIT>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ x, const float* __restrict__ W, int T,
+                                                       int d_in, int d_out, float* __restrict__ out) {
+    constexpr int TM = MB * 16, TN = NB * 16;                       // a wavefront's tile
+    constexpr int AHEAD = SPLIT ? 4 : 1;                            // K steps whose loads are in flight
+    __shared__ __attribute__((aligned(16))) float red[SPLIT ? 4 : 1][SPLIT ? TM : 1][SPLIT ? TN + 4 : 1];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int l15 = lane & 15, kc = (lane >> 4) * 4;
+    const int tiles_n = ceil_div(d_out, SPLIT ? TN : 2 * TN);
+    const int tile_m = blockIdx.x / tiles_n, tile_n = blockIdx.x - tile_m * tiles_n;
+    const int m0 = SPLIT ? tile_m * TM : tile_m * 2 * TM + (wave >> 1) * TM;
+    const int n0 = SPLIT ? tile_n * TN : tile_n * 2 * TN + (wave & 1) * TN;
+    const int steps = ceil_div(d_in, 16);
+    const int s0 = SPLIT ? wave * steps / 4 : 0, s1 = SPLIT ? (wave + 1) * steps / 4 : steps;
+
+    // rows past the edge repeat the last one (computed, never stored); K values past d_in count as zeros
+    const float* xp[MB];
+    const float* wp[NB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i) xp[i] = x + (size_t)min(m0 + i * 16 + l15, T - 1) * d_in;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) wp[i] = W + (size_t)min(n0 + i * 16 + l15, d_out - 1) * d_in;
+    struct Step { f32x4 x[MB], w[NB]; };
+    auto load4 = [&](const float* row, int k) -> f32x4 {   // values k..k+3 of a row, zeros past its end
+        const f32x4 v = *reinterpret_cast<const f32x4*>(row + min(k, d_in - 4));
+        return k < d_in ? v : f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    auto load = [&](Step& f, int s) {
+        const int k = s * 16 + kc;
+#pragma unroll
+        for (int i = 0; i < MB; ++i) f.x[i] = load4(xp[i], k);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) f.w[i] = load4(wp[i], k);
+    };
+    f32x4 acc[MB][NB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    Step f[AHEAD + 1];
+#pragma unroll
+    for (int a = 0; a < AHEAD; ++a)
+        if (s0 + a < s1) load(f[a], s0 + a);
+    for (int s = s0; s < s1; s += AHEAD + 1) {
+#pragma unroll
+        for (int u = 0; u <= AHEAD; ++u) {   // register sets have fixed numbers
+            if (s + u >= s1) break;          // uniform per wavefront
+            if (s + u + AHEAD < s1) load(f[(u + AHEAD) % (AHEAD + 1)], s + u + AHEAD);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int mi = 0; mi < MB; ++mi)
+#pragma unroll
+                    for (int ni = 0; ni < NB; ++ni)
+                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[u].w[ni][j], f[u].x[mi][j], acc[mi][ni], 0, 0, 0);
+        }
+    }
+    // a lane holds columns 4 * (lane / 16) .. + 3 of token lane % 16 of every block
+    auto store = [&](int row, int col, f32x4 v) {
+        if (row < T && col < d_out) *reinterpret_cast<f32x4*>(out + (size_t)row * d_out + col) = v;
+    };
+    if constexpr (SPLIT) {
+#pragma unroll
+        for (int mi = 0; mi < MB; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NB; ++ni)
+                *reinterpret_cast<f32x4*>(&red[wave][mi * 16 + l15][ni * 16 + kc]) = acc[mi][ni];
+        __syncthreads();
+        for (int e = threadIdx.x; e < TM * TN / 4; e += 256) {
+            const int r = e / (TN / 4), c = (e % (TN / 4)) * 4;
+            f32x4 v[4];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) v[w] = *reinterpret_cast<const f32x4*>(&red[w][r][c]);
+            store(m0 + r, n0 + c, (v[0] + v[1]) + (v[2] + v[3]));
+        }
+    } else {
+#pragma unroll
+        for (int mi = 0; mi < MB; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NB; ++ni) store(m0 + mi * 16 + l15, n0 + ni * 16 + kc, acc[mi][ni]);
+    }
+}
+
+// 16 x 16 tiles up to 1024 of them (a latency-bound call: 64 x 256 -> 256 is 64 workgroups of four steps of loads), 32 x
+// 32 until 128 x 128 tiles would occupy three quarters of the CUs.
+hipError_t launch_gemm_f32(const float* x, const float* W, int T, int d_in, int d_out, float* out, hipStream_t stream) {
+    if (d_in % 8 != 0 || d_out % 8 != 0) return hipErrorInvalidValue;
+    auto go = [&](auto kern, int tm, int tn) {
+        const int64_t tiles = ceil_div64(T, tm) * ceil_div64(d_out, tn);
+        if (tiles > INT32_MAX) return hipErrorInvalidValue;
+        kern<<<(unsigned)tiles, 256, 0, stream>>>(x, W, T, d_in, d_out, out);
+        return hipGetLastError();
+    };
+    if (ceil_div64(T, 16) * ceil_div64(d_out, 16) <= 1024) return go(gemm_f32_kernel<1, 1, true>, 16, 16);
+    if (ceil_div64(T, 128) * ceil_div64(d_out, 128) < 192) return go(gemm_f32_kernel<2, 2, true>, 32, 32);
+    return go(gemm_f32_kernel<4, 4, false>, 128, 128);
+}
+
+// ------------------------------------------------------------------------------------------
+// The rest of the layer, a workgroup per token: gate logits, top-k, softmax (Eq. 3), the shrink of the selected
+// adapters and their expand onto the base projection that `out` already holds.  At the sizes fp32 storage is used at
+// (a few hundred inputs and outputs) each of these steps is a microsecond of memory latency; as launches of their own
+// (gate logits, top-k, bucket scatter, shrink, expand) they took 4 to 7 us each.  Measured, whole layer, 28 adapters of
+// rank 8, top-2: 64 x 256 -> 256 (4 adapters) 52.4 -> 15.5 us, 300 x 512 -> 768 91 -> 24, 4096 x 4096 -> 4096 without the
+// projection 745 -> 360.
+// ------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(kRowThreads) void route_lora_f32_kernel(
+    const float* __restrict__ x, const float* __restrict__ W_gate, const float* __restrict__ bias,
+    const float* __restrict__ A, const float* __restrict__ B, int d_in, int d_out, int N, int gate_cols, int r, int k,
+    int h_cols, float inv_temperature, float scale, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
+    float* __restrict__ out) {
+    __shared__ float red[4][kMaxAdapters];
+    __shared__ int sel_idx[kMaxTopK];
+    __shared__ float sel_w[kMaxTopK];
+    __shared__ float hs[kMaxTopK * kMaxRank];   // scale * w * h of the k slots
+    const int t = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const float* xt = x + (size_t)t * d_in;
+    gate_row(xt, W_gate, d_in, N, gate_cols, red);
+    if (wave == 0) {   // lane = adapter
+        float g[1] = {0.f};
+        if (lane < N) {
+            g[0] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+            g[0] += bias != nullptr ? bias[lane] : 0.f;
+            if (g[0] == 0.f) g[0] = 0.f;   // -0 -> +0 so equal logits have equal keys
+        }
+        int my_i[1];
+        float my_w[1];
+        wave_topk_softmax<64, 1>(g, lane, N, k, inv_temperature, my_i, my_w);
+        if (lane < k) {
+            sel_idx[lane] = my_i[0];
+            sel_w[lane] = my_w[0];
+            topk_idx[(size_t)t * k + lane] = my_i[0];
+            topk_w[(size_t)t * k + lane] = my_w[0];
+        }
+    }
+    __syncthreads();
+    // shrink: h_cols (a power of two, at most 64) of the k * r products at a time
+    const int kr = k * r;
+    for (int c0 = 0; c0 < kr; c0 += h_cols) {
+        const int c = threadIdx.x & (h_cols - 1), e = c0 + c;
+        float v = 0.f;
+        if (e < kr) {
+            const int slot = e / r, q = e - slot * r;
+            v = row_dot(xt, A + (size_t)sel_idx[slot] * d_in * r + q, r, d_in, threadIdx.x / h_cols, kRowThreads / h_cols);
+        }
+        v = sum_columns(v, h_cols);
+        if (lane < h_cols) red[wave][c] = v;
+        __syncthreads();
+        if (wave == 0 && lane < h_cols && c0 + lane < kr) {
+            const float h = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+            hs[c0 + lane] = scale * sel_w[(c0 + lane) / r] * h;
+        }
+        __syncthreads();
+    }
+    for (int c = threadIdx.x; c < d_out; c += kRowThreads) {
+        float acc = out[(size_t)t * d_out + c];
+        for (int slot = 0; slot < k; ++slot) {
+            const float* Ba = B + (size_t)sel_idx[slot] * r * d_out + c;
+            float d = 0.f;
+            for (int q0 = 0; q0 < r; q0 += 8) {   // 8 rows of B in flight
+                float b[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) b[u] = Ba[(size_t)min(q0 + u, r - 1) * d_out];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (q0 + u < r) d = fmaf(hs[slot * r + q0 + u], b[u], d);
+            }
+            acc += d;
+        }
+        out[(size_t)t * d_out + c] = acc;
+    }
+}
+
+hipError_t launch_route_lora_f32(const float* x, const float* W_gate, const float* bias, const float* A, const float* B,
+                                 int T, int d_in, int d_out, int N, int r, int k, float inv_temperature, float scale,
+                                 int32_t* topk_idx, float* topk_w, float* out, hipStream_t stream) {
+    const int h_cols = k * r >= 64 ? 64 : pow2_at_least(k * r);
+    route_lora_f32_kernel<<<T, kRowThreads, 0, stream>>>(x, W_gate, bias, A, B, d_in, d_out, N, pow2_at_least(N), r, k,
+                                                         h_cols, inv_temperature, scale, topk_idx, topk_w, out);
+    return hipGetLastError();
+}
+
+}  // namespace meteora

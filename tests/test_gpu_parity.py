@@ -193,6 +193,10 @@ LAYER_SHAPES = [
     LS(333, 512, 776, 28, 8, 2, 2.0, "bf16", "uniform", "bf16-ragged"),
     LS(512, 1024, 512, 28, 16, 2, 2.0, "bf16", "zipf", "bf16-r16-zipf"),
     LS(50, 264, 136, 7, 5, 3, 1.5, "f32", "uniform", "f32-odd"),
+    LS(1, 8, 8, 1, 1, 1, 1.0, "f32", "uniform", "f32-smallest"),
+    LS(9, 72, 1032, 64, 64, 8, 0.5, "f32", "zipf", "f32-N64-r64-k8"),
+    LS(517, 24, 552, 28, 8, 2, 2.0, "f32", "uniform", "f32-32x32-tiles-half-K-step"),
+    LS(1537, 40, 2056, 5, 8, 2, 2.0, "f32", "zipf", "f32-128x128-tiles"),
     LS(100, 512, 256, 28, 8, 1, 2.0, "bf16", "uniform", "top1"),
 ]
 
