@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from typing import Optional, Sequence, Tuple
 
 import torch
@@ -103,7 +104,7 @@ def _dt(t: torch.Tensor) -> int:
 
 
 def _p(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()   # the argument types make it a void*
 
 
 def _chk(t: Optional[torch.Tensor], name: str, dtype=None, shape=None):
@@ -113,12 +114,13 @@ def _chk(t: Optional[torch.Tensor], name: str, dtype=None, shape=None):
         raise ValueError(f"{name} must be a contiguous device tensor")
     if dtype is not None and t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:   # torch.Size compares as a tuple
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current device's current stream, without a Stream object around it (1.5 us of a 17 us decode call)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def workspace_bytes(T, d_in, d_out, N, r, k, dtype) -> int:
@@ -148,9 +150,10 @@ def workspace_regions(T, d_in, d_out, N, r, k, dtype, with_packed: bool = False)
     return [(names[j].decode(), int(off[j]), int(res[j]), int(wr[j])) for j in range(n)]
 
 
-def _ws(ws: Optional[torch.Tensor], need: int, device) -> torch.Tensor:
+def _ws(ws: Optional[torch.Tensor], need, device) -> torch.Tensor:
+    """ws, or a new workspace of need() bytes; whether a given one is large enough the library checks itself."""
     if ws is None:
-        ws = torch.empty(max(need, 256), dtype=torch.uint8, device=device)
+        ws = torch.empty(max(need(), 256), dtype=torch.uint8, device=device)
     return ws
 
 
@@ -163,7 +166,7 @@ def gate_topk(x, W_gate, gate_bias, k: int, inv_temperature: float = 1.0, want_l
     idx = torch.empty((T, k), dtype=torch.int32, device=x.device)
     w = torch.empty((T, k), dtype=torch.float32, device=x.device)
     logits = torch.empty((T, N), dtype=torch.float32, device=x.device) if want_logits else None
-    ws = _ws(ws, workspace_bytes(T, d_in, 8, N, 1, k, x.dtype), x.device)
+    ws = _ws(ws, lambda: workspace_bytes(T, d_in, 8, N, 1, k, x.dtype), x.device)
     st = load_library().meteora_gate_topk(_p(x), _p(W_gate), _p(gate_bias), T, d_in, N, k, _dt(x),
                                           float(inv_temperature), _p(idx), _p(w), _p(logits), _p(ws),
                                           ws.numel(), _stream())
@@ -181,7 +184,7 @@ def bucket_tokens(topk_idx, N: int, ws: Optional[torch.Tensor] = None):
     offsets = torch.empty(N + 1, dtype=torch.int32, device=dev)
     tok = torch.empty(T * k, dtype=torch.int32, device=dev)
     slot = torch.empty(T * k, dtype=torch.int32, device=dev)
-    ws = _ws(ws, workspace_bytes(T, 8, 8, N, 1, k, torch.float32), dev)
+    ws = _ws(ws, lambda: workspace_bytes(T, 8, 8, N, 1, k, torch.float32), dev)
     st = load_library().meteora_bucket_tokens(_p(topk_idx), T, k, N, _p(counts), _p(offsets), _p(tok), _p(slot),
                                               _p(ws), ws.numel(), _stream())
     if st != 0:
@@ -220,7 +223,7 @@ def lora_forward(x, A, B, topk_idx, topk_w, scale: float, out: Optional[torch.Te
             raise ValueError("accumulate needs an existing out")
         out = torch.empty((T, d_out), dtype=x.dtype, device=x.device)
     _chk(out, "out", x.dtype, (T, d_out))
-    ws = _ws(ws, workspace_bytes(T, d_in, d_out, N, r, k, x.dtype), x.device)
+    ws = _ws(ws, lambda: workspace_bytes(T, d_in, d_out, N, r, k, x.dtype), x.device)
     st = load_library().meteora_lora_forward(_p(x), _p(A), _p(B), _p(topk_idx), _p(topk_w), T, d_in, d_out, N,
                                              r, k, float(scale), _dt(x), _p(out), int(bool(accumulate)), _p(ws),
                                              ws.numel(), _stream())
@@ -267,7 +270,7 @@ def linear_forward(x, W, W_gate, gate_bias, A, B, k: int, scale: float, out: Opt
     if return_routing:
         idx = torch.empty((T, k), dtype=torch.int32, device=x.device)
         w = torch.empty((T, k), dtype=torch.float32, device=x.device)
-    ws = _ws(ws, workspace_bytes(T, d_in, d_out, N, r, k, x.dtype), x.device)
+    ws = _ws(ws, lambda: workspace_bytes(T, d_in, d_out, N, r, k, x.dtype), x.device)
     lib = load_library()
     if packed is None:
         st = lib.meteora_linear_forward(_p(x), _p(W), _p(W_gate), _p(gate_bias), _p(A), _p(B), T, d_in, d_out, N, r,
@@ -291,6 +294,11 @@ class GroupMember(ctypes.Structure):
                 ("topk_idx_out", ctypes.c_void_p), ("topk_w_out", ctypes.c_void_p)]
 
 
+# the same members as one packed record (native sizes and alignment), written without a ctypes object per member
+_MEMBER = struct.Struct("@6PNi3P")
+assert _MEMBER.size == ctypes.sizeof(GroupMember)
+
+
 def group_workspace_bytes(d_outs: Sequence[int], T: int, d_in: int, N: int, r: int, k: int, dtype) -> int:
     """meteora_group_workspace_bytes."""
     arr = (ctypes.c_int * len(d_outs))(*d_outs)
@@ -306,29 +314,37 @@ def linear_forward_group(x, members, k: int, scale: float, ws: Optional[torch.Te
     T, d_in = x.shape
     N, _, r = members[0]["A"].shape
     _chk(x, "x")
-    arr = (GroupMember * len(members))()
+    dtype, f32 = x.dtype, torch.float32
+    arr = bytearray(_MEMBER.size * len(members))
     keep, res = [], []
     for g, mb in enumerate(members):
         W, Wg, bias, A, B, packed = mb["W"], mb["W_gate"], mb.get("gate_bias"), mb["A"], mb["B"], mb.get("packed")
         d_out = W.shape[0]
-        _chk(W, "W", x.dtype, (d_out, d_in)); _chk(Wg, "W_gate", torch.float32, (d_in, N))
-        _chk(bias, "gate_bias", torch.float32, (N,))
-        _chk(A, "A", x.dtype, (N, d_in, r)); _chk(B, "B", x.dtype, (N, r, d_out)); _chk(packed, "packed", torch.uint8)
         out = mb.get("out")
         if out is None:
-            out = torch.empty((T, d_out), dtype=x.dtype, device=x.device)
-        _chk(out, "out", x.dtype, (T, d_out))
+            out = torch.empty((T, d_out), dtype=dtype, device=x.device)
+        # written out: as calls of _chk the tests of three members are a quarter of a decode call's host time
+        if not (W.dtype == dtype and A.dtype == dtype and B.dtype == dtype and out.dtype == dtype and Wg.dtype == f32 and
+                W.shape == (d_out, d_in) and A.shape == (N, d_in, r) and B.shape == (N, r, d_out) and
+                out.shape == (T, d_out) and Wg.shape == (d_in, N) and
+                W.is_cuda and A.is_cuda and B.is_cuda and out.is_cuda and Wg.is_cuda and
+                W.is_contiguous() and A.is_contiguous() and B.is_contiguous() and out.is_contiguous() and
+                Wg.is_contiguous()):
+            _chk(W, "W", dtype, (d_out, d_in)); _chk(Wg, "W_gate", f32, (d_in, N))
+            _chk(A, "A", dtype, (N, d_in, r)); _chk(B, "B", dtype, (N, r, d_out)); _chk(out, "out", dtype, (T, d_out))
+        _chk(bias, "gate_bias", f32, (N,)); _chk(packed, "packed", torch.uint8)
         idx = w = None
         if return_routing:
             idx = torch.empty((T, k), dtype=torch.int32, device=x.device)
             w = torch.empty((T, k), dtype=torch.float32, device=x.device)
-        ptr = lambda t: None if t is None else t.data_ptr()
-        arr[g] = GroupMember(ptr(W), ptr(Wg), ptr(bias), ptr(A), ptr(B), ptr(packed),
-                             packed.numel() if packed is not None else 0, d_out, ptr(out), ptr(idx), ptr(w))
+        _MEMBER.pack_into(arr, g * _MEMBER.size, W.data_ptr(), Wg.data_ptr(), _p(bias) or 0, A.data_ptr(), B.data_ptr(),
+                          _p(packed) or 0, packed.numel() if packed is not None else 0, d_out, out.data_ptr(),
+                          _p(idx) or 0, _p(w) or 0)
         keep.append((out, idx, w))
         res.append((out, idx, w) if return_routing else out)
-    ws = _ws(ws, group_workspace_bytes([mb["W"].shape[0] for mb in members], T, d_in, N, r, k, x.dtype), x.device)
-    st = load_library().meteora_linear_forward_group(_p(x), arr, len(members), T, d_in, N, r, k, float(scale),
+    ws = _ws(ws, lambda: group_workspace_bytes([mb["W"].shape[0] for mb in members], T, d_in, N, r, k, x.dtype), x.device)
+    st = load_library().meteora_linear_forward_group(_p(x), (ctypes.c_char * len(arr)).from_buffer(arr),
+                                                     len(members), T, d_in, N, r, k, float(scale),
                                                      float(inv_temperature), _dt(x), _p(ws), ws.numel(), _stream())
     if st != 0:
         raise MeteoraError(st, "meteora_linear_forward_group")
@@ -363,7 +379,7 @@ def gate_backward(x, dy, gate_bias, B, packed, k: int, scale: float, labels=None
     need = gate_backward_workspace_bytes(T, d_in, d_out, N, r, k, x.dtype)
     if need == 0 and T > 0:
         raise MeteoraError(2, "meteora_gate_backward_workspace_bytes")
-    ws = _ws(ws, need, x.device)
+    ws = _ws(ws, lambda: need, x.device)
     dW = torch.empty((d_in, N), dtype=torch.float32, device=x.device)
     db = torch.empty((N,), dtype=torch.float32, device=x.device) if want_dbias else None
     dl = torch.empty((T, N), dtype=torch.float32, device=x.device) if want_d_logits else None
@@ -408,7 +424,7 @@ def variant_forward(variant: int, x, W, W_gate, gate_bias, A, B, k: int, scale: 
     need = variant_workspace_bytes(variant, T, d_in, d_out, N, r, k, x.dtype)
     if need == 0 and T > 0:
         raise MeteoraError(2, "meteora_variant_workspace_bytes")
-    ws = _ws(ws, need, x.device)
+    ws = _ws(ws, lambda: need, x.device)
     st = load_library().meteora_variant_forward(int(variant), _p(x), _p(W), _p(W_gate), _p(gate_bias), _p(A), _p(B),
                                                 T, d_in, d_out, N, r, k, float(scale), _dt(x), _p(out), _p(idx),
                                                 _p(w), _p(ws), ws.numel(), _stream())
