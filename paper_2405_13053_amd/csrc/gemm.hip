@@ -137,7 +137,7 @@ static bool dma_ok(const GemmArgs& a, int BM, int BN) {
 }
 
 template <typename K>
-static hipError_t launch_w3(K kern, const GemmArgs& a, int lds_bytes, int splits, hipStream_t stream) {
+static hipError_t launch_ring(K kern, const GemmArgs& a, int lds_bytes, int splits, hipStream_t stream) {
     const hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(kern), lds_bytes);
     if (e != hipSuccess) return e;
     kern<<<dim3(a.tiles_m * a.tiles_n, splits), 256, lds_bytes, stream>>>(a);
@@ -145,14 +145,14 @@ static hipError_t launch_w3(K kern, const GemmArgs& a, int lds_bytes, int splits
 }
 
 // One workgroup per (MI*64) x (NI*64) output tile; the output is written, or added to, by the kernel itself.
-template <int MI, int NI>
+template <int MI, int NI, int D>
 static hipError_t launch_tiles(GemmArgs a, hipStream_t stream) {
     a.tiles_m = ceil_div(a.T, MI * 64);
     a.tiles_n = ceil_div(a.d_out, NI * 64);
     if (dma_ok(a, MI * 64, NI * 64)) {
-        constexpr int smem = gemm_w3_lds_bytes<MI, NI>();
-        return a.accumulate ? launch_w3(&gemm_mfma_w3_kernel<MI, NI, kEpiAccumulate>, a, smem, 1, stream)
-                            : launch_w3(&gemm_mfma_w3_kernel<MI, NI, kEpiStore>, a, smem, 1, stream);
+        constexpr int smem = gemm_ring_lds_bytes<2 * MI, 2 * NI, D>();
+        return a.accumulate ? launch_ring(&gemm_mfma_ring_kernel<2 * MI, 2 * NI, D, kEpiAccumulate>, a, smem, 1, stream)
+                            : launch_ring(&gemm_mfma_ring_kernel<2 * MI, 2 * NI, D, kEpiStore>, a, smem, 1, stream);
     }
     constexpr int MF = MI < NI ? MI : NI, smem = gemm_lds_bytes<MF, MF>();   // any d_in, any size
     const hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(&gemm_mfma_kernel<MF, MF>), smem);
@@ -194,7 +194,7 @@ static hipError_t launch_skinny(GemmArgs a, hipStream_t stream) {
 // ------------------------------------------------------------------------------------------
 // Up to 4096 tokens: 128 x 128 tiles, two workgroups per CU (one computes while the other waits for its
 // loads), about 384 workgroups; above: 128 x 320 tiles (x is read once), one workgroup per CU.  Both with
-// the three-deep W ring.  Measured on T = 4096 and 8192, d_in = 4096 and 14336.
+// the two-deep ring.  Measured on T = 4096 and 8192, d_in = 4096 and 14336.
 static bool dense_small_tiles(int T) { return T <= 4096; }
 
 bool gemm_dense_splitk_ok(int T, int d_in, int rows) {
@@ -212,11 +212,11 @@ int gemm_dense_splits(int T, int d_in, int rows) {
     return S < 1 ? 1 : S;
 }
 
-template <int MI, int NI>
-static hipError_t launch_dense(GemmArgs a, hipStream_t stream) {   // three-deep W ring, fp32 split-K tiles
-    a.tiles_m = ceil_div(a.T, MI * 64);
-    a.tiles_n = ceil_div(a.d_out, NI * 64);
-    return launch_w3(&gemm_mfma_w3_kernel<MI, NI, kEpiPartial>, a, gemm_w3_lds_bytes<MI, NI>(), a.splits, stream);
+template <int MB, int NB, int D>
+static hipError_t launch_dense(GemmArgs a, hipStream_t stream) {   // fp32 split-K tiles; tiles_n is the caller's
+    a.tiles_m = ceil_div(a.T, MB * 32);
+    if (a.tiles_n == 0) a.tiles_n = ceil_div(a.d_out, NB * 32);
+    return launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiPartial>, a, gemm_ring_lds_bytes<MB, NB, D>(), a.splits, stream);
 }
 
 hipError_t launch_gemm_dense_splitk(const void* x, const void* Wcat, int T, int d_in, int rows, float* partial,
@@ -227,18 +227,20 @@ hipError_t launch_gemm_dense_splitk(const void* x, const void* Wcat, int T, int 
     a.partial = partial;
     a.splits = gemm_dense_splits(T, d_in, rows);
     a.tiles_per_split = ceil_div(d_in / kGemmBK, a.splits);
-    return dense_small_tiles(T) ? launch_dense<2, 2>(a, stream) : launch_dense<2, 5>(a, stream);
+    return dense_small_tiles(T) ? launch_dense<4, 4, 2>(a, stream) : launch_dense<4, 10, 2>(a, stream);
 }
 
 // Several matrices in one split-K launch (few-tile batches): ops[i].partial[s][T][rows_i] = x * W_i^T over the K
-// range of split s, the 128-column tiles of all of them in one grid.  The tiles are 128 rows high up to 128 tokens
-// and 256 rows above (a wavefront's 128 x 64 piece needs 0.75 fragment reads per MFMA against 1.0 at 128 x 128),
-// one workgroup per CU at most, so the number of K splits is capped for them.  Measured, 256 x 128 against 128 x
-// 128 tiles, whole call at 4096 -> 4096: T = 160 24.2 against 26.1 us, T = 400 34.5 against 43.6, T = 512 37.1
-// against 44.6, T = 640 44.1 against 50.7; at 14336 -> 4096 T = 512 77.3 against 97.9.
-bool gemm_multi_big_rows(int T) { return T > 128; }
+// range of split s, the 128-column tiles of all of them in one grid, one workgroup per CU at most.  The tiles are up to
+// 256 rows high (a wavefront's 128 x 64 piece needs 0.75 fragment reads per MFMA against 1.0 at 128 x 128), in steps
+// of 32 so that the rows are dealt evenly: 300 tokens are two tiles of 160 rows.  Whole calls, against 256 rows above
+// 128 tokens and 128 (two workgroups per CU) up to there, both with the two-deep ring: 4096 -> 4096 T = 80 23.6 ->
+// 20.2 us, T = 300 40.7 -> 31.6, T = 512 43.0 -> 40.6; 14336 -> 4096 T = 128 58.7 -> 44.4, T = 300 102 -> 69.6.
+static int gemm_multi_row_blocks(int T) {
+    const int b = ceil_div(ceil_div(T, ceil_div(T, 256)), 32);
+    return b < 3 ? 3 : b;
+}
 int gemm_multi_cap_splits(int T, int col_tiles, int S) {
-    if (!gemm_multi_big_rows(T)) return S;
     const int cap = 256 / (ceil_div(T, 256) * (col_tiles > 0 ? col_tiles : 1));   // 256 CUs
     return S > cap ? (cap > 0 ? cap : 1) : S;
 }
@@ -258,13 +260,15 @@ hipError_t launch_gemm_dense_splitk_multi(const void* x, const DenseOperand* ops
     a.nseg = n_ops;
     a.W = a.seg[0].W; a.d_out = a.seg[0].rows; a.partial = a.seg[0].partial;   // replaced per workgroup
     a.tiles_n = tile0;
-    if (gemm_multi_big_rows(T)) {
-        if (((uint64_t)T + 256) * ((uint64_t)d_in * 2) >= (1ull << 32)) return hipErrorInvalidValue;
-        a.tiles_m = ceil_div(T, 256);
-        return launch_w3(&gemm_mfma_w3_kernel<4, 2, kEpiPartial>, a, gemm_w3_lds_bytes<4, 2>(), S, stream);
+    if (((uint64_t)T + 256) * ((uint64_t)d_in * 2) >= (1ull << 32)) return hipErrorInvalidValue;
+    switch (gemm_multi_row_blocks(T)) {
+        case 3: return launch_dense<3, 4, 5>(a, stream);
+        case 4: return launch_dense<4, 4, 4>(a, stream);
+        case 5: return launch_dense<5, 4, 4>(a, stream);
+        case 6: return launch_dense<6, 4, 3>(a, stream);
+        case 7: return launch_dense<7, 4, 3>(a, stream);
+        default: return launch_dense<8, 4, 3>(a, stream);
     }
-    a.tiles_m = ceil_div(T, 128);
-    return launch_w3(&gemm_mfma_w3_kernel<2, 2, kEpiPartial>, a, gemm_w3_lds_bytes<2, 2>(), S, stream);
 }
 
 hipError_t launch_gemm_decode_finish(const DecodeMember* mem, int G, int S, int T, int k, int r,
@@ -294,15 +298,20 @@ hipError_t gemm_init_kernels() {
     lim(&gemm_mfma_kernel<2, 2>, gemm_lds_bytes<2, 2>());
     lim(&gemm_mfma_kernel<1, 1>, gemm_lds_bytes<1, 1>());
     lim(&gemm_mfma_dma_kernel<1, 1>, gemm_lds_bytes<1, 1>());
-    lim(&gemm_mfma_w3_kernel<4, 4, kEpiStore>, gemm_w3_lds_bytes<4, 4>());
-    lim(&gemm_mfma_w3_kernel<4, 4, kEpiAccumulate>, gemm_w3_lds_bytes<4, 4>());
-    lim(&gemm_mfma_w3_kernel<4, 2, kEpiStore>, gemm_w3_lds_bytes<4, 2>());
-    lim(&gemm_mfma_w3_kernel<4, 2, kEpiAccumulate>, gemm_w3_lds_bytes<4, 2>());
-    lim(&gemm_mfma_w3_kernel<4, 2, kEpiPartial>, gemm_w3_lds_bytes<4, 2>());
-    lim(&gemm_mfma_w3_kernel<2, 2, kEpiStore>, gemm_w3_lds_bytes<2, 2>());
-    lim(&gemm_mfma_w3_kernel<2, 2, kEpiAccumulate>, gemm_w3_lds_bytes<2, 2>());
-    lim(&gemm_mfma_w3_kernel<2, 2, kEpiPartial>, gemm_w3_lds_bytes<2, 2>());
-    lim(&gemm_mfma_w3_kernel<2, 5, kEpiPartial>, gemm_w3_lds_bytes<2, 5>());
+    lim(&gemm_mfma_ring_kernel<8, 8, 2, kEpiStore>, gemm_ring_lds_bytes<8, 8, 2>());
+    lim(&gemm_mfma_ring_kernel<8, 8, 2, kEpiAccumulate>, gemm_ring_lds_bytes<8, 8, 2>());
+    lim(&gemm_mfma_ring_kernel<8, 4, 3, kEpiStore>, gemm_ring_lds_bytes<8, 4, 3>());
+    lim(&gemm_mfma_ring_kernel<8, 4, 3, kEpiAccumulate>, gemm_ring_lds_bytes<8, 4, 3>());
+    lim(&gemm_mfma_ring_kernel<4, 4, 2, kEpiStore>, gemm_ring_lds_bytes<4, 4, 2>());
+    lim(&gemm_mfma_ring_kernel<4, 4, 2, kEpiAccumulate>, gemm_ring_lds_bytes<4, 4, 2>());
+    lim(&gemm_mfma_ring_kernel<4, 4, 2, kEpiPartial>, gemm_ring_lds_bytes<4, 4, 2>());
+    lim(&gemm_mfma_ring_kernel<4, 10, 2, kEpiPartial>, gemm_ring_lds_bytes<4, 10, 2>());
+    lim(&gemm_mfma_ring_kernel<3, 4, 5, kEpiPartial>, gemm_ring_lds_bytes<3, 4, 5>());
+    lim(&gemm_mfma_ring_kernel<4, 4, 4, kEpiPartial>, gemm_ring_lds_bytes<4, 4, 4>());
+    lim(&gemm_mfma_ring_kernel<5, 4, 4, kEpiPartial>, gemm_ring_lds_bytes<5, 4, 4>());
+    lim(&gemm_mfma_ring_kernel<6, 4, 3, kEpiPartial>, gemm_ring_lds_bytes<6, 4, 3>());
+    lim(&gemm_mfma_ring_kernel<7, 4, 3, kEpiPartial>, gemm_ring_lds_bytes<7, 4, 3>());
+    lim(&gemm_mfma_ring_kernel<8, 4, 3, kEpiPartial>, gemm_ring_lds_bytes<8, 4, 3>());
     return e;
 }
 
@@ -329,15 +338,15 @@ hipError_t launch_gemm(const void* x, const void* W, int T, int d_in, int d_out,
         // 256 x 256 tiles costs more than the smaller tiles' lower efficiency (4096 -> 4096: T = 4608, 288 tiles, 174
         // us against 155 with 128 x 128 tiles; T = 5120 176 against 163; 336 tiles and more: the big tiles win again,
         // and with two rounds or more they always do: 544 tiles 275 against 279)
-        if (T > 128 && big_tiles >= 160 && !(big_tiles > 256 && big_tiles <= 328)) return launch_tiles<4, 4>(a, stream);
+        if (T > 128 && big_tiles >= 160 && !(big_tiles > 256 && big_tiles <= 328)) return launch_tiles<4, 4, 2>(a, stream);
         // between the two: 256 x 128 tiles where 160 to 256 of them cover the output, one per CU (a wavefront's
         // 128 x 64 piece needs 0.75 fragment reads per MFMA against 1.0 at 128 x 128).  Measured against 128 x 128
         // tiles: T = 1280 at 4096 -> 4096 (160 tiles) 50.2 against 55.2 us, T = 2048 (256 tiles) 62.3 against 66.0,
         // T = 512 at 4096 -> 14336 59.2 against 63.6, T = 2048 at 14336 -> 4096 199 against 219; with 128 tiles
         // (T = 1024) 47.0 against 39.1, so not below 160
         const int64_t mid_tiles = (int64_t)ceil_div(T, 256) * ceil_div(d_out, 128);
-        if (T > 128 && mid_tiles >= 160 && mid_tiles <= 256 && dma_ok(a, 256, 128)) return launch_tiles<4, 2>(a, stream);
-        if (T > 64) return launch_tiles<2, 2>(a, stream);
+        if (T > 128 && mid_tiles >= 160 && mid_tiles <= 256 && dma_ok(a, 256, 128)) return launch_tiles<4, 2, 3>(a, stream);
+        if (T > 64) return launch_tiles<2, 2, 2>(a, stream);
         return launch_skinny(a, stream);
     }
     if (accumulate) return hipErrorInvalidValue;   // the expand adds to the output by itself

@@ -58,7 +58,7 @@ struct GemmArgs {
     // split == splits (only if ext_k > 0) takes the expand extension; fp32 tiles go to partial[split][T][d_out]
     float* partial;       // nullptr: no split, the kernel writes `out` itself
     int splits, tiles_per_split;
-    // few-tile batches (fp32 tiles of the three-deep-ring kernel only): the column tiles of one launch may belong to
+    // few-tile batches (fp32 tiles of the ring kernel only): the column tiles of one launch may belong to
     // several row-major matrices that share x (the base weights of the layers of a group, and for each layer its
     // Wcat, so the routing products ride in the launch that reads W).  Segment e owns column tiles
     // [seg[e].tile0, seg[e+1].tile0) and writes fp32 tiles seg[e].partial[split][T][seg[e].rows].  nseg = 0: off.
@@ -618,14 +618,17 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(const GemmArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------
-// The same pipeline with a three-deep ring for the W operand (2 x-slots + 3 W-slots: the whole 160 KB of
-// LDS for the 256 x 256 tile).  A global->LDS load occupies the CU's address unit for ~16 cycles, so the
+// The same pipeline with a ring of D x-slots and D+1 W-slots: the loads of D K tiles are in flight.  D = 2 fills the
+// whole 160 KB of LDS for the 256 x 256 tile; smaller tiles of one workgroup per CU take as many slots as fit, since
+// with two their K tile is shorter than a load's latency (300 x 4096 -> 4096 as K-split 160 x 128 tiles, 22 K tiles
+// each: 21 us with D = 4, 28.9 us with 256 x 128 tiles and D = 2; 512 rows, 256 x 128 tiles: 26.8 against 29.7 us).
+// A global->LDS load occupies the CU's address unit for ~16 cycles, so the
 // four wavefronts can sustain one load per two 32-cycle MFMAs each; issued in one burst (all pieces of a tile in
-// the last phase, the only time a two-slot ring has a free slot) they stall the MFMAs queued behind them.
-// Here tile it+2's W pieces go out during the first k-step of tile it, into the W-slot that no
+// the last phase, the only time a slot of x is free) they stall the MFMAs queued behind them.
+// So tile it+D's W pieces go out during the first k-step of tile it, into the W-slot that no
 // wavefront has read since the previous barrier, and only its x pieces wait for the barrier, spread over
 // the MFMAs of the second.  Loads complete in order, so the barrier of tile it waits for everything
-// but the newest W pieces (vmcnt = W pieces per wavefront).
+// but the newest tiles and W pieces (vmcnt).
 //
 // The contraction runs on v_mfma_f32_16x16x32_bf16: on the layer's data the chip is power-limited, and per multiply
 // this shape reads and writes half as many accumulator registers as 32x32x16.  Measured against the same kernel with
@@ -636,10 +639,10 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(const GemmArgs a) {
 // and loads itself, group by group between scheduling barriers; (2) nothing but MFMAs touches an accumulator inside
 // the K loop, and mfma_drain() stands between the last MFMA and the first read of a result.
 // ------------------------------------------------------------------------------------------
-template <int MI, int NI>
-__host__ __device__ constexpr int gemm_w3_lds_bytes() {
-    constexpr int ring = (2 * MI * 64 + 3 * NI * 64) * kGemmBK * 2;
-    constexpr int stage = 4 * 32 * gemm_partial_stride<NI>();   // the widest epilogue: 32 fp32 rows per wavefront
+template <int MB, int NB, int D>
+__host__ __device__ constexpr int gemm_ring_lds_bytes() {
+    constexpr int ring = (D * MB * 32 + (D + 1) * NB * 32) * kGemmBK * 2;
+    constexpr int stage = 4 * 32 * (NB * 64 + 16);   // the widest epilogue: 32 fp32 rows per wavefront
     return ring > stage ? ring : stage;
 }
 
@@ -648,7 +651,7 @@ __host__ __device__ constexpr int pieces_after_read(int i, int NPC, int NR) {
     return (i + 1) * NPC / NR - i * NPC / NR;
 }
 
-// Epilogue of the three-deep-ring kernel.  EPI fixes at compile time which form a kernel carries: with one form the
+// Epilogue of the ring kernel.  EPI fixes at compile time which form a kernel carries: with one form the
 // accumulators leave their registers as they are converted (with all three behind run-time branches the compiler
 // copies every accumulator out, and spills, before it branches).  A lane holds 4 consecutive output columns of token
 // row l & 15 per block; the tile is staged in this wavefront's own LDS region, RS rows at a time, and leaves as
@@ -658,7 +661,7 @@ template <int MB, int NB, int EPI>
 __device__ __forceinline__ void gemm_epilogue16(const GemmArgs& a, f32x4 (&acc)[MB][NB], unsigned char* smem_raw, int m0,
                                                 int n0, int wm, int wn, int wave, int lane) {
     constexpr bool F32 = EPI == kEpiPartial;
-    constexpr int RS = 32;                                     // staged rows
+    constexpr int RS = MB % 2 == 0 ? 32 : 16;                  // staged rows
     constexpr int EB = F32 ? 4 : 2;                            // bytes per staged value
     constexpr int EST = NB * 16 * EB + 16;                     // bytes per staged row
     constexpr int PPR = NB * 16 * EB / 16;                     // 16-byte pieces per staged row
@@ -753,11 +756,14 @@ __device__ __forceinline__ void mfma_drain() {
 }
 
 // Order of the MB x NB products of a k-step: 2 x 2 micro-blocks, each a cycle, walked as a snake, so that one operand
-// register changes from one MFMA to the next (0.5% less time than sweeping whole rows).
-template <int NB>
-__host__ __device__ constexpr int order_mi(int k) { return (k / (2 * NB)) * 2 + ((k >> 1) & 1); }
-template <int NB>
+// register changes from one MFMA to the next (0.5% less time than sweeping whole rows).  An odd last row is swept.
+template <int MB, int NB>
+__host__ __device__ constexpr int order_mi(int k) {
+    return k >= MB / 2 * 2 * NB ? MB - 1 : (k / (2 * NB)) * 2 + ((k >> 1) & 1);
+}
+template <int MB, int NB>
 __host__ __device__ constexpr int order_ni(int k) {
+    if (k >= MB / 2 * 2 * NB) return k - MB / 2 * 2 * NB;
     const int col = (k >> 2) % (NB / 2), in = k & 3;
     return (((k / (2 * NB)) & 1) ? NB / 2 - 1 - col : col) * 2 + ((in == 1 || in == 2) ? 1 : 0);
 }
@@ -775,12 +781,12 @@ __device__ __forceinline__ void load_frag16(Frags16<MB, NB>& f, const bf16_t* xs
     }
 }
 
-template <int MI, int NI, int EPI>
-__global__ __launch_bounds__(256) void gemm_mfma_w3_kernel(const GemmArgs a_in) {
+template <int MB, int NB, int D, int EPI>
+__global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in) {
     GemmArgs a = a_in;
-    constexpr int BM = MI * 64, BN = NI * 64;
-    constexpr int MB = MI * 2, NB = NI * 2;     // 16 x 16 blocks of a wavefront
+    constexpr int BM = MB * 32, BN = NB * 32;   // 2 x 2 wavefronts of MB x NB blocks of 16 x 16
     constexpr int PX = BM / 32, PW = BN / 32;   // pieces per wavefront per tile
+    static_assert(NB % 2 == 0 && D >= 2 && (D - 1) * (PX + PW) < 64, "whole 2 x 2 micro-blocks; vmcnt holds 6 bits");
     constexpr int NR = MB + NB, NM = MB * NB;   // fragment reads and MFMAs per k-step
     // MFMAs per fragment read: k-step 0's reads (of k-step 1) end early, since the barrier waits for them; k-step 1's
     // (of the next tile) are spread over all of it
@@ -834,8 +840,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_w3_kernel(const GemmArgs a_in) 
     const DmaOperand oh = dma_operand(a.hd, nk_ext > 0 ? a.T : 0, a.ext_stride, m0, wave, lane);
     const DmaOperand ob = dma_operand(a.Bt, nk_ext > 0 ? a.d_out : 0, a.ext_stride, n0, wave, lane);
 
-    auto xslot = [&](int it) { return smem + (it & 1) * kXElems; };
-    auto wslot = [&](int it) { return smem + 2 * kXElems + (it % 3) * kWElems; };
+    auto xslot = [&](int it) { return smem + (it % D) * kXElems; };
+    auto wslot = [&](int it) { return smem + D * kXElems + (it % (D + 1)) * kWElems; };
     // piece i of the x-like / W-like operand of local tile `it` (main tiles first, then the extension)
     auto request_x = [&](bf16_t* slot, int it, int i, auto is_ext) {
         if constexpr (decltype(is_ext)::value) dma_piece(slot, oh, it - nk_main, i, wave);
@@ -860,15 +866,20 @@ __global__ __launch_bounds__(256) void gemm_mfma_w3_kernel(const GemmArgs a_in) 
     };
 
     Frags16<MB, NB> f0, f1;
-    if (nk > 1) {
-        request_tile(0);
-        request_tile(1);
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PX + PW) : "memory");
-        __syncthreads();
-    } else if (nk > 0) {
-        request_tile(0);
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
+    // tile t is needed next: the loads of at most `left` tiles, requested after it, may still be in flight
+    auto wait_tiles = [&](int left) {
+        if (D > 4 && left >= 4) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(D > 4 ? 4 * (PX + PW) : 0) : "memory");
+        else if (D > 3 && left == 3) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(D > 3 ? 3 * (PX + PW) : 0) : "memory");
+        else if (D > 2 && left == 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(D > 2 ? 2 * (PX + PW) : 0) : "memory");
+        else if (left == 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(PX + PW) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    };
+    static_assert(D <= 5, "wait_tiles");
+    if (nk > 0) {
+#pragma unroll
+        for (int t = 0; t < D; ++t)
+            if (t < nk) request_tile(t);
+        wait_tiles(min(nk, D) - 1);
     }
     if (nk > 0) {
 #pragma unroll
@@ -879,27 +890,27 @@ __global__ __launch_bounds__(256) void gemm_mfma_w3_kernel(const GemmArgs a_in) 
     auto mfmas = [&](const Frags16<MB, NB>& f, int k0, int k1) {
 #pragma unroll
         for (int k = k0; k < k1; ++k)
-            mfma16(acc[order_mi<NB>(k)][order_ni<NB>(k)], f.w[order_ni<NB>(k)], f.x[order_mi<NB>(k)]);
+            mfma16(acc[order_mi<MB, NB>(k)][order_ni<MB, NB>(k)], f.w[order_ni<MB, NB>(k)], f.x[order_mi<MB, NB>(k)]);
     };
-    // REQ: 0 = tile it+2 is a main tile, 1 = it is an extension tile, 2 = there is none (last two tiles)
+    // REQ: 0 = tile it+D is a main tile, 1 = it is an extension tile, 2 = there is none (last D tiles)
     // PH: it % 6 when it is known at compile time (the unrolled main loop: every slot address is then a
     // constant and no address arithmetic sits between two tiles), -1 otherwise
     auto tile_step = [&](int it, auto req, auto ph) {
         constexpr int REQ = decltype(req)::value, PH = decltype(ph)::value;
         using IsExt = std::integral_constant<bool, REQ == 1>;
         auto xsl = [&](int d) {   // x-slot / W-slot of tile it + d
-            if constexpr (PH >= 0) return smem + ((PH + d) & 1) * kXElems;
+            if constexpr (PH >= 0) return smem + ((PH + d) % D) * kXElems;
             else return xslot(it + d);
         };
         auto wsl = [&](int d) {
-            if constexpr (PH >= 0) return smem + 2 * kXElems + ((PH + d) % 3) * kWElems;
+            if constexpr (PH >= 0) return smem + D * kXElems + ((PH + d) % (D + 1)) * kWElems;
             else return wslot(it + d);
         };
         const bf16_t* xs = xsl(0);
         const bf16_t* ws = wsl(0);
-        bf16_t* const xreq = xsl(2);
-        bf16_t* const wreq = wsl(2);
-        // k-step 0: its MFMAs, the fragment reads of k-step 1 and the W pieces of tile it+2
+        bf16_t* const xreq = xsl(D);
+        bf16_t* const wreq = wsl(D);
+        // k-step 0: its MFMAs, the fragment reads of k-step 1 and the W pieces of tile it+D
         int issued = 0;
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
@@ -907,22 +918,20 @@ __global__ __launch_bounds__(256) void gemm_mfma_w3_kernel(const GemmArgs a_in) 
             load_frag16<MB, NB>(f1, xs, ws, wm, wn, l15, kq, 1, i);
             if constexpr (REQ < 2) {
 #pragma unroll
-                for (int c = 0; c < pieces_after_read(i, PW, NR); ++c) request_w(wreq, it + 2, issued++, IsExt{});
+                for (int c = 0; c < pieces_after_read(i, PW, NR); ++c) request_w(wreq, it + D, issued++, IsExt{});
             }
             __builtin_amdgcn_sched_barrier(0);
         }
         mfmas(f0, NR * RA, NM);
         __builtin_amdgcn_sched_barrier(0);
-        // tile it+1 (x requested one tile ago, W before that) must have landed, and every wavefront's reads of
-        // tile it must be complete; the W pieces of tile it+2 just issued may still be in flight
+        // tile it+1 (requested D-1 tiles ago) must have landed, and every wavefront's reads of tile it must be complete;
+        // the tiles after it and the W pieces of tile it+D just issued may still be in flight
         // (a plain s_barrier: __syncthreads() carries a fence, for which the compiler waits for every load)
-        if constexpr (REQ < 2) {
-            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(PW) : "memory");
-        } else {
-            __builtin_amdgcn_s_waitcnt(0);
-            __syncthreads();
-        }
-        // k-step 1: its MFMAs, the first fragments of tile it+1 and the x pieces of tile it+2 into the x-slot just
+        if constexpr (REQ < 2)
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(PW + (D - 2) * (PX + PW)) : "memory");
+        else
+            wait_tiles(nk - 2 - it);
+        // k-step 1: its MFMAs, the first fragments of tile it+1 and the x pieces of tile it+D into the x-slot just
         // drained
         const bf16_t* xn = xsl(1);
         const bf16_t* wnx = wsl(1);
@@ -933,7 +942,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_w3_kernel(const GemmArgs a_in) 
                 mfmas(f1, i * RB, (i + 1) * RB);
                 load_frag16<MB, NB>(f0, xn, wnx, wm, wn, l15, kq, 0, i);
 #pragma unroll
-                for (int c = 0; c < pieces_after_read(i, PX, NR); ++c) request_x(xreq, it + 2, issued++, IsExt{});
+                for (int c = 0; c < pieces_after_read(i, PX, NR); ++c) request_x(xreq, it + D, issued++, IsExt{});
                 __builtin_amdgcn_sched_barrier(0);
             }
             mfmas(f1, NR * RB, NM);
@@ -959,28 +968,27 @@ __global__ __launch_bounds__(256) void gemm_mfma_w3_kernel(const GemmArgs a_in) 
     int it = 0;
     if (idle) {
         for (; it < nk - (half_last ? 1 : 0); ++it) {
-            if (it + 2 < nk) {
-                const bool ext = it + 2 >= nk_main;
+            if (it + D < nk) {
+                const bool ext = it + D >= nk_main;
 #pragma unroll
                 for (int i = 0; i < PW; ++i) {
-                    if (ext) request_w(wslot(it + 2), it + 2, i, std::true_type{});
-                    else request_w(wslot(it + 2), it + 2, i, std::false_type{});
+                    if (ext) request_w(wslot(it + D), it + D, i, std::true_type{});
+                    else request_w(wslot(it + D), it + D, i, std::false_type{});
                 }
-                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(PW) : "memory");
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(PW + (D - 2) * (PX + PW)) : "memory");
 #pragma unroll
                 for (int i = 0; i < PX; ++i) {
-                    if (ext) request_x(xslot(it + 2), it + 2, i, std::true_type{});
-                    else request_x(xslot(it + 2), it + 2, i, std::false_type{});
+                    if (ext) request_x(xslot(it + D), it + D, i, std::true_type{});
+                    else request_x(xslot(it + D), it + D, i, std::false_type{});
                 }
             } else {
-                __builtin_amdgcn_s_waitcnt(0);
-                __syncthreads();
+                wait_tiles(nk - 2 - it);
             }
         }
         it = nk;
     }
     // six tiles per trip in the 256 x 256 kernel: the period of the 2-slot and 3-slot rings
-    if constexpr (MI == 4 && NI == 4) {
+    if constexpr (MB == 8 && NB == 8 && D == 2) {
         for (; it + 7 < nk_main; it += 6) {
             tile_step(it, Req0{}, std::integral_constant<int, 0>{});
             tile_step(it + 1, Req0{}, std::integral_constant<int, 1>{});
@@ -990,8 +998,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_w3_kernel(const GemmArgs a_in) 
             tile_step(it + 5, Req0{}, std::integral_constant<int, 5>{});
         }
     }
-    for (; it + 2 < nk_main; ++it) tile_step(it, Req0{}, Rt{});
-    for (; it + 2 < nk; ++it) tile_step(it, std::integral_constant<int, 1>{}, Rt{});
+    for (; it + D < nk_main; ++it) tile_step(it, Req0{}, Rt{});
+    for (; it + D < nk; ++it) tile_step(it, std::integral_constant<int, 1>{}, Rt{});
     for (; it < nk - (half_last ? 1 : 0); ++it) tile_step(it, std::integral_constant<int, 2>{}, Rt{});
     if (half_last && !idle) mfmas(f0, 0, NM);   // read, behind the barrier, in the previous step's last phase
     mfma_drain();

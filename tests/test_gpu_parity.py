@@ -324,6 +324,12 @@ DENSE_ROUTE_SHAPES = [
     LS(256, 4096, 4096, 28, 8, 2, 2.0, "bf16", "uniform", "T=256-split-K-projection"),
     LS(200, 1024, 1096, 28, 8, 2, 2.0, "bf16", "zipf", "T=200-split-K-ragged-columns"),
     LS(513, 2048, 520, 7, 32, 3, 0.5, "bf16", "uniform", "T=513-split-K-r32"),
+    # every height of the split tiles (96 to 256 rows in steps of 32), ragged, few K tiles per split
+    LS(66, 512, 1032, 28, 8, 2, 2.0, "bf16", "uniform", "T=66-96-rows"),
+    LS(128, 1088, 520, 28, 8, 2, 2.0, "bf16", "zipf", "T=128-128-rows"),
+    LS(289, 1024, 1032, 28, 8, 2, 2.0, "bf16", "uniform", "T=289-160-rows"),
+    LS(161, 576, 264, 28, 8, 2, 2.0, "bf16", "uniform", "T=161-192-rows"),
+    LS(577, 1024, 264, 28, 8, 2, 2.0, "bf16", "uniform", "T=577-224-rows"),
     # the split projection has more K splits (8) than the routing products alone would take (5)
     LS(3000, 4096, 256, 28, 8, 2, 2.0, "bf16", "uniform", "T=3000-narrow-output-more-splits"),
     # 28 adapters of rank 16: 544 rows of Wcat, several column tiles of the routing products
