@@ -407,7 +407,8 @@ static meteora_status run_lora(const void* x, const void* W, const void* A, cons
         StageScope sc(ST_GEMM, st, tslot);
         METEORA_HIP(launch_gemm(x, W, T, W ? d_in : 0, d_out, bf16, at<void>(ws, L.hdense), L.ext_stride,
                                 pk.btrans, N * r, out, accumulate,
-                                gemm_splitk_bytes(T, d_in, d_out, bf16) > 0 ? at<float>(ws, L.splitk) : nullptr, st));
+                                gemm_splitk_bytes(T, d_in, d_out, bf16) > 0 ? at<float>(ws, L.splitk) : nullptr, st,
+                                topk_idx, k, r));
     } else {
         StageScope sc(ST_EXPAND, st, tslot);
         METEORA_HIP(launch_expand(h32, B, topk_idx, topk_w, T, d_out, N, r, k, scale, bf16, out,
@@ -575,7 +576,7 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
         }
         StageScope sc(ST_GEMM, st, tslot);
         METEORA_HIP(launch_gemm(x, W, T, d_in, d_out, bf16, at<void>(ws, L.hdense), L.ext_stride, pk.btrans, N * r,
-                                out, 0, nullptr, st));
+                                out, 0, nullptr, st, idx, k, r));
         return METEORA_OK;
     }
     if (!bf16) {

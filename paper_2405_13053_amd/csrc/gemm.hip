@@ -317,13 +317,15 @@ hipError_t gemm_init_kernels() {
 
 hipError_t launch_gemm(const void* x, const void* W, int T, int d_in, int d_out, bool bf16,
                        const void* hdense, int ext_stride, const void* Bt, int ext_k,
-                       void* out, int accumulate, float* splitk_ws, hipStream_t stream) {
+                       void* out, int accumulate, float* splitk_ws, hipStream_t stream,
+                       const int32_t* topk_idx, int k, int r) {
     if (bf16) {
         if (hdense && (ext_stride % kGemmBK != 0 || ext_stride < ext_k || !Bt)) return hipErrorInvalidValue;
         GemmArgs a{};
         a.x = (const bf16_t*)x; a.W = (const bf16_t*)W; a.hd = (const bf16_t*)hdense; a.Bt = (const bf16_t*)Bt;
         a.out = (bf16_t*)out; a.T = T; a.d_in = d_in; a.d_out = d_out;
         a.ext_k = hdense ? ext_k : 0; a.ext_stride = ext_stride; a.accumulate = accumulate;
+        if (a.ext_k > 0 && r > 0 && a.ext_k <= 64 * kGemmBK) { a.topk_idx = topk_idx; a.topk = k; a.rank = r; }
         const int S = splitk_ws ? gemm_splitk_splits(T, d_in, d_out, true) : 0;
         if (S > 0 && d_in > 0) {
             a.partial = splitk_ws;

@@ -201,6 +201,7 @@ bool gemm_fuses_expand(bool bf16);
 size_t gemm_splitk_bytes(int T, int d_in, int d_out, bool bf16);
 hipError_t launch_gemm(const void* x, const void* W, int T, int d_in, int d_out, bool bf16,
                        const void* hdense, int ext_stride, const void* Bt, int ext_k,
-                       void* out, int accumulate, float* splitk_ws, hipStream_t stream);
+                       void* out, int accumulate, float* splitk_ws, hipStream_t stream,
+                       const int32_t* topk_idx = nullptr, int k = 0, int r = 0);
 
 }  // namespace meteora

@@ -187,6 +187,23 @@ def test_lora_accumulate_in_each_tile_shape(T, d_out, N, r):
     assert util.rel_max_err(out, old.double().cpu().numpy() + ref) <= util.tol(shape)
 
 
+# Routing that leaves most of the expand's K tiles (64 columns of N*r) empty: the first or last tile alone, tiles far
+# apart, a rank that straddles tiles, and in the second half of the tokens other adapters than in the first.
+@pytest.mark.parametrize("N,r,used", [(28, 8, (27,)), (28, 8, (0, 9)), (64, 32, (3, 40, 63)), (9, 24, (2, 5)), (28, 16, (4,))])
+def test_lora_with_unused_adapters(N, r, used):
+    T, d_out, k = 700, 264, 2
+    shape = LS(T, 128, d_out, N, r, k, 2.0, "bf16")
+    ops, dev = util.make_case(shape, seed=34, condition=False)
+    rng = np.random.default_rng(5)
+    first = np.array(used)
+    idx = np.stack([first[rng.integers(0, len(first), T)], np.full(T, 1)], 1).astype(np.int32)   # 1 is in no `used`
+    idx[T // 2:, 1] = N // 2
+    w = rng.uniform(0.2, 0.8, (T, k)).astype(np.float32)
+    out = m.lora_forward(dev["x"], dev["A"], dev["B"], torch.from_numpy(idx).cuda(), torch.from_numpy(w).cuda(), 2.0)
+    ref = oracle.lora_delta(ops["x"], ops["A"], ops["B"], idx, w.astype(np.float64), 2.0)
+    assert util.rel_max_err(out, ref) <= util.tol(shape)
+
+
 # --------------------------------------------------------------------------------- whole layer
 LAYER_SHAPES = [
     LS(64, 256, 256, 4, 8, 2, 2.0, "f32", "uniform", "cfg1"),
