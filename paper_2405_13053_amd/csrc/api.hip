@@ -83,8 +83,12 @@ WsLayout ws_layout(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
     // the routing products come in the K splits of the launch that writes them: the products launch's own count, or
     // that of the split base projection when both share one launch (which may be the larger of the two)
     const int S_mid = dense_midsplit_splits(T, d_in, d_out, N, r, bf16);
-    L.dpart = take(S_mid > 0 ? (size_t)S_mid * T * prep_wcat_rows(N, r) * sizeof(float)
-                             : route_dense_part_bytes(T, d_in, N, r, bf16));
+    size_t dpart = S_mid > 0 ? (size_t)S_mid * T * prep_wcat_rows(N, r) * sizeof(float)
+                             : route_dense_part_bytes(T, d_in, N, r, bf16);
+    // lora_forward at such a size: the adapters' rows alone, in the splits their own launch takes
+    const size_t lora = lora_dense_applies(T, d_in, N, r, k, bf16)
+                            ? (size_t)gemm_dense_splits(T, d_in, N * r) * T * N * r * sizeof(float) : 0;
+    L.dpart = take(lora > dpart ? lora : dpart);
     L.gpart = take((size_t)S_decode * T * prep_wcat_rows(N, r) * sizeof(float));
     L.spart = take((size_t)S_mid * T * d_out * sizeof(float));
     L.total = off;
@@ -430,6 +434,25 @@ meteora_status meteora_lora_forward(const void* x, const void* A, const void* B,
     const WsLayout L = ws_layout(T, d_in, d_out, N, r, k, bf16);
     if (!ws || !aligned256(ws) || ws_bytes < L.total) return METEORA_ERR_WORKSPACE;
     if (T == 0) return METEORA_OK;
+    if (lora_dense_applies(T, d_in, N, r, k, bf16)) {
+        // x * A_i of every adapter in one MFMA launch, then the selected columns as the expand operand: three short
+        // launches fewer than bucket lists and grouped shrink, and x is read in order
+        hipStream_t st = static_cast<hipStream_t>(stream);
+        const int tslot = timing_begin_call(st);
+        float* part = at<float>(ws, L.dpart);
+        METEORA_HIP(launch_prep(nullptr, nullptr, A, nullptr, B, at<void>(ws, L.btrans), at<void>(ws, L.wcat), d_in, d_out,
+                                N, r, st));
+        {
+            StageScope sc(ST_SHRINK, st, tslot);
+            METEORA_HIP(launch_gemm_dense_splitk(x, at<void>(ws, L.wcat), T, d_in, N * r, part, st));
+            METEORA_HIP(launch_dense_expand_operand(part, gemm_dense_splits(T, d_in, N * r), topk_idx, topk_w, T, N, r, k,
+                                                    scale, at<void>(ws, L.hdense), L.ext_stride, st));
+        }
+        StageScope sc(ST_GEMM, st, tslot);
+        METEORA_HIP(launch_gemm(x, nullptr, T, 0, d_out, bf16, at<void>(ws, L.hdense), L.ext_stride, at<void>(ws, L.btrans),
+                                N * r, out, accumulate, nullptr, st, topk_idx, k, r));
+        return METEORA_OK;
+    }
     {
         const bool pa = shrink_apack_bytes(d_in, N, r, bf16) > 0, pb = prep_btrans_bytes(d_out, N, r, bf16) > 0;
         METEORA_HIP(launch_prep(nullptr, nullptr, pa ? A : nullptr, pa ? at<void>(ws, L.apack) : nullptr,

@@ -22,8 +22,9 @@ hipError_t bucket_init_scratch();
 // stacked B -> its transpose Bt[d_out, N*r rounded up to 64] (zero-padded) for the GEMM's K-extension.
 // Any pair (W_gate, wsplit) / (A, apack) / (B, btrans) may be NULL to skip it; sizes are gate_wsplit_bytes,
 // shrink_apack_bytes and prep_btrans_bytes (0 = that operand is not packed for this dtype/rank: pass NULL).
-// wcat (optional, needs W_gate and A, d_in % 64 == 0, r % 8 == 0): Wcat[prep_wcat_rows, d_in] bf16 for the dense routing path,
+// wcat (optional, needs A, d_in % 64 == 0, r % 8 == 0): Wcat[prep_wcat_rows, d_in] bf16 for the dense routing path,
 // rows = hi | mid | lo terms of the gate columns (padded_adapters(N) rows each), then column q of A_a as row a*r+q.
+// Without W_gate: the rows of A alone.
 size_t prep_btrans_bytes(int d_out, int N, int r, bool bf16);
 int prep_wcat_rows(int N, int r);
 size_t prep_wcat_bytes(int d_in, int N, int r, bool bf16);
@@ -62,8 +63,13 @@ hipError_t launch_route_shrink_small(const void* x, const float* partials, int K
 constexpr int kRouteDenseMaxTokens = 8192;
 bool route_dense_possible(int d_in, int N, int r, bool bf16);            // whatever T: is Wcat worth packing
 bool route_dense_applies(int T, int d_in, int N, int r, bool bf16);
+bool lora_dense_applies(int T, int d_in, int N, int r, int k, bool bf16);   // lora_forward, whose routing is given
 size_t route_dense_part_bytes(int T, int d_in, int N, int r, bool bf16);  // 0 if the path does not apply
 hipError_t launch_route_dense_products(const void* x, const void* wcat, int T, int d_in, int N, int r, float* part,
+                                       hipStream_t stream);
+// the expand operand for a routing that is given: part[S][T][N*r] = x * A_i of every adapter
+hipError_t launch_dense_expand_operand(const float* part, int S, const int32_t* topk_idx, const float* topk_w, int T,
+                                       int N, int r, int k, float scale, void* hdense, int ext_stride,
                                        hipStream_t stream);
 hipError_t launch_route_dense_select(const float* part, const float* bias, int T, int d_in, int N, int r, int k,
                                      float inv_temperature, float scale, int32_t* topk_idx, float* topk_w,

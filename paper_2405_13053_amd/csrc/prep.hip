@@ -155,7 +155,7 @@ __global__ __launch_bounds__(256) void prep_kernel(const float* __restrict__ W_g
         return;
     }
     if ((int)blockIdx.x < bblocks + cblocks) {
-        wcat_tile(W_gate, reinterpret_cast<const uint16_t*>(A), d_in, N, padded_adapters(N), r, cat_rows,
+        wcat_tile(W_gate, reinterpret_cast<const uint16_t*>(A), d_in, N, W_gate ? padded_adapters(N) : 0, r, cat_rows,
                   blockIdx.x - bblocks, threadIdx.x, Wcat);
         return;
     }
@@ -187,8 +187,8 @@ hipError_t launch_prep(const float* W_gate, void* wsplit, const void* A, void* a
     const int ext_stride = (int)align_up((size_t)N * r, 64);
     const int bblocks = (B && btrans) ? (ext_stride / 64) * ceil_div(d_out, 64) : 0;
     const int wblocks = ceil_div(wfrags, 4);
-    const int cat_rows = prep_wcat_rows(N, r);
-    if (wcat && (!W_gate || !A || d_in % 64 != 0 || r % 8 != 0)) return hipErrorInvalidValue;
+    const int cat_rows = W_gate ? prep_wcat_rows(N, r) : N * r;
+    if (wcat && (!A || d_in % 64 != 0 || r % 8 != 0)) return hipErrorInvalidValue;
     const int cblocks = wcat ? ceil_div(cat_rows, 64) * (d_in / 64) : 0;
     const int64_t blocks = (int64_t)bblocks + cblocks + wblocks + ceil_div64(afrags, 4);
     if (blocks == 0) return hipSuccess;

@@ -107,6 +107,55 @@ __global__ __launch_bounds__(kSelThreads) void route_dense_select_kernel(const S
     }
 }
 
+// Rows of hdense for a routing the caller holds, from the products of every adapter (no gate columns in `part`): a thread
+// owns a 16-byte piece, 8 columns of one adapter.  An adapter named twice by a token counts in its last slot, ids outside
+// [0, N) nowhere, as in the bucketed path.
+__global__ __launch_bounds__(256) void dense_expand_operand_kernel(const float* __restrict__ part, int S,
+                                                                   const int32_t* __restrict__ topk_idx,
+                                                                   const float* __restrict__ topk_w, int T, int N,
+                                                                   int r, int k, float scale,
+                                                                   bf16_t* __restrict__ hdense, int ext_stride) {
+    const int C8 = ext_stride / 8;
+    const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (gid >= (int64_t)T * C8) return;
+    const int t = (int)(gid / C8), c0 = (int)(gid - (int64_t)t * C8) * 8, NR = N * r;
+    u32x4 pk = {0u, 0u, 0u, 0u};
+    if (c0 < NR) {
+        const int a = c0 / r;
+        int slot = -1;
+        for (int s = 0; s < k; ++s)
+            if (topk_idx[(size_t)t * k + s] == a) slot = s;
+        if (slot >= 0) {
+            f32x4 h0 = {0.f, 0.f, 0.f, 0.f}, h1 = {0.f, 0.f, 0.f, 0.f};
+            const float* src = part + (size_t)t * NR + c0;
+            const float sw = scale * topk_w[(size_t)t * k + slot];
+            f32x4 v0[8], v1[8];   // at most 8 splits, added in order
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const float* p = src + (size_t)min(u, S - 1) * T * NR;
+                v0[u] = *reinterpret_cast<const f32x4*>(p);
+                v1[u] = *reinterpret_cast<const f32x4*>(p + 4);
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (u < S) { h0 += v0[u]; h1 += v1[u]; }
+            pk[0] = pack_bf16x2(sw * h0[0], sw * h0[1]); pk[1] = pack_bf16x2(sw * h0[2], sw * h0[3]);
+            pk[2] = pack_bf16x2(sw * h1[0], sw * h1[1]); pk[3] = pack_bf16x2(sw * h1[2], sw * h1[3]);
+        }
+    }
+    *reinterpret_cast<u32x4*>(hdense + (size_t)t * ext_stride + c0) = pk;
+}
+
+hipError_t launch_dense_expand_operand(const float* part, int S, const int32_t* topk_idx, const float* topk_w, int T,
+                                       int N, int r, int k, float scale, void* hdense, int ext_stride,
+                                       hipStream_t stream) {
+    if (S < 1 || S > 8 || r % 8 != 0 || ext_stride < N * r) return hipErrorInvalidValue;
+    const int64_t pieces = (int64_t)T * (ext_stride / 8);
+    dense_expand_operand_kernel<<<(unsigned)ceil_div64(pieces, 256), 256, 0, stream>>>(
+        part, S, topk_idx, topk_w, T, N, r, k, scale, (bf16_t*)hdense, ext_stride);
+    return hipGetLastError();
+}
+
 // Shapes the dense path takes, whatever the batch size (decides whether Wcat is part of the packed weights).
 bool route_dense_possible(int d_in, int N, int r, bool bf16) {
     // up to 640 rows of Wcat (28 adapters of rank 16: 544): measured against the bucketed sequence on 4096 -> 4096,
@@ -126,6 +175,15 @@ bool route_dense_applies(int T, int d_in, int N, int r, bool bf16) {
     if (T <= kRouteDenseMaxTokens || CR <= 320) return true;
     const int64_t wgs = (int64_t)ceil_div(T, 128) * ceil_div(CR, 320) * gemm_dense_splits(T, d_in, CR);
     return wgs * 10 >= (wgs + 255) / 256 * 256 * 9;   // at least 90% of the CUs' slots over the launch
+}
+
+// The LoRA term alone on a given routing: the products of every adapter cost T * N * r, the bucketed sequence (histogram,
+// scatter, grouped shrink, finalize) about 25 us and T * k * r.  Whole lora_forward calls, dense against bucketed: N * r =
+// 224, d_in = 4096: top-1 T = 500 20.4 against 26.6 us, 4096 30.3 against 32.3, 8192 44.1 against 43.2; top-2 T = 500 20.5
+// against 27.3, 10000 53.1 against 65.7, 12000 97.8 against 97.1 (4096 outputs), 16384 x 14336 174 against 225; N * r = 448:
+// top-1 T = 1000 27.7 against 29.1, 2000 34.0 against 32.1; top-2 3000 x 14336 71.3 against 69.8.
+bool lora_dense_applies(int T, int d_in, int N, int r, int k, bool bf16) {
+    return route_dense_applies(T, d_in, N, r, bf16) && (N * r <= 256 ? T <= 4096 || k >= 2 : T <= 1024);
 }
 
 size_t route_dense_part_bytes(int T, int d_in, int N, int r, bool bf16) {

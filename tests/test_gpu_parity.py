@@ -204,6 +204,36 @@ def test_lora_with_unused_adapters(N, r, used):
     assert util.rel_max_err(out, ref) <= util.tol(shape)
 
 
+# lora_forward on a given routing on either side of the rule between products of every adapter and bucket lists (T = 64,
+# 1024, 4096 tokens; N*r = 256), with ids outside [0, N), accumulate on and off.
+@pytest.mark.parametrize("T,d_in,N,r,k", [(64, 128, 28, 8, 2), (65, 128, 28, 8, 2), (1024, 192, 28, 16, 1), (1025, 192, 28, 16, 1),
+                                          (4096, 64, 32, 8, 1), (4097, 64, 32, 8, 1), (4097, 64, 32, 8, 2), (300, 320, 3, 24, 3)])
+def test_lora_given_routing_on_both_paths(T, d_in, N, r, k):
+    d_out = 136
+    shape = LS(T, d_in, d_out, N, r, k, 2.0, "bf16")
+    ops, dev = util.make_case(shape, seed=35, condition=False)
+    rng = np.random.default_rng(6)
+    idx = np.argsort(rng.random((T, N)), 1)[:, :k].astype(np.int32)
+    w = rng.uniform(0.2, 0.8, (T, k)).astype(np.float32)
+    ref = oracle.lora_delta(ops["x"], ops["A"], ops["B"], idx, w.astype(np.float64), 2.0)
+    idx_d, w_d = torch.from_numpy(idx).cuda(), torch.from_numpy(w).cuda()
+    out = m.lora_forward(dev["x"], dev["A"], dev["B"], idx_d, w_d, 2.0)
+    assert util.rel_max_err(out, ref) <= util.tol(shape)
+    old = torch.randn((T, d_out), device="cuda", generator=torch.Generator(device="cuda").manual_seed(4)).bfloat16()
+    out = m.lora_forward(dev["x"], dev["A"], dev["B"], idx_d, w_d, 2.0, out=old.clone(), accumulate=True)
+    assert util.rel_max_err(out, old.double().cpu().numpy() + ref) <= util.tol(shape)
+    # ids outside [0, N) count nowhere
+    bad = idx_d.clone()
+    bad[::7, k - 1] = N
+    bad[3::7, k - 1] = -1
+    keep = torch.ones_like(w_d)
+    keep[::7, k - 1] = 0
+    keep[3::7, k - 1] = 0
+    out = m.lora_forward(dev["x"], dev["A"], dev["B"], bad, w_d, 2.0)
+    ref = oracle.lora_delta(ops["x"], ops["A"], ops["B"], idx, (w_d * keep).cpu().numpy().astype(np.float64), 2.0)
+    assert util.rel_max_err(out, ref) <= util.tol(shape)
+
+
 # --------------------------------------------------------------------------------- whole layer
 LAYER_SHAPES = [
     LS(64, 256, 256, 4, 8, 2, 2.0, "f32", "uniform", "cfg1"),
