@@ -22,7 +22,7 @@
 //   columns a*r + q:        hx = scale * w * (B_a dy)_q for the selected adapters, else 0;   Xt[c] = A[a][c][q]
 //   next 3 blocks of 32:    hx = hi(d_logits) | hi(d_logits) | lo(d_logits);  Xt[c] = hi(W_gate[c]) | lo(W_gate[c]) | hi(W_gate[c])
 // (two-term bf16 splits, the lo * lo product dropped: the gate term to about 2^-16 of its size).
-// gate_bwd_dlogits_kernel writes hx, gate_bwd_pack_kernel writes Xt (W_gate changes with every optimizer step).
+// gate_bwd_dlogits_kernel writes hx and Xt (W_gate changes with every optimizer step).
 #include <type_traits>
 #include "common.hpp"
 #include "kernels.hpp"
@@ -31,8 +31,11 @@
 
 namespace meteora {
 
-constexpr int kBwdTokens = 16;          // tokens per workgroup of the d_logits kernel
-constexpr int kBwdTokensPerWave = 4;
+// Tokens per workgroup of the d_logits kernel: it waits on two rounds of loads, so many small workgroups (4096 tokens:
+// 512).  With Xt written by the same launch it takes 11.5 us; 16 tokens per workgroup, the splits four at a time and Xt in
+// a launch of its own took 11.9 + 6.0.
+constexpr int kBwdTokens = 8;
+constexpr int kBwdTokensPerWave = 2;
 constexpr int kBwdThreads = kBwdTokens / kBwdTokensPerWave * 64;
 constexpr int kBwdNP = 32;              // logit columns (N <= 32, as the dense products require)
 
@@ -49,9 +52,23 @@ struct DlogitsArgs {
     int ext;                 // columns of hx: N*r + 96 rounded up to 64
     int S1, S2, CR, NR, T, N, r, k;
     float scale, beta;
+    // workgroups from token_blocks on write Xt instead (a launch of its own would cost more than its work)
+    int token_blocks;
+    const uint16_t* A;       // [N, d_in, r]
+    const float* W_gate;     // [d_in, N]
+    int d_in;
+    uint16_t* Xt;            // [d_in][ext]
 };
 
+__device__ void pack_xt(const uint16_t* __restrict__ A, const float* __restrict__ W_gate, int d_in, int N, int r, int ext,
+                        size_t e, uint16_t* __restrict__ Xt);
+
 __global__ __launch_bounds__(kBwdThreads) void gate_bwd_dlogits_kernel(const DlogitsArgs a) {
+    if ((int)blockIdx.x >= a.token_blocks) {   // uniform
+        pack_xt(a.A, a.W_gate, a.d_in, a.N, a.r, a.ext,
+                (size_t)(blockIdx.x - a.token_blocks) * kBwdThreads + threadIdx.x, a.Xt);
+        return;
+    }
     constexpr int NP = kBwdNP;
     constexpr int TPP = 64 / NP;
     constexpr int G = kBwdTokensPerWave / TPP;
@@ -113,29 +130,20 @@ __global__ __launch_bounds__(kBwdThreads) void gate_bwd_dlogits_kernel(const Dlo
         const float* ph = a.part_x + (size_t)t * a.CR + 3 * NP + ad * r + c * 8;
         const float* pu = a.part_dy + (size_t)t * a.NR + ad * r + c * 8;
         f32x4 h0 = {0.f, 0.f, 0.f, 0.f}, h1 = h0, u0 = h0, u1 = h0;
-        for (int s0 = 0; s0 < a.S1; s0 += 4) {
-            f32x4 v0[4], v1[4];
+        f32x4 x0[8], x1[8], y0[8], y1[8];   // both products' splits in one round of loads: there are at most 8 of each
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float* p = ph + (size_t)min(s0 + u, a.S1 - 1) * T * a.CR;
-                v0[u] = *reinterpret_cast<const f32x4*>(p);
-                v1[u] = *reinterpret_cast<const f32x4*>(p + 4);
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (s0 + u < a.S1) { h0 += v0[u]; h1 += v1[u]; }
+        for (int u = 0; u < 8; ++u) {
+            const float* p = ph + (size_t)min(u, a.S1 - 1) * T * a.CR;
+            x0[u] = *reinterpret_cast<const f32x4*>(p);
+            x1[u] = *reinterpret_cast<const f32x4*>(p + 4);
+            p = pu + (size_t)min(u, a.S2 - 1) * T * a.NR;
+            y0[u] = *reinterpret_cast<const f32x4*>(p);
+            y1[u] = *reinterpret_cast<const f32x4*>(p + 4);
         }
-        for (int s0 = 0; s0 < a.S2; s0 += 4) {
-            f32x4 v0[4], v1[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float* p = pu + (size_t)min(s0 + u, a.S2 - 1) * T * a.NR;
-                v0[u] = *reinterpret_cast<const f32x4*>(p);
-                v1[u] = *reinterpret_cast<const f32x4*>(p + 4);
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (s0 + u < a.S2) { u0 += v0[u]; u1 += v1[u]; }
+        for (int u = 0; u < 8; ++u) {
+            if (u < a.S1) { h0 += x0[u]; h1 += x1[u]; }
+            if (u < a.S2) { u0 += y0[u]; u1 += y1[u]; }
         }
         float d = 0.f;
 #pragma unroll
@@ -212,12 +220,10 @@ __global__ __launch_bounds__(kBwdThreads) void gate_bwd_dlogits_kernel(const Dlo
 }
 
 // Xt[c][ext] for the input-gradient GEMM: A[a][c][:] at columns a*r.., then hi | lo | hi of W_gate[c][:] in blocks
-// of 32 columns, zero elsewhere.  A thread owns 8 columns of one row c.
-__global__ __launch_bounds__(256) void gate_bwd_pack_kernel(const uint16_t* __restrict__ A,
-                                                             const float* __restrict__ W_gate, int d_in, int N, int r,
-                                                             int ext, uint16_t* __restrict__ Xt) {
+// of 32 columns, zero elsewhere.  Piece e: 8 columns of one row c.
+__device__ void pack_xt(const uint16_t* __restrict__ A, const float* __restrict__ W_gate, int d_in, int N, int r, int ext,
+                        size_t e, uint16_t* __restrict__ Xt) {
     const int C8 = ext / 8, NR = N * r;
-    const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= (size_t)d_in * C8) return;
     const int c = (int)(e / C8), c0 = (int)(e - (size_t)c * C8) * 8;
     u32x4 pk = {0u, 0u, 0u, 0u};
@@ -446,14 +452,17 @@ hipError_t launch_gate_backward(const void* x, const void* dy, const void* wcat,
     a.S2 = gemm_dense_splits(T, d_out, NR);
     a.CR = CR; a.NR = NR; a.T = T; a.N = N; a.r = r; a.k = k; a.scale = scale; a.beta = beta;
     const size_t u_bytes = dx != nullptr ? (size_t)kBwdTokens * k * r * sizeof(float) : 0;   // at most 32 KB
-    gate_bwd_dlogits_kernel<<<ceil_div(T, kBwdTokens), kBwdThreads, u_bytes, stream>>>(a);
+    if (a.S1 > 8 || a.S2 > 8) return hipErrorInvalidValue;
+    a.token_blocks = ceil_div(T, kBwdTokens);
+    uint16_t* xt = reinterpret_cast<uint16_t*>(ws + L.xt);
+    int64_t blocks_all = a.token_blocks;
+    if (dx != nullptr) {
+        a.A = (const uint16_t*)A; a.W_gate = W_gate; a.d_in = d_in; a.Xt = xt;
+        blocks_all += ceil_div64((int64_t)d_in * (L.ext / 8), kBwdThreads);
+    }
+    gate_bwd_dlogits_kernel<<<(unsigned)blocks_all, kBwdThreads, u_bytes, stream>>>(a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (dx != nullptr) {
-        uint16_t* xt = reinterpret_cast<uint16_t*>(ws + L.xt);
-        const int64_t chunks = (int64_t)d_in * (L.ext / 8);
-        gate_bwd_pack_kernel<<<(unsigned)ceil_div64(chunks, 256), 256, 0, stream>>>((const uint16_t*)A, W_gate, d_in, N,
-                                                                                    r, L.ext, xt);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
         // dx = dy * W_t^T continued over hx * Xt^T: the forward's GEMM with d_in and d_out swapped
         e = launch_gemm(dy, W_t, T, d_out, d_in, true, ws + L.hx, L.ext, xt, L.ext, dx, 0, nullptr, stream);
         if (e != hipSuccess) return e;
