@@ -409,9 +409,9 @@ def summarize_pmc(fetch_dir, write_dir, workload="config2/layer0"):
                       "read_bytes": fa * fs * 1024, "written_bytes": wa * wsc * 1024,
                       "bytes": (fa * fs + wa * wsc) * 1024}
     # the workload's dominant kernel: the 256 x 256 GEMM, else (decode) the split-K GEMM that streams W
-    gemm = [k for k in kernels if "gemm_mfma_w3_kernel<4, 4" in k or "gemm_mfma_w3_kernel<4,4" in k]
+    gemm = [k for k in kernels if "gemm_mfma_ring_kernel<8, 8" in k or "gemm_mfma_ring_kernel<8,8" in k]
     if not gemm:
-        gemm = sorted((k for k in kernels if "gemm_mfma" in k), key=lambda k: -kernels[k]["bytes"])[:1]
+        gemm = sorted((k for k in kernels if "gemm_mfma" in k or "gemm_decode" in k), key=lambda k: -kernels[k]["bytes"])[:1]
     try:
         head = subprocess.check_output(["git", "-C", ROOT, "rev-parse", "--short", "HEAD"], text=True).strip()
     except Exception:

@@ -144,22 +144,25 @@ static hipError_t launch_ring(K kern, const GemmArgs& a, int lds_bytes, int spli
     return hipGetLastError();
 }
 
-// One workgroup per (MI*64) x (NI*64) output tile; the output is written, or added to, by the kernel itself.
-template <int MI, int NI, int D>
+// One workgroup per (MB*32) x (NB*32) output tile; the output is written, or added to, by the kernel itself.
+template <int MB, int NB, int D>
 static hipError_t launch_tiles(GemmArgs a, hipStream_t stream) {
-    a.tiles_m = ceil_div(a.T, MI * 64);
-    a.tiles_n = ceil_div(a.d_out, NI * 64);
-    if (dma_ok(a, MI * 64, NI * 64)) {
-        constexpr int smem = gemm_ring_lds_bytes<2 * MI, 2 * NI, D>();
-        return a.accumulate ? launch_ring(&gemm_mfma_ring_kernel<2 * MI, 2 * NI, D, kEpiAccumulate>, a, smem, 1, stream)
-                            : launch_ring(&gemm_mfma_ring_kernel<2 * MI, 2 * NI, D, kEpiStore>, a, smem, 1, stream);
-    }
-    constexpr int MF = MI < NI ? MI : NI, smem = gemm_lds_bytes<MF, MF>();   // any d_in, any size
-    const hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(&gemm_mfma_kernel<MF, MF>), smem);
+    a.tiles_m = ceil_div(a.T, MB * 32);
+    a.tiles_n = ceil_div(a.d_out, NB * 32);
+    constexpr int smem = gemm_ring_lds_bytes<MB, NB, D>();
+    return a.accumulate ? launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiAccumulate>, a, smem, 1, stream)
+                        : launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore>, a, smem, 1, stream);
+}
+
+// The same without the ring: any d_in, any size.
+template <int M>
+static hipError_t launch_plain(GemmArgs a, hipStream_t stream) {
+    constexpr int smem = gemm_lds_bytes<M, M>();
+    const hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(&gemm_mfma_kernel<M, M>), smem);
     if (e != hipSuccess) return e;
-    a.tiles_m = ceil_div(a.T, MF * 64);
-    a.tiles_n = ceil_div(a.d_out, MF * 64);
-    gemm_mfma_kernel<MF, MF><<<a.tiles_m * a.tiles_n, 256, smem, stream>>>(a);
+    a.tiles_m = ceil_div(a.T, M * 64);
+    a.tiles_n = ceil_div(a.d_out, M * 64);
+    gemm_mfma_kernel<M, M><<<a.tiles_m * a.tiles_n, 256, smem, stream>>>(a);
     return hipGetLastError();
 }
 
@@ -302,6 +305,14 @@ hipError_t gemm_init_kernels() {
     lim(&gemm_mfma_ring_kernel<8, 8, 2, kEpiAccumulate>, gemm_ring_lds_bytes<8, 8, 2>());
     lim(&gemm_mfma_ring_kernel<8, 4, 3, kEpiStore>, gemm_ring_lds_bytes<8, 4, 3>());
     lim(&gemm_mfma_ring_kernel<8, 4, 3, kEpiAccumulate>, gemm_ring_lds_bytes<8, 4, 3>());
+    lim(&gemm_mfma_ring_kernel<7, 4, 3, kEpiStore>, gemm_ring_lds_bytes<7, 4, 3>());
+    lim(&gemm_mfma_ring_kernel<7, 4, 3, kEpiAccumulate>, gemm_ring_lds_bytes<7, 4, 3>());
+    lim(&gemm_mfma_ring_kernel<6, 4, 3, kEpiStore>, gemm_ring_lds_bytes<6, 4, 3>());
+    lim(&gemm_mfma_ring_kernel<6, 4, 3, kEpiAccumulate>, gemm_ring_lds_bytes<6, 4, 3>());
+    lim(&gemm_mfma_ring_kernel<5, 4, 4, kEpiStore>, gemm_ring_lds_bytes<5, 4, 4>());
+    lim(&gemm_mfma_ring_kernel<5, 4, 4, kEpiAccumulate>, gemm_ring_lds_bytes<5, 4, 4>());
+    lim(&gemm_mfma_ring_kernel<4, 4, 4, kEpiStore>, gemm_ring_lds_bytes<4, 4, 4>());
+    lim(&gemm_mfma_ring_kernel<4, 4, 4, kEpiAccumulate>, gemm_ring_lds_bytes<4, 4, 4>());
     lim(&gemm_mfma_ring_kernel<4, 4, 2, kEpiStore>, gemm_ring_lds_bytes<4, 4, 2>());
     lim(&gemm_mfma_ring_kernel<4, 4, 2, kEpiAccumulate>, gemm_ring_lds_bytes<4, 4, 2>());
     lim(&gemm_mfma_ring_kernel<4, 4, 2, kEpiPartial>, gemm_ring_lds_bytes<4, 4, 2>());
@@ -340,15 +351,26 @@ hipError_t launch_gemm(const void* x, const void* W, int T, int d_in, int d_out,
         // 256 x 256 tiles costs more than the smaller tiles' lower efficiency (4096 -> 4096: T = 4608, 288 tiles, 174
         // us against 155 with 128 x 128 tiles; T = 5120 176 against 163; 336 tiles and more: the big tiles win again,
         // and with two rounds or more they always do: 544 tiles 275 against 279)
-        if (T > 128 && big_tiles >= 160 && !(big_tiles > 256 && big_tiles <= 328)) return launch_tiles<4, 4, 2>(a, stream);
-        // between the two: 256 x 128 tiles where 160 to 256 of them cover the output, one per CU (a wavefront's
-        // 128 x 64 piece needs 0.75 fragment reads per MFMA against 1.0 at 128 x 128).  Measured against 128 x 128
-        // tiles: T = 1280 at 4096 -> 4096 (160 tiles) 50.2 against 55.2 us, T = 2048 (256 tiles) 62.3 against 66.0,
-        // T = 512 at 4096 -> 14336 59.2 against 63.6, T = 2048 at 14336 -> 4096 199 against 219; with 128 tiles
-        // (T = 1024) 47.0 against 39.1, so not below 160
-        const int64_t mid_tiles = (int64_t)ceil_div(T, 256) * ceil_div(d_out, 128);
-        if (T > 128 && mid_tiles >= 160 && mid_tiles <= 256 && dma_ok(a, 256, 128)) return launch_tiles<4, 2, 3>(a, stream);
-        if (T > 64) return launch_tiles<2, 2, 2>(a, stream);
+        if (T > 128 && big_tiles >= 160 && !(big_tiles > 256 && big_tiles <= 328))
+            return dma_ok(a, 256, 256) ? launch_tiles<8, 8, 2>(a, stream) : launch_plain<4>(a, stream);
+        if (T > 64 && !dma_ok(a, 256, 128)) return launch_plain<2>(a, stream);
+        // otherwise tiles of 128 columns, one per CU, as low as that allows, with the deepest ring that fits: more CUs
+        // busy and less padding than at 256 rows (a wavefront's 128 x 64 piece has 0.75 fragment reads per MFMA, a 64 x
+        // 64 piece 1.0, so not lower than needed).  The GEMM inside the layer against 256-row
+        // tiles (or two 128-row tiles per CU) with shallower rings: 4096 -> 4096 T = 1000 44.8 -> 41.3 us, 1280 59.1 ->
+        // 47.3, 1531 61.0 -> 52.8, 1700 63.1 -> 59.6; 4096 -> 14336 T = 300 57.7 -> 50.5; 5120 -> 5120 T = 1000 79.7 ->
+        // 64.1; 14336 -> 4096 T = 1280 177 -> 149.
+        const int row_tiles = 256 / ceil_div(d_out, 128);
+        if (T > 64 && row_tiles > 0) {
+            switch (ceil_div(ceil_div(T, row_tiles), 32)) {
+                case 1: case 2: case 3: case 4: return launch_tiles<4, 4, 4>(a, stream);
+                case 5: return launch_tiles<5, 4, 4>(a, stream);
+                case 6: return launch_tiles<6, 4, 3>(a, stream);
+                case 7: return launch_tiles<7, 4, 3>(a, stream);
+                case 8: return launch_tiles<8, 4, 3>(a, stream);
+            }
+        }
+        if (T > 64) return launch_tiles<4, 4, 2>(a, stream);   // more than one tile per CU: two share it
         return launch_skinny(a, stream);
     }
     if (accumulate) return hipErrorInvalidValue;   // the expand adds to the output by itself

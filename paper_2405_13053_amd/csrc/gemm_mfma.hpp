@@ -781,6 +781,17 @@ __device__ __forceinline__ void mfma_drain() {
     asm volatile("s_nop 15" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
 }
+// The same for what the compiler may read: behind this statement, and not before it, the accumulators have values.  (The
+// wait alone does not say so: where the K loop's exits meet, reads of a result have been moved in front of it.)
+template <int MB, int NB>
+__device__ __forceinline__ void mfma_results(f32x4 (&acc)[MB][NB]) {
+    mfma_drain();
+#pragma unroll
+    for (int mi = 0; mi < MB; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NB; ni += 2) asm volatile("" : "+a"(acc[mi][ni]), "+a"(acc[mi][ni + 1]));
+    __builtin_amdgcn_sched_barrier(0);
+}
 
 // Order of the MB x NB products of a k-step: 2 x 2 micro-blocks, each a cycle, walked as a snake, so that one operand
 // register changes from one MFMA to the next (0.5% less time than sweeping whole rows).  An odd last row is swept.
@@ -1039,8 +1050,11 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
     for (; it + D < nk_main; ++it) tile_step(it, Req0{}, Rt{});
     for (; it + D < nk; ++it) tile_step(it, std::integral_constant<int, 1>{}, Rt{});
     for (; it < nk - (half_last ? 1 : 0); ++it) tile_step(it, std::integral_constant<int, 2>{}, Rt{});
-    if (half_last && !idle) mfmas(f0, 0, NM);   // read, behind the barrier, in the previous step's last phase
-    mfma_drain();
+    if (half_last && !idle) {   // read, behind the barrier, in the previous step's last phase
+        mfmas(f0, 0, NM);
+        mfma_drain();
+    }
+    mfma_results<MB, NB>(acc);
 
     gemm_epilogue16<MB, NB, EPI>(a, acc, smem_raw, m0, n0, wm, wn, wave, lane);
 }

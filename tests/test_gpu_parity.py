@@ -163,7 +163,8 @@ def test_base_gemm_matches_oracle(T, d_in, d_out, dtype):
 # The 16x16x32 kernel at the edges of its K loop (1, 2 and 3 K tiles, one short of and one past an unrolled trip of six,
 # a trip and a remainder) in each of its tile shapes, ragged in both directions.
 @pytest.mark.parametrize("d_in", [64, 128, 192, 448, 512, 1088])
-@pytest.mark.parametrize("T,d_out", [(2600, 4104), (1300, 4104), (300, 264)], ids=["256x256", "256x128", "128x128"])
+@pytest.mark.parametrize("T,d_out", [(2600, 4104), (1300, 4104), (300, 264), (1100, 4104), (1500, 4104), (1700, 4104), (1700, 5128)],
+                         ids=["256x256", "192x128", "128x128", "160x128", "224x128", "256x128", "128x128-two-per-CU"])
 def test_base_gemm_k_loop_edges(T, d_out, d_in):
     shape = LS(T, d_in, d_out, 2, 2, 1, 1.0, "bf16")
     _, dev = util.make_case(shape, seed=32, condition=False)
@@ -176,7 +177,8 @@ def test_base_gemm_k_loop_edges(T, d_out, d_in):
 # accumulate = 1 in each tile shape: the old output is read, added in fp32 and rounded once; ranks whose last
 # extension K tile is a half (N*r % 64 <= 32) and a whole one
 @pytest.mark.parametrize("N,r", [(28, 8), (7, 8)], ids=["half-tile", "whole-tile"])
-@pytest.mark.parametrize("T,d_out", [(2600, 4104), (1300, 4104), (300, 264)], ids=["256x256", "256x128", "128x128"])
+@pytest.mark.parametrize("T,d_out", [(2600, 4104), (1300, 4104), (300, 264), (1100, 4104), (1500, 4104), (1700, 4104), (1700, 5128)],
+                         ids=["256x256", "192x128", "128x128", "160x128", "224x128", "256x128", "128x128-two-per-CU"])
 def test_lora_accumulate_in_each_tile_shape(T, d_out, N, r):
     shape = LS(T, 64, d_out, N, r, 2, 2.0, "bf16")
     ops, dev = util.make_case(shape, seed=33, condition=False)
