@@ -261,7 +261,8 @@ int meteora_workspace_regions(int T, int d_in, int d_out, int N, int r, int k, m
     wr("topk_w", pairs * sizeof(float));
     if (!with_packed) {
         if (!dense && !decode3) { wr("wsplit", gate_wsplit_bytes(d_in, N, bf16)); wr("apack", shrink_apack_bytes(d_in, N, r, bf16)); }
-        if (!decode3) wr("btrans", prep_btrans_bytes(d_out, N, r, bf16));
+        if (!decode3 && !(dense && dense_midsplit_splits(T, d_in, d_out, N, r, bf16) > 0))
+            wr("btrans", prep_btrans_bytes(d_out, N, r, bf16));
         if (dense || decode3) wr("wcat", prep_wcat_bytes(d_in, N, r, bf16));
     }
     if (decode3) {
@@ -541,7 +542,8 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
         StageScope sc(ST_PREP, st, tslot);
         const bool pw = !dense && !decode3 && gate_wsplit_bytes(d_in, N, bf16) > 0;
         const bool pa = !dense && !decode3 && shrink_apack_bytes(d_in, N, r, bf16) > 0;
-        const bool pb = !decode3 && prep_btrans_bytes(d_out, N, r, bf16) > 0;
+        const bool mid = dense && dense_midsplit_splits(T, d_in, d_out, N, r, bf16) > 0;   // reads B as it is, like decode
+        const bool pb = !decode3 && !mid && prep_btrans_bytes(d_out, N, r, bf16) > 0;
         METEORA_HIP(launch_prep(W_gate, pw ? pk.wsplit : nullptr, A, pa ? pk.apack : nullptr, pb ? B : nullptr,
                                 pb ? pk.btrans : nullptr, dense || decode3 ? pk.wcat : nullptr, d_in, d_out, N, r, st));
     }
