@@ -641,7 +641,10 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(const GemmArgs a) {
 // the compiler lets the result land in other registers than the accumulator and moves about 100 of them per K tile.
 // The compiler does not know that the statement is an MFMA, so (1) the source states the order of MFMAs, LDS reads
 // and loads itself, group by group between scheduling barriers; (2) nothing but MFMAs touches an accumulator inside
-// the K loop, and mfma_drain() stands between the last MFMA and the first read of a result.
+// the K loop, and mfma_drain() stands between the last MFMA and the first read of a result; (3) the accumulators' first
+// values are written ahead of mfma_start(), two wait states or more before the first MFMA.  What the source cannot state
+// (that the compiler writes no copy of a fragment right in front of an MFMA) tests/test_mfma_waits_host.py checks in the
+// assembly of every instance.
 // ------------------------------------------------------------------------------------------
 template <int MB, int NB, int D>
 __host__ __device__ constexpr int gemm_ring_lds_bytes() {
@@ -774,8 +777,22 @@ struct Frags16 {
 __device__ __forceinline__ void mfma16(f32x4& acc, const bf16x8& w, const bf16x8& x) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(x));
 }
+// The accumulators' first values, in place here: an MFMA may read a register two wait states after another vector
+// instruction has written it (the compiler sees to that for the builtin only).
+template <int MB, int NB>
+__device__ __forceinline__ void mfma_start(f32x4 (&acc)[MB][NB]) {
+#pragma unroll
+    for (int mi = 0; mi < MB; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NB; ni += 2) {
+            acc[mi][ni] = acc[mi][ni + 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+            asm volatile("" : "+a"(acc[mi][ni]), "+a"(acc[mi][ni + 1]));
+        }
+    asm volatile("s_nop 1" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
 // The wait states between an MFMA and another instruction's read of its result (the compiler inserts them for the
-// builtin only; 16x16x32 is 8 passes: at most 11 are required).
+// builtin only; 16x16x32 is 8 passes: at most 12 are required).
 __device__ __forceinline__ void mfma_drain() {
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_nop 15" ::: "memory");
@@ -852,12 +869,6 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
         a.partial = a_in.seg[e].partial;
     }
 
-    f32x4 acc[MB][NB];
-#pragma unroll
-    for (int mi = 0; mi < MB; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < NB; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
-
     // this workgroup's share of the contraction: main K tiles [kt0, kt0 + nk_main) and/or the extension
     int kt0 = 0, nk_main = a.d_in / kGemmBK;
     int nk_ext = a.ext_k > 0 ? a.ext_stride / kGemmBK : 0;
@@ -925,13 +936,13 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
         else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     };
     static_assert(D <= 5, "wait_tiles");
-    if (nk > 0) {
 #pragma unroll
-        for (int t = 0; t < D; ++t)
-            if (t < nk) request_tile(t);
-        wait_tiles(min(nk, D) - 1);
-    }
+    for (int t = 0; t < D; ++t)
+        if (t < nk) request_tile(t);
+    f32x4 acc[MB][NB];
+    mfma_start<MB, NB>(acc);   // while the first tile is on its way
     if (nk > 0) {
+        wait_tiles(min(nk, D) - 1);
 #pragma unroll
         for (int i = 0; i < NR; ++i) load_frag16<MB, NB>(f0, xslot(0), wslot(0), wm, wn, l15, kq, 0, i);
     }
