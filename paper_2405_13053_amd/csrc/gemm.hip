@@ -237,14 +237,22 @@ hipError_t launch_gemm_dense_splitk(const void* x, const void* Wcat, int T, int 
 // range of split s, the 128-column tiles of all of them in one grid, one workgroup per CU at most.  The tiles are up to
 // 256 rows high (a wavefront's 128 x 64 piece needs 0.75 fragment reads per MFMA against 1.0 at 128 x 128), in steps
 // of 32 so that the rows are dealt evenly: 300 tokens are two tiles of 160 rows.  Whole calls, against 256 rows above
-// 128 tokens and 128 (two workgroups per CU) up to there, both with the two-deep ring: 4096 -> 4096 T = 80 23.6 ->
-// 20.2 us, T = 300 40.7 -> 31.6, T = 512 43.0 -> 40.6; 14336 -> 4096 T = 128 58.7 -> 44.4, T = 300 102 -> 69.6.
+// 128 tokens and 128 (two workgroups per CU) up to there, both with the two-deep ring, W not in any cache: 4096 -> 4096
+// T = 80 23.6 -> 20.2 us, T = 300 40.7 -> 31.6, T = 512 43.0 -> 40.6; 14336 -> 4096 T = 128 58.7 -> 44.4, T = 300 102 -> 69.6.
 static int gemm_multi_row_blocks(int T) {
     const int b = ceil_div(ceil_div(T, ceil_div(T, 256)), 32);
     return b < 3 ? 3 : b;
 }
+// One row tile, and so many columns that one workgroup per CU would mean a single split and half of the CUs without one:
+// the splits stay as they are and two workgroups of the two-deep ring share a CU, if there are three splits or more (up
+// to 153 column tiles; with two of them the second workgroup of most CUs is missing).  Whole calls, one against two per
+// CU, at 65 and 128 tokens: 4096 -> 16384 (131 column tiles) 56.0 and 63.2 -> 43.0 and 50.5 us, 4096 -> 18432 56.7 and 64.2
+// -> 45.8 and 55.2, 5120 -> 5120 three times (129) 67.4 and 80.6 -> 55.6 and 69.2, 4096 -> 9216 twice (150) 52.1 and 62.9 ->
+// 47.4 and 58.8; with two splits 4096 -> 9728 twice (158) 55.6 and 66.5 against 57.8 and 69.2, 4096 -> 20480 (163) 59.0 and
+// 65.2 against 58.0 and 66.0.
 int gemm_multi_cap_splits(int T, int col_tiles, int S) {
     const int cap = 256 / (ceil_div(T, 256) * (col_tiles > 0 ? col_tiles : 1));   // 256 CUs
+    if (T <= 128 && cap < 2 && S >= 3) return S;
     return S > cap ? (cap > 0 ? cap : 1) : S;
 }
 
@@ -264,6 +272,8 @@ hipError_t launch_gemm_dense_splitk_multi(const void* x, const DenseOperand* ops
     a.W = a.seg[0].W; a.d_out = a.seg[0].rows; a.partial = a.seg[0].partial;   // replaced per workgroup
     a.tiles_n = tile0;
     if (((uint64_t)T + 256) * ((uint64_t)d_in * 2) >= (1ull << 32)) return hipErrorInvalidValue;
+    if (T <= 128 && tile0 * S > 256)   // two per CU
+        return T <= 96 ? launch_dense<3, 4, 2>(a, stream) : launch_dense<4, 4, 2>(a, stream);
     switch (gemm_multi_row_blocks(T)) {
         case 3: return launch_dense<3, 4, 5>(a, stream);
         case 4: return launch_dense<4, 4, 4>(a, stream);
@@ -317,6 +327,7 @@ hipError_t gemm_init_kernels() {
     lim(&gemm_mfma_ring_kernel<4, 4, 2, kEpiAccumulate>, gemm_ring_lds_bytes<4, 4, 2>());
     lim(&gemm_mfma_ring_kernel<4, 4, 2, kEpiPartial>, gemm_ring_lds_bytes<4, 4, 2>());
     lim(&gemm_mfma_ring_kernel<4, 10, 2, kEpiPartial>, gemm_ring_lds_bytes<4, 10, 2>());
+    lim(&gemm_mfma_ring_kernel<3, 4, 2, kEpiPartial>, gemm_ring_lds_bytes<3, 4, 2>());
     lim(&gemm_mfma_ring_kernel<3, 4, 5, kEpiPartial>, gemm_ring_lds_bytes<3, 4, 5>());
     lim(&gemm_mfma_ring_kernel<4, 4, 4, kEpiPartial>, gemm_ring_lds_bytes<4, 4, 4>());
     lim(&gemm_mfma_ring_kernel<5, 4, 4, kEpiPartial>, gemm_ring_lds_bytes<5, 4, 4>());

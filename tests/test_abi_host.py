@@ -80,6 +80,14 @@ def test_workspace_regions_hold_what_the_launches_write():
         assert regs["dpart"][2] <= regs["dpart"][1]
 
 
+@pytest.mark.parametrize("T", [65, 96, 128])
+@pytest.mark.parametrize("d_out", [16008, 16384, 18432, 19584])
+def test_wide_layers_of_up_to_128_tokens_split_along_k(T, d_out):
+    """From 65 to 128 tokens the projection is cut into three K splits, up to 153 tiles of 128 outputs."""
+    regs = {n: w for n, _, _, w in m.workspace_regions(T, 4096, d_out, 28, 8, 2, "bf16", True)}
+    assert regs["spart"] == 3 * T * d_out * 4
+
+
 def test_init_without_a_device_reports_an_error(lib):
     """meteora_init is host code around HIP calls: on a machine with no GPU it returns an error code, it does not
     abort; with a GPU it succeeds and may be repeated."""

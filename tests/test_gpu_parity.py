@@ -379,6 +379,9 @@ DENSE_ROUTE_SHAPES = [
     LS(289, 1024, 1032, 28, 8, 2, 2.0, "bf16", "uniform", "T=289-160-rows"),
     LS(161, 576, 264, 28, 8, 2, 2.0, "bf16", "uniform", "T=161-192-rows"),
     LS(577, 1024, 264, 28, 8, 2, 2.0, "bf16", "uniform", "T=577-224-rows"),
+    # so many columns that two workgroups share a CU, tiles of 96 and 128 rows
+    LS(67, 768, 16392, 28, 8, 2, 2.0, "bf16", "uniform", "T=67-two-per-CU"),
+    LS(128, 832, 17416, 28, 16, 2, 2.0, "bf16", "zipf", "T=128-two-per-CU"),
     # the split projection has more K splits (8) than the routing products alone would take (5)
     LS(3000, 4096, 256, 28, 8, 2, 2.0, "bf16", "uniform", "T=3000-narrow-output-more-splits"),
     # 28 adapters of rank 16: 544 rows of Wcat, several column tiles of the routing products
@@ -532,10 +535,11 @@ def _group_case(T, d_in, d_outs, N, r, k, routing, seed):
     (128, 1024, (520, 136, 136), 28, 8, 2, "uniform", True),     # q/k/v-like at T = 128
     (200, 1024, (776, 776), 12, 16, 3, "zipf", True),            # gate/up-like, r = 16, bias, ragged token tile
     (130, 512, (256, 264, 136, 72), 28, 8, 2, "uniform", True),  # four members: eight matrices in one launch
+    (96, 768, (8200, 8192), 28, 8, 2, "uniform", True),          # 135 column tiles: two workgroups per CU
     (300, 512, (256, 264), 28, 8, 2, "uniform", False),          # a few hundred tokens, not packed: member by member
     (2000, 512, (2048, 2048, 2048), 28, 8, 2, "uniform", True),  # too many output tiles for one launch: member by member
 ], ids=["qkv", "gate-up-r16", "four", "unpacked", "T=300", "one", "qkv-T128", "gate-up-T200-r16", "four-T130",
-        "T=300-unpacked", "T=2000"])
+        "T=96-two-per-CU", "T=300-unpacked", "T=2000"])
 def test_group_call_matches_oracle_and_single_calls(T, d_in, d_outs, N, r, k, routing, packed):
     shapes, all_ops, members, x, rows = _group_case(T, d_in, d_outs, N, r, k, routing, seed=50)
     for mb in members:
