@@ -21,6 +21,7 @@
 #include <utility>
 
 #include "common.hpp"
+#include "topk_key.hpp"
 
 namespace meteora {
 
@@ -744,28 +745,42 @@ __device__ __forceinline__ void gemm_epilogue16(const GemmArgs& a, f32x4 (&acc)[
     }
 }
 
-// Which K tiles of the extension hold anything for tokens row0 .. row0 + ROWS - 1: bit e = one of them selected an adapter
-// with columns in tile e.  Uniform over the wavefront.  With a skewed load most adapters are in no token's choice: 2000
-// tokens, 64 adapters of rank 32, top-4, logits falling off as -2 log(j): the layer takes 119 us instead of 130.  (28
-// adapters of rank 8 are four tiles after 64 or more: under 1%.)
+// Which K tiles of the extension hold anything for tokens row0 .. row0 + ROWS - 1: with a skewed load most adapters are in
+// no token's choice.  Where every tile holds something the look at the routing must cost nothing, so the ids, which lie
+// next to each other, are read 16 bytes a lane, all at once and ahead of the first operand tiles, on whose arrival the
+// workgroup waits anyway.  Layers of 4096 -> 4096 without a look, with one id after the other read up front, and so:
+// 4096 tokens, 64 adapters of rank 32, top-4, every tile in use 206.3, 210.4, 206.0 us, logits falling off as -2 log(j)
+// 198.1, 176.3, 172.7; 28 adapters of rank 8, top-8 (four tiles) 123.5, 129.1, 123.9.
 template <int ROWS>
-__device__ __forceinline__ uint64_t ext_tiles_used(const GemmArgs& a, int row0, int lane) {
-    uint64_t mine = 0;
+struct ExtIds {
+    static constexpr int P = ROWS * kMaxTopK / 256;   // pieces of 4 ids per lane
+    u32x4 v[P];
+    int n;
+    __device__ __forceinline__ void load(const GemmArgs& a, int row0, int lane) {
+        n = min(ROWS, a.T - row0) * a.topk;
+        const __amdgpu_buffer_rsrc_t ids = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<int32_t*>(a.topk_idx) + (size_t)row0 * a.topk, 0, (uint32_t)n * 4, 0x00020000);
 #pragma unroll
-    for (int i = 0; i < ROWS; i += 64) {
-        const int t = row0 + i + lane;
-        if (i + lane < ROWS && t < a.T) {
-            for (int s = 0; s < a.topk; ++s) {
-                const int ad = a.topk_idx[(size_t)t * a.topk + s], c = ad * a.rank;
-                if (ad >= 0 && c < a.ext_k) mine |= (1ull << (c / kGemmBK)) | (1ull << ((c + a.rank - 1) / kGemmBK));
-            }
-        }
+        for (int i = 0; i < P; ++i)   // the last piece again past the end (fewer than 4 ids: zeros)
+            v[i] = __builtin_amdgcn_raw_buffer_load_b128(ids, max(min((i * 64 + lane) * 16, n * 4 - 16), 0), 0, 0);
     }
-    uint64_t used = 0;
-    for (int e = 0; e * kGemmBK < a.ext_k; ++e)
-        if (__ballot((int)((mine >> e) & 1)) != 0) used |= 1ull << e;
-    return used;
-}
+    // Bit e = one of the tokens selected an adapter with columns in tile e (or an id outside [0, N) that shares its low
+    // bits with such a one: that tile is multiplied for nothing).  Uniform over the wavefront.
+    __device__ __forceinline__ uint64_t used(const GemmArgs& a, int lane) const {
+        uint64_t mine = 0;   // adapters
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            if (i * 256 >= n) break;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) mine |= 1ull << (v[i][j] & (kMaxAdapters - 1));
+        }
+        const uint64_t all = (uint64_t)wave_or((uint32_t)(mine >> 32)) << 32 | wave_or((uint32_t)mine);
+        // lane = tile: its columns belong to adapters lo to hi (the halves keep the quotients clear of whole numbers)
+        const float inv = 1.f / (float)a.rank;
+        const int lo = min((int)((lane * kGemmBK + 0.5f) * inv), 63), hi = min((int)((lane * kGemmBK + 63.5f) * inv), 63);
+        return __ballot(lane * kGemmBK < a.ext_k && (all >> lo << lo & ~0ull >> (63 - hi)) != 0);
+    }
+};
 
 // Fragments of one k-step of 32 for a wavefront's MB x NB blocks of 16 x 16: lane l holds row (l & 15), k chunk l >> 4.
 template <int MB, int NB>
@@ -882,28 +897,15 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
             nk_main = 0;
         }
     }
-    // the extension's K tiles: all of them, or those that hold anything for this workgroup's tokens
-    uint64_t ext_left = nk_ext >= 64 ? ~0ull : (1ull << nk_ext) - 1;
-    if (EPI != kEpiPartial && nk_ext > 0 && a.topk_idx != nullptr) {   // uniform
-        ext_left &= ext_tiles_used<BM>(a, m0, lane);
-    }
-    // the last extension tile may hold data in its first k-step only (28 adapters of rank 8: 224 of 256 columns;
-    // the rest is zero padding): that k-step is all it gets
-    const bool half_last = nk_ext > 0 && ((a.ext_k - 1) % kGemmBK) < kGemmBK / 2 && (ext_left >> (nk_ext - 1) & 1) != 0;
-    nk_ext = __popcll(ext_left);
-    const int nk = nk_main + nk_ext;
+    const bool look = EPI != kEpiPartial && nk_ext > 0 && a.topk_idx != nullptr;   // uniform
+    ExtIds<BM> ids;
+    if (look) ids.load(a, m0, lane);
 
     const DmaOperand ox = dma_operand(a.x, a.T, a.d_in, m0, wave, lane);
     const DmaOperand ow = dma_operand(a.W, a.d_out, a.d_in, n0, wave, lane);
     const DmaOperand oh = dma_operand(a.hd, nk_ext > 0 ? a.T : 0, a.ext_stride, m0, wave, lane);
     const DmaOperand ob = dma_operand(a.Bt, nk_ext > 0 ? a.d_out : 0, a.ext_stride, n0, wave, lane);
 
-    // tiles are requested in order: the K tile of the extension that comes next
-    auto next_ext = [&]() {
-        const int e = __ffsll((unsigned long long)ext_left) - 1;
-        ext_left &= ext_left - 1;
-        return e;
-    };
     auto xslot = [&](int it) { return smem + (it % D) * kXElems; };
     auto wslot = [&](int it) { return smem + D * kXElems + (it % (D + 1)) * kWElems; };
     // piece i of the x-like / W-like operand of K tile kt of the main operands or of the extension
@@ -915,16 +917,41 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
         if constexpr (decltype(is_ext)::value) dma_piece(slot, ob, kt, i, wave);
         else dma_piece(slot, ow, kt, i, wave);
     };
-    auto request_tile = [&](int it) {
-        auto go = [&](int kt, auto is_ext) {
+    auto request_tile = [&](int it, int kt, auto is_ext) {
 #pragma unroll
-            for (int i = 0; i < PX; ++i) request_x(xslot(it), kt, i, is_ext);
+        for (int i = 0; i < PX; ++i) request_x(xslot(it), kt, i, is_ext);
 #pragma unroll
-            for (int i = 0; i < PW; ++i) request_w(wslot(it), kt, i, is_ext);
-        };
-        if (it < nk_main) go(kt0 + it, std::false_type{});
-        else go(next_ext(), std::true_type{});
+        for (int i = 0; i < PW; ++i) request_w(wslot(it), kt, i, is_ext);
     };
+    // the extension's K tiles: all of them, or those that hold anything for this workgroup's tokens
+    uint64_t ext_left = nk_ext >= 64 ? ~0ull : (1ull << nk_ext) - 1;
+    f32x4 acc[MB][NB];
+    if (nk_main >= D) {   // each branch looks by itself: where they meet, the compiler waits for every load
+#pragma unroll
+        for (int t = 0; t < D; ++t) request_tile(t, kt0 + t, std::false_type{});
+        mfma_start<MB, NB>(acc);   // while the first tile is on its way
+        if (look) ext_left &= ids.used(a, lane);
+    } else {
+#pragma unroll
+        for (int t = 0; t < D - 1; ++t)
+            if (t < nk_main) request_tile(t, kt0 + t, std::false_type{});
+        mfma_start<MB, NB>(acc);
+        if (look) ext_left &= ids.used(a, lane);
+    }
+    // the last extension tile may hold data in its first k-step only (28 adapters of rank 8: 224 of 256 columns;
+    // the rest is zero padding): that k-step is all it gets
+    const bool half_last = nk_ext > 0 && ((a.ext_k - 1) % kGemmBK) < kGemmBK / 2 && (ext_left >> (nk_ext - 1) & 1) != 0;
+    nk_ext = __popcll(ext_left);
+    const int nk = nk_main + nk_ext;
+    // tiles are requested in order: the K tile of the extension that comes next
+    auto next_ext = [&]() {
+        const int e = __ffsll((unsigned long long)ext_left) - 1;
+        ext_left &= ext_left - 1;
+        return e;
+    };
+#pragma unroll
+    for (int t = 0; t < D; ++t)
+        if (t >= nk_main && t < nk) request_tile(t, next_ext(), std::true_type{});
 
     Frags16<MB, NB> f0, f1;
     // tile t is needed next: the loads of at most `left` tiles, requested after it, may still be in flight
@@ -936,11 +963,6 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
         else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     };
     static_assert(D <= 5, "wait_tiles");
-#pragma unroll
-    for (int t = 0; t < D; ++t)
-        if (t < nk) request_tile(t);
-    f32x4 acc[MB][NB];
-    mfma_start<MB, NB>(acc);   // while the first tile is on its way
     if (nk > 0) {
         wait_tiles(min(nk, D) - 1);
 #pragma unroll

@@ -43,6 +43,17 @@ __device__ __forceinline__ uint32_t group_max(uint32_t v, int lane) {
     }
 }
 
+// Bitwise or over the lanes of a wavefront, known to all of them.
+__device__ __forceinline__ uint32_t wave_or(uint32_t v) {
+    v |= dpp<kDppRowShr + 1>(v);
+    v |= dpp<kDppRowShr + 2>(v);
+    v |= dpp<kDppRowShr + 4>(v);
+    v |= dpp<kDppRowShr + 8>(v);
+    v |= dpp<kDppBcast15>(v);
+    v |= dpp<kDppBcast31>(v);
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
 // A token's NP (32 or 64) logit columns sit in NP adjacent lanes (col = lane % NP), so a wavefront ranks
 // 64/NP tokens per group and G interleaved groups (their latencies overlap).  g[i] is this lane's
 // logit of group i (lanes col >= N are padding; -0 must already be +0).  Selecting k adapters is k maxima over the NP

@@ -206,6 +206,37 @@ def test_lora_with_unused_adapters(N, r, used):
     assert util.rel_max_err(out, ref) <= util.tol(shape)
 
 
+# The fewest K tiles the extension can have, lora_forward being nothing else: a lone half tile (28 adapters of rank 8, all
+# tokens on the last; 4 adapters), and none at all for whole row tiles whose tokens name no adapter (ids outside [0, N));
+# any integer as an id; token counts that end inside a 16-byte piece of the ids.
+@pytest.mark.parametrize("T,N,r,k,pick", [(301, 28, 8, 1, "last"), (99, 4, 8, 2, "any"), (703, 28, 8, 1, "none-first"),
+                                          (703, 28, 8, 3, "any-int-first"), (2601, 64, 32, 8, "any-int-first"),
+                                          (389, 28, 12, 5, "none-first"), (65, 28, 8, 1, "any")])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_lora_with_a_lone_half_tile_or_none(T, N, r, k, pick, accumulate):
+    d_in, d_out = 128, 4104 if T > 2000 else 264
+    shape = LS(T, d_in, d_out, N, r, k, 2.0, "bf16")
+    ops, dev = util.make_case(shape, seed=36, condition=False)
+    rng = np.random.default_rng(7)
+    idx = np.argsort(rng.random((T, N)), 1)[:, :k].astype(np.int32)
+    if pick == "last":
+        idx[:] = N - 1
+    w = rng.uniform(0.2, 0.8, (T, k)).astype(np.float32)
+    old = torch.randn((T, d_out), device="cuda", generator=torch.Generator(device="cuda").manual_seed(5)).bfloat16()
+    given, counts = idx.copy(), w.copy()
+    nobody = 256 if pick.endswith("first") else 0
+    outside = [N, -1, 2**31 - 1] + ([-2**31, 64, 2**26] if pick == "any-int-first" else [])
+    given[:nobody] = np.resize(np.array(outside, np.int32), (nobody, k))
+    counts[:nobody] = 0
+    out = m.lora_forward(dev["x"], dev["A"], dev["B"], torch.from_numpy(given).cuda(), torch.from_numpy(w).cuda(), 2.0,
+                         out=old.clone(), accumulate=accumulate)
+    ref = oracle.lora_delta(ops["x"], ops["A"], ops["B"], idx, counts.astype(np.float64), 2.0)
+    if accumulate:
+        ref = ref + old.double().cpu().numpy()
+    assert torch.equal(out[:nobody], old[:nobody] if accumulate else torch.zeros_like(old[:nobody]))
+    assert util.rel_max_err(out, ref) <= util.tol(shape)
+
+
 # lora_forward on a given routing on either side of the rule between products of every adapter and bucket lists (T = 64,
 # 1024, 4096 tokens; N*r = 256), with ids outside [0, N), accumulate on and off.
 @pytest.mark.parametrize("T,d_in,N,r,k", [(64, 128, 28, 8, 2), (65, 128, 28, 8, 2), (1024, 192, 28, 16, 1), (1025, 192, 28, 16, 1),
