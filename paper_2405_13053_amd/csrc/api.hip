@@ -274,7 +274,9 @@ int meteora_workspace_regions(int T, int d_in, int d_out, int N, int r, int k, m
             wr("dpart", (size_t)gemm_dense_splits(T, d_in, CR) * T * CR * sizeof(float));
             wr("hdense", (size_t)T * L.ext_stride * sizeof(uint16_t));
         }
-    } else if (bf16) {   // fp32 storage needs no more
+    } else if (!bf16) {
+        wr("h32", f32_expand_apart(d_out, r, k) ? pairs * r * sizeof(float) : 0);
+    } else {
         wr("partials", (size_t)gate_kslices(d_in, bf16) * T * NP * sizeof(float));
         const bool fused = gemm_fuses_expand(bf16);
         if (fused) wr("hdense", (size_t)T * L.ext_stride * sizeof(uint16_t));
@@ -607,7 +609,8 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
         }
         StageScope sc(ST_EXPAND, st, tslot);
         METEORA_HIP(launch_route_lora_f32((const float*)x, W_gate, gate_bias, (const float*)A, (const float*)B, T, d_in,
-                                          d_out, N, r, k, inv_temperature, scale, idx, w, (float*)out, st));
+                                          d_out, N, r, k, inv_temperature, scale, idx, w, (float*)out,
+                                          at<float>(ws, L.h32), st));
         return METEORA_OK;
     }
     {

@@ -139,7 +139,9 @@ hipError_t launch_expand(const float* h32, const void* B, const int32_t* topk_id
 hipError_t launch_gemm_f32(const float* x, const float* W, int T, int d_in, int d_out, float* out, hipStream_t stream);
 hipError_t launch_route_lora_f32(const float* x, const float* W_gate, const float* bias, const float* A, const float* B,
                                  int T, int d_in, int d_out, int N, int r, int k, float inv_temperature, float scale,
-                                 int32_t* topk_idx, float* topk_w, float* out, hipStream_t stream);
+                                 int32_t* topk_idx, float* topk_w, float* out, float* h /*[T,k,r], if apart*/,
+                                 hipStream_t stream);
+bool f32_expand_apart(int d_out, int r, int k);   // the expand is a launch of its own and h is used
 
 constexpr int kMaxDecodeGroup = 4;
 struct DecodeMember {

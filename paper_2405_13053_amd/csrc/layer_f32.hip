@@ -124,13 +124,13 @@ hipError_t launch_gemm_f32(const float* x, const float* W, int T, int d_in, int 
 // (a few hundred inputs and outputs) each of these steps is a microsecond of memory latency; as launches of their own
 // (gate logits, top-k, bucket scatter, shrink, expand) they took 4 to 7 us each.  Measured, whole layer, 28 adapters of
 // rank 8, top-2: 64 x 256 -> 256 (4 adapters) 52.4 -> 15.5 us, 300 x 512 -> 768 91 -> 24, 4096 x 4096 -> 4096 without the
-// projection 745 -> 360.
+// projection 745 -> 360.  Wide outputs get the expand as a launch of its own, see below.
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kRowThreads) void route_lora_f32_kernel(
     const float* __restrict__ x, const float* __restrict__ W_gate, const float* __restrict__ bias,
     const float* __restrict__ A, const float* __restrict__ B, int d_in, int d_out, int N, int gate_cols, int r, int k,
     int h_cols, float inv_temperature, float scale, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
-    float* __restrict__ out) {
+    float* __restrict__ out, float* __restrict__ h_out) {
     __shared__ float red[4][kMaxAdapters];
     __shared__ int sel_idx[kMaxTopK];
     __shared__ float sel_w[kMaxTopK];
@@ -174,6 +174,10 @@ __global__ __launch_bounds__(kRowThreads) void route_lora_f32_kernel(
         }
         __syncthreads();
     }
+    if (h_out != nullptr) {   // expand_f32_kernel follows
+        for (int i = threadIdx.x; i < kr; i += kRowThreads) h_out[(size_t)t * kr + i] = hs[i];
+        return;
+    }
     for (int c = threadIdx.x; c < d_out; c += kRowThreads) {
         float acc = out[(size_t)t * d_out + c];
         for (int slot = 0; slot < k; ++slot) {
@@ -193,12 +197,66 @@ __global__ __launch_bounds__(kRowThreads) void route_lora_f32_kernel(
     }
 }
 
+// The expand of the same as a launch of its own: a wavefront adds to 256 columns of a token, and the tokens of one stretch
+// of columns come before the next stretch, so that the workgroups under way share the N * r KB of B that belong to one.
+__global__ __launch_bounds__(256) void expand_f32_kernel(const float* __restrict__ h, const float* __restrict__ B,
+                                                         const int32_t* __restrict__ topk_idx, int T, int d_out, int r,
+                                                         int k, float* __restrict__ out) {
+    __shared__ __attribute__((aligned(16))) float hs[4][kMaxTopK * kMaxRank];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, blocks = ceil_div(T, 4);
+    const int stretch = blockIdx.x / blocks;
+    const int t = min((int)(blockIdx.x - stretch * blocks) * 4 + wave, T - 1);   // the last token again past the end
+    const int c = stretch * 256 + lane * 4, kr = k * r;
+    for (int i = lane; i < kr; i += 64) hs[wave][i] = h[(size_t)t * kr + i];
+    __syncthreads();
+    if (c >= d_out || (int)(blockIdx.x - stretch * blocks) * 4 + wave >= T) return;
+    f32x4* o = reinterpret_cast<f32x4*>(out + (size_t)t * d_out + c);
+    f32x4 acc = *o;
+    for (int slot = 0; slot < k; ++slot) {
+        const int a = __builtin_amdgcn_readfirstlane(topk_idx[(size_t)t * k + slot]);
+        const float* Ba = B + (size_t)a * r * d_out + c;
+        f32x4 d = {0.f, 0.f, 0.f, 0.f};
+        for (int q0 = 0; q0 < r; q0 += 8) {   // 8 rows of B in flight
+            f32x4 b[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) b[u] = *reinterpret_cast<const f32x4*>(Ba + (size_t)min(q0 + u, r - 1) * d_out);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (q0 + u < r) {
+                    const float hv = hs[wave][slot * r + q0 + u];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) d[j] = fmaf(hv, b[u][j], d[j]);
+                }
+        }
+        acc += d;
+    }
+    *o = acc;
+}
+
+// Bound by B from L2.  In the launch of everything a workgroup walks the k * r rows of its token at columns of its own, so
+// that with many tokens the whole of B is in use at a time; where a thread of it has a single column, or few rows to
+// walk, the second launch costs more than it saves.  Whole layer, without and with it: 28 adapters of rank 64, top-8, 256
+// -> 4096 64 tokens 816 -> 119 us, 1024 1032 -> 627, 4096 3344 -> 1408 (bucketed: 2546); rank 8, top-2, 256 -> 4096 64 tokens
+// 43 -> 19, 4096 213 -> 177; 512 -> 768 (6 groups of 8 rows per thread) 64 tokens 20.2 against 18.7, 4096 103.4 against
+// 104.8; 256 -> 264, 12 adapters of rank 16, top-3 (6.2 groups) 5000 tokens 75.2 against 78.0; 256 -> 256 64 tokens 10.5
+// against 13.8, with 64 adapters of rank 32, top-4, 31.2 against 34.5.
+bool f32_expand_apart(int d_out, int r, int k) {
+    return d_out > kRowThreads && (int64_t)d_out * k * ceil_div(r, 8) >= 8 * kRowThreads;
+}
+
 hipError_t launch_route_lora_f32(const float* x, const float* W_gate, const float* bias, const float* A, const float* B,
                                  int T, int d_in, int d_out, int N, int r, int k, float inv_temperature, float scale,
-                                 int32_t* topk_idx, float* topk_w, float* out, hipStream_t stream) {
+                                 int32_t* topk_idx, float* topk_w, float* out, float* h, hipStream_t stream) {
+    const bool apart = f32_expand_apart(d_out, r, k);
+    const int64_t blocks = ceil_div64(d_out, 256) * ceil_div64(T, 4);
+    if (apart && (h == nullptr || blocks > INT32_MAX)) return hipErrorInvalidValue;
     const int h_cols = k * r >= 64 ? 64 : pow2_at_least(k * r);
     route_lora_f32_kernel<<<T, kRowThreads, 0, stream>>>(x, W_gate, bias, A, B, d_in, d_out, N, pow2_at_least(N), r, k,
-                                                         h_cols, inv_temperature, scale, topk_idx, topk_w, out);
+                                                         h_cols, inv_temperature, scale, topk_idx, topk_w, out,
+                                                         apart ? h : nullptr);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !apart) return e;
+    expand_f32_kernel<<<(unsigned)blocks, 256, 0, stream>>>(h, B, topk_idx, T, d_out, r, k, out);
     return hipGetLastError();
 }
 

@@ -88,6 +88,14 @@ def test_wide_layers_of_up_to_128_tokens_split_along_k(T, d_out):
     assert regs["spart"] == 3 * T * d_out * 4
 
 
+def test_fp32_layers_with_wide_outputs_expand_in_a_launch_of_their_own():
+    """It reads scale * w * h of every token from the workspace; narrow outputs and few ranks per token stay in one launch."""
+    def apart(d_out, r, k):
+        return {n: w for n, _, _, w in m.workspace_regions(4096, 256, d_out, 28, r, k, "f32")}["h32"] == 4096 * k * r * 4
+    assert apart(4096, 64, 8) and apart(1024, 8, 2) and apart(264, 64, 8)
+    assert not apart(256, 64, 8) and not apart(768, 8, 2) and not apart(264, 16, 3)
+
+
 def test_init_without_a_device_reports_an_error(lib):
     """meteora_init is host code around HIP calls: on a machine with no GPU it returns an error code, it does not
     abort; with a GPU it succeeds and may be repeated."""

@@ -277,6 +277,8 @@ LAYER_SHAPES = [
     LS(9, 72, 1032, 64, 64, 8, 0.5, "f32", "zipf", "f32-N64-r64-k8"),
     LS(517, 24, 552, 28, 8, 2, 2.0, "f32", "uniform", "f32-32x32-tiles-half-K-step"),
     LS(1537, 40, 2056, 5, 8, 2, 2.0, "f32", "zipf", "f32-128x128-tiles"),
+    LS(2049, 72, 2056, 28, 64, 4, 0.5, "f32", "zipf", "f32-expand-apart"),
+    LS(7, 40, 1288, 9, 5, 8, 0.5, "f32", "uniform", "f32-expand-apart-r5"),
     LS(100, 512, 256, 28, 8, 1, 2.0, "bf16", "uniform", "top1"),
 ]
 
