@@ -150,8 +150,9 @@ static hipError_t launch_tiles(GemmArgs a, hipStream_t stream) {
     a.tiles_m = ceil_div(a.T, MB * 32);
     a.tiles_n = ceil_div(a.d_out, NB * 32);
     constexpr int smem = gemm_ring_lds_bytes<MB, NB, D>();
-    return a.accumulate ? launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiAccumulate>, a, smem, 1, stream)
-                        : launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore>, a, smem, 1, stream);
+    if (a.accumulate) return launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiAccumulate, true>, a, smem, 1, stream);
+    return a.topk_idx != nullptr ? launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, true>, a, smem, 1, stream)
+                                 : launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, false>, a, smem, 1, stream);
 }
 
 // The same without the ring: any d_in, any size.
@@ -219,7 +220,7 @@ template <int MB, int NB, int D>
 static hipError_t launch_dense(GemmArgs a, hipStream_t stream) {   // fp32 split-K tiles; tiles_n is the caller's
     a.tiles_m = ceil_div(a.T, MB * 32);
     if (a.tiles_n == 0) a.tiles_n = ceil_div(a.d_out, NB * 32);
-    return launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiPartial>, a, gemm_ring_lds_bytes<MB, NB, D>(), a.splits, stream);
+    return launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiPartial, false>, a, gemm_ring_lds_bytes<MB, NB, D>(), a.splits, stream);
 }
 
 hipError_t launch_gemm_dense_splitk(const void* x, const void* Wcat, int T, int d_in, int rows, float* partial,
@@ -311,29 +312,29 @@ hipError_t gemm_init_kernels() {
     lim(&gemm_mfma_kernel<2, 2>, gemm_lds_bytes<2, 2>());
     lim(&gemm_mfma_kernel<1, 1>, gemm_lds_bytes<1, 1>());
     lim(&gemm_mfma_dma_kernel<1, 1>, gemm_lds_bytes<1, 1>());
-    lim(&gemm_mfma_ring_kernel<8, 8, 2, kEpiStore>, gemm_ring_lds_bytes<8, 8, 2>());
-    lim(&gemm_mfma_ring_kernel<8, 8, 2, kEpiAccumulate>, gemm_ring_lds_bytes<8, 8, 2>());
-    lim(&gemm_mfma_ring_kernel<8, 4, 3, kEpiStore>, gemm_ring_lds_bytes<8, 4, 3>());
-    lim(&gemm_mfma_ring_kernel<8, 4, 3, kEpiAccumulate>, gemm_ring_lds_bytes<8, 4, 3>());
-    lim(&gemm_mfma_ring_kernel<7, 4, 3, kEpiStore>, gemm_ring_lds_bytes<7, 4, 3>());
-    lim(&gemm_mfma_ring_kernel<7, 4, 3, kEpiAccumulate>, gemm_ring_lds_bytes<7, 4, 3>());
-    lim(&gemm_mfma_ring_kernel<6, 4, 3, kEpiStore>, gemm_ring_lds_bytes<6, 4, 3>());
-    lim(&gemm_mfma_ring_kernel<6, 4, 3, kEpiAccumulate>, gemm_ring_lds_bytes<6, 4, 3>());
-    lim(&gemm_mfma_ring_kernel<5, 4, 4, kEpiStore>, gemm_ring_lds_bytes<5, 4, 4>());
-    lim(&gemm_mfma_ring_kernel<5, 4, 4, kEpiAccumulate>, gemm_ring_lds_bytes<5, 4, 4>());
-    lim(&gemm_mfma_ring_kernel<4, 4, 4, kEpiStore>, gemm_ring_lds_bytes<4, 4, 4>());
-    lim(&gemm_mfma_ring_kernel<4, 4, 4, kEpiAccumulate>, gemm_ring_lds_bytes<4, 4, 4>());
-    lim(&gemm_mfma_ring_kernel<4, 4, 2, kEpiStore>, gemm_ring_lds_bytes<4, 4, 2>());
-    lim(&gemm_mfma_ring_kernel<4, 4, 2, kEpiAccumulate>, gemm_ring_lds_bytes<4, 4, 2>());
-    lim(&gemm_mfma_ring_kernel<4, 4, 2, kEpiPartial>, gemm_ring_lds_bytes<4, 4, 2>());
-    lim(&gemm_mfma_ring_kernel<4, 10, 2, kEpiPartial>, gemm_ring_lds_bytes<4, 10, 2>());
-    lim(&gemm_mfma_ring_kernel<3, 4, 2, kEpiPartial>, gemm_ring_lds_bytes<3, 4, 2>());
-    lim(&gemm_mfma_ring_kernel<3, 4, 5, kEpiPartial>, gemm_ring_lds_bytes<3, 4, 5>());
-    lim(&gemm_mfma_ring_kernel<4, 4, 4, kEpiPartial>, gemm_ring_lds_bytes<4, 4, 4>());
-    lim(&gemm_mfma_ring_kernel<5, 4, 4, kEpiPartial>, gemm_ring_lds_bytes<5, 4, 4>());
-    lim(&gemm_mfma_ring_kernel<6, 4, 3, kEpiPartial>, gemm_ring_lds_bytes<6, 4, 3>());
-    lim(&gemm_mfma_ring_kernel<7, 4, 3, kEpiPartial>, gemm_ring_lds_bytes<7, 4, 3>());
-    lim(&gemm_mfma_ring_kernel<8, 4, 3, kEpiPartial>, gemm_ring_lds_bytes<8, 4, 3>());
+#define METEORA_RING(MB, NB, D, EPI, LOOK) lim(&gemm_mfma_ring_kernel<MB, NB, D, EPI, LOOK>, gemm_ring_lds_bytes<MB, NB, D>())
+#define METEORA_TILES(MB, NB, D)                   \
+    METEORA_RING(MB, NB, D, kEpiStore, false);     \
+    METEORA_RING(MB, NB, D, kEpiStore, true);      \
+    METEORA_RING(MB, NB, D, kEpiAccumulate, true)
+    METEORA_TILES(8, 8, 2);
+    METEORA_TILES(8, 4, 3);
+    METEORA_TILES(7, 4, 3);
+    METEORA_TILES(6, 4, 3);
+    METEORA_TILES(5, 4, 4);
+    METEORA_TILES(4, 4, 3);
+    METEORA_TILES(4, 4, 2);
+    METEORA_RING(4, 10, 2, kEpiPartial, false);
+    METEORA_RING(4, 4, 2, kEpiPartial, false);
+    METEORA_RING(3, 4, 2, kEpiPartial, false);
+    METEORA_RING(3, 4, 5, kEpiPartial, false);
+    METEORA_RING(4, 4, 4, kEpiPartial, false);
+    METEORA_RING(5, 4, 4, kEpiPartial, false);
+    METEORA_RING(6, 4, 3, kEpiPartial, false);
+    METEORA_RING(7, 4, 3, kEpiPartial, false);
+    METEORA_RING(8, 4, 3, kEpiPartial, false);
+#undef METEORA_TILES
+#undef METEORA_RING
     return e;
 }
 
@@ -365,7 +366,7 @@ hipError_t launch_gemm(const void* x, const void* W, int T, int d_in, int d_out,
         if (T > 128 && big_tiles >= 160 && !(big_tiles > 256 && big_tiles <= 328))
             return dma_ok(a, 256, 256) ? launch_tiles<8, 8, 2>(a, stream) : launch_plain<4>(a, stream);
         if (T > 64 && !dma_ok(a, 256, 128)) return launch_plain<2>(a, stream);
-        // otherwise tiles of 128 columns, one per CU, as low as that allows, with the deepest ring that fits: more CUs
+        // otherwise tiles of 128 columns, one per CU, as low as that allows, with a ring that is as deep as helps: more CUs
         // busy and less padding than at 256 rows (a wavefront's 128 x 64 piece has 0.75 fragment reads per MFMA, a 64 x
         // 64 piece 1.0, so not lower than needed).  The GEMM inside the layer against 256-row
         // tiles (or two 128-row tiles per CU) with shallower rings: 4096 -> 4096 T = 1000 44.8 -> 41.3 us, 1280 59.1 ->
@@ -374,7 +375,13 @@ hipError_t launch_gemm(const void* x, const void* W, int T, int d_in, int d_out,
         const int row_tiles = 256 / ceil_div(d_out, 128);
         if (T > 64 && row_tiles > 0) {
             switch (ceil_div(ceil_div(T, row_tiles), 32)) {
-                case 1: case 2: case 3: case 4: return launch_tiles<4, 4, 4>(a, stream);
+                case 1: case 2: case 3: case 4:
+                    // three tiles ahead cover a load from HBM (four cost the start of the kernel more than they save); up
+                    // to 8 K tiles that start is most of it, and two are enough.  Two, three and four tiles, W in cache and
+                    // out of it: 65 x 512 -> 1024 6.8, 6.4, 6.8 and 6.5, 6.5, 7.0 us; 65 x 1024 -> 1024 8.6, 9.0, 9.3 and
+                    // 9.2, 9.0, 9.5; 65 x 4096 -> 1024 23.8, 24.2, 24.5 and 35.2, 30.9, 31.3
+                    return (a.d_in + (a.ext_k > 0 ? a.ext_stride : 0)) / kGemmBK <= 8 ? launch_tiles<4, 4, 2>(a, stream)
+                                                                                      : launch_tiles<4, 4, 3>(a, stream);
                 case 5: return launch_tiles<5, 4, 4>(a, stream);
                 case 6: return launch_tiles<6, 4, 3>(a, stream);
                 case 7: return launch_tiles<7, 4, 3>(a, stream);

@@ -851,7 +851,9 @@ __device__ __forceinline__ void load_frag16(Frags16<MB, NB>& f, const bf16_t* xs
     }
 }
 
-template <int MB, int NB, int D, int EPI>
+// LOOK: whether the kernel looks for empty tiles of the extension.  The base projection and the backward pass have a
+// kernel without: the code alone, not run, costs a short call with cold weights 0.8 us (65 x 1024 -> 4096 11.5 against 10.6).
+template <int MB, int NB, int D, int EPI, bool LOOK>
 __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in) {
     GemmArgs a = a_in;
     constexpr int BM = MB * 32, BN = NB * 32;   // 2 x 2 wavefronts of MB x NB blocks of 16 x 16
@@ -897,7 +899,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
             nk_main = 0;
         }
     }
-    const bool look = EPI != kEpiPartial && nk_ext > 0 && a.topk_idx != nullptr;   // uniform
+    const bool look = LOOK && nk_ext > 0 && a.topk_idx != nullptr;   // uniform
     ExtIds<BM> ids;
     if (look) ids.load(a, m0, lane);
 
@@ -926,12 +928,13 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
     // the extension's K tiles: all of them, or those that hold anything for this workgroup's tokens
     uint64_t ext_left = nk_ext >= 64 ? ~0ull : (1ull << nk_ext) - 1;
     f32x4 acc[MB][NB];
-    if (nk_main >= D) {   // each branch looks by itself: where they meet, the compiler waits for every load
+    if (!LOOK || nk_main >= D) {
 #pragma unroll
-        for (int t = 0; t < D; ++t) request_tile(t, kt0 + t, std::false_type{});
+        for (int t = 0; t < D; ++t)
+            if (LOOK || t < nk_main) request_tile(t, kt0 + t, std::false_type{});
         mfma_start<MB, NB>(acc);   // while the first tile is on its way
         if (look) ext_left &= ids.used(a, lane);
-    } else {
+    } else {   // looks by itself: behind a join of the two branches the compiler would wait for every load
 #pragma unroll
         for (int t = 0; t < D - 1; ++t)
             if (t < nk_main) request_tile(t, kt0 + t, std::false_type{});
@@ -975,19 +978,25 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
         for (int k = k0; k < k1; ++k)
             mfma16(acc[order_mi<MB, NB>(k)][order_ni<MB, NB>(k)], f.w[order_ni<MB, NB>(k)], f.x[order_mi<MB, NB>(k)]);
     };
+    // Where tile `it` lies, outside the unrolled main loop: carried along, since the remainders by D and D + 1 sit between
+    // two tiles (64 K tiles of 128 x 128, one workgroup per CU, D = 4: 27.2 us with them, 24.5 without)
+    int slot_x = 0, slot_w = D * kXElems;
     // REQ: 0 = tile it+D is a main tile, 1 = it is an extension tile, 2 = there is none (last D tiles)
     // PH: it % 6 when it is known at compile time (the unrolled main loop: every slot address is then a
     // constant and no address arithmetic sits between two tiles), -1 otherwise
     auto tile_step = [&](int it, auto req, auto ph) {
         constexpr int REQ = decltype(req)::value, PH = decltype(ph)::value;
         using IsExt = std::integral_constant<bool, REQ == 1>;
-        auto xsl = [&](int d) {   // x-slot / W-slot of tile it + d
+        auto xsl = [&](int d) {   // x-slot / W-slot of tile it + d, d = 0, 1 or D
             if constexpr (PH >= 0) return smem + ((PH + d) % D) * kXElems;
-            else return xslot(it + d);
+            else return smem + (d != 1 ? slot_x : slot_x == (D - 1) * kXElems ? 0 : slot_x + kXElems);
         };
         auto wsl = [&](int d) {
-            if constexpr (PH >= 0) return smem + D * kXElems + ((PH + d) % (D + 1)) * kWElems;
-            else return wslot(it + d);
+            constexpr int first = D * kXElems, last = first + D * kWElems;
+            if constexpr (PH >= 0) return smem + first + ((PH + d) % (D + 1)) * kWElems;
+            else if (d == 0) return smem + slot_w;
+            else if (d == 1) return smem + (slot_w == last ? first : slot_w + kWElems);
+            else return smem + (slot_w == first ? last : slot_w - kWElems);
         };
         const bf16_t* xs = xsl(0);
         const bf16_t* ws = wsl(0);
@@ -1038,6 +1047,10 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
             __builtin_amdgcn_sched_barrier(0);
             mfmas(f1, 0, NM);
         }
+        if constexpr (PH < 0) {
+            slot_x = (int)(xn - smem);
+            slot_w = (int)(wnx - smem);
+        }
         __builtin_amdgcn_sched_barrier(0);
     };
     using Req0 = std::integral_constant<int, 0>;
@@ -1079,6 +1092,10 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
             tile_step(it + 4, Req0{}, std::integral_constant<int, 4>{});
             tile_step(it + 5, Req0{}, std::integral_constant<int, 5>{});
         }
+    }
+    if constexpr (MB == 8 && NB == 8 && D == 2) {
+        slot_x = (int)(xslot(it) - smem);
+        slot_w = (int)(wslot(it) - smem);
     }
     for (; it + D < nk_main; ++it) tile_step(it, Req0{}, Rt{});
     for (; it + D < nk; ++it) tile_step(it, std::integral_constant<int, 1>{}, Rt{});

@@ -162,7 +162,7 @@ def test_base_gemm_matches_oracle(T, d_in, d_out, dtype):
 
 # The 16x16x32 kernel at the edges of its K loop (1, 2 and 3 K tiles, one short of and one past an unrolled trip of six,
 # a trip and a remainder) in each of its tile shapes, ragged in both directions.
-@pytest.mark.parametrize("d_in", [64, 128, 192, 448, 512, 1088])
+@pytest.mark.parametrize("d_in", [64, 128, 192, 448, 512, 576, 1088, 1152])
 @pytest.mark.parametrize("T,d_out", [(2600, 4104), (1300, 4104), (300, 264), (1100, 4104), (1500, 4104), (1700, 4104), (1700, 5128)],
                          ids=["256x256", "192x128", "128x128", "160x128", "224x128", "256x128", "128x128-two-per-CU"])
 def test_base_gemm_k_loop_edges(T, d_out, d_in):
