@@ -324,21 +324,25 @@ def linear_forward_group(x, members, k: int, scale: float, ws: Optional[torch.Te
         if out is None:
             out = torch.empty((T, d_out), dtype=dtype, device=x.device)
         # written out: as calls of _chk the tests of three members are a quarter of a decode call's host time
-        if not (W.dtype == dtype and A.dtype == dtype and B.dtype == dtype and out.dtype == dtype and Wg.dtype == f32 and
+        if (Wg is None or A is None or B is None or not (
+                W.dtype == dtype and A.dtype == dtype and B.dtype == dtype and out.dtype == dtype and Wg.dtype == f32 and
                 W.shape == (d_out, d_in) and A.shape == (N, d_in, r) and B.shape == (N, r, d_out) and
                 out.shape == (T, d_out) and Wg.shape == (d_in, N) and
                 W.is_cuda and A.is_cuda and B.is_cuda and out.is_cuda and Wg.is_cuda and
                 W.is_contiguous() and A.is_contiguous() and B.is_contiguous() and out.is_contiguous() and
-                Wg.is_contiguous()):
+                Wg.is_contiguous())):
             _chk(W, "W", dtype, (d_out, d_in)); _chk(Wg, "W_gate", f32, (d_in, N))
             _chk(A, "A", dtype, (N, d_in, r)); _chk(B, "B", dtype, (N, r, d_out)); _chk(out, "out", dtype, (T, d_out))
+            pg, pa, pb = _p(Wg) or 0, _p(A) or 0, _p(B) or 0   # the library refuses a missing one
+        else:
+            pg, pa, pb = Wg.data_ptr(), A.data_ptr(), B.data_ptr()
         _chk(bias, "gate_bias", f32, (N,)); _chk(packed, "packed", torch.uint8)
         idx = w = None
         if return_routing:
             idx = torch.empty((T, k), dtype=torch.int32, device=x.device)
             w = torch.empty((T, k), dtype=torch.float32, device=x.device)
-        _MEMBER.pack_into(arr, g * _MEMBER.size, W.data_ptr(), Wg.data_ptr(), _p(bias) or 0, A.data_ptr(), B.data_ptr(),
-                          _p(packed) or 0, packed.numel() if packed is not None else 0, d_out, out.data_ptr(),
+        _MEMBER.pack_into(arr, g * _MEMBER.size, W.data_ptr(), pg, _p(bias) or 0, pa, pb, _p(packed) or 0,
+                          packed.numel() if packed is not None else 0, d_out, out.data_ptr(),
                           _p(idx) or 0, _p(w) or 0)
         keep.append((out, idx, w))
         res.append((out, idx, w) if return_routing else out)

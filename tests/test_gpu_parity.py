@@ -628,6 +628,18 @@ def test_linear_forward_top1(shape):
     assert torch.equal(idx1, idx2) and torch.equal(y1, y2)
 
 
+@pytest.mark.parametrize("missing", ["W_gate", "A", "B"])
+def test_group_call_with_a_missing_tensor_is_refused_by_the_library(missing):
+    """A member without one of its tensors: the library's invalid-argument status, as in the single-layer call."""
+    _, _, members, x, _ = _group_case(33, 1024, (520, 136), 28, 8, 2, "uniform", seed=53)
+    for mb in members:
+        mb["packed"] = m.pack_weights(mb["W_gate"], mb["A"], mb["B"])
+    members[1][missing] = None
+    with pytest.raises(m.MeteoraError) as e:
+        m.linear_forward_group(x, members, 2, 2.0)
+    assert e.value.status == 1
+
+
 def test_group_call_with_temperature():
     """The grouped call passes the temperature on to every member (decode-sized group, two launches)."""
     shapes, all_ops, members, x, rows = _group_case(33, 1024, (520, 136), 28, 8, 2, "uniform", seed=53)
