@@ -267,6 +267,23 @@ def test_lora_given_routing_on_both_paths(T, d_in, N, r, k):
     assert util.rel_max_err(out, ref) <= util.tol(shape)
 
 
+@pytest.mark.parametrize("T,N,r", [(65, 28, 8), (1025, 28, 16)], ids=["dense", "bucketed"])
+def test_lora_adapter_named_twice_counts_in_its_last_slot(T, N, r):
+    shape = LS(T, 192, 136, N, r, 3, 2.0, "bf16")
+    ops, dev = util.make_case(shape, seed=37, condition=False)
+    rng = np.random.default_rng(8)
+    idx = np.argsort(rng.random((T, N)), 1)[:, :3].astype(np.int32)
+    w = rng.uniform(0.2, 0.8, (T, 3)).astype(np.float32)
+    counts = w.copy()
+    idx[::2, 2] = idx[::2, 0]
+    counts[::2, 0] = 0
+    idx[::4, 1] = idx[::4, 0]
+    counts[::4, 1] = 0
+    out = m.lora_forward(dev["x"], dev["A"], dev["B"], torch.from_numpy(idx).cuda(), torch.from_numpy(w).cuda(), 2.0)
+    ref = oracle.lora_delta(ops["x"], ops["A"], ops["B"], idx, counts.astype(np.float64), 2.0)
+    assert util.rel_max_err(out, ref) <= util.tol(shape)
+
+
 # --------------------------------------------------------------------------------- whole layer
 LAYER_SHAPES = [
     LS(64, 256, 256, 4, 8, 2, 2.0, "f32", "uniform", "cfg1"),
@@ -369,8 +386,9 @@ SMALL_BATCH_SHAPES = [
     LS(16, 576, 264, 28, 8, 2, 2.0, "bf16", "uniform", "T=16-half-K-step"),
     LS(17, 1088, 136, 28, 16, 2, 2.0, "bf16", "zipf", "T=17-half-K-step"),
     LS(32, 1600, 1288, 28, 8, 2, 2.0, "bf16", "uniform", "T=32-half-K-step"),
-    # 131 row tiles: runs that cut row tiles at any K step; 258: runs that are longer than a row tile
+    # 131 and 89 row tiles: runs that cut row tiles at any K step; 258: runs that are longer than a row tile
     LS(33, 512, 16384, 28, 8, 2, 2.0, "bf16", "uniform", "T=33-runs"),
+    LS(17, 576, 11008, 28, 8, 2, 2.0, "bf16", "uniform", "T=17-89-row-tiles-runs"),
     LS(5, 512, 32640, 28, 8, 2, 2.0, "bf16", "zipf", "T=5-long-runs"),
 ]
 
@@ -460,6 +478,40 @@ def test_dense_route_exact_ties_and_zero_gate():
             # whenever one of the tied columns is chosen, the lowest of them (2) is among the choices
             assert np.all(has2 | ~((idx == 5) | (idx == 9)).any(axis=1))
             assert np.all(~(idx == 9).any(axis=1) | (idx == 5).any(axis=1))
+
+
+# A bias of -inf masks an adapter; a token whose input is NaN must not disturb the others.  One shape per place that ranks:
+# decode, a few hundred tokens, dense routing, more than 32 adapters, fp32.
+@pytest.mark.parametrize("T,d_in,d_out,N,k,dtype", [(33, 512, 136, 28, 3, "bf16"), (200, 512, 264, 28, 3, "bf16"), (2500, 256, 2056, 28, 3, "bf16"),
+                                                    (300, 256, 136, 64, 8, "bf16"), (40, 256, 136, 64, 3, "f32"), (40, 256, 1288, 12, 8, "f32")])
+def test_masked_adapters_and_a_token_of_nan(T, d_in, d_out, N, k, dtype):
+    shape = LS(T, d_in, d_out, N, 8, k, 2.0, dtype)
+    ops, dev = util.make_case(shape, seed=57, condition=False)
+    bias = np.zeros(N, np.float32)
+    open_ = np.array([1, N // 2, N - 1][:max(1, k - 1)])     # fewer than k adapters are left
+    bias[np.setdiff1d(np.arange(N), open_)] = -np.inf
+    masked = np.setdiff1d(np.arange(N), open_)
+    bias_d = torch.from_numpy(bias).cuda()
+    x = dev["x"].clone()
+    x[T // 2] = float("nan")
+    good = torch.arange(T, device="cuda") != T // 2
+    for xin in (dev["x"], x):
+        rows = good if xin is x else torch.ones_like(good)
+        idx_g, w_g, _ = m.gate_topk(xin, dev["W_gate"], bias_d, k)
+        out, idx, w = m.linear_forward(xin, dev["W"], dev["W_gate"], bias_d, dev["A"], dev["B"], k, 2.0, return_routing=True)
+        for i, wt in ((idx_g, w_g), (idx, w)):
+            i, wt = _np(i[rows]), _np(wt[rows])
+            assert np.array_equal(np.sort(i[:, :len(open_)], 1), np.tile(open_, (len(i), 1)))
+            # the rest are ties at -inf: the lowest of the masked ones, with no weight
+            assert np.array_equal(i[:, len(open_):], np.tile(masked[:k - len(open_)], (len(i), 1)))
+            assert np.all(wt[:, len(open_):] == 0)
+            np.testing.assert_allclose(wt.sum(1), 1, rtol=0, atol=1e-6)
+        if xin is x:
+            assert torch.equal(out[rows], clean[rows])
+            i = _np(idx)
+            assert i.min() >= 0 and i.max() < N and all(len(set(r)) == k for r in i)
+            assert bool(torch.isnan(out[T // 2]).all())
+        clean = out
 
 
 GRAPH_SHAPES = [
@@ -562,6 +614,8 @@ def _group_case(T, d_in, d_outs, N, r, k, routing, seed):
     (33, 1024, (520, 136, 136), 28, 8, 2, "uniform", True),      # q/k/v-like, two launches for the group
     (64, 4096, (1032, 1032), 12, 16, 3, "zipf", True),           # gate/up-like, r = 16, bias
     (8, 512, (256, 264, 136, 72), 28, 8, 2, "uniform", True),    # four members
+    (33, 512, (8200, 4104, 3080), 28, 8, 2, "uniform", True),    # 132 row tiles: runs that go on from member to member
+    (5, 512, (16392, 8200, 8200), 28, 16, 2, "zipf", True),      # 274: runs longer than a row tile, two Wcat tiles cut
     (33, 1024, (520, 136), 28, 8, 2, "uniform", False),          # not packed: member by member
     (300, 512, (256, 264), 28, 8, 2, "uniform", True),           # a few hundred tokens: three launches with 128-row tiles
     (16, 512, (264,), 28, 8, 2, "zipf", True),                   # a group of one is the single-layer call
@@ -571,7 +625,7 @@ def _group_case(T, d_in, d_outs, N, r, k, routing, seed):
     (96, 768, (8200, 8192), 28, 8, 2, "uniform", True),          # 135 column tiles: two workgroups per CU
     (300, 512, (256, 264), 28, 8, 2, "uniform", False),          # a few hundred tokens, not packed: member by member
     (2000, 512, (2048, 2048, 2048), 28, 8, 2, "uniform", True),  # too many output tiles for one launch: member by member
-], ids=["qkv", "gate-up-r16", "four", "unpacked", "T=300", "one", "qkv-T128", "gate-up-T200-r16", "four-T130",
+], ids=["qkv", "gate-up-r16", "four", "runs", "long-runs", "unpacked", "T=300", "one", "qkv-T128", "gate-up-T200-r16", "four-T130",
         "T=96-two-per-CU", "T=300-unpacked", "T=2000"])
 def test_group_call_matches_oracle_and_single_calls(T, d_in, d_outs, N, r, k, routing, packed):
     shapes, all_ops, members, x, rows = _group_case(T, d_in, d_outs, N, r, k, routing, seed=50)
