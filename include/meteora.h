@@ -347,7 +347,8 @@ meteora_status meteora_base_gemm(const void* x, const void* W, int T, int d_in, 
  * the gate logits and the shrink, gate_topk the top-k, softmax and selection (batches with few output tiles:
  * gemm covers the K-split projection with those products, shrink the launch after it); for
  * T <= 64 gemm covers the base projection's split-K launch (with the gate logits and every adapter's shrink),
- * shrink the launch after it (top-k, softmax, reduction, expand).  meteora_stage_timing_read waits
+ * shrink the launch after it (top-k, softmax, reduction, expand); for METEORA_F32 meteora_linear_forward reports gemm
+ * (the base projection) and expand (everything after it).  meteora_stage_timing_read waits
  * for those events, returns per stage the summed milliseconds and the number
  * of timed launches (arrays of meteora_stage_count() entries, host memory)
  * and the number of calls covered, and starts a new window.  Not thread-safe;

@@ -451,7 +451,7 @@ hipError_t launch_gate_backward(const void* x, const void* dy, const void* wcat,
     a.S1 = (part_x_given != nullptr && part_x_splits > 0) ? part_x_splits : gemm_dense_splits(T, d_in, CR);
     a.S2 = gemm_dense_splits(T, d_out, NR);
     a.CR = CR; a.NR = NR; a.T = T; a.N = N; a.r = r; a.k = k; a.scale = scale; a.beta = beta;
-    const size_t u_bytes = dx != nullptr ? (size_t)kBwdTokens * k * r * sizeof(float) : 0;   // at most 32 KB
+    const size_t u_bytes = dx != nullptr ? (size_t)kBwdTokens * k * r * sizeof(float) : 0;   // at most 16 KB
     if (a.S1 > 8 || a.S2 > 8) return hipErrorInvalidValue;
     a.token_blocks = ceil_div(T, kBwdTokens);
     uint16_t* xt = reinterpret_cast<uint16_t*>(ws + L.xt);

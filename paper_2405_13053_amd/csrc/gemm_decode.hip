@@ -175,8 +175,10 @@ __global__ __launch_bounds__(kStreamThreads) void gemm_decode_stream_kernel(cons
 }
 
 // S equal K splits per row tile where that occupies at least three quarters of the 256 CUs with one workgroup each;
-// otherwise (129 to 191 row tiles, or more than 256) 256 runs of equal length over all units of the launch, which cut
-// row tiles where they fall.  A split is two K steps or more.
+// otherwise (86 to 95 or 129 to 191 row tiles, or more than 256) 256 runs of equal length over all units of the launch,
+// which cut row tiles where they fall.  A split is two K steps or more.  Whole layers of 89 row tiles (11008 outputs), two
+// equal splits against runs, 1, 16 and 64 tokens: 4096 inputs 23.5, 24.4, 29.3 against 21.7, 22.8, 28.6 us, 8192 36.9,
+// 38.1, 46.0 against 35.7, 36.9, 45.0, 2048 14.9, 15.9, 20.4 against 15.0, 16.1, 21.3.
 SplitPlan gemm_decode_plan(int d_in, const int* d_out, int G, int gate_rows) {
     SplitPlan p{};
     p.nk = ceil_div(d_in, kStreamK);

@@ -10,12 +10,15 @@
 // exactly scale * sum_{i in I(x)} w_i (x A_i) B_i of Eq. 2, accumulated in the same fp32
 // registers as the base term, so the output is rounded once.
 //
-// Tiling (gfx950): a workgroup of 4 wavefronts (2x2) owns a BM x BN output tile; each wavefront
-// owns (BM/2) x (BN/2) as MI x NI blocks of v_mfma_f32_32x32x16_bf16.  K advances in steps of
-// 64 through a double-buffered LDS tile; rows are 128 B and their 16-B chunks are XOR-swizzled
-// with the row index (see swz) so that a ds_read_b128 pass touches every bank once.
-// The MFMA is issued with W as the first operand, so a lane ends up with 4 consecutive output
-// columns of one token row and stores them as one 8-byte word.
+// Three kernels share the operand layout (a workgroup of 4 wavefronts, 2 x 2, owns an output tile; K advances in steps of
+// 64 through LDS tiles whose rows are 128 B, their 16-B chunks XOR-swizzled with the row index (see swz) so that a
+// ds_read_b128 pass touches every bank once; W is the MFMA's first operand, so a lane ends up with 4 consecutive output
+// columns of one token row):
+//   gemm_mfma_ring_kernel  d_in % 64 == 0, more than 64 tokens, and every fp32-tile launch: v_mfma_f32_16x16x32_bf16 on a
+//                          ring of LDS slots that global->LDS loads fill two to five K tiles ahead;
+//   gemm_mfma_dma_kernel   d_in % 64 == 0, up to 64 tokens: 64 x 64 tiles, v_mfma_f32_32x32x16_bf16, two slots;
+//   gemm_mfma_kernel       any other d_in, and sizes whose byte offsets pass 32 bits: v_mfma_f32_32x32x16_bf16, tiles
+//                          through registers into two LDS buffers.
 #pragma once
 #include <type_traits>
 #include <utility>
@@ -28,7 +31,7 @@ namespace meteora {
 constexpr int kGemmBK = 64;          // K elements per LDS tile
 constexpr int kGemmChunks = 8;       // 16-byte chunks per LDS row
 
-// LDS staging of the output tile in the pipelined kernel: a wavefront's (MI*32) x (NI*32) bf16 block,
+// LDS staging of the output tile in the two-slot kernel: a wavefront's (MI*32) x (NI*32) bf16 block,
 // rows padded by 16 bytes; the dynamic LDS size is the larger of the operand ring and this stage.
 template <int NI>
 __host__ __device__ constexpr int gemm_epilogue_stride() { return NI * 64 + 16; }
@@ -235,7 +238,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const GemmArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Pipelined version for d_in % 64 == 0 (all model shapes): the tiles of both operands go from
+// Two-slot version for d_in % 64 == 0 and few tokens: the tiles of both operands go from
 // global memory straight into LDS with 16-byte buffer_load ... lds (no staging registers), the
 // MFMA operand fragments are double-buffered in registers so the ds_reads of k-step s+1 are in
 // flight while the MFMAs of k-step s run, and there is one barrier per 64-wide K tile, placed
@@ -287,19 +290,6 @@ __device__ __forceinline__ void mma_frags(f32x16 (&acc)[MI][NI], const Frags<MI,
             acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.w[ni], f.x[mi], acc[mi][ni], 0, 0, 0);
 }
 
-// The first k-step of a tile's contraction: the accumulators start from the MFMA's own zero C operand instead of
-// being cleared beforehand (256 register writes per lane in the 256 x 256 kernel, which would sit between the
-// arrival of the first tile and the first MFMA).
-template <int MI, int NI>
-__device__ __forceinline__ void mma_frags_first(f32x16 (&acc)[MI][NI], const Frags<MI, NI>& f) {
-    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
-            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.w[ni], f.x[mi], zero, 0, 0, 0);
-}
-
 // A [rows x 64-element-tiles] operand as the global->LDS loads see it.  An instruction moves 8 rows
 // (8 lanes x 16 B per 128-byte tile row); lane (rsub, p) fetches the chunk whose swizzled position
 // (see swz) is p, so the LDS image is the swizzled layout.  Wavefront `wave` moves rows (j*4 + wave)*8 .. +8 of the tile
@@ -331,22 +321,6 @@ __device__ __forceinline__ void dma_piece(bf16_t* lds_tile, const DmaOperand& o,
         (int)(o.piece_step * (uint32_t)j + (uint32_t)ktile * (kGemmBK * 2)), 0, 0);
 }
 
-// Instruction-order hints for one phase (the code between two sched_barrier(0)): the compiler's own
-// order bunches the LDS reads and the global->LDS loads and exposes their issue time and latency;
-// these groups alternate them with the MFMAs instead.  Masks: 0x008 MFMA, 0x100 LDS read, 0x020 VMEM read.
-#define METEORA_SGB(mask, n) __builtin_amdgcn_sched_group_barrier(mask, n, 0)
-
-// Tail of the last phase of a K tile: RM MFMAs with RV global->LDS loads spread evenly between them.
-template <int RM, int RV, int J>
-__device__ __forceinline__ void paced_tail() {
-    if constexpr (J < RM) {
-        METEORA_SGB(0x008, 1);
-        constexpr int nv = RV / RM + (J < RV % RM ? 1 : 0);
-        if constexpr (nv > 0) METEORA_SGB(0x020, nv);
-        paced_tail<RM, RV, J + 1>();
-    }
-}
-
 // Map a workgroup id to an output tile: ids are dealt round-robin to the 8 XCDs, so each XCD
 // gets a contiguous run of the tile order, and the order walks groups of 4 tile rows column by
 // column: the 32 tiles an XCD works on at a time share few rows of x and W in its L2.
@@ -364,19 +338,15 @@ __device__ __forceinline__ void tile_of_workgroup(int wg, int tiles_m, int tiles
 }
 
 // Epilogue of the two-slot kernel: store a workgroup's 32 x 32 accumulators.
-// EPI fixes at compile time which of the three forms a kernel carries (kEpiAny: decided at run time).
-constexpr int kEpiAny = -1, kEpiStore = 0, kEpiAccumulate = 1, kEpiPartial = 2;
-template <int MI, int NI, int EPI = kEpiAny>
+template <int MI, int NI>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[MI][NI], unsigned char* smem_raw, int m0,
                                               int n0, int wm, int wn, int wave, int lane) {
     const int lrow = lane & 31, khalf = lane >> 5;
-    const bool is_partial = EPI == kEpiAny ? a.partial != nullptr : EPI == kEpiPartial;
-    const bool is_store = EPI == kEpiAny ? (a.partial == nullptr && !a.accumulate) : EPI == kEpiStore;
     // Epilogue.  A lane holds 4 consecutive columns per block row, so direct stores are 8-byte pieces
     // of 32 different rows per instruction; when the output is simply written (no split-K partials,
     // no accumulate) the bf16 tile is staged in this wavefront's own LDS region and stored as
     // 16-byte pieces that cover whole 128-byte lines.
-    if (is_store) {
+    if (a.partial == nullptr && !a.accumulate) {
         constexpr int EST = gemm_epilogue_stride<NI>();   // bytes per staged row
         __syncthreads();                                   // every wavefront is done with the operand tiles
         unsigned char* ep = smem_raw + wave * (MI * 32) * EST;
@@ -410,7 +380,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[M
         return;
     }
 
-    if (is_partial) {
+    if (a.partial != nullptr) {
         // fp32 split-K tile: same staging, one block row at a time, so the stores are 16-byte pieces of whole rows
         constexpr int PST = gemm_partial_stride<NI>();
         __syncthreads();
@@ -554,18 +524,9 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(const GemmArgs a) {
     }
     // One K tile = 4 phases of (MI*NI MFMA + the fragment reads of the next k-step); sched_barrier keeps
     // each phase's reads from sinking into the next phase, where they would be waited on at once.
-    // In the 256x256 kernel the reads are issued one per MFMA in the first half of the phase, so each
-    // has at least half a phase of MFMAs to land under.
-    constexpr bool kPaced = (MI == 4 && NI == 4);   // measured: no gain from the hints on the smaller tiles
-    static_assert(!kPaced || MI * NI >= MI + NI, "a phase needs one MFMA per fragment read");
     auto phase = [&](Frags<MI, NI>& fnext, const Frags<MI, NI>& fcur, const bf16_t* xs, int ks) {
         load_frags<MI, NI>(fnext, xs, xs + BM * kGemmBK, wm, wn, lrow, khalf, ks);
         mma_frags<MI, NI>(acc, fcur);
-        if constexpr (kPaced) {
-#pragma unroll
-            for (int i = 0; i < MI + NI; ++i) { METEORA_SGB(0x008, 1); METEORA_SGB(0x100, 1); }
-            METEORA_SGB(0x008, MI * NI - (MI + NI));
-        }
         __builtin_amdgcn_sched_barrier(0);
     };
     // REQ: 0 = tile it+2 is a main tile, 1 = it is an extension tile, 2 = there is none (last two tiles)
@@ -592,25 +553,9 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(const GemmArgs a) {
 #pragma unroll
             for (int i = NR; i < NPC; ++i) request_piece(it + 2, it & 1, i, std::integral_constant<bool, REQ == 1>{});
             mma_frags<MI, NI>(acc, f1);
-            if constexpr (kPaced) {
-#pragma unroll
-                for (int i = 0; i < NR; ++i) { METEORA_SGB(0x008, 1); METEORA_SGB(0x100, 1); METEORA_SGB(0x020, 1); }
-                // the remaining pieces spread evenly over the remaining MFMAs
-                constexpr int RM = MI * NI - NR, RV = NPC - NR;
-                if constexpr (RM > 0) {
-                    paced_tail<RM, RV, 0>();
-                } else if constexpr (RV > 0) {
-                    METEORA_SGB(0x020, RV);
-                }
-            }
         } else {
             if (it + 1 < nk) load_frags<MI, NI>(f0, xn, xn + BM * kGemmBK, wm, wn, lrow, khalf, 0);
             mma_frags<MI, NI>(acc, f1);
-            if constexpr (kPaced) {
-#pragma unroll
-                for (int i = 0; i < MI + NI; ++i) { METEORA_SGB(0x008, 1); METEORA_SGB(0x100, 1); }
-                METEORA_SGB(0x008, MI * NI - (MI + NI));
-            }
         }
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -659,6 +604,7 @@ __host__ __device__ constexpr int pieces_after_read(int i, int NPC, int NR) {
     return (i + 1) * NPC / NR - i * NPC / NR;
 }
 
+constexpr int kEpiStore = 0, kEpiAccumulate = 1, kEpiPartial = 2;
 // Epilogue of the ring kernel.  EPI fixes at compile time which form a kernel carries: with one form the
 // accumulators leave their registers as they are converted (with all three behind run-time branches the compiler
 // copies every accumulator out, and spills, before it branches).  A lane holds 4 consecutive output columns of token

@@ -86,7 +86,8 @@ int gemm_multi_cap_splits(int T, int col_tiles, int S);
 hipError_t launch_gemm_dense_splitk(const void* x, const void* Wcat, int T, int d_in, int rows, float* partial,
                                     hipStream_t stream);
 
-// the same for several matrices in one launch of 128 x 128 tiles, all with S splits (at most 8 matrices)
+// the same for several matrices in one launch (tiles of 128 columns and 96 to 256 rows), all with S splits (at most 8
+// matrices)
 struct DenseOperand { const void* W; int rows; float* partial; };
 hipError_t launch_gemm_dense_splitk_multi(const void* x, const DenseOperand* ops, int n_ops, int S, int T, int d_in,
                                           hipStream_t stream);
@@ -126,6 +127,14 @@ hipError_t launch_expand(const float* h32, const void* B, const int32_t* topk_id
                          int T, int d_out, int N, int r, int k, float scale, bool bf16, void* out,
                          int accumulate, hipStream_t stream);
 
+// ---- fp32 storage (layer_f32.hip): the base projection, and the rest of the layer onto it
+hipError_t launch_gemm_f32(const float* x, const float* W, int T, int d_in, int d_out, float* out, hipStream_t stream);
+hipError_t launch_route_lora_f32(const float* x, const float* W_gate, const float* bias, const float* A, const float* B,
+                                 int T, int d_in, int d_out, int N, int r, int k, float inv_temperature, float scale,
+                                 int32_t* topk_idx, float* topk_w, float* out, float* h /*[T,k,r], if apart*/,
+                                 hipStream_t stream);
+bool f32_expand_apart(int d_out, int r, int k);   // the expand is a launch of its own and h is used
+
 // ---- decode-sized batches in two launches (T <= 64, bf16, r in {8, 16, 32}, Wcat packed), for one layer or for a
 // group of up to kMaxDecodeGroup layers that share x (q/k/v, gate/up):
 // launch_gemm_decode_main: the main K splits of x * W_g^T as fp32 tiles partial_g[S][T][d_out_g], and in the same
@@ -135,14 +144,6 @@ hipError_t launch_expand(const float* h32, const void* B, const int32_t* topk_id
 //   out_g = bf16(sum of the S tiles in order + sum_slot (scale * w * h from the shrink tiles) * B_g[idx_g]).
 // launch_gemm_decode_finish: the reduction with the expand alone, from hs_g[T,k,r] = scale * w * h (the few-tile
 //   form of mid-sized batches below).
-// ---- fp32 storage (layer_f32.hip): the base projection, and the rest of the layer onto it
-hipError_t launch_gemm_f32(const float* x, const float* W, int T, int d_in, int d_out, float* out, hipStream_t stream);
-hipError_t launch_route_lora_f32(const float* x, const float* W_gate, const float* bias, const float* A, const float* B,
-                                 int T, int d_in, int d_out, int N, int r, int k, float inv_temperature, float scale,
-                                 int32_t* topk_idx, float* topk_w, float* out, float* h /*[T,k,r], if apart*/,
-                                 hipStream_t stream);
-bool f32_expand_apart(int d_out, int r, int k);   // the expand is a launch of its own and h is used
-
 constexpr int kMaxDecodeGroup = 4;
 struct DecodeMember {
     const void* W;        // [d_out, d_in]
@@ -206,6 +207,8 @@ hipError_t launch_gate_backward(const void* x, const void* dy, const void* wcat,
 // true if launch_gemm applies the hdense/B extension for this dtype (else run launch_expand after it)
 bool gemm_fuses_expand(bool bf16);
 // splitk_ws: scratch of gemm_splitk_bytes (0 = this shape is not split) or NULL to forbid splitting.
+// topk_idx[T,k], r (optional): the routing that hdense was made from; K tiles of the extension that are zero for all
+// tokens of an output tile are left out.
 size_t gemm_splitk_bytes(int T, int d_in, int d_out, bool bf16);
 hipError_t launch_gemm(const void* x, const void* W, int T, int d_in, int d_out, bool bf16,
                        const void* hdense, int ext_stride, const void* Bt, int ext_k,

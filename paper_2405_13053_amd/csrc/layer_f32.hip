@@ -12,7 +12,8 @@ namespace meteora {
 // v_mfma_f32_16x16x4_f32 takes one K value per lane, 16 rows x 4 K values per operand.  A lane loads 16 bytes, the K
 // values 4c..4c+3 of its row (c = lane / 16), and feeds them to four MFMAs: the j-th multiplies K values 4c + j of
 // both operands, which is the same set.  The matrix cores take 32 cycles for what two such loads of 1 KB feed to one
-// block, so operands come straight from L2 into registers, one step of 16 K values ahead, without LDS.
+// block, so operands come straight from L2 into registers, one step of 16 K values ahead (four with the split), without
+// LDS.
 // A wavefront owns MB x NB blocks of 16 x 16; the four of a workgroup either share one such tile, each taking a
 // quarter of K (small outputs: latency counts, and tiles are few), or are 2 x 2 tiles next to each other.
 // Rows of all three matrices are whole 32-byte pieces.
