@@ -50,7 +50,7 @@ __device__ __forceinline__ StreamOperand stream_operand(const bf16_t* base, int 
 // Cache policy of a load: the default, or "nt".  W is read "nt": a decode step streams the weights of a whole model, and
 // what a call reads is gone before its next.  A caller who does come back to the same weights finds them in the Infinity
 // Cache with ordinary loads only (64 tokens, 4096 -> 4096 over and over 16.1 against 17.8 us, 4096 -> 14336 27.7 against
-// 32.8; out of cache 17.8 against 17.9 and 34.9 against 33.1); ordinary loads for launches of up to 56 MB alone made the
+// 32.8; out of cache 17.7 against 18.0 and 34.9 against 33.1); ordinary loads for launches of up to 56 MB alone made the
 // seven linears of a block 128.5 us instead of 121.1.
 constexpr int kReused = 0, kReadOnce = 2;
 template <int POLICY>
