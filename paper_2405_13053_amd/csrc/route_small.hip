@@ -5,6 +5,7 @@
 // top-k, scatter, shrink and finalize launches of the large-batch path (each on a ~2.5 us launch
 // floor) collapse into this one.  Consumes the same K-slice logit partials as gate_topk_kernel, adds
 // them in the same order and ranks with the same routine, so the routing is identical.
+#include <type_traits>
 #include "common.hpp"
 #include "kernels.hpp"
 #include "topk_key.hpp"
@@ -186,7 +187,10 @@ __device__ __forceinline__ int split_count(const SplitPlan& p, int g) {
 // one wavefront per workgroup (measured: 64, 128 and 256 threads per workgroup time the same)
 constexpr int kTailThreads = 64;
 
-template <int R8>   // r = 8 * R8
+// U: K splits whose loads are in flight.  The loads of a round are unconditional, those past the last split repeat it, so U
+// follows the number of splits of the launch.  Whole calls with eight always, and so: 300 x 4096 -> 4096 (three splits) 26.6
+// and 26.1 us, 1531 x 4096 -> 1024 rank 16 (three) 38.4 and 37.7, 64 x 5120 -> 13824 (two) 36.6 and 36.2.
+template <int R8, int U>   // r = 8 * R8
 __global__ __launch_bounds__(kTailThreads) void decode_tail_kernel(int T, int N, int CR, int k, float inv_temperature,
                                                                    float scale, const RouteGroup rg,
                                                                    const FinishGroup fg) {
@@ -209,10 +213,10 @@ __global__ __launch_bounds__(kTailThreads) void decode_tail_kernel(int T, int N,
 
     const int tile = c / kSplitRows, nsplit = split_count(fg.plan, fg.m[member].tile0 + tile);
 
-    // the projection's split tiles do not depend on the routing: the first 8 go out first
-    f32x4 pre0[8], pre1[8];
+    // the projection's split tiles do not depend on the routing: the first U go out first
+    f32x4 pre0[U], pre1[U];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < U; ++u) {
         const float* src = partial + (size_t)min(u, nsplit - 1) * pstride;
         pre0[u] = *reinterpret_cast<const f32x4*>(src);
         pre1[u] = *reinterpret_cast<const f32x4*>(src + 4);
@@ -221,7 +225,7 @@ __global__ __launch_bounds__(kTailThreads) void decode_tail_kernel(int T, int N,
     const int lt[1] = {0};
     static_assert(3 * NP <= kSplitRows, "the gate terms are rows of Wcat's first row tile");
     const int gate_tile0 = fg.m[member].gate_tile0;
-    dense_logits<NP, 1, 8>(gpart, split_count(fg.plan, gate_tile0), CR, rg.m[member].bias, T, N, t, lt, lane & (NP - 1), g);
+    dense_logits<NP, 1, U>(gpart, split_count(fg.plan, gate_tile0), CR, rg.m[member].bias, T, N, t, lt, lane & (NP - 1), g);
     int sel_i[1];
     float sel_w[1];
     wave_topk_softmax<NP, 1>(g, lane, N, k, inv_temperature, sel_i, sel_w);   // lane s < k: the s-th choice
@@ -231,18 +235,18 @@ __global__ __launch_bounds__(kTailThreads) void decode_tail_kernel(int T, int N,
     }
     f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
+    for (int u = 0; u < U; ++u)
         if (u < nsplit) { lo += pre0[u]; hi += pre1[u]; }
-    for (int s0 = 8; s0 < S; s0 += 8) {   // tiles in order, 8 tiles' loads in flight
-        f32x4 v0[8], v1[8];
+    for (int s0 = U; s0 < S; s0 += U) {   // tiles in order, U tiles' loads in flight
+        f32x4 v0[U], v1[U];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < U; ++u) {
             const float* src = partial + (size_t)min(s0 + u, nsplit - 1) * pstride;
             v0[u] = *reinterpret_cast<const f32x4*>(src);
             v1[u] = *reinterpret_cast<const f32x4*>(src + 4);
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
+        for (int u = 0; u < U; ++u)
             if (s0 + u < nsplit) { lo += v0[u]; hi += v1[u]; }
     }
 
@@ -262,21 +266,21 @@ __global__ __launch_bounds__(kTailThreads) void decode_tail_kernel(int T, int N,
         const int hcol = 3 * NP + a_e * r + (lane & (r - 1));
         const float* hsrc = gpart + (size_t)t * CR + hcol;
         const int hsplit = split_count(fg.plan, gate_tile0 + hcol / kSplitRows);
-        float hv8[8];
+        float hvs[U];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) hv8[u] = hsrc[(size_t)min(u, hsplit - 1) * T * CR];
+        for (int u = 0; u < U; ++u) hvs[u] = hsrc[(size_t)min(u, hsplit - 1) * T * CR];
         u32x4 bcur[8];
         load_rows(s0, 0, bcur);   // the first rows of B are under way while the shrink tiles arrive
         float h = 0.f;
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (u < hsplit) h += hv8[u];
-        for (int p0 = 8; p0 < S; p0 += 8) {
-            float v[8];
+        for (int u = 0; u < U; ++u)
+            if (u < hsplit) h += hvs[u];
+        for (int p0 = U; p0 < S; p0 += U) {
+            float v[U];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = hsrc[(size_t)min(p0 + u, hsplit - 1) * T * CR];
+            for (int u = 0; u < U; ++u) v[u] = hsrc[(size_t)min(p0 + u, hsplit - 1) * T * CR];
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
+            for (int u = 0; u < U; ++u)
                 if (p0 + u < hsplit) h += v[u];
         }
         const float hv = scale * w_e * h;
@@ -337,9 +341,16 @@ hipError_t launch_decode_tail_group(const DecodeMember* mem, int G, const SplitP
         kern<<<grid, kTailThreads, 0, stream>>>(T, N, gate_rows, k, inv_temperature, scale, rg, fg);
         return hipGetLastError();
     };
-    if (r == 8) return go(decode_tail_kernel<1>);
-    if (r == 16) return go(decode_tail_kernel<2>);
-    if (r == 32) return go(decode_tail_kernel<4>);
+    auto by_splits = [&](auto r8) {
+        constexpr int R8 = decltype(r8)::value;
+        if (plan.S == 1) return go(decode_tail_kernel<R8, 1>);
+        if (plan.S == 2) return go(decode_tail_kernel<R8, 2>);
+        if (plan.S <= 4) return go(decode_tail_kernel<R8, 4>);
+        return go(decode_tail_kernel<R8, 8>);
+    };
+    if (r == 8) return by_splits(std::integral_constant<int, 1>{});
+    if (r == 16) return by_splits(std::integral_constant<int, 2>{});
+    if (r == 32) return by_splits(std::integral_constant<int, 4>{});
     return hipErrorInvalidValue;
 }
 

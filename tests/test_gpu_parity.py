@@ -335,6 +335,14 @@ def test_linear_forward_matches_oracle(shape):
     _check_layer(shape, seed=41)
 
 
+# row tiles of 128 outputs and of 320 (r = 8), 544 (16) or 320 (7 adapters of 32) rows of Wcat share 256 CUs: 1, 2, 3, 5 and 16 K splits
+@pytest.mark.parametrize("d_in,d_out", [(512, 24584), (512, 13832), (512, 9224), (1280, 5640), (4096, 264)],
+                         ids=["S1", "S2", "S3", "S5", "S16"])
+@pytest.mark.parametrize("N,r,k", [(28, 8, 2), (28, 16, 1), (7, 32, 3)], ids=["r8", "r16", "r32"])
+def test_decode_tail_at_each_split_count(d_in, d_out, N, r, k):
+    _check_layer(LS(5, d_in, d_out, N, r, k, 2.0, "bf16", "zipf", "tail"), seed=61)
+
+
 @pytest.mark.parametrize("d_in,same_kernel", [(128, True), (512, False)])
 def test_linear_forward_zero_B_is_base_and_deterministic(d_in, same_kernel):
     """B = 0: the layer is the base projection.  d_in = 128: the same GEMM kernel as meteora_base_gemm runs, equal
