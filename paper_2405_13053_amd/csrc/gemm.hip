@@ -216,11 +216,11 @@ int gemm_dense_splits(int T, int d_in, int rows) {
     return S < 1 ? 1 : S;
 }
 
-template <int MB, int NB, int D>
+template <int MB, int NB, int D, int EPI = kEpiPartialThrough>
 static hipError_t launch_dense(GemmArgs a, hipStream_t stream) {   // fp32 split-K tiles; tiles_n is the caller's
     a.tiles_m = ceil_div(a.T, MB * 32);
     if (a.tiles_n == 0) a.tiles_n = ceil_div(a.d_out, NB * 32);
-    return launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiPartial, false>, a, gemm_ring_lds_bytes<MB, NB, D>(), a.splits, stream);
+    return launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, EPI, false>, a, gemm_ring_lds_bytes<MB, NB, D>(), a.splits, stream);
 }
 
 hipError_t launch_gemm_dense_splitk(const void* x, const void* Wcat, int T, int d_in, int rows, float* partial,
@@ -231,7 +231,7 @@ hipError_t launch_gemm_dense_splitk(const void* x, const void* Wcat, int T, int 
     a.partial = partial;
     a.splits = gemm_dense_splits(T, d_in, rows);
     a.tiles_per_split = ceil_div(d_in / kGemmBK, a.splits);
-    return dense_small_tiles(T) ? launch_dense<4, 4, 2>(a, stream) : launch_dense<4, 10, 2>(a, stream);
+    return dense_small_tiles(T) ? launch_dense<4, 4, 2, kEpiPartial>(a, stream) : launch_dense<4, 10, 2, kEpiPartial>(a, stream);
 }
 
 // Several matrices in one split-K launch (few-tile batches): ops[i].partial[s][T][rows_i] = x * W_i^T over the K
@@ -326,13 +326,14 @@ hipError_t gemm_init_kernels() {
     METEORA_TILES(4, 4, 2);
     METEORA_RING(4, 10, 2, kEpiPartial, false);
     METEORA_RING(4, 4, 2, kEpiPartial, false);
-    METEORA_RING(3, 4, 2, kEpiPartial, false);
-    METEORA_RING(3, 4, 5, kEpiPartial, false);
-    METEORA_RING(4, 4, 4, kEpiPartial, false);
-    METEORA_RING(5, 4, 4, kEpiPartial, false);
-    METEORA_RING(6, 4, 3, kEpiPartial, false);
-    METEORA_RING(7, 4, 3, kEpiPartial, false);
-    METEORA_RING(8, 4, 3, kEpiPartial, false);
+    METEORA_RING(4, 4, 2, kEpiPartialThrough, false);
+    METEORA_RING(3, 4, 2, kEpiPartialThrough, false);
+    METEORA_RING(3, 4, 5, kEpiPartialThrough, false);
+    METEORA_RING(4, 4, 4, kEpiPartialThrough, false);
+    METEORA_RING(5, 4, 4, kEpiPartialThrough, false);
+    METEORA_RING(6, 4, 3, kEpiPartialThrough, false);
+    METEORA_RING(7, 4, 3, kEpiPartialThrough, false);
+    METEORA_RING(8, 4, 3, kEpiPartialThrough, false);
 #undef METEORA_TILES
 #undef METEORA_RING
     return e;

@@ -604,7 +604,14 @@ __host__ __device__ constexpr int pieces_after_read(int i, int NPC, int NR) {
     return (i + 1) * NPC / NR - i * NPC / NR;
 }
 
-constexpr int kEpiStore = 0, kEpiAccumulate = 1, kEpiPartial = 2;
+constexpr int kEpiStore = 0, kEpiAccumulate = 1, kEpiPartial = 2, kEpiPartialThrough = 3;
+// Cache policy of the output's stores ("sc1"): written through the L2.  Where all workgroups of a launch end together,
+// lines left in the L2 are only written back when the launch is over, and the next one waits for that.  Whole calls,
+// ordinary stores, "nt", "sc1": the fp32 tiles of 300 x 4096 -> 4096 26.35, 25.6, 25.2 us, of 1531 x 4096 -> 1024 of rank
+// 16 38.1, 37.75, 36.7; bf16 outputs: a training step of 4096 tokens 273.1 and 271.0 ("sc1"), 3000 x 5120 -> 5120 from its
+// parts 174.5 and 172.8.  The routing products of a prefill (kEpiPartial, two workgroups per CU at different stages) gain
+// nothing: 4096 tokens 120.9 and 121.7.
+constexpr int kWriteThrough = 16;
 // Epilogue of the ring kernel.  EPI fixes at compile time which form a kernel carries: with one form the
 // accumulators leave their registers as they are converted (with all three behind run-time branches the compiler
 // copies every accumulator out, and spills, before it branches).  A lane holds 4 consecutive output columns of token
@@ -614,7 +621,8 @@ constexpr int kEpiStore = 0, kEpiAccumulate = 1, kEpiPartial = 2;
 template <int MB, int NB, int EPI>
 __device__ __forceinline__ void gemm_epilogue16(const GemmArgs& a, f32x4 (&acc)[MB][NB], unsigned char* smem_raw, int m0,
                                                 int n0, int wm, int wn, int wave, int lane) {
-    constexpr bool F32 = EPI == kEpiPartial;
+    constexpr bool F32 = EPI == kEpiPartial || EPI == kEpiPartialThrough;
+    constexpr int POLICY = EPI == kEpiPartial ? 0 : kWriteThrough;
     constexpr int RS = MB % 2 == 0 ? 32 : 16;                  // staged rows
     constexpr int EB = F32 ? 4 : 2;                            // bytes per staged value
     constexpr int EST = NB * 16 * EB + 16;                     // bytes per staged row
@@ -684,7 +692,7 @@ __device__ __forceinline__ void gemm_epilogue16(const GemmArgs& a, f32x4 (&acc)[
         for (int i = 0; i < NP; ++i) {
             const int p = i * 64 + lane;
             const u32x4 v = *reinterpret_cast<const u32x4*>(ep + (p / PPR) * EST + (p % PPR) * 16);
-            __builtin_amdgcn_raw_buffer_store_b128(v, out, offset(i, mb), 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(v, out, offset(i, mb), 0, POLICY);
         }
         sync();
         __builtin_amdgcn_sched_barrier(0);   // accumulators leave their registers 32 rows at a time
