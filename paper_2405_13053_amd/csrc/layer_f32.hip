@@ -261,4 +261,182 @@ hipError_t launch_route_lora_f32(const float* x, const float* W_gate, const floa
     return hipGetLastError();
 }
 
+// ------------------------------------------------------------------------------------------
+// The whole layer in one launch, for few adapters: a workgroup computes 16 columns for 16 tokens, and on the
+// way, from the same x in registers, the tokens' gate logits and x * A_i of every adapter (EB blocks of 16 columns in all)
+// instead of waiting for a launch that does so once.  The four wavefronts take a quarter of K each; what is left is one
+// round through LDS, the ranking, and the rows of B of the chosen adapters.  A layer of this size is latency and launches:
+// 64 x 256 -> 256 with 4 adapters of rank 8 is two rounds of loads instead of six.
+// ------------------------------------------------------------------------------------------
+template <int EB>
+__global__ __launch_bounds__(256) void layer_f32_kernel(
+    const float* __restrict__ x, const float* __restrict__ W, const float* __restrict__ W_gate,
+    const float* __restrict__ bias, const float* __restrict__ A, const float* __restrict__ B, int T, int d_in, int d_out,
+    int N, int r, int k, float inv_temperature, float scale, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
+    float* __restrict__ out) {
+    constexpr int TN = 16, C = (1 + EB) * 16, AHEAD = 4;
+    __shared__ __attribute__((aligned(16))) float red[4][16][C + 4];
+    __shared__ int sel_idx[16][kMaxTopK];
+    __shared__ float sel_sw[16][kMaxTopK];   // scale * w
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int l15 = lane & 15, kc = (lane >> 4) * 4;
+    const int tiles_n = ceil_div(d_out, TN);
+    const int tile_m = blockIdx.x / tiles_n, tile_n = blockIdx.x - tile_m * tiles_n;
+    const int m0 = tile_m * 16, n0 = tile_n * TN, NR = N * r;
+    const int steps = ceil_div(d_in, 16);
+    const int s0 = wave * steps / 4, s1 = (wave + 1) * steps / 4;
+
+    // Loads through buffer resources: offsets of a lane that never change and a uniform K offset, so that no address
+    // arithmetic stands between the loads of a step.  Rows past the edge repeat the last one (computed, never stored);
+    // columns past the last and K values past d_in are outside for the hardware and count as zeros.
+    constexpr uint32_t kOutside = 0x80000000u;
+    auto resource = [](const float* p, uint32_t floats) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, floats * 4u, 0x00020000);
+    };
+    const uint32_t ld = (uint32_t)d_in;
+    const __amdgpu_buffer_rsrc_t xr = resource(x, T * ld), wr = resource(W, d_out * ld), gr = resource(W_gate, ld * N),
+                                 ar = resource(A, (uint32_t)NR * ld);
+    const uint32_t xo = (uint32_t)min(m0 + l15, T - 1) * ld * 4;
+    const uint32_t wo = (uint32_t)min(n0 + l15, d_out - 1) * ld * 4;
+    // block 0: a column of W_gate per lane; the others: component q of adapter a, column a * r + q
+    uint32_t eo[EB];
+#pragma unroll
+    for (int e = 0; e < EB; ++e) {
+        const int c = e == 0 ? l15 : (e - 1) * 16 + l15;
+        if (e == 0) eo[e] = c < N ? (uint32_t)(kc * N + c) * 4 : kOutside;
+        else eo[e] = c < NR ? (uint32_t)((c / r) * d_in * r + kc * r + c % r) * 4 : kOutside;
+    }
+    struct Step { f32x4 x, w, e[EB]; };
+    auto load = [&](Step& f, int s) {
+        const bool inside = s * 16 + kc < d_in;   // d_in % 8 == 0: all four values or none
+        f.x = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, inside ? xo + kc * 4 : kOutside, s * 64, 0));
+        f.w = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(wr, inside ? wo + kc * 4 : kOutside, s * 64, 0));
+#pragma unroll
+        for (int e = 0; e < EB; ++e) {
+            const uint32_t off = inside ? eo[e] : kOutside;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                f.e[e][j] = __builtin_bit_cast(
+                    float, __builtin_amdgcn_raw_buffer_load_b32(e == 0 ? gr : ar, off, (s * 16 + j) * (e == 0 ? N : r) * 4, 0));
+        }
+    };
+    f32x4 acc[1 + EB];
+#pragma unroll
+    for (int i = 0; i < 1 + EB; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    Step f[AHEAD + 1];
+#pragma unroll
+    for (int a = 0; a < AHEAD; ++a)
+        if (s0 + a < s1) load(f[a], s0 + a);
+    for (int s = s0; s < s1; s += AHEAD + 1) {
+#pragma unroll
+        for (int u = 0; u <= AHEAD; ++u) {   // register sets have fixed numbers
+            if (s + u >= s1) break;          // uniform per wavefront
+            if (s + u + AHEAD < s1) load(f[(u + AHEAD) % (AHEAD + 1)], s + u + AHEAD);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[u].w[j], f[u].x[j], acc[0], 0, 0, 0);
+#pragma unroll
+                for (int e = 0; e < EB; ++e)
+                    acc[1 + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[u].e[e][j], f[u].x[j], acc[1 + e], 0, 0, 0);
+            }
+        }
+    }
+    // a lane holds columns 4 * (lane / 16) .. + 3 of token lane % 16 of every block
+#pragma unroll
+    for (int i = 0; i < 1 + EB; ++i) *reinterpret_cast<f32x4*>(&red[wave][l15][i * 16 + kc]) = acc[i];
+    __syncthreads();
+    for (int e = threadIdx.x; e < 16 * C / 4; e += 256) {
+        const int t = e / (C / 4), c = (e % (C / 4)) * 4;
+        f32x4 v[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) v[w] = *reinterpret_cast<const f32x4*>(&red[w][t][c]);
+        *reinterpret_cast<f32x4*>(&red[0][t][c]) = (v[0] + v[1]) + (v[2] + v[3]);
+    }
+    __syncthreads();
+    {   // a wavefront ranks four tokens, two at a time
+        constexpr int NP = 32, G = 2;
+        const int col = lane & (NP - 1), sub = lane / NP;
+        float g[G];
+        int si[G];
+        float sw[G];
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            g[i] = 0.f;
+            if (col < N) {
+                g[i] = red[0][wave * 4 + i * 2 + sub][TN + col] + (bias != nullptr ? bias[col] : 0.f);
+                if (g[i] == 0.f) g[i] = 0.f;   // -0 -> +0 so equal logits have equal keys
+            }
+        }
+        wave_topk_softmax<NP, G>(g, lane, N, k, inv_temperature, si, sw);
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const int t = wave * 4 + i * 2 + sub;
+            if (col < k) {
+                sel_idx[t][col] = si[i];
+                sel_sw[t][col] = scale * sw[i];
+                if (tile_n == 0 && m0 + t < T) {
+                    topk_idx[(size_t)(m0 + t) * k + col] = si[i];
+                    topk_w[(size_t)(m0 + t) * k + col] = sw[i];
+                }
+            }
+        }
+    }
+    __syncthreads();
+    const int t = threadIdx.x / TN, c = n0 + threadIdx.x % TN;
+    if (m0 + t >= T || c >= d_out) return;
+    float v = red[0][t][c - n0];
+    const int R8 = ceil_div(r, 8), groups = k * R8;   // (slot, 8 rows of B): the rows of two groups in flight
+    for (int g0 = 0; g0 < groups; g0 += 2) {
+        float b[2][8], d[2] = {0.f, 0.f};
+        int at[2], q0[2], slot[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int g = min(g0 + i, groups - 1);
+            slot[i] = g / R8;
+            q0[i] = (g - slot[i] * R8) * 8;
+            const int a = sel_idx[t][slot[i]];
+            at[i] = TN + 16 + a * r;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) b[i][u] = B[((size_t)a * r + min(q0[i] + u, r - 1)) * d_out + c];
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            if (g0 + i >= groups) break;
+            const float sw = sel_sw[t][slot[i]];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (q0[i] + u < r) d[i] = fmaf(sw * red[0][t][at[i] + q0[i] + u], b[i][u], d[i]);
+            v += d[i];
+        }
+    }
+    out[(size_t)(m0 + t) * d_out + c] = v;
+}
+
+// Every workgroup reads the whole of W_gate and A, so this is for what one round or two of workgroups finish: the product
+// of rounds, inputs and 16-column blocks is what the time goes with.  Against two launches, whole calls (the host takes 7.9
+// us to issue one launch and 10.3 for two): 4 adapters of rank 8, top-2: 64 x 256 -> 256 10.5 and 7.8 us, 8 x 256 -> 4096 12.7
+// and 7.8, 64 x 384 -> 384 10.8 and 9.1, 64 x 512 -> 512 11.4 and 10.6, 64 x 768 -> 64 12.1 and 13.4, 200 x 256 -> 768 13.4 and
+// 15.2; 7 of rank 8: 64 x 128 -> 128 10.2 and 7.9, 64 x 256 -> 256 10.4 and 10.7; 16 of rank 2 (8-byte pieces of A): 64 x
+// 256 -> 256 10.6 and 8.8, 64 x 512 -> 512 10.5 and 13.1; 1024 workgroups (512 x 64 -> 512) 10.5 and 11.3.
+bool layer_f32_applies(int T, int d_in, int d_out, int N, int r) {
+    if (N > 16 || N * r > 64) return false;
+    const int64_t tiles = ceil_div64(T, 16) * ceil_div64(d_out, 16);
+    const int blocks = N * r <= 32 ? 4 : 6;
+    return tiles <= 512 && ceil_div64(tiles, 256) * d_in * blocks <= (blocks == 4 && r >= 8 ? 2048 : 1024);
+}
+
+hipError_t launch_layer_f32(const float* x, const float* W, const float* W_gate, const float* bias, const float* A,
+                            const float* B, int T, int d_in, int d_out, int N, int r, int k, float inv_temperature,
+                            float scale, int32_t* topk_idx, float* topk_w, float* out, hipStream_t stream) {
+    if (d_in % 8 != 0 || d_out % 8 != 0 || !layer_f32_applies(T, d_in, d_out, N, r) || k < 1 || k > N || k > kMaxTopK)
+        return hipErrorInvalidValue;
+    const int64_t tiles = ceil_div64(T, 16) * ceil_div64(d_out, 16);
+    auto go = [&](auto kern) {
+        kern<<<(unsigned)tiles, 256, 0, stream>>>(x, W, W_gate, bias, A, B, T, d_in, d_out, N, r, k, inv_temperature, scale,
+                                                  topk_idx, topk_w, out);
+        return hipGetLastError();
+    };
+    return N * r <= 32 ? go(layer_f32_kernel<3>) : go(layer_f32_kernel<5>);
+}
+
 }  // namespace meteora

@@ -335,6 +335,14 @@ def test_linear_forward_matches_oracle(shape):
     _check_layer(shape, seed=41)
 
 
+# fp32 layers with few adapters in one launch: tiles of 16 tokens and 16 columns, K in steps of 16 over four wavefronts
+@pytest.mark.parametrize("T,d_in,d_out,N,r,k", [
+    (1, 8, 8, 1, 1, 1), (16, 16, 16, 16, 2, 8), (17, 24, 24, 16, 4, 3), (33, 72, 264, 4, 8, 2), (15, 512, 8, 4, 8, 1),
+    (64, 328, 136, 2, 16, 2), (129, 64, 904, 7, 8, 3), (40, 168, 40, 1, 64, 1), (9, 136, 4096, 5, 12, 4)])
+def test_fp32_layer_in_one_launch(T, d_in, d_out, N, r, k):
+    _check_layer(LS(T, d_in, d_out, N, r, k, 2.0, "f32", "zipf", "f32-one-launch"), seed=62)
+
+
 # row tiles of 128 outputs and of 320 (r = 8), 544 (16) or 320 (7 adapters of 32) rows of Wcat share 256 CUs: 1, 2, 3, 5 and 16 K splits
 @pytest.mark.parametrize("d_in,d_out", [(512, 24584), (512, 13832), (512, 9224), (1280, 5640), (4096, 264)],
                          ids=["S1", "S2", "S3", "S5", "S16"])
