@@ -12,7 +12,7 @@
 // x * Wcat^T gives the logits and x A_i of EVERY adapter (the forward's own first launch, so the logits and with
 // them the top-k are bit-identical to that path's), dy * Bflat^T with Bflat = B viewed as [N*r, d_out] gives
 // B_i dy of every adapter; both as fp32 K-split partials.  gate_bwd_dlogits_kernel (this file) turns them
-// into d_logits per token, gate_bwd_wgrad_kernel accumulates x^T d_logits over token slices with fp32 MFMAs
+// into d_logits per token, gate_bwd_wgrad_kernel accumulates x^T d_logits over token slices
 // (a [d_in, T] x [T, 32] product whose x operand is not K-contiguous), and gate_bwd_reduce_kernel adds the
 // slices in order.
 //
@@ -46,19 +46,32 @@ struct DlogitsArgs {
     const int32_t* idx_in;   // [T,k] routing of the forward call, or NULL: rank again here
     const float* w_in;       // [T,k]
     const int32_t* labels;   // [T] or NULL
-    float* dg;               // [T][32], columns >= N zero
+    bf16_t* dgs;             // d_logits in three bf16 terms, see split3_exact: [blocks of 8 tokens][term][32][8 tokens]
     float* d_logits;         // [T,N] or NULL
     bf16_t* hx;              // [T][ext] extension operand of the input-gradient GEMM, or NULL
     int ext;                 // columns of hx: N*r + 96 rounded up to 64
     int S1, S2, CR, NR, T, N, r, k;
     float scale, beta;
-    // workgroups from token_blocks on write Xt instead (a launch of its own would cost more than its work)
+    // (an even number of token blocks: past T they write zeros); workgroups from token_blocks on write Xt instead (a launch of its own would cost more than its work)
     int token_blocks;
     const uint16_t* A;       // [N, d_in, r]
     const float* W_gate;     // [d_in, N]
     int d_in;
     uint16_t* Xt;            // [d_in][ext]
 };
+
+// The three bf16 terms of an fp32 value, hi + mid + lo == v exactly: its 24 significand bits, 8 to a term (cut, not rounded:
+// the largest values stay finite).  What is not finite is its first term alone.
+struct Split3 { uint16_t term[3]; };
+__device__ __forceinline__ Split3 split3_exact(float v) {
+    const uint32_t hi = __float_as_uint(v) & 0xffff0000u;
+    const bool finite = (hi & 0x7f800000u) != 0x7f800000u;
+    const float r1 = finite ? v - __uint_as_float(hi) : 0.f;
+    const uint32_t mid = __float_as_uint(r1) & 0xffff0000u;
+    const float r2 = r1 - __uint_as_float(mid);
+    // a NaN keeps its quiet bit (its payload may lie in the bits cut off)
+    return {{(uint16_t)((hi >> 16) | (v != v ? 0x40u : 0u)), (uint16_t)(mid >> 16), (uint16_t)(__float_as_uint(r2) >> 16)}};
+}
 
 __device__ void pack_xt(const uint16_t* __restrict__ A, const float* __restrict__ W_gate, int d_in, int N, int r, int ext,
                         size_t e, uint16_t* __restrict__ Xt);
@@ -178,9 +191,21 @@ __global__ __launch_bounds__(kBwdThreads) void gate_bwd_dlogits_kernel(const Dlo
     for (int i = 0; i < G; ++i) {
         const int t = t0 + lt[i];
         if (t >= T) continue;
-        const float v = col < N ? s_dg[lt[i]][col] : 0.f;
-        a.dg[(size_t)t * NP + col] = v;
-        if (a.d_logits != nullptr && col < N) a.d_logits[(size_t)t * N + col] = v;
+        if (a.d_logits != nullptr && col < N) a.d_logits[(size_t)t * N + col] = s_dg[lt[i]][col];
+    }
+    static_assert(kBwdTokens == 8 && kBwdThreads >= 3 * kBwdNP, "one 16-byte piece per thread: 8 tokens of a term's column");
+    if (threadIdx.x < 3 * NP) {
+        const int term = threadIdx.x / NP, n = threadIdx.x % NP;
+        uint16_t v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const Split3 sp = split3_exact(t0 + j < T && n < N ? s_dg[j][n] : 0.f);
+            v[j] = term == 0 ? sp.term[0] : term == 1 ? sp.term[1] : sp.term[2];
+        }
+        u32x4 pk;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) pk[j] = (uint32_t)v[2 * j] | (uint32_t)v[2 * j + 1] << 16;
+        *reinterpret_cast<u32x4*>(a.dgs + ((size_t)blockIdx.x * 3 * NP + threadIdx.x) * 8) = pk;
     }
     if (a.hx == nullptr) return;
 
@@ -246,115 +271,107 @@ __device__ void pack_xt(const uint16_t* __restrict__ A, const float* __restrict_
 }
 
 // ---- dW_gate partials: wpart[slice][c][32] = sum over the slice's tokens of x[t][c] * dg[t][:] ----
-// The contraction runs over tokens, and x[T, d_in] is not token-contiguous, so the bf16 MFMA operand layout
-// (eight consecutive K values per lane) would need a transposed copy of x.  The fp32 MFMA 32x32x2 takes ONE K
-// value per lane: lane l holds A[m = l % 32][k = l / 32] and B[k = l / 32][n = l % 32].  With m = adapter,
-// k = token and n = column slot, both operands are plain coalesced loads and the product keeps full fp32
-// accuracy.  The kernel is bound by the number of vector loads it issues (a CU takes a 4-byte-per-lane load
-// every ~6 cycles, a 2-, 8- or 16-byte one every 15 to 29), so a lane loads one dword of x, two adjacent
-// columns, per token pair and feeds two MFMAs with column slots c0 + 2n and c0 + 2n + 1: one x load and one dg
-// load per two MFMAs.  A wavefront covers 64 columns; the four wavefronts of a workgroup are 2 column halves
-// x 2 token halves of a 128-column slice, the token halves added through LDS in a fixed order.
+// The contraction runs over tokens: an operand of v_mfma_f32_32x32x16_bf16 is 8 consecutive tokens of a column per lane.
+// x[T, d_in] is not token-contiguous, so a lane loads 4 columns of 8 tokens (8 bytes each, whole lines per half wavefront)
+// and pairs the halves of its registers (two v_perm per 4 values).  d_logits comes as three bf16 terms that add up to its
+// fp32 value, in the operand's own order: every product is exact in fp32, as in the forward gate, and a multiply of K = 16
+// takes 32 cycles where the fp32 MFMA takes 512.  Bound by the latency of the loads: a wavefront owns 128 columns and an
+// eighth of the workgroup's tokens, all of whose loads are in flight for up to 64 tokens.  The eight sums meet in LDS.
 // Workgroups of column tile 0 also add up dg for dbias.
-constexpr int kWgCols = 128;
-constexpr int kWgRing = 16;      // token pairs whose loads are in flight per wavefront
-constexpr int kWgChunk = 2 * kWgRing;
+constexpr int kWgCols = 128, kWgThreads = 512, kWgParts = kWgThreads / 64, kWgChunk = 16;   // chunk: tokens per MFMA
+constexpr int kWgRing = 4;                                       // chunks whose loads are in flight per wavefront
+constexpr int kWgLds = kWgParts * 16 * 64 * 16;                  // the accumulators of every wavefront
 
-__global__ __launch_bounds__(256, 2) void gate_bwd_wgrad_kernel(const uint16_t* __restrict__ x,
-                                                                 const float* __restrict__ dg, int T, int d_in,
-                                                                 int slice_tokens, float* __restrict__ wpart,
-                                                                 float* __restrict__ bpart) {
-    constexpr int R = kWgRing;
-    __shared__ float red[2][32][64];                         // [column half][acc entry][lane] of the second token half
-    __shared__ float s_b[kBwdNP];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = lane & 31, kh = lane >> 5;
-    const int chalf = wave & 1, thalf = wave >> 1;
-    const int c = blockIdx.x * kWgCols + chalf * 64 + 2 * n; // d_in is even: both columns inside or both outside
-    const int cc = min(c, d_in - 2);
-    const int slice = blockIdx.y;
-    const int s_begin = slice * slice_tokens, s_end = min(T, s_begin + slice_tokens);
-    const int half_tokens = slice_tokens / 2;                // a multiple of kWgChunk
-    const int t_begin = s_begin + thalf * half_tokens, t_end = min(s_end, t_begin + half_tokens);
-    f32x16 acc0, acc1;
+__global__ __launch_bounds__(kWgThreads) void gate_bwd_wgrad_kernel(const uint16_t* __restrict__ x,
+                                                                     const uint16_t* __restrict__ dgs, int T, int d_in,
+                                                                     int slice_chunks, float* __restrict__ wpart,
+                                                                     float* __restrict__ bpart) {
+    extern __shared__ __attribute__((aligned(16))) f32x4 red[];  // [part][fragment * 4 + entry group][lane]
+    __shared__ float s_b[kWgParts][kBwdNP];
+    const int lane = threadIdx.x & 63, l31 = lane & 31, kh = lane >> 5;
+    const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c0 = blockIdx.x * kWgCols, slice = blockIdx.y;
+    const int c = min(c0 + 4 * l31, d_in - 4);                   // d_in % 8 == 0: 4 columns inside or the last ones again
+    const int chunks = ceil_div(T, kWgChunk);
+    const int s_begin = slice * slice_chunks, s_n = min(slice_chunks, chunks - s_begin);
+    const int k0 = s_begin + part * s_n / kWgParts, k1 = s_begin + (part + 1) * s_n / kWgParts;
+
+    struct Chunk { uint2 x[8]; u32x4 d[3]; };
+    auto load = [&](Chunk& f, int ch) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) { acc0[i] = 0.f; acc1[i] = 0.f; }
+        for (int j = 0; j < 8; ++j) {   // tokens past the last one: the last one again, their dg is zero
+            const int t = min(ch * kWgChunk + kh * 8 + j, T - 1);
+            f.x[j] = *reinterpret_cast<const uint2*>(x + (size_t)t * d_in + c);
+        }
+        const uint16_t* d = dgs + ((size_t)(ch * 2 + kh) * 3 * kBwdNP + l31) * 8;
+#pragma unroll
+        for (int term = 0; term < 3; ++term) f.d[term] = *reinterpret_cast<const u32x4*>(d + term * kBwdNP * 8);
+    };
+    f32x16 acc[4];
+#pragma unroll
+    for (int f = 0; f < 4; ++f)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[f][i] = 0.f;
     float bsum = 0.f;
-    uint32_t xv[R];
-    float dv[R];
-    const uint32_t* xw = reinterpret_cast<const uint32_t*>(x);
-    // lane part of the addresses (in dwords); the token part is uniform, so a full pair needs no per-lane arithmetic
-    const int lane_x = (kh * d_in + cc) >> 1;
-    const int row_dwords = d_in >> 1;
-    // pair p of this wavefront = tokens t_begin + 2p (lanes 0..31) and t_begin + 2p + 1 (lanes 32..63)
-    auto load_pair = [&](int slot, int pair, bool inside) {
-        const int t0 = t_begin + 2 * pair;
-        if (inside) {                                        // both tokens lie in [t_begin, t_end)
-            xv[slot] = xw[(size_t)t0 * row_dwords + lane_x];
-            dv[slot] = dg[(size_t)t0 * kBwdNP + lane];
-        } else {
-            const int t = t0 + kh;
-            const int tc = min(t, T - 1);
-            xv[slot] = xw[((size_t)tc * d_in + cc) >> 1];
-            const float d = dg[(size_t)tc * kBwdNP + n];
-            dv[slot] = t < t_end ? d : 0.f;                  // tokens past the range contribute nothing
-        }
-    };
-    const int pairs = (max(t_end - t_begin, 0) + 1) / 2;
-    // The loads of R pairs are in flight; each step consumes one pair (two MFMAs) and then requests the pair R
-    // steps ahead into the same registers, so the load unit and the matrix cores work side by side instead of in
-    // bursts.  The scheduling barriers keep the compiler from gathering the loads of a round at its top.
-    // The operands of a step are converted one step ahead, while the matrix cores run the step before (a conversion
-    // placed right in front of its MFMA holds the MFMA back by about 20 cycles).
-    float cur_d = 0.f, cur_a0 = 0.f, cur_a1 = 0.f;
-    auto convert = [&](int slot) {
-        cur_d = dv[slot];
-        cur_a0 = __uint_as_float(xv[slot] << 16);
-        cur_a1 = __uint_as_float(xv[slot] & 0xffff0000u);
-    };
-    auto round = [&](auto mode, int p) {                     // mode 0: refill inside, 1: refill at the ragged end, 2: none
+    const bool bias_tile = blockIdx.x == 0;                      // uniform
+    auto multiply = [&](const Chunk& f) {
 #pragma unroll
-        for (int u = 0; u < R; ++u) {
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(cur_d, cur_a0, acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(cur_d, cur_a1, acc1, 0, 0, 0);
-            bsum += cur_d;
-            if constexpr (decltype(mode)::value != 2) load_pair(u, p + R + u, decltype(mode)::value == 0);
-            convert((u + 1) % R);                            // slot 0 at the end of a round: refilled at its first step
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    };
-    if (pairs > 0) {
+        for (int q = 0; q < 4; ++q) {                            // column c + q
+            u32x4 v;
 #pragma unroll
-        for (int u = 0; u < R; ++u) load_pair(u, u, false);
-        convert(0);
-        for (int p = 0; p < pairs; p += R) {
-            if (t_begin + 2 * (p + 2 * R) <= t_end) round(std::integral_constant<int, 0>{}, p);
-            else if (p + R < pairs) round(std::integral_constant<int, 1>{}, p);
-            else round(std::integral_constant<int, 2>{}, p);
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t even = q < 2 ? f.x[2 * j].x : f.x[2 * j].y, odd = q < 2 ? f.x[2 * j + 1].x : f.x[2 * j + 1].y;
+                v[j] = __builtin_amdgcn_perm(odd, even, q % 2 == 0 ? 0x05040100u : 0x07060302u);
+            }
+#pragma unroll
+            for (int term = 2; term >= 0; --term)
+                acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.d[term]),
+                                                                 __builtin_bit_cast(bf16x8, v), acc[q], 0, 0, 0);
+        }
+        if (bias_tile)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                bsum += ((bf16_bits_to_float(f.d[2][j] & 0xffffu) + bf16_bits_to_float(f.d[1][j] & 0xffffu)) +
+                         bf16_bits_to_float(f.d[0][j] & 0xffffu)) +
+                        ((bf16_bits_to_float(f.d[2][j] >> 16) + bf16_bits_to_float(f.d[1][j] >> 16)) +
+                         bf16_bits_to_float(f.d[0][j] >> 16));
+    };
+    Chunk f[kWgRing];
+#pragma unroll
+    for (int u = 0; u < kWgRing; ++u)
+        if (k0 + u < k1) load(f[u], k0 + u);
+    for (int ch = k0; ch < k1; ch += kWgRing) {
+#pragma unroll
+        for (int u = 0; u < kWgRing; ++u) {
+            if (ch + u >= k1) break;                             // uniform per wavefront
+            multiply(f[u]);
+            if (ch + u + kWgRing < k1) load(f[u], ch + u + kWgRing);
         }
     }
-    // ---- second token half into LDS, first half adds it ----
+    // accumulator entry i of lane l: adapter 8*(i/4) + 4*(l/32) + i%4, column c0 + 4 * (l%32) + fragment
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            red[(part * 16 + q * 4 + g) * 64 + lane] = f32x4{acc[q][4 * g], acc[q][4 * g + 1], acc[q][4 * g + 2], acc[q][4 * g + 3]};
     bsum += __shfl_xor(bsum, 32);
-    if (thalf == 1) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) { red[chalf][i][lane] = acc0[i]; red[chalf][16 + i][lane] = acc1[i]; }
-        if (chalf == 0 && kh == 0) s_b[n] = bsum;
-    }
+    if (kh == 0) s_b[part][l31] = bsum;
     __syncthreads();
-    if (thalf == 1) return;
+    // 16-byte pieces in the order of wpart, the parts added in order
+    for (int p = threadIdx.x; p < kWgCols * kBwdNP / 4; p += kWgThreads) {
+        const int col = p / (kBwdNP / 4), piece = p % (kBwdNP / 4);
+        const int at = ((col & 3) * 4 + piece / 2) * 64 + (piece & 1) * 32 + col / 4;
+        f32x4 v = red[at];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) { acc0[i] += red[chalf][i][lane]; acc1[i] += red[chalf][16 + i][lane]; }
-    // accumulator entry i of lane l: adapter 8*(i/4) + 4*(l/32) + i%4, column slot l%32
-    if (c < d_in) {
-        float* p = wpart + ((size_t)slice * d_in + c) * kBwdNP + kh * 4;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            *reinterpret_cast<f32x4*>(p + q * 8) = f32x4{acc0[4 * q], acc0[4 * q + 1], acc0[4 * q + 2], acc0[4 * q + 3]};
-            *reinterpret_cast<f32x4*>(p + kBwdNP + q * 8) =
-                f32x4{acc1[4 * q], acc1[4 * q + 1], acc1[4 * q + 2], acc1[4 * q + 3]};
-        }
+        for (int w = 1; w < kWgParts; ++w) v += red[w * 16 * 64 + at];
+        if (c0 + col < d_in) *reinterpret_cast<f32x4*>(wpart + ((size_t)slice * d_in + c0 + col) * kBwdNP + piece * 4) = v;
     }
-    if (blockIdx.x == 0 && chalf == 0 && kh == 0) bpart[slice * kBwdNP + n] = bsum + s_b[n];
+    if (bias_tile && threadIdx.x < kBwdNP) {
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWgParts; ++w) v += s_b[w][threadIdx.x];
+        bpart[slice * kBwdNP + threadIdx.x] = v;
+    }
 }
 
 // dW_gate[c][n] = sum of the slices in order (thread per (c, padded n)); the last workgroup does dbias.
@@ -393,16 +410,11 @@ bool gate_backward_applies(int T, int d_in, int d_out, int N, int r, bool bf16) 
            gemm_dense_splitk_ok(T, d_in, prep_wcat_rows(N, r)) && gemm_dense_splitk_ok(T, d_out, N * r);
 }
 
-static int wgrad_slices(int T, int d_in) {
-    const int col_tiles = ceil_div(d_in, kWgCols);
-    int slices = ceil_div(512, col_tiles);   // two workgroups per CU (measured: 256 to 2048 workgroups tried)
-    const int most = ceil_div(T, 2 * kWgChunk);
-    if (slices > most) slices = most;
-    return slices < 1 ? 1 : slices;
-}
-static int wgrad_slice_tokens(int T, int d_in) {   // a multiple of one chunk per token half
-    constexpr int step = 2 * kWgChunk;
-    return ceil_div(ceil_div(T, wgrad_slices(T, d_in)), step) * step;
+// Chunks of 16 tokens per slice: about one workgroup per CU, a chunk or more for each wavefront.
+static int wgrad_slice_chunks(int T, int d_in) {
+    const int chunks = ceil_div(T, kWgChunk), col_tiles = ceil_div(d_in, kWgCols);
+    const int most = ceil_div(chunks, kWgParts), want = ceil_div(256, col_tiles);
+    return ceil_div(chunks, want < most ? want : most);
 }
 
 GateBackwardLayout gate_backward_layout(int T, int d_in, int d_out, int N, int r) {
@@ -412,8 +424,8 @@ GateBackwardLayout gate_backward_layout(int T, int d_in, int d_out, int N, int r
     auto take = [&](size_t bytes) { const size_t o = off; off = align_up(off + bytes, 256); return o; };
     L.part_x = take((size_t)gemm_dense_splits(T, d_in, CR) * T * CR * sizeof(float));
     L.part_dy = take((size_t)gemm_dense_splits(T, d_out, NR) * T * NR * sizeof(float));
-    L.dg = take((size_t)T * kBwdNP * sizeof(float));
-    const int slices = ceil_div(T, wgrad_slice_tokens(T, d_in));
+    L.dgs = take((size_t)align_up(ceil_div(T, 8), 2) * 3 * kBwdNP * 8 * sizeof(uint16_t));
+    const int slices = ceil_div(ceil_div(T, kWgChunk), wgrad_slice_chunks(T, d_in));
     L.wpart = take((size_t)slices * d_in * kBwdNP * sizeof(float));
     L.bpart = take((size_t)slices * kBwdNP * sizeof(float));
     L.ext = (int)align_up((size_t)NR + 3 * kBwdNP, 64);
@@ -421,6 +433,10 @@ GateBackwardLayout gate_backward_layout(int T, int d_in, int d_out, int N, int r
     L.xt = take((size_t)d_in * L.ext * sizeof(uint16_t));
     L.total = off;
     return L;
+}
+
+hipError_t gate_bwd_init_kernels() {
+    return ensure_lds_limit(reinterpret_cast<const void*>(&gate_bwd_wgrad_kernel), kWgLds);
 }
 
 hipError_t launch_gate_backward(const void* x, const void* dy, const void* wcat, const void* B, const float* bias,
@@ -435,7 +451,7 @@ hipError_t launch_gate_backward(const void* x, const void* dy, const void* wcat,
     const int CR = prep_wcat_rows(N, r), NR = N * r;
     const float* part_x = part_x_given != nullptr ? part_x_given : reinterpret_cast<float*>(ws + L.part_x);
     float* part_dy = reinterpret_cast<float*>(ws + L.part_dy);
-    float* dg = reinterpret_cast<float*>(ws + L.dg);
+    bf16_t* dgs = reinterpret_cast<bf16_t*>(ws + L.dgs);
     float* wpart = reinterpret_cast<float*>(ws + L.wpart);
     float* bpart = reinterpret_cast<float*>(ws + L.bpart);
     hipError_t e = hipSuccess;
@@ -445,7 +461,7 @@ hipError_t launch_gate_backward(const void* x, const void* dy, const void* wcat,
     if (e != hipSuccess) return e;
     DlogitsArgs a{};
     a.part_x = part_x; a.part_dy = part_dy; a.bias = bias; a.idx_in = idx_in; a.w_in = w_in; a.labels = labels;
-    a.dg = dg; a.d_logits = d_logits;
+    a.dgs = dgs; a.d_logits = d_logits;
     a.hx = dx != nullptr ? reinterpret_cast<bf16_t*>(ws + L.hx) : nullptr;
     a.ext = L.ext;
     a.S1 = (part_x_given != nullptr && part_x_splits > 0) ? part_x_splits : gemm_dense_splits(T, d_in, CR);
@@ -453,7 +469,7 @@ hipError_t launch_gate_backward(const void* x, const void* dy, const void* wcat,
     a.CR = CR; a.NR = NR; a.T = T; a.N = N; a.r = r; a.k = k; a.scale = scale; a.beta = beta;
     const size_t u_bytes = dx != nullptr ? (size_t)kBwdTokens * k * r * sizeof(float) : 0;   // at most 16 KB
     if (a.S1 > 8 || a.S2 > 8) return hipErrorInvalidValue;
-    a.token_blocks = ceil_div(T, kBwdTokens);
+    a.token_blocks = (int)align_up(ceil_div(T, kBwdTokens), 2);
     uint16_t* xt = reinterpret_cast<uint16_t*>(ws + L.xt);
     int64_t blocks_all = a.token_blocks;
     if (dx != nullptr) {
@@ -467,10 +483,11 @@ hipError_t launch_gate_backward(const void* x, const void* dy, const void* wcat,
         e = launch_gemm(dy, W_t, T, d_out, d_in, true, ws + L.hx, L.ext, xt, L.ext, dx, 0, nullptr, stream);
         if (e != hipSuccess) return e;
     }
-    const int slice_tokens = wgrad_slice_tokens(T, d_in);
-    const int slices = ceil_div(T, slice_tokens);
-    gate_bwd_wgrad_kernel<<<dim3(ceil_div(d_in, kWgCols), slices), 256, 0, stream>>>(
-        (const uint16_t*)x, dg, T, d_in, slice_tokens, wpart, bpart);
+    const int slice_chunks = wgrad_slice_chunks(T, d_in);
+    const int slices = ceil_div(ceil_div(T, kWgChunk), slice_chunks);
+    if ((e = ensure_lds_limit(reinterpret_cast<const void*>(&gate_bwd_wgrad_kernel), kWgLds)) != hipSuccess) return e;
+    gate_bwd_wgrad_kernel<<<dim3(ceil_div(d_in, kWgCols), slices), kWgThreads, kWgLds, stream>>>(
+        (const uint16_t*)x, (const uint16_t*)dgs, T, d_in, slice_chunks, wpart, bpart);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const int blocks = (int)ceil_div64((int64_t)d_in * kBwdNP, 256) + 1;
     gate_bwd_reduce_kernel<<<blocks, 256, 0, stream>>>(wpart, bpart, slices, d_in, N, dW_gate, dbias);

@@ -16,6 +16,7 @@ hipError_t gemm_init_kernels();
 hipError_t gemm_decode_init_kernels();
 hipError_t gate_init_kernels();
 hipError_t shrink_init_kernels();
+hipError_t gate_bwd_init_kernels();
 hipError_t bucket_init_scratch();
 
 // ---- weight repacking, one launch: W_gate -> split bf16 fragments (bf16 gate), A -> MFMA fragments,
@@ -193,7 +194,7 @@ hipError_t launch_route_dense_select_group(const DecodeMember* mem, int G, int S
 // dx (optional, bf16 [T, d_in]): the input gradient; needs A, W_gate and W_t = the base weight transposed,
 // [d_in, d_out].
 constexpr int kGateBackwardMaxTokens = 65536;
-struct GateBackwardLayout { size_t part_x, part_dy, dg, wpart, bpart, hx, xt, total; int ext; };
+struct GateBackwardLayout { size_t part_x, part_dy, dgs, wpart, bpart, hx, xt, total; int ext; };
 bool gate_backward_applies(int T, int d_in, int d_out, int N, int r, bool bf16);
 GateBackwardLayout gate_backward_layout(int T, int d_in, int d_out, int N, int r);
 hipError_t launch_gate_backward(const void* x, const void* dy, const void* wcat, const void* B, const float* bias,

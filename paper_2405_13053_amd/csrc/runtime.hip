@@ -49,6 +49,8 @@ hipError_t init_kernels() {
     if (e != hipSuccess) return e;
     e = shrink_init_kernels();
     if (e != hipSuccess) return e;
+    e = gate_bwd_init_kernels();
+    if (e != hipSuccess) return e;
     return bucket_init_scratch();
 }
 
