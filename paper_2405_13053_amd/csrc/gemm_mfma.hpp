@@ -805,6 +805,11 @@ __device__ __forceinline__ void load_frag16(Frags16<MB, NB>& f, const bf16_t* xs
     }
 }
 
+template <int... PH, typename F>
+__device__ __forceinline__ void for_each_phase(std::integer_sequence<int, PH...>, F f) {
+    (f(std::integral_constant<int, PH>{}), ...);
+}
+
 // LOOK: whether the kernel looks for empty tiles of the extension.  The base projection and the backward pass have a
 // kernel without: the code alone, not run, costs a short call with cold weights 0.8 us (65 x 1024 -> 4096 11.5 against 10.6).
 template <int MB, int NB, int D, int EPI, bool LOOK>
@@ -936,9 +941,9 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
     // two tiles (64 K tiles of 128 x 128, one workgroup per CU, D = 4: 27.2 us with them, 24.5 without)
     int slot_x = 0, slot_w = D * kXElems;
     // REQ: 0 = tile it+D is a main tile, 1 = it is an extension tile, 2 = there is none (last D tiles)
-    // PH: it % 6 when it is known at compile time (the unrolled main loop: every slot address is then a
+    // PH: `it` in its trip when it is known at compile time (the unrolled main loop: every slot address is then a
     // constant and no address arithmetic sits between two tiles), -1 otherwise
-    auto tile_step = [&](int it, auto req, auto ph) {
+    auto tile_step = [&](int it, auto req, auto ph) __attribute__((always_inline)) {
         constexpr int REQ = decltype(req)::value, PH = decltype(ph)::value;
         using IsExt = std::integral_constant<bool, REQ == 1>;
         auto xsl = [&](int d) {   // x-slot / W-slot of tile it + d, d = 0, 1 or D
@@ -1036,18 +1041,15 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
         }
         it = nk;
     }
-    // six tiles per trip in the 256 x 256 kernel: the period of the 2-slot and 3-slot rings
-    if constexpr (MB == 8 && NB == 8 && D == 2) {
-        for (; it + 7 < nk_main; it += 6) {
-            tile_step(it, Req0{}, std::integral_constant<int, 0>{});
-            tile_step(it + 1, Req0{}, std::integral_constant<int, 1>{});
-            tile_step(it + 2, Req0{}, std::integral_constant<int, 2>{});
-            tile_step(it + 3, Req0{}, std::integral_constant<int, 3>{});
-            tile_step(it + 4, Req0{}, std::integral_constant<int, 4>{});
-            tile_step(it + 5, Req0{}, std::integral_constant<int, 5>{});
-        }
-    }
-    if constexpr (MB == 8 && NB == 8 && D == 2) {
+    // The main loop of the large tiles, a whole period of both rings (6 or 12 tiles) per trip: no slot arithmetic between two
+    // tiles.  12 tiles against one, 256 x 128 tiles: 2000 x 4096 -> 4096 54.4 and 51.6 us, with 64 adapters of rank 32 103.3
+    // and 100.8; 192 and 224 x 128: 850 28.7 and 27.2, 1531 41.5 and 40.1.  128 x 128 tiles wait on memory: no difference.
+    constexpr int TRIP = D * (D + 1);
+    if constexpr (MB >= 6 && D <= 3) {
+        for (; it + TRIP - 1 + D < nk_main; it += TRIP)
+            for_each_phase(std::make_integer_sequence<int, TRIP>{}, [&](auto ph) __attribute__((always_inline)) {
+                tile_step(it + decltype(ph)::value, Req0{}, ph);
+            });
         slot_x = (int)(xslot(it) - smem);
         slot_w = (int)(wslot(it) - smem);
     }
