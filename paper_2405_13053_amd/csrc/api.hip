@@ -57,7 +57,7 @@ WsLayout ws_layout(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
     L.ext_stride = (int)align_up((size_t)N * r, 64);
     L.wsplit = take(gate_wsplit_bytes(d_in, N, bf16));
     L.partials = take((size_t)gate_kslices(d_in, bf16) * T * NP * sizeof(float));
-    L.chunk_counts = take((size_t)bucket_chunks(T) * N * sizeof(int32_t));
+    L.chunk_counts = take((size_t)routing_chunks(T) * N * sizeof(int32_t));
     L.counts = take((size_t)N * sizeof(int32_t));
     L.offsets = take((size_t)(N + 1) * sizeof(int32_t));
     L.bucket_tok = take(pairs * sizeof(int32_t));
@@ -284,7 +284,7 @@ int meteora_workspace_regions(int T, int d_in, int d_out, int N, int r, int k, m
             const int S = gemm_splitk_splits(T, d_in, d_out, bf16);
             if (S > 0) wr("splitk", (size_t)(S + 1) * T * d_out * sizeof(float));
         } else {
-            wr("chunk_counts", (size_t)bucket_chunks(T) * N * sizeof(int32_t));
+            wr("chunk_counts", (size_t)routing_chunks(T) * N * sizeof(int32_t));
             wr("counts", (size_t)N * sizeof(int32_t));
             wr("offsets", (size_t)(N + 1) * sizeof(int32_t));
             wr("bucket_tok", pairs * sizeof(int32_t));

@@ -77,7 +77,8 @@ __global__ __launch_bounds__(256) void bucket_scatter_kernel(const int32_t* __re
                                                              int32_t* __restrict__ offsets,
                                                              int32_t* __restrict__ bucket_tok,
                                                              int32_t* __restrict__ bucket_slot,
-                                                             u32x4* __restrict__ clear, int clear_row16, int T) {
+                                                             u32x4* __restrict__ clear, int clear_row16, int T,
+                                                             int chunk_tokens) {
     __shared__ int part_total[4][kMaxAdapters], part_before[4][kMaxAdapters];
     __shared__ int running[kMaxAdapters];    // next write position of adapter j for this chunk
     __shared__ int wave_hist[4][kMaxAdapters];
@@ -85,8 +86,8 @@ __global__ __launch_bounds__(256) void bucket_scatter_kernel(const int32_t* __re
     const int c = blockIdx.x;
 
     if (clear != nullptr) {   // this chunk's rows of the dense expand operand start as zeros
-        const int rows = min(kBucketChunkTokens, T - c * kBucketChunkTokens);
-        u32x4* dst = clear + (size_t)c * kBucketChunkTokens * clear_row16;
+        const int rows = min(chunk_tokens, T - c * chunk_tokens);
+        u32x4* dst = clear + (size_t)c * chunk_tokens * clear_row16;
         for (int i = threadIdx.x; i < rows * clear_row16; i += 256) dst[i] = u32x4{0u, 0u, 0u, 0u};
     }
 
@@ -130,7 +131,7 @@ __global__ __launch_bounds__(256) void bucket_scatter_kernel(const int32_t* __re
     }
     __syncthreads();
 
-    const int chunk_pairs = kBucketChunkTokens * k;
+    const int chunk_pairs = chunk_tokens * k;
     const int64_t base = (int64_t)c * chunk_pairs;
     for (int it = 0; it * 256 < chunk_pairs; ++it) {
         const int i = it * 256 + threadIdx.x;
@@ -170,7 +171,8 @@ hipError_t launch_bucket(const int32_t* topk_idx, int T, int k, int N, int32_t* 
                          int32_t* counts, int32_t* offsets, int32_t* bucket_tok, int32_t* bucket_slot,
                          void* clear_rows, int clear_row_bytes, hipStream_t stream) {
     const int64_t pairs = (int64_t)T * k;
-    const int nchunks = bucket_chunks(T);
+    const int chunk_tokens = have_hist ? routing_chunk_tokens(T) : kBucketChunkTokens;
+    const int nchunks = ceil_div(T, chunk_tokens);
     if (!have_hist) {
         bucket_hist_kernel<<<nchunks, 256, 0, stream>>>(topk_idx, pairs, k, N, chunk_counts);
         hipError_t e = hipGetLastError();
@@ -178,7 +180,7 @@ hipError_t launch_bucket(const int32_t* topk_idx, int T, int k, int N, int32_t* 
     }
     bucket_scatter_kernel<<<nchunks, 256, 0, stream>>>(topk_idx, pairs, k, N, nchunks, chunk_counts, counts,
                                                        offsets, bucket_tok, bucket_slot, (u32x4*)clear_rows,
-                                                       clear_row_bytes / 16, T);
+                                                       clear_row_bytes / 16, T, chunk_tokens);
     return hipGetLastError();
 }
 

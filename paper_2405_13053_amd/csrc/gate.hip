@@ -36,11 +36,11 @@ __global__ __launch_bounds__(kRowThreads) void gate_logits_f32_kernel(const floa
 // leaves the chunk's adapter histogram for the scatter pass.
 // ------------------------------------------------------------------------------------------
 constexpr int kTopkTokensPerWave = 4;
-constexpr int kTopkWaves = kBucketChunkTokens / kTopkTokensPerWave;
-static_assert(kTopkWaves * 64 <= 1024, "one workgroup per bucketing chunk");
+static_assert(kBucketChunkTokens / kTopkTokensPerWave * 64 <= 1024, "one workgroup per bucketing chunk");
 
-template <int NP>
-__global__ __launch_bounds__(kTopkWaves * 64) void gate_topk_kernel(
+// WAVES: a workgroup is a bucketing chunk of 4 * WAVES tokens.  U: K slices whose loads are in flight
+template <int NP, int WAVES, int U>
+__global__ __launch_bounds__(WAVES * 64) void gate_topk_kernel(
     const float* __restrict__ partials, int KS, const float* __restrict__ bias, int T, int N, int k,
     float inv_temperature, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, float* __restrict__ logits,
     int32_t* __restrict__ chunk_counts) {
@@ -51,24 +51,24 @@ __global__ __launch_bounds__(kTopkWaves * 64) void gate_topk_kernel(
     const int col = lane & (NP - 1), sub = lane / NP;
     if (threadIdx.x < kMaxAdapters) hist[threadIdx.x] = 0;
     __syncthreads();
-    const int t0 = blockIdx.x * kBucketChunkTokens + wave * kTopkTokensPerWave;
+    const int t0 = (blockIdx.x * WAVES + wave) * kTopkTokensPerWave;
 
     float g[G];
     int tok[G];
 #pragma unroll
     for (int i = 0; i < G; ++i) { g[i] = 0.f; tok[i] = t0 + i * TPP + sub; }
     if (col < N) {
-        // fixed order over K-slices; 16 slices' loads are issued together, from clamped addresses so that no
+        // fixed order over K-slices; U slices' loads are issued together, from clamped addresses so that no
         // branch separates them (the loop is latency-bound); a slice past the end is not added
-        for (int s0 = 0; s0 < KS; s0 += 16) {
-            float v[16][G];
+        for (int s0 = 0; s0 < KS; s0 += U) {
+            float v[U][G];
 #pragma unroll
-            for (int u = 0; u < 16; ++u)
+            for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int i = 0; i < G; ++i)
                     v[u][i] = partials[((size_t)min(s0 + u, KS - 1) * T + min(tok[i], T - 1)) * NP + col];
 #pragma unroll
-            for (int u = 0; u < 16; ++u)
+            for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int i = 0; i < G; ++i)
                     if (s0 + u < KS) g[i] += v[u][i];
@@ -265,13 +265,18 @@ hipError_t gate_init_kernels() {
 hipError_t launch_gate_topk(const float* partials, int KS, const float* bias, int T, int N, int k,
                             float inv_temperature, int32_t* topk_idx, float* topk_w, float* logits,
                             int32_t* chunk_counts, hipStream_t stream) {
-    if (padded_adapters(N) == 32)
-        gate_topk_kernel<32><<<bucket_chunks(T), kTopkWaves * 64, 0, stream>>>(
-            partials, KS, bias, T, N, k, inv_temperature, topk_idx, topk_w, logits, chunk_counts);
-    else
-        gate_topk_kernel<64><<<bucket_chunks(T), kTopkWaves * 64, 0, stream>>>(
-            partials, KS, bias, T, N, k, inv_temperature, topk_idx, topk_w, logits, chunk_counts);
-    return hipGetLastError();
+    auto go = [&](auto kern, int waves) {
+        kern<<<ceil_div(T, waves * kTopkTokensPerWave), waves * 64, 0, stream>>>(partials, KS, bias, T, N, k, inv_temperature,
+                                                                                topk_idx, topk_w, logits, chunk_counts);
+        return hipGetLastError();
+    };
+    const bool fine = chunk_counts == nullptr || routing_chunk_tokens(T) == kFineChunkTokens;
+    if (padded_adapters(N) == 32) {
+        if (fine) return KS <= 8 ? go(gate_topk_kernel<32, 4, 8>, 4) : go(gate_topk_kernel<32, 4, 16>, 4);
+        return KS <= 8 ? go(gate_topk_kernel<32, 16, 8>, 16) : go(gate_topk_kernel<32, 16, 16>, 16);
+    }
+    if (fine) return KS <= 8 ? go(gate_topk_kernel<64, 4, 8>, 4) : go(gate_topk_kernel<64, 4, 16>, 4);
+    return KS <= 8 ? go(gate_topk_kernel<64, 16, 8>, 16) : go(gate_topk_kernel<64, 16, 16>, 16);
 }
 
 }  // namespace meteora

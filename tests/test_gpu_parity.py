@@ -335,6 +335,12 @@ def test_linear_forward_matches_oracle(shape):
     _check_layer(shape, seed=41)
 
 
+# bucketed sequence (more than 32 adapters): chunks of 16 tokens up to 2048 tokens, of 64 above; up to 8 K slices and more
+@pytest.mark.parametrize("T,d_in,N,k", [(65, 136, 64, 8), (95, 4616, 33, 3), (2047, 72, 64, 4), (2048, 136, 40, 1), (2049, 136, 64, 4)])
+def test_bucketing_chunk_sizes(T, d_in, N, k):
+    _check_layer(LS(T, d_in, 136, N, 8, k, 2.0, "bf16", "zipf", "chunks"), seed=63, rows="sample")
+
+
 # fp32 layers with few adapters in one launch: tiles of 16 tokens and 16 columns, K in steps of 16 over four wavefronts
 @pytest.mark.parametrize("T,d_in,d_out,N,r,k", [
     (1, 8, 8, 1, 1, 1), (16, 16, 16, 16, 2, 8), (17, 24, 24, 16, 4, 3), (33, 72, 264, 4, 8, 2), (15, 512, 8, 4, 8, 1),
