@@ -210,7 +210,9 @@ bool gemm_dense_splitk_ok(int T, int d_in, int rows) {
 int gemm_dense_splits(int T, int d_in, int rows) {
     const bool small = dense_small_tiles(T);
     const int tiles = ceil_div(T, 128) * ceil_div(rows, small ? 128 : 320), nk = d_in / kGemmBK;
-    int S = ((small ? 384 : 256) + tiles / 2) / tiles;
+    // 128 x 320 tiles: one workgroup per CU at most, since a few more take a second round (layers of 4096 -> 1024, rank 8, on
+    // 282 and 188 workgroups: 12000 x 5120 155.3 and 148.0 us)
+    int S = small ? (384 + tiles / 2) / tiles : 256 / tiles;
     if (S > nk / 4) S = nk / 4;                // at least 4 K tiles per split
     if (S > 8) S = 8;                          // more splits cost the kernel that adds them more than they save here
     return S < 1 ? 1 : S;

@@ -1043,9 +1043,10 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
     }
     // The main loop of the large tiles, a whole period of both rings (6 or 12 tiles) per trip: no slot arithmetic between two
     // tiles.  12 tiles against one, 256 x 128 tiles: 2000 x 4096 -> 4096 54.4 and 51.6 us, with 64 adapters of rank 32 103.3
-    // and 100.8; 192 and 224 x 128: 850 28.7 and 27.2, 1531 41.5 and 40.1.  128 x 128 tiles wait on memory: no difference.
+    // and 100.8; 192 and 224 x 128: 850 28.7 and 27.2, 1531 41.5 and 40.1.  6 tiles, 128 x 320: layers
+    // of 16384 x 14336 -> 1024 with 544 rows of Wcat 585 and 575.  128 x 128 tiles wait on memory: no difference.
     constexpr int TRIP = D * (D + 1);
-    if constexpr (MB >= 6 && D <= 3) {
+    if constexpr ((MB >= 6 || NB > 8) && D <= 3) {
         for (; it + TRIP - 1 + D < nk_main; it += TRIP)
             for_each_phase(std::make_integer_sequence<int, TRIP>{}, [&](auto ph) __attribute__((always_inline)) {
                 tile_step(it + decltype(ph)::value, Req0{}, ph);
