@@ -39,7 +39,7 @@ int dense_midsplit_splits(int T, int d_in, int d_out, int N, int r, bool bf16) {
     // 4096 -> 4096; 43.3 against 47.6 at T = 160 for 4096 -> 14336; 107 against 131 at T = 704 for 14336 -> 4096)
     if (!route_dense_applies(T, d_in, N, r, bf16) || d_out % 8 != 0 || !gemm_dense_splitk_ok(T, d_in, d_out)) return 0;
     const int S = gemm_multi_cap_splits(T, ceil_div(d_out, 128) + ceil_div(prep_wcat_rows(N, r), 128),
-                                        gemm_dense_splits(T, d_in, d_out));
+                                        gemm_dense_splits(T, d_in, d_out), d_in / 64, (int64_t)d_out + prep_wcat_rows(N, r));
     return S >= 2 ? S : 0;
 }
 
@@ -674,8 +674,12 @@ int group_mid_splits(const int* d_out, const bool* packed, int G, int T, int d_i
     if (S > nk / 4) S = nk / 4;
     if (S > 8) S = 8;
     int col_tiles = 0;
-    for (int g = 0; g < G; ++g) col_tiles += ceil_div(d_out[g], 128) + ceil_div(cat_rows, 128);
-    S = gemm_multi_cap_splits(T, col_tiles, S);
+    int64_t rows = 0;
+    for (int g = 0; g < G; ++g) {
+        col_tiles += ceil_div(d_out[g], 128) + ceil_div(cat_rows, 128);
+        rows += d_out[g] + cat_rows;
+    }
+    S = gemm_multi_cap_splits(T, col_tiles, S, nk, rows);
     return S < 1 ? 1 : S;
 }
 

@@ -253,10 +253,22 @@ static int gemm_multi_row_blocks(int T) {
 // -> 45.8 and 55.2, 5120 -> 5120 three times (129) 67.4 and 80.6 -> 55.6 and 69.2, 4096 -> 9216 twice (150) 52.1 and 62.9 ->
 // 47.4 and 58.8; with two splits 4096 -> 9728 twice (158) 55.6 and 66.5 against 57.8 and 69.2, 4096 -> 20480 (163) 59.0 and
 // 65.2 against 58.0 and 66.0.
-int gemm_multi_cap_splits(int T, int col_tiles, int S) {
+// Of the splits that leaves, the number at which the K tiles of a split and the fp32 tiles written and read again take the
+// least: a K tile takes about 0.2 + 0.07 us for every 32 rows, a MB of fp32 tiles 0.45 us.  Whole calls, as many splits as
+// fit and so: 512 x 2048 -> 2048 22.3 (6 splits) and 20.2 us (4), 700 x 4096 -> 1024 26.0 and 24.7, 900 x 1024 -> 1024 20.7 and
+// 18.9, 200 x 1024 -> 4096 19.4 and 17.7, 96 x 4096 -> 4096 18.7 and 18.2; 1531 x 1024 -> 1024 20.1 and 21.1.
+int gemm_multi_cap_splits(int T, int col_tiles, int S, int nk, int64_t rows) {
     const int cap = 256 / (ceil_div(T, 256) * (col_tiles > 0 ? col_tiles : 1));   // 256 CUs
     if (T <= 128 && cap < 2 && S >= 3) return S;
-    return S > cap ? (cap > 0 ? cap : 1) : S;
+    if (S > cap) S = cap > 0 ? cap : 1;
+    const float per_tile = 0.2f + 0.07f * (float)gemm_multi_row_blocks(T), per_split = 0.45e-6f * 4.f * (float)T * (float)rows;
+    int best = S;
+    float least = 0.f;
+    for (int s = S; s >= 2; --s) {
+        const float us = per_tile * (float)ceil_div(nk, s) + per_split * (float)s;
+        if (s == S || us < least) { least = us; best = s; }
+    }
+    return best;
 }
 
 hipError_t launch_gemm_dense_splitk_multi(const void* x, const DenseOperand* ops, int n_ops, int S, int T, int d_in,

@@ -83,7 +83,7 @@ bool gemm_dense_splitk_ok(int T, int d_in, int rows);
 int gemm_dense_splits(int T, int d_in, int rows);
 // few-tile split-K launches over several matrices: S capped to one workgroup per CU, or for few tokens to two
 // (col_tiles: the 128-column tiles of all the matrices of the launch)
-int gemm_multi_cap_splits(int T, int col_tiles, int S);
+int gemm_multi_cap_splits(int T, int col_tiles, int S, int nk, int64_t rows);
 hipError_t launch_gemm_dense_splitk(const void* x, const void* Wcat, int T, int d_in, int rows, float* partial,
                                     hipStream_t stream);
 
