@@ -257,29 +257,43 @@ def linear_forward(x, W, W_gate, gate_bias, A, B, k: int, scale: float, out: Opt
                    packed: Optional[torch.Tensor] = None, inv_temperature: float = 1.0):
     """meteora_linear_forward / meteora_linear_forward_packed (if `packed` is given): the whole layer (Eq. 2)."""
     T, d_in = x.shape
-    d_out = W.shape[0]
-    N, _, r = A.shape
-    _chk(x, "x"); _chk(W, "W", x.dtype, (d_out, d_in)); _chk(W_gate, "W_gate", torch.float32, (d_in, N))
-    _chk(gate_bias, "gate_bias", torch.float32, (N,))
-    _chk(A, "A", x.dtype, (N, d_in, r)); _chk(B, "B", x.dtype, (N, r, d_out))
-    _chk(packed, "packed", torch.uint8)
+    Ws, As, dtype = W.shape, A.shape, x.dtype
+    d_out = Ws[0]
+    N, _, r = As
     if out is None:
-        out = torch.empty((T, d_out), dtype=x.dtype, device=x.device)
-    _chk(out, "out", x.dtype, (T, d_out))
+        _chk(x, "x"); _chk(W, "W", dtype, (d_out, d_in))
+        out = torch.empty((T, d_out), dtype=dtype, device=x.device)
+    # written out: as calls of _chk the tests of a call are an eighth of a small layer's host time; they say what is wrong
+    if not (W_gate is not None and B is not None and
+            W.dtype == dtype and A.dtype == dtype and B.dtype == dtype and out.dtype == dtype and
+            W_gate.dtype == torch.float32 and
+            Ws == (d_out, d_in) and As == (N, d_in, r) and B.shape == (N, r, d_out) and out.shape == (T, d_out) and
+            W_gate.shape == (d_in, N) and
+            x.is_cuda and W.is_cuda and A.is_cuda and B.is_cuda and out.is_cuda and W_gate.is_cuda and
+            x.is_contiguous() and W.is_contiguous() and A.is_contiguous() and B.is_contiguous() and out.is_contiguous() and
+            W_gate.is_contiguous()):
+        _chk(x, "x"); _chk(W, "W", dtype, (d_out, d_in)); _chk(W_gate, "W_gate", torch.float32, (d_in, N))
+        _chk(A, "A", dtype, (N, d_in, r)); _chk(B, "B", dtype, (N, r, d_out))
+        _chk(out, "out", dtype, (T, d_out))
+    if gate_bias is not None:
+        _chk(gate_bias, "gate_bias", torch.float32, (N,))
+    if packed is not None:
+        _chk(packed, "packed", torch.uint8)
     idx = w = None
     if return_routing:
         idx = torch.empty((T, k), dtype=torch.int32, device=x.device)
         w = torch.empty((T, k), dtype=torch.float32, device=x.device)
-    ws = _ws(ws, lambda: workspace_bytes(T, d_in, d_out, N, r, k, x.dtype), x.device)
-    lib = load_library()
+    if ws is None:
+        ws = _ws(None, lambda: workspace_bytes(T, d_in, d_out, N, r, k, dtype), x.device)
+    lib = _lib or load_library()
     if packed is None:
-        st = lib.meteora_linear_forward(_p(x), _p(W), _p(W_gate), _p(gate_bias), _p(A), _p(B), T, d_in, d_out, N, r,
-                                        k, float(scale), float(inv_temperature), _dt(x), _p(out), _p(idx), _p(w),
-                                        _p(ws), ws.numel(), _stream())
+        st = lib.meteora_linear_forward(x.data_ptr(), W.data_ptr(), _p(W_gate), _p(gate_bias), A.data_ptr(), _p(B), T, d_in,
+                                        d_out, N, r, k, float(scale), float(inv_temperature), _dt(x), out.data_ptr(), _p(idx), _p(w),
+                                        ws.data_ptr(), ws.numel(), _stream())
     else:
-        st = lib.meteora_linear_forward_packed(_p(x), _p(W), _p(W_gate), _p(gate_bias), _p(A), _p(B), _p(packed),
-                                               packed.numel(), T, d_in, d_out, N, r, k, float(scale),
-                                               float(inv_temperature), _dt(x), _p(out), _p(idx), _p(w), _p(ws),
+        st = lib.meteora_linear_forward_packed(x.data_ptr(), W.data_ptr(), _p(W_gate), _p(gate_bias), A.data_ptr(), _p(B),
+                                               packed.data_ptr(), packed.numel(), T, d_in, d_out, N, r, k,
+                                               float(scale), float(inv_temperature), _dt(x), out.data_ptr(), _p(idx), _p(w), ws.data_ptr(),
                                                ws.numel(), _stream())
     if st != 0:
         raise MeteoraError(st, "meteora_linear_forward")
