@@ -218,7 +218,7 @@ int gemm_dense_splits(int T, int d_in, int rows) {
     return S < 1 ? 1 : S;
 }
 
-template <int MB, int NB, int D, int EPI = kEpiPartialThrough>
+template <int MB, int NB, int D, int EPI>
 static hipError_t launch_dense(GemmArgs a, hipStream_t stream) {   // fp32 split-K tiles; tiles_n is the caller's
     a.tiles_m = ceil_div(a.T, MB * 32);
     if (a.tiles_n == 0) a.tiles_n = ceil_div(a.d_out, NB * 32);
@@ -271,6 +271,25 @@ int gemm_multi_cap_splits(int T, int col_tiles, int S, int nk, int64_t rows) {
     return best;
 }
 
+// The fp32 tiles go through the L2 (kWriteThrough) unless the launch streams many weights: those writes then share HBM with the
+// stream.  Whole calls of 96, 144 and 256 tokens, weights not in the caches, ordinary and written through: 4096 -> 4096
+// (36 MB) 19.5, 22.7, 28.1 and 18.6, 21.6, 26.8 us; 5120 -> 5120 (56 MB) 26.4, 31.6, 38.4 and 27.0, 32.2, 39.3; 14336 -> 4096
+// (127 MB) 40.5, 45.0, 56.1 and 40.8, 45.8, 56.6.
+constexpr int64_t kWriteThroughWeights = 48 << 20;
+
+template <int EPI>
+static hipError_t launch_multi_tiles(const GemmArgs& a, bool two, hipStream_t stream) {
+    if (two) return a.T <= 96 ? launch_dense<3, 4, 2, EPI>(a, stream) : launch_dense<4, 4, 2, EPI>(a, stream);
+    switch (gemm_multi_row_blocks(a.T)) {
+        case 3: return launch_dense<3, 4, 5, EPI>(a, stream);
+        case 4: return launch_dense<4, 4, 4, EPI>(a, stream);
+        case 5: return launch_dense<5, 4, 4, EPI>(a, stream);
+        case 6: return launch_dense<6, 4, 3, EPI>(a, stream);
+        case 7: return launch_dense<7, 4, 3, EPI>(a, stream);
+        default: return launch_dense<8, 4, 3, EPI>(a, stream);
+    }
+}
+
 hipError_t launch_gemm_dense_splitk_multi(const void* x, const DenseOperand* ops, int n_ops, int S, int T, int d_in,
                                           hipStream_t stream) {
     if (S < 1 || n_ops < 1 || n_ops > GemmArgs::kMaxSegments) return hipErrorInvalidValue;
@@ -278,25 +297,20 @@ hipError_t launch_gemm_dense_splitk_multi(const void* x, const DenseOperand* ops
     a.x = (const bf16_t*)x; a.T = T; a.d_in = d_in;
     a.splits = S; a.tiles_per_split = ceil_div(d_in / kGemmBK, S);
     int tile0 = 0;
+    int64_t rows = 0;
     for (int i = 0; i < n_ops; ++i) {
         if (!gemm_dense_splitk_ok(T, d_in, ops[i].rows)) return hipErrorInvalidValue;
         a.seg[i] = {(const bf16_t*)ops[i].W, ops[i].partial, ops[i].rows, tile0};
         tile0 += ceil_div(ops[i].rows, 128);
+        rows += ops[i].rows;
     }
     a.nseg = n_ops;
     a.W = a.seg[0].W; a.d_out = a.seg[0].rows; a.partial = a.seg[0].partial;   // replaced per workgroup
     a.tiles_n = tile0;
     if (((uint64_t)T + 256) * ((uint64_t)d_in * 2) >= (1ull << 32)) return hipErrorInvalidValue;
-    if (T <= 128 && tile0 * S > 256)   // two per CU
-        return T <= 96 ? launch_dense<3, 4, 2>(a, stream) : launch_dense<4, 4, 2>(a, stream);
-    switch (gemm_multi_row_blocks(T)) {
-        case 3: return launch_dense<3, 4, 5>(a, stream);
-        case 4: return launch_dense<4, 4, 4>(a, stream);
-        case 5: return launch_dense<5, 4, 4>(a, stream);
-        case 6: return launch_dense<6, 4, 3>(a, stream);
-        case 7: return launch_dense<7, 4, 3>(a, stream);
-        default: return launch_dense<8, 4, 3>(a, stream);
-    }
+    const bool two = T <= 128 && tile0 * S > 256;   // two per CU
+    return rows * d_in * 2 <= kWriteThroughWeights ? launch_multi_tiles<kEpiPartialThrough>(a, two, stream)
+                                                   : launch_multi_tiles<kEpiPartial>(a, two, stream);
 }
 
 hipError_t launch_gemm_decode_finish(const DecodeMember* mem, int G, int S, int T, int k, int r,
@@ -339,15 +353,18 @@ hipError_t gemm_init_kernels() {
     METEORA_TILES(4, 4, 3);
     METEORA_TILES(4, 4, 2);
     METEORA_RING(4, 10, 2, kEpiPartial, false);
-    METEORA_RING(4, 4, 2, kEpiPartial, false);
-    METEORA_RING(4, 4, 2, kEpiPartialThrough, false);
-    METEORA_RING(3, 4, 2, kEpiPartialThrough, false);
-    METEORA_RING(3, 4, 5, kEpiPartialThrough, false);
-    METEORA_RING(4, 4, 4, kEpiPartialThrough, false);
-    METEORA_RING(5, 4, 4, kEpiPartialThrough, false);
-    METEORA_RING(6, 4, 3, kEpiPartialThrough, false);
-    METEORA_RING(7, 4, 3, kEpiPartialThrough, false);
-    METEORA_RING(8, 4, 3, kEpiPartialThrough, false);
+#define METEORA_PARTIAL(MB, NB, D)                   \
+    METEORA_RING(MB, NB, D, kEpiPartial, false);     \
+    METEORA_RING(MB, NB, D, kEpiPartialThrough, false)
+    METEORA_PARTIAL(4, 4, 2);
+    METEORA_PARTIAL(3, 4, 2);
+    METEORA_PARTIAL(3, 4, 5);
+    METEORA_PARTIAL(4, 4, 4);
+    METEORA_PARTIAL(5, 4, 4);
+    METEORA_PARTIAL(6, 4, 3);
+    METEORA_PARTIAL(7, 4, 3);
+    METEORA_PARTIAL(8, 4, 3);
+#undef METEORA_PARTIAL
 #undef METEORA_TILES
 #undef METEORA_RING
     return e;
