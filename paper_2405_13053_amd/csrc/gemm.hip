@@ -274,7 +274,8 @@ int gemm_multi_cap_splits(int T, int col_tiles, int S, int nk, int64_t rows) {
 // The fp32 tiles go through the L2 (kWriteThrough) unless the launch streams many weights: those writes then share HBM with the
 // stream.  Whole calls of 96, 144 and 256 tokens, weights not in the caches, ordinary and written through: 4096 -> 4096
 // (36 MB) 19.5, 22.7, 28.1 and 18.6, 21.6, 26.8 us; 5120 -> 5120 (56 MB) 26.4, 31.6, 38.4 and 27.0, 32.2, 39.3; 14336 -> 4096
-// (127 MB) 40.5, 45.0, 56.1 and 40.8, 45.8, 56.6.
+// (127 MB) 40.5, 45.0, 56.1 and 40.8, 45.8, 56.6.  The line is below the smallest size that loses: from 50 to 60 MB sizes differ
+// (4096 -> 6144, 53 MB: 22.9, 25.7, 32.1 and 21.9, 24.5, 31.0), below it all of those tried gain 2 to 6%.
 constexpr int64_t kWriteThroughWeights = 48 << 20;
 
 template <int EPI>
