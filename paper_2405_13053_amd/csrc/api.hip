@@ -275,7 +275,7 @@ int meteora_workspace_regions(int T, int d_in, int d_out, int N, int r, int k, m
             wr("hdense", (size_t)T * L.ext_stride * sizeof(uint16_t));
         }
     } else if (!bf16) {
-        wr("h32", !layer_f32_applies(T, d_in, d_out, N, r) && f32_expand_apart(d_out, r, k) ? pairs * r * sizeof(float) : 0);
+        wr("h32", !layer_f32_applies(T, d_in, d_out, N, r, k) && f32_expand_apart(d_out, r, k) ? pairs * r * sizeof(float) : 0);
     } else {
         wr("partials", (size_t)gate_kslices(d_in, bf16) * T * NP * sizeof(float));
         const bool fused = gemm_fuses_expand(bf16);
@@ -603,7 +603,7 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
         return METEORA_OK;
     }
     if (!bf16) {
-        if (layer_f32_applies(T, d_in, d_out, N, r)) {
+        if (layer_f32_applies(T, d_in, d_out, N, r, k)) {
             StageScope sc(ST_GEMM, st, tslot);
             METEORA_HIP(launch_layer_f32((const float*)x, (const float*)W, W_gate, gate_bias, (const float*)A, (const float*)B,
                                          T, d_in, d_out, N, r, k, inv_temperature, scale, idx, w, (float*)out, st));

@@ -141,7 +141,7 @@ hipError_t launch_route_lora_f32(const float* x, const float* W_gate, const floa
                                  int T, int d_in, int d_out, int N, int r, int k, float inv_temperature, float scale,
                                  int32_t* topk_idx, float* topk_w, float* out, float* h /*[T,k,r], if apart*/,
                                  hipStream_t stream);
-bool layer_f32_applies(int T, int d_in, int d_out, int N, int r);   // everything in one launch
+bool layer_f32_applies(int T, int d_in, int d_out, int N, int r, int k);   // everything in one launch
 hipError_t launch_layer_f32(const float* x, const float* W, const float* W_gate, const float* bias, const float* A,
                             const float* B, int T, int d_in, int d_out, int N, int r, int k, float inv_temperature,
                             float scale, int32_t* topk_idx, float* topk_w, float* out, hipStream_t stream);

@@ -1,4 +1,5 @@
 // The layer with fp32 storage: the base projection on fp32 MFMAs, and everything else of Eq. 2 per token.
+#include <type_traits>
 #include "common.hpp"
 #include "gate_row.hpp"
 #include "kernels.hpp"
@@ -263,28 +264,152 @@ hipError_t launch_route_lora_f32(const float* x, const float* W_gate, const floa
 
 // ------------------------------------------------------------------------------------------
 // The whole layer in one launch, for few adapters: a workgroup computes 16 columns for 16 tokens, and on the
-// way, from the same x in registers, the tokens' gate logits and x * A_i of every adapter (EB blocks of 16 columns in all)
-// instead of waiting for a launch that does so once.  The four wavefronts take a quarter of K each; what is left is one
-// round through LDS, the ranking, and the rows of B of the chosen adapters.  A layer of this size is latency and launches:
-// 64 x 256 -> 256 with 4 adapters of rank 8 is two rounds of loads instead of six.
+// way the tokens' gate logits and x * A_i of every adapter (EB blocks of 16 columns in all) instead of waiting for a launch
+// that does so once.  Four wavefronts take a quarter of K each of the two products on the matrix cores, four others the
+// logits; what is left is one round through LDS, the ranking, and the rows of B of the chosen adapters.  A layer of this
+// size is latency and launches: 64 x 256 -> 256 with 4 adapters of rank 8 is two rounds of loads instead of six.
 // ------------------------------------------------------------------------------------------
+constexpr int kF32LayerThreads = 512, kF32LayerInputs = 512, kF32LayerAdapters = 16;
+constexpr int kF32LayerGate = 2048;   // most values of W_gate, four columns at least
+
+// Where gate_row's 256 threads are (part, column), its wavefront w has the parts from w * mine, and the rows m * 4 * mine
+// + part of a part are its m-th, M of them for every part (past d_in: zeros).
+struct GateRows {
+    int mine, mine_log2, stride, stride_log2, M, x_row;   // stride: values per row of W_gate in LDS; x_row: x per token
+    __host__ __device__ GateRows(int d_in, int N) {
+        const int cols_log2 = N > 8 ? 4 : N > 4 ? 3 : N > 2 ? 2 : N > 1 ? 1 : 0;   // columns: N to a power of two
+        stride_log2 = cols_log2 < 2 ? 2 : cols_log2;
+        stride = 1 << stride_log2;
+        mine_log2 = 6 - cols_log2;
+        mine = 1 << mine_log2;
+        M = ceil_div(d_in, 4 * mine);
+        x_row = M * mine + 4;           // rows four banks apart
+    }
+    __host__ __device__ int wave_floats() const { return 16 * x_row + M * mine * stride; }
+};
+
+// gate_row of 16 tokens, the part of its wavefront w, bit for bit: the same products in the same four chains per part, added
+// as there, so that a token's routing is the same in gate_topk, in the launches of the larger layers and here.  The rows
+// of x and W_gate that belong to w's parts pass through LDS (`staged`, this wavefront's own: no barrier); a lane takes a part
+// (two or four adjacent ones where N leaves fewer than 4 columns) of 4 tokens and 4 columns.
+__device__ __forceinline__ void gate_rows_f32(const __amdgpu_buffer_rsrc_t xr, const __amdgpu_buffer_rsrc_t gr, int m0, int T,
+                                              int d_in, int N, int w, int lane, float* staged,
+                                              float (&gate)[16][kF32LayerAdapters + 4]) {
+    constexpr uint32_t kOutside = 0x80000000u;
+    constexpr int XP = kF32LayerInputs / 64, WP = kF32LayerGate / 256;
+    const GateRows g(d_in, N);
+    const int rows = g.M * g.mine;
+    // row of x and W_gate that is the l-th of this wavefront
+    auto row = [&](int l) { return (((l >> g.mine_log2) * 4 + w) << g.mine_log2) + (l & (g.mine - 1)); };
+    float* const xs = staged;
+    float* const ws = staged + 16 * g.x_row;
+    // a token's x: 16-byte pieces, four lanes to a token;  W_gate: 64 / stride rows at a time
+    const int tok = lane >> 2, sub = lane & 3;
+    const uint32_t xo = (uint32_t)min(m0 + tok, T - 1) * (uint32_t)d_in;
+    u32x4 xv[XP];
+    float wv[WP];
+#pragma unroll
+    for (int p = 0; p < XP; ++p) {
+        const int i = row((p * 4 + sub) * 4);
+        if (p * 16 < rows) xv[p] = __builtin_amdgcn_raw_buffer_load_b128(xr, i < d_in ? (xo + i) * 4 : kOutside, 0, 0);
+    }
+    const int wrows = 64 >> g.stride_log2, lr = lane >> g.stride_log2, c = lane & (g.stride - 1);
+#pragma unroll
+    for (int p = 0; p < WP; ++p) {
+        const int i = row(p * wrows + lr);
+        if (p * wrows < rows)
+            wv[p] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                  gr, c < N && i < d_in ? (uint32_t)(i * N + c) * 4 : kOutside, 0, 0));
+    }
+#pragma unroll
+    for (int p = 0; p < XP; ++p)
+        if ((p * 4 + sub) * 4 < rows) *reinterpret_cast<u32x4*>(&xs[tok * g.x_row + (p * 4 + sub) * 4]) = xv[p];
+#pragma unroll
+    for (int p = 0; p < WP; ++p)
+        if (p * wrows + lr < rows) ws[p * 64 + lane] = wv[p];
+    __builtin_amdgcn_wave_barrier();
+
+    const int pl = lane & 15;
+    const int local = g.mine > 16 ? g.mine >> 4 : 1;                      // parts of a lane
+    const int first = g.mine > 16 ? pl * local : pl & (g.mine - 1);
+    const int c0 = (pl >> g.mine_log2) * 4;
+#pragma unroll 1
+    for (int t0 = (lane >> 4) * 4, half = 0; half < 2; ++half, t0 += 2) {   // two tokens at a time: 128 registers at most
+        f32x4 sum[2], held[2];
+#pragma unroll 1
+        for (int n = 0; n < local; ++n) {
+            f32x4 a[4][2];   // [chain][token]
+#pragma unroll
+            for (int u = 0; u < 4; ++u) a[u][0] = a[u][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+            const float* xl = xs + t0 * g.x_row + first + n;
+            const float* wl = ws + (first + n) * g.stride + c0;
+            for (int m = 0; m < g.M; m += 4) {
+                f32x4 wq[4];
+                float xq[4][2];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int at = min(m + u, g.M - 1) << g.mine_log2;
+                    wq[u] = *reinterpret_cast<const f32x4*>(wl + (at << g.stride_log2));
+                    xq[u][0] = xl[at];
+                    xq[u][1] = xl[g.x_row + at];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (m + u >= g.M) break;   // uniform
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) a[u][t][j] = fmaf(xq[u][t], wq[u][j], a[u][t][j]);
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {   // the lane's parts in pairs, then pairs of pairs
+                const f32x4 v = (a[0][t] + a[1][t]) + (a[2][t] + a[3][t]);
+                if (n == 0) sum[t] = v;
+                else if (n == 1) sum[t] = sum[t] + v;
+                else if (n == 2) held[t] = v;
+                else sum[t] = sum[t] + (held[t] + v);
+            }
+        }
+        // the other parts are in the lanes beside this one: quads, then the quads of 8 and of 16 lanes (each level leaves
+        // its sum in all lanes of a group, so that a mirrored lane is as good as the one across)
+        auto across = [&](auto ctrl) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    sum[t][j] += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, (float)sum[t][j]),
+                                                                                    decltype(ctrl)::value, 0xf, 0xf, true));
+        };
+        across(std::integral_constant<int, 0xB1>{});   // quad_perm 1,0,3,2
+        across(std::integral_constant<int, 0x4E>{});   // quad_perm 2,3,0,1
+        if (g.mine >= 8) across(std::integral_constant<int, 0x141>{});    // row_half_mirror
+        if (g.mine >= 16) across(std::integral_constant<int, 0x140>{});   // row_mirror
+        if ((pl & (g.mine - 1)) == 0) {
+            *reinterpret_cast<f32x4*>(&gate[t0][c0]) = sum[0];
+            *reinterpret_cast<f32x4*>(&gate[t0 + 1][c0]) = sum[1];
+        }
+    }
+}
+
 template <int EB>
-__global__ __launch_bounds__(256) void layer_f32_kernel(
+__global__ __launch_bounds__(kF32LayerThreads, EB == 2 ? 4 : 2) void layer_f32_kernel(
     const float* __restrict__ x, const float* __restrict__ W, const float* __restrict__ W_gate,
     const float* __restrict__ bias, const float* __restrict__ A, const float* __restrict__ B, int T, int d_in, int d_out,
     int N, int r, int k, float inv_temperature, float scale, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
     float* __restrict__ out) {
-    constexpr int TN = 16, C = (1 + EB) * 16, AHEAD = 4;
+    constexpr int TN = 16, C = (1 + EB) * 16, AHEAD = EB == 2 ? 3 : 4;
     __shared__ __attribute__((aligned(16))) float red[4][16][C + 4];
+    __shared__ __attribute__((aligned(16))) float gate[4][16][kF32LayerAdapters + 4];   // gate_row's sums per wavefront
     __shared__ int sel_idx[16][kMaxTopK];
     __shared__ float sel_sw[16][kMaxTopK];   // scale * w
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    extern __shared__ __attribute__((aligned(16))) float staged[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l15 = lane & 15, kc = (lane >> 4) * 4;
     const int tiles_n = ceil_div(d_out, TN);
     const int tile_m = blockIdx.x / tiles_n, tile_n = blockIdx.x - tile_m * tiles_n;
     const int m0 = tile_m * 16, n0 = tile_n * TN, NR = N * r;
     const int steps = ceil_div(d_in, 16);
-    const int s0 = wave * steps / 4, s1 = (wave + 1) * steps / 4;
 
     // Loads through buffer resources: offsets of a lane that never change and a uniform K offset, so that no address
     // arithmetic stands between the loads of a step.  Rows past the edge repeat the last one (computed, never stored);
@@ -296,74 +421,74 @@ __global__ __launch_bounds__(256) void layer_f32_kernel(
     const uint32_t ld = (uint32_t)d_in;
     const __amdgpu_buffer_rsrc_t xr = resource(x, T * ld), wr = resource(W, d_out * ld), gr = resource(W_gate, ld * N),
                                  ar = resource(A, (uint32_t)NR * ld);
-    const uint32_t xo = (uint32_t)min(m0 + l15, T - 1) * ld * 4;
-    const uint32_t wo = (uint32_t)min(n0 + l15, d_out - 1) * ld * 4;
-    // block 0: a column of W_gate per lane; the others: component q of adapter a, column a * r + q
-    uint32_t eo[EB];
-#pragma unroll
-    for (int e = 0; e < EB; ++e) {
-        const int c = e == 0 ? l15 : (e - 1) * 16 + l15;
-        if (e == 0) eo[e] = c < N ? (uint32_t)(kc * N + c) * 4 : kOutside;
-        else eo[e] = c < NR ? (uint32_t)((c / r) * d_in * r + kc * r + c % r) * 4 : kOutside;
-    }
-    struct Step { f32x4 x, w, e[EB]; };
-    auto load = [&](Step& f, int s) {
-        const bool inside = s * 16 + kc < d_in;   // d_in % 8 == 0: all four values or none
-        f.x = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, inside ? xo + kc * 4 : kOutside, s * 64, 0));
-        f.w = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(wr, inside ? wo + kc * 4 : kOutside, s * 64, 0));
+    if (wave >= 4) {
+        gate_rows_f32(xr, gr, m0, T, d_in, N, wave - 4, lane, staged + (wave - 4) * GateRows(d_in, N).wave_floats(),
+                      gate[wave - 4]);
+    } else {
+        const int s0 = wave * steps / 4, s1 = (wave + 1) * steps / 4;
+        const uint32_t xo = (uint32_t)min(m0 + l15, T - 1) * ld * 4;
+        const uint32_t wo = (uint32_t)min(n0 + l15, d_out - 1) * ld * 4;
+        // component q of adapter a is column a * r + q
+        uint32_t eo[EB];
 #pragma unroll
         for (int e = 0; e < EB; ++e) {
-            const uint32_t off = inside ? eo[e] : kOutside;
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                f.e[e][j] = __builtin_bit_cast(
-                    float, __builtin_amdgcn_raw_buffer_load_b32(e == 0 ? gr : ar, off, (s * 16 + j) * (e == 0 ? N : r) * 4, 0));
+            const int c = e * 16 + l15;
+            eo[e] = c < NR ? (uint32_t)((c / r) * d_in * r + kc * r + c % r) * 4 : kOutside;
         }
-    };
-    f32x4 acc[1 + EB][4];   // a chain for each of a lane's four K values: less latency and a smaller rounding error than one
+        struct Step { f32x4 x, w, e[EB]; };
+        auto load = [&](Step& f, int s) {
+            const bool inside = s * 16 + kc < d_in;   // d_in % 8 == 0: all four values or none
+            const uint32_t xk = inside ? xo + kc * 4 : kOutside, wk = inside ? wo + kc * 4 : kOutside;
+            f.x = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, xk, s * 64, 0));
+            f.w = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(wr, wk, s * 64, 0));
 #pragma unroll
-    for (int i = 0; i < 1 + EB; ++i)
+            for (int e = 0; e < EB; ++e) {
+                const uint32_t off = inside ? eo[e] : kOutside;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    f32x4 odd[4];           // the gate's products of every other step
+                for (int j = 0; j < 4; ++j)
+                    f.e[e][j] = __builtin_bit_cast(
+                        float, __builtin_amdgcn_raw_buffer_load_b32(ar, off, (s * 16 + j) * r * 4, 0));
+            }
+        };
+        // a chain for each of a lane's four K values: less latency and a smaller rounding error than one
+        f32x4 acc[1 + EB][4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) odd[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    Step f[AHEAD + 1];
+        for (int i = 0; i < 1 + EB; ++i)
 #pragma unroll
-    for (int a = 0; a < AHEAD; ++a)
-        if (s0 + a < s1) load(f[a], s0 + a);
-    for (int s = s0; s < s1; s += AHEAD + 1) {
+            for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        Step f[AHEAD + 1];
 #pragma unroll
-        for (int u = 0; u <= AHEAD; ++u) {   // register sets have fixed numbers
-            if (s + u >= s1) break;          // uniform per wavefront
-            if (s + u + AHEAD < s1) load(f[(u + AHEAD) % (AHEAD + 1)], s + u + AHEAD);
+        for (int a = 0; a < AHEAD; ++a)
+            if (s0 + a < s1) load(f[a], s0 + a);
+        for (int s = s0; s < s1; s += AHEAD + 1) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                acc[0][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[u].w[j], f[u].x[j], acc[0][j], 0, 0, 0);
+            for (int u = 0; u <= AHEAD; ++u) {   // register sets have fixed numbers
+                if (s + u >= s1) break;          // uniform per wavefront
+                if (s + u + AHEAD < s1) load(f[(u + AHEAD) % (AHEAD + 1)], s + u + AHEAD);
 #pragma unroll
-                for (int e = 0; e < EB; ++e) {
-                    f32x4& c = e == 0 && u % 2 == 1 ? odd[j] : acc[1 + e][j];
-                    c = __builtin_amdgcn_mfma_f32_16x16x4f32(f[u].e[e][j], f[u].x[j], c, 0, 0, 0);
+                for (int j = 0; j < 4; ++j) {
+                    acc[0][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[u].w[j], f[u].x[j], acc[0][j], 0, 0, 0);
+#pragma unroll
+                    for (int e = 0; e < EB; ++e)
+                        acc[1 + e][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[u].e[e][j], f[u].x[j], acc[1 + e][j], 0, 0, 0);
                 }
             }
         }
-    }
+        // a lane holds columns 4 * (lane / 16) .. + 3 of token lane % 16 of every block
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[1][j] += odd[j];
-    // a lane holds columns 4 * (lane / 16) .. + 3 of token lane % 16 of every block
-#pragma unroll
-    for (int i = 0; i < 1 + EB; ++i)
-        *reinterpret_cast<f32x4*>(&red[wave][l15][i * 16 + kc]) = (acc[i][0] + acc[i][1]) + (acc[i][2] + acc[i][3]);
-    __syncthreads();
-    for (int e = threadIdx.x; e < 16 * C / 4; e += 256) {
-        const int t = e / (C / 4), c = (e % (C / 4)) * 4;
-        f32x4 v[4];
-#pragma unroll
-        for (int w = 0; w < 4; ++w) v[w] = *reinterpret_cast<const f32x4*>(&red[w][t][c]);
-        *reinterpret_cast<f32x4*>(&red[0][t][c]) = (v[0] + v[1]) + (v[2] + v[3]);
+        for (int i = 0; i < 1 + EB; ++i)
+            *reinterpret_cast<f32x4*>(&red[wave][l15][i * 16 + kc]) = (acc[i][0] + acc[i][1]) + (acc[i][2] + acc[i][3]);
     }
     __syncthreads();
-    {   // a wavefront ranks four tokens, two at a time
+    if (wave < 4) {
+        for (int e = threadIdx.x; e < 16 * C / 4; e += 256) {
+            const int t = e / (C / 4), c = (e % (C / 4)) * 4;
+            f32x4 v[4];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) v[w] = *reinterpret_cast<const f32x4*>(&red[w][t][c]);
+            *reinterpret_cast<f32x4*>(&red[0][t][c]) = (v[0] + v[1]) + (v[2] + v[3]);
+        }
+    } else {   // a wavefront ranks four tokens, two at a time
         constexpr int NP = 32, G = 2;
         const int col = lane & (NP - 1), sub = lane / NP;
         float g[G];
@@ -373,14 +498,16 @@ __global__ __launch_bounds__(256) void layer_f32_kernel(
         for (int i = 0; i < G; ++i) {
             g[i] = 0.f;
             if (col < N) {
-                g[i] = red[0][wave * 4 + i * 2 + sub][TN + col] + (bias != nullptr ? bias[col] : 0.f);
+                const int t = (wave - 4) * 4 + i * 2 + sub;
+                g[i] = (gate[0][t][col] + gate[1][t][col]) + (gate[2][t][col] + gate[3][t][col]);
+                g[i] += bias != nullptr ? bias[col] : 0.f;
                 if (g[i] == 0.f) g[i] = 0.f;   // -0 -> +0 so equal logits have equal keys
             }
         }
         wave_topk_softmax<NP, G>(g, lane, N, k, inv_temperature, si, sw);
 #pragma unroll
         for (int i = 0; i < G; ++i) {
-            const int t = wave * 4 + i * 2 + sub;
+            const int t = (wave - 4) * 4 + i * 2 + sub;
             if (col < k) {
                 sel_idx[t][col] = si[i];
                 sel_sw[t][col] = scale * sw[i];
@@ -393,7 +520,7 @@ __global__ __launch_bounds__(256) void layer_f32_kernel(
     }
     __syncthreads();
     const int t = threadIdx.x / TN, c = n0 + threadIdx.x % TN;
-    if (m0 + t >= T || c >= d_out) return;
+    if (wave >= 4 || m0 + t >= T || c >= d_out) return;
     float v = red[0][t][c - n0];
     const int R8 = ceil_div(r, 8), groups = k * R8;   // (slot, 8 rows of B): the rows of two groups in flight
     for (int g0 = 0; g0 < groups; g0 += 2) {
@@ -405,7 +532,7 @@ __global__ __launch_bounds__(256) void layer_f32_kernel(
             slot[i] = g / R8;
             q0[i] = (g - slot[i] * R8) * 8;
             const int a = sel_idx[t][slot[i]];
-            at[i] = TN + 16 + a * r;
+            at[i] = TN + a * r;
 #pragma unroll
             for (int u = 0; u < 8; ++u) b[i][u] = B[((size_t)a * r + min(q0[i] + u, r - 1)) * d_out + c];
         }
@@ -424,29 +551,36 @@ __global__ __launch_bounds__(256) void layer_f32_kernel(
 
 // Every workgroup reads the whole of W_gate and A, so this is for what one round or two of workgroups finish: the product
 // of rounds, inputs and 16-column blocks is what the time goes with.  Against two launches, whole calls (the host takes 7.9
-// us to issue one launch and 10.3 for two): 4 adapters of rank 8, top-2: 64 x 256 -> 256 10.5 and 7.8 us, 8 x 256 -> 4096 12.7
-// and 7.8, 64 x 384 -> 384 10.8 and 9.1, 64 x 512 -> 512 11.4 and 10.6, 64 x 768 -> 64 12.1 and 13.4, 200 x 256 -> 768 13.4 and
-// 15.2; 7 of rank 8: 64 x 128 -> 128 10.2 and 7.9, 64 x 256 -> 256 10.4 and 10.7; 16 of rank 2 (8-byte pieces of A): 64 x
-// 256 -> 256 10.6 and 8.8, 64 x 512 -> 512 10.5 and 13.1; 1024 workgroups (512 x 64 -> 512) 10.5 and 11.3.
-bool layer_f32_applies(int T, int d_in, int d_out, int N, int r) {
-    if (N > 16 || N * r > 64) return false;
+// us to issue one launch and 10.3 to 11 for two), 4 adapters of rank 8, top-2: 64 x 256 -> 256 11.1 and 8.1 us, 8 x 256 -> 4096
+// 13.7 and 8.2, 64 x 384 -> 384 11.1 and 9.3, 64 x 512 -> 512 11.6 and 10.4, 512 workgroups (128 x 256 -> 1024) 13.8 and
+// 10.4; 8 of rank 8: 64 x 168 -> 256 11.2 and 8.2.  Not taken, the line as it lies where the second figure is the larger one:
+// more adapters and inputs, the logits take the longest (16 of rank 2, 64 x 256 -> 256 10.9 and 12.9, 128 -> 256 11.1 and
+// 8.7; one adapter, whose columns fill a quarter of the lanes, 64 x 512 -> 256 12.2 and 12.8, of rank 64 12.1 and 13.8); two
+// workgroups per CU with many adapter columns (4 of rank 16, 128 x 80 -> 1024 13.9 and 15.7); top-8 of many (8 of rank 4,
+// 64 x 256 -> 256 12.6 and 13.4; of 4 adapters top-4 10.7 and 9.8).
+bool layer_f32_applies(int T, int d_in, int d_out, int N, int r, int k) {
+    if (N > kF32LayerAdapters || N * r > 64 || d_in > kF32LayerInputs) return false;
+    if ((d_in << GateRows(d_in, N).stride_log2) > kF32LayerGate) return false;
+    if ((N == 1 && (r > 32 || d_in > 256)) || (N > 4 && k > 4)) return false;
     const int64_t tiles = ceil_div64(T, 16) * ceil_div64(d_out, 16);
     const int blocks = N * r <= 32 ? 4 : 6;
-    return tiles <= 512 && ceil_div64(tiles, 256) * d_in * blocks <= (blocks == 4 && r >= 8 ? 2048 : 1024);
+    return tiles <= (N <= 8 && N * r <= 32 ? 512 : 256) &&
+           ceil_div64(tiles, 256) * d_in * blocks <= (blocks == 4 && r >= 8 ? 2048 : 1024);
 }
 
 hipError_t launch_layer_f32(const float* x, const float* W, const float* W_gate, const float* bias, const float* A,
                             const float* B, int T, int d_in, int d_out, int N, int r, int k, float inv_temperature,
                             float scale, int32_t* topk_idx, float* topk_w, float* out, hipStream_t stream) {
-    if (d_in % 8 != 0 || d_out % 8 != 0 || !layer_f32_applies(T, d_in, d_out, N, r) || k < 1 || k > N || k > kMaxTopK)
+    if (d_in % 8 != 0 || d_out % 8 != 0 || !layer_f32_applies(T, d_in, d_out, N, r, k) || k < 1 || k > N || k > kMaxTopK)
         return hipErrorInvalidValue;
     const int64_t tiles = ceil_div64(T, 16) * ceil_div64(d_out, 16);
+    const size_t lds = (size_t)4 * GateRows(d_in, N).wave_floats() * sizeof(float);
     auto go = [&](auto kern) {
-        kern<<<(unsigned)tiles, 256, 0, stream>>>(x, W, W_gate, bias, A, B, T, d_in, d_out, N, r, k, inv_temperature, scale,
-                                                  topk_idx, topk_w, out);
+        kern<<<(unsigned)tiles, kF32LayerThreads, lds, stream>>>(x, W, W_gate, bias, A, B, T, d_in, d_out, N, r, k,
+                                                                 inv_temperature, scale, topk_idx, topk_w, out);
         return hipGetLastError();
     };
-    return N * r <= 32 ? go(layer_f32_kernel<3>) : go(layer_f32_kernel<5>);
+    return N * r <= 32 ? go(layer_f32_kernel<2>) : go(layer_f32_kernel<4>);
 }
 
 }  // namespace meteora

@@ -344,9 +344,27 @@ def test_bucketing_chunk_sizes(T, d_in, N, k):
 # fp32 layers with few adapters in one launch: tiles of 16 tokens and 16 columns, K in steps of 16 over four wavefronts
 @pytest.mark.parametrize("T,d_in,d_out,N,r,k", [
     (1, 8, 8, 1, 1, 1), (16, 16, 16, 16, 2, 8), (17, 24, 24, 16, 4, 3), (33, 72, 264, 4, 8, 2), (15, 512, 8, 4, 8, 1),
-    (64, 328, 136, 2, 16, 2), (129, 64, 904, 7, 8, 3), (40, 168, 40, 1, 64, 1), (9, 136, 4096, 5, 12, 4)])
+    (64, 328, 136, 2, 16, 2), (129, 64, 904, 7, 8, 3), (40, 168, 40, 1, 64, 1), (9, 136, 4096, 5, 12, 4),
+    (16, 16, 16, 16, 2, 3), (40, 168, 40, 1, 32, 1), (77, 128, 136, 13, 4, 4)])
 def test_fp32_layer_in_one_launch(T, d_in, d_out, N, r, k):
     _check_layer(LS(T, d_in, d_out, N, r, k, 2.0, "f32", "zipf", "f32-one-launch"), seed=62)
+
+
+# fp32 routing is one sum in one order, whichever launches run: gate_topk, the layer in one launch, the layer in two or three
+@pytest.mark.parametrize("d_in,d_out,N,r,k", [
+    (256, 256, 4, 8, 2), (8, 8, 1, 1, 1), (256, 256, 16, 2, 8), (72, 264, 16, 4, 3), (512, 8, 4, 8, 1), (328, 136, 2, 16, 2),
+    (64, 904, 7, 8, 3), (168, 40, 1, 64, 1), (248, 40, 11, 2, 4), (200, 64, 3, 8, 3), (128, 256, 16, 2, 2), (256, 264, 1, 32, 1),
+    (160, 72, 5, 8, 4), (120, 72, 9, 3, 4)])
+def test_fp32_routing_does_not_depend_on_the_launches(d_in, d_out, N, r, k):
+    shape = LS(4096, d_in, d_out, N, r, k, 2.0, "f32", "zipf", "f32-routing")
+    _, dev = util.make_case(shape, seed=66, condition=False)
+    idx_ref, w_ref, _ = m.gate_topk(dev["x"], dev["W_gate"], dev["bias"], k)
+    for T in (1, 5, 16, 64, 129, 4096):   # 4096 tokens never run in one launch for these widths, except the narrowest
+        _, idx, w = m.linear_forward(dev["x"][:T], dev["W"], dev["W_gate"], dev["bias"], dev["A"], dev["B"], k, 2.0,
+                                     return_routing=True)
+        torch.cuda.synchronize()
+        assert torch.equal(idx, idx_ref[:T]), f"T = {T}: adapters differ"
+        assert torch.equal(w, w_ref[:T]), f"T = {T}: weights differ"
 
 
 # row tiles of 128 outputs and of 320 (r = 8), 544 (16) or 320 (7 adapters of 32) rows of Wcat share 256 CUs: 1, 2, 3, 5 and 16 K splits
