@@ -32,14 +32,16 @@ bool decode_fused_applies(int T, int d_in, int d_out, int N, int r, bool bf16) {
 // Mid-sized batches whose 128 x 128 output tiles would leave most CUs idle (a few hundred tokens): the base
 // projection is split along K over workgroups like the routing products (fp32 tiles), and the reduction adds the
 // LoRA expand, as for decode.  Returns the number of K splits, 0 = the fused GEMM runs instead.
-int dense_midsplit_splits(int T, int d_in, int d_out, int N, int r, bool bf16) {
+// `reserve`: as many as a workspace has room for.
+int dense_midsplit_splits(int T, int d_in, int d_out, int N, int r, bool bf16, bool reserve = false) {
     // measured on 4096 -> 4096, 4096 -> 14336 and 14336 -> 4096, T = 65 ... 2048: the split form wins as long as the
-    // projection can still be cut into at least two K splits (see gemm_multi_cap_splits for how many) (19.0 against 56.1 us
+    // projection can still be cut into at least two K splits (see gemm_multi_splits for how many) (19.0 against 56.1 us
     // at T = 65, 36.1 against 60.1 at T = 512, 45.6 against 48.7 at T = 704, 47.6 against 48.8 at T = 768 for
     // 4096 -> 4096; 43.3 against 47.6 at T = 160 for 4096 -> 14336; 107 against 131 at T = 704 for 14336 -> 4096)
     if (!route_dense_applies(T, d_in, N, r, bf16) || d_out % 8 != 0 || !gemm_dense_splitk_ok(T, d_in, d_out)) return 0;
-    const int S = gemm_multi_cap_splits(T, ceil_div(d_out, 128) + ceil_div(prep_wcat_rows(N, r), 128),
-                                        gemm_dense_splits(T, d_in, d_out), d_in / 64, (int64_t)d_out + prep_wcat_rows(N, r));
+    const int col_tiles = ceil_div(d_out, 128) + ceil_div(prep_wcat_rows(N, r), 128), fit = gemm_dense_splits(T, d_in, d_out);
+    const int S = reserve ? gemm_multi_splits_reserved(T, col_tiles, fit)
+                          : gemm_multi_splits(T, col_tiles, fit, d_in / 64, (int64_t)d_out + prep_wcat_rows(N, r));
     return S >= 2 ? S : 0;
 }
 
@@ -57,7 +59,8 @@ WsLayout ws_layout(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
     L.ext_stride = (int)align_up((size_t)N * r, 64);
     L.wsplit = take(gate_wsplit_bytes(d_in, N, bf16));
     L.partials = take((size_t)gate_kslices(d_in, bf16) * T * NP * sizeof(float));
-    L.chunk_counts = take((size_t)routing_chunks(T) * N * sizeof(int32_t));
+    L.chunk_counts = take((size_t)bucket_chunks(T) * N * sizeof(int32_t));
+    take((size_t)routing_chunks_extra(T) * N * sizeof(int32_t));   // of chunk_counts
     L.counts = take((size_t)N * sizeof(int32_t));
     L.offsets = take((size_t)(N + 1) * sizeof(int32_t));
     L.bucket_tok = take(pairs * sizeof(int32_t));
@@ -78,12 +81,12 @@ WsLayout ws_layout(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
     L.wcat = take(dense || decode3 ? prep_wcat_bytes(d_in, N, r, bf16) : 0);
     // the routing products come in the K splits of the launch that writes them: the products launch's own count, or
     // that of the split base projection when both share one launch (which may be the larger of the two)
-    const int S_mid = dense_midsplit_splits(T, d_in, d_out, N, r, bf16);
+    const int S_mid = dense_midsplit_splits(T, d_in, d_out, N, r, bf16, true);
     size_t dpart = S_mid > 0 ? (size_t)S_mid * T * prep_wcat_rows(N, r) * sizeof(float)
                              : route_dense_part_bytes(T, d_in, N, r, bf16);
     // lora_forward at such a size: the adapters' rows alone, in the splits their own launch takes
     const size_t lora = lora_dense_applies(T, d_in, N, r, k, bf16)
-                            ? (size_t)gemm_dense_splits(T, d_in, N * r) * T * N * r * sizeof(float) : 0;
+                            ? (size_t)gemm_dense_splits_reserved(T, d_in, N * r) * T * N * r * sizeof(float) : 0;
     L.dpart = take(lora > dpart ? lora : dpart);
     L.gpart = take((size_t)S_decode * T * prep_wcat_rows(N, r) * sizeof(float));
     L.spart = take((size_t)S_mid * T * d_out * sizeof(float));
@@ -659,8 +662,10 @@ bool group_fused(const meteora_group_member* m, int G, int T, int d_in, int N, i
 
 // Second fused form: a few hundred tokens, every member on the dense routing path with packed weights, few output
 // tiles in all: the projections and routing products of all members as K-split tiles of one launch, one selection
-// launch, one reduction with the expands.  Returns the number of K splits, 0 = not this form.
-int group_mid_splits(const int* d_out, const bool* packed, int G, int T, int d_in, int N, int r, bool bf16) {
+// launch, one reduction with the expands.  Returns the number of K splits (`reserve`: as many as a workspace has room for), 0
+// = not this form.
+int group_mid_splits(const int* d_out, const bool* packed, int G, int T, int d_in, int N, int r, bool bf16,
+                     bool reserve = false) {
     if (G < 2 || G > kMaxDecodeGroup || !route_dense_applies(T, d_in, N, r, bf16)) return 0;
     const int cat_rows = prep_wcat_rows(N, r);
     int64_t tiles = 0;
@@ -679,7 +684,7 @@ int group_mid_splits(const int* d_out, const bool* packed, int G, int T, int d_i
         col_tiles += ceil_div(d_out[g], 128) + ceil_div(cat_rows, 128);
         rows += d_out[g] + cat_rows;
     }
-    S = gemm_multi_cap_splits(T, col_tiles, S, nk, rows);
+    S = reserve ? gemm_multi_splits_reserved(T, col_tiles, S) : gemm_multi_splits(T, col_tiles, S, nk, rows);
     return S < 1 ? 1 : S;
 }
 
@@ -726,7 +731,7 @@ extern "C" size_t meteora_group_workspace_bytes(const int* d_out, int G, int T, 
     }
     if (G >= 2 && G <= kMaxDecodeGroup) {
         bool all_packed[kMaxDecodeGroup] = {true, true, true, true};   // sized as if packed: the larger need
-        if (const int S = group_mid_splits(d_out, all_packed, G, T, d_in, N, r, bf16)) {
+        if (const int S = group_mid_splits(d_out, all_packed, G, T, d_in, N, r, bf16, true)) {
             const size_t f = group_layout(d_out, G, T, d_in, N, r, k, S, prep_wcat_rows(N, r)).total + 256;
             need = f > need ? f : need;
         }

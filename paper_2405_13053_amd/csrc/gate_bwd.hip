@@ -417,15 +417,23 @@ static int wgrad_slice_chunks(int T, int d_in) {
     return ceil_div(chunks, want < most ? want : most);
 }
 
+// The slices a workspace has room for: up to twice as many, in whole blocks of 64 tokens, so that its size does not fall where
+// the number of slices does.
+static int wgrad_slices_reserved(int T, int d_in) {
+    const int blocks = ceil_div(T, 64), want = ceil_div(512, ceil_div(d_in, kWgCols));
+    return ceil_div(blocks, ceil_div(blocks, want < blocks ? want : blocks));
+}
+
 GateBackwardLayout gate_backward_layout(int T, int d_in, int d_out, int N, int r) {
     GateBackwardLayout L{};
     const int CR = prep_wcat_rows(N, r), NR = N * r;
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off = align_up(off + bytes, 256); return o; };
-    L.part_x = take((size_t)gemm_dense_splits(T, d_in, CR) * T * CR * sizeof(float));
-    L.part_dy = take((size_t)gemm_dense_splits(T, d_out, NR) * T * NR * sizeof(float));
-    L.dgs = take((size_t)align_up(ceil_div(T, 8), 2) * 3 * kBwdNP * 8 * sizeof(uint16_t));
-    const int slices = ceil_div(ceil_div(T, kWgChunk), wgrad_slice_chunks(T, d_in));
+    L.part_x = take((size_t)gemm_dense_splits_reserved(T, d_in, CR) * T * CR * sizeof(float));
+    L.part_dy = take((size_t)gemm_dense_splits_reserved(T, d_out, NR) * T * NR * sizeof(float));
+    // whole pairs of 8-token blocks, 3072 bytes each: less than 192 T + 3072
+    L.dgs = take((size_t)T * 192 + 3072);
+    const int slices = wgrad_slices_reserved(T, d_in);
     L.wpart = take((size_t)slices * d_in * kBwdNP * sizeof(float));
     L.bpart = take((size_t)slices * kBwdNP * sizeof(float));
     L.ext = (int)align_up((size_t)NR + 3 * kBwdNP, 64);

@@ -207,15 +207,25 @@ bool gemm_dense_splitk_ok(int T, int d_in, int rows) {
            ((uint64_t)rows + 5 * 64) * widest < (1ull << 32) && (uint64_t)rows * 4 * 256 < (1ull << 32);
 }
 
+static int dense_split_bounds(int S, int nk) {
+    if (S > nk / 4) S = nk / 4;                // at least 4 K tiles per split
+    if (S > 8) S = 8;                          // more splits cost the kernel that adds them more than they save here
+    return S < 1 ? 1 : S;
+}
+
 int gemm_dense_splits(int T, int d_in, int rows) {
     const bool small = dense_small_tiles(T);
     const int tiles = ceil_div(T, 128) * ceil_div(rows, small ? 128 : 320), nk = d_in / kGemmBK;
     // 128 x 320 tiles: one workgroup per CU at most, since a few more take a second round (layers of 4096 -> 1024, rank 8, on
     // 282 and 188 workgroups: 12000 x 5120 155.3 and 148.0 us)
-    int S = small ? (384 + tiles / 2) / tiles : 256 / tiles;
-    if (S > nk / 4) S = nk / 4;                // at least 4 K tiles per split
-    if (S > 8) S = 8;                          // more splits cost the kernel that adds them more than they save here
-    return S < 1 ? 1 : S;
+    const int S = small ? (384 + tiles / 2) / tiles : 256 / tiles;
+    return dense_split_bounds(S, nk);
+}
+
+int gemm_dense_splits_reserved(int T, int d_in, int rows) {
+    if (dense_small_tiles(T)) return gemm_dense_splits(T, d_in, rows);
+    const int tiles = ceil_div(T, 128) * ceil_div(rows, 320);
+    return dense_split_bounds((256 + tiles / 2) / tiles, d_in / kGemmBK);
 }
 
 template <int MB, int NB, int D, int EPI>
@@ -257,10 +267,17 @@ static int gemm_multi_row_blocks(int T) {
 // least: a K tile takes about 0.2 + 0.07 us for every 32 rows, a MB of fp32 tiles 0.45 us.  Whole calls, as many splits as
 // fit and so: 512 x 2048 -> 2048 22.3 (6 splits) and 20.2 us (4), 700 x 4096 -> 1024 26.0 and 24.7, 900 x 1024 -> 1024 20.7 and
 // 18.9, 200 x 1024 -> 4096 19.4 and 17.7, 96 x 4096 -> 4096 18.7 and 18.2; 1531 x 1024 -> 1024 20.1 and 21.1.
-int gemm_multi_cap_splits(int T, int col_tiles, int S, int nk, int64_t rows) {
-    const int cap = 256 / (ceil_div(T, 256) * (col_tiles > 0 ? col_tiles : 1));   // 256 CUs
+static int multi_cap(int T, int col_tiles) { return 256 / (ceil_div(T, 256) * (col_tiles > 0 ? col_tiles : 1)); }   // 256 CUs
+
+int gemm_multi_splits_reserved(int T, int col_tiles, int S) {
+    const int cap = multi_cap(T, col_tiles);
     if (T <= 128 && cap < 2 && S >= 3) return S;
-    if (S > cap) S = cap > 0 ? cap : 1;
+    return S > cap ? (cap > 0 ? cap : 1) : S;
+}
+
+int gemm_multi_splits(int T, int col_tiles, int S, int nk, int64_t rows) {
+    if (T <= 128 && multi_cap(T, col_tiles) < 2 && S >= 3) return S;
+    S = gemm_multi_splits_reserved(T, col_tiles, S);
     const float per_tile = 0.2f + 0.07f * (float)gemm_multi_row_blocks(T), per_split = 0.45e-6f * 4.f * (float)T * (float)rows;
     int best = S;
     float least = 0.f;

@@ -81,9 +81,13 @@ hipError_t launch_route_dense_select(const float* part, const float* bias, int T
 // the GEMM behind launch_route_dense_products: partial[split][T][rows] = x * Wcat^T over the split's K range
 bool gemm_dense_splitk_ok(int T, int d_in, int rows);
 int gemm_dense_splits(int T, int d_in, int rows);
-// few-tile split-K launches over several matrices: S capped to one workgroup per CU, or for few tokens to two
-// (col_tiles: the 128-column tiles of all the matrices of the launch)
-int gemm_multi_cap_splits(int T, int col_tiles, int S, int nk, int64_t rows);
+// few-tile split-K launches over several matrices (col_tiles: the 128-column tiles of all of them, rows: their rows): S
+// capped to one workgroup per CU, or for few tokens to two, and of what that leaves the number that costs the least
+int gemm_multi_splits(int T, int col_tiles, int S, int nk, int64_t rows);
+// What a workspace reserves: as many splits as fit.  The two above come and go with the token count; a workspace for the
+// largest batch has to hold the smaller ones, and with these its size falls at few of them.
+int gemm_dense_splits_reserved(int T, int d_in, int rows);
+int gemm_multi_splits_reserved(int T, int col_tiles, int S);
 hipError_t launch_gemm_dense_splitk(const void* x, const void* Wcat, int T, int d_in, int rows, float* partial,
                                     hipStream_t stream);
 
@@ -103,6 +107,11 @@ constexpr int kFineChunkTokens = 16;
 inline int routing_chunk_tokens(int T) { return T <= 2048 ? kFineChunkTokens : kBucketChunkTokens; }
 inline int routing_chunks(int T) { return (T + routing_chunk_tokens(T) - 1) / routing_chunk_tokens(T); }
 inline int bucket_chunks(int T) { return (T + kBucketChunkTokens - 1) / kBucketChunkTokens; }
+// Beyond bucket_chunks, for batches of up to T tokens: a workspace for 3000 tokens (47 chunks) holds 2048 (128 chunks) too.
+inline int routing_chunks_extra(int T) {
+    const int most = T <= 2048 ? T : 2048;
+    return routing_chunks(most) - bucket_chunks(most);
+}
 // The library's own histogram scratch (a file-scope device array, one copy per GPU) for the entry point that takes
 // no workspace: room for kStaticBucketMaxTokens tokens and any supported N; the pointer is the current device's.
 constexpr int kStaticBucketMaxTokens = 65536;

@@ -189,7 +189,7 @@ bool lora_dense_applies(int T, int d_in, int N, int r, int k, bool bf16) {
 size_t route_dense_part_bytes(int T, int d_in, int N, int r, bool bf16) {
     if (!route_dense_applies(T, d_in, N, r, bf16)) return 0;
     const int CR = prep_wcat_rows(N, r);
-    return (size_t)gemm_dense_splits(T, d_in, CR) * T * CR * sizeof(float);
+    return (size_t)gemm_dense_splits_reserved(T, d_in, CR) * T * CR * sizeof(float);
 }
 
 hipError_t launch_route_dense_products(const void* x, const void* wcat, int T, int d_in, int N, int r, float* part,

@@ -80,6 +80,25 @@ def test_workspace_regions_hold_what_the_launches_write():
         assert regs["dpart"][2] <= regs["dpart"][1]
 
 
+# a program allocates for its largest batch: between two sizes at which a whole K split no longer fits, the size never falls
+@pytest.mark.parametrize("d_in,d_out,N,r,k,Ts", [
+    (136, 136, 64, 8, 4, (1, 5000)), (2048, 2048, 28, 8, 2, (65, 257)), (2048, 2048, 28, 8, 2, (257, 513)),
+    (4096, 1024, 28, 8, 2, (257, 513)), (1024, 1024, 28, 8, 2, (513, 769)), (4096, 1024, 28, 16, 1, (257, 513))])
+def test_a_workspace_for_more_tokens_holds_fewer(d_in, d_out, N, r, k, Ts):
+    for dtype in ("bf16", "f32"):
+        sizes = [m.workspace_bytes(T, d_in, d_out, N, r, k, dtype) for T in range(*Ts)]
+        assert sizes == sorted(sizes), dtype
+    sizes = [m.group_workspace_bytes((d_out, d_out), T, d_in, N, r, k, "bf16") for T in range(*Ts)]
+    assert sizes == sorted(sizes)
+
+
+@pytest.mark.parametrize("d_in,d_out,r,fewer,more", [(4096, 4096, 8, 2049, 2177), (5120, 5120, 8, 2030, 2177),
+                                                     (4096, 1024, 16, 1174, 1281)])
+def test_a_backward_workspace_for_more_tokens_holds_fewer(d_in, d_out, r, fewer, more):
+    size = lambda T: m.gate_backward_workspace_bytes(T, d_in, d_out, 28, r, 1, "bf16")
+    assert size(fewer) <= size(more)
+
+
 @pytest.mark.parametrize("T", [65, 96, 128])
 @pytest.mark.parametrize("d_out", [16008, 16384, 18432, 19584])
 def test_wide_layers_of_up_to_128_tokens_split_along_k(T, d_out):
