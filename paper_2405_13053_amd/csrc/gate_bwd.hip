@@ -23,7 +23,7 @@
 //   next 3 blocks of 32:    hx = hi(d_logits) | hi(d_logits) | lo(d_logits);  Xt[c] = hi(W_gate[c]) | lo(W_gate[c]) | hi(W_gate[c])
 // (two-term bf16 splits, the lo * lo product dropped: the gate term to about 2^-16 of its size).
 // gate_bwd_dlogits_kernel writes hx and Xt (W_gate changes with every optimizer step).
-#include <type_traits>
+#include <initializer_list>
 #include "common.hpp"
 #include "kernels.hpp"
 #include "topk_key.hpp"
@@ -275,26 +275,27 @@ __device__ void pack_xt(const uint16_t* __restrict__ A, const float* __restrict_
 // x[T, d_in] is not token-contiguous, so a lane loads 4 columns of 8 tokens (8 bytes each, whole lines per half wavefront)
 // and pairs the halves of its registers (two v_perm per 4 values).  d_logits comes as three bf16 terms that add up to its
 // fp32 value, in the operand's own order: every product is exact in fp32, as in the forward gate, and a multiply of K = 16
-// takes 32 cycles where the fp32 MFMA takes 512.  Bound by the latency of the loads: a wavefront owns 128 columns and an
-// eighth of the workgroup's tokens, all of whose loads are in flight for up to 64 tokens.  The eight sums meet in LDS.
+// takes 32 cycles where the fp32 MFMA takes 512.  Bound by the latency of the loads: a wavefront owns 128 columns and one of
+// PARTS shares of the workgroup's tokens, all of whose loads are in flight for up to 64 tokens.  The sums meet in LDS.
 // Workgroups of column tile 0 also add up dg for dbias.
-constexpr int kWgCols = 128, kWgThreads = 512, kWgParts = kWgThreads / 64, kWgChunk = 16;   // chunk: tokens per MFMA
+constexpr int kWgCols = 128, kWgChunk = 16;                      // chunk: tokens per MFMA
 constexpr int kWgRing = 4;                                       // chunks whose loads are in flight per wavefront
-constexpr int kWgLds = kWgParts * 16 * 64 * 16;                  // the accumulators of every wavefront
+constexpr int wgrad_lds(int parts) { return parts * 16 * 64 * 16; }   // the accumulators of every wavefront
 
-__global__ __launch_bounds__(kWgThreads) void gate_bwd_wgrad_kernel(const uint16_t* __restrict__ x,
+template <int PARTS>
+__global__ __launch_bounds__(PARTS * 64) void gate_bwd_wgrad_kernel(const uint16_t* __restrict__ x,
                                                                      const uint16_t* __restrict__ dgs, int T, int d_in,
                                                                      int slice_chunks, float* __restrict__ wpart,
                                                                      float* __restrict__ bpart) {
     extern __shared__ __attribute__((aligned(16))) f32x4 red[];  // [part][fragment * 4 + entry group][lane]
-    __shared__ float s_b[kWgParts][kBwdNP];
+    __shared__ float s_b[PARTS][kBwdNP];
     const int lane = threadIdx.x & 63, l31 = lane & 31, kh = lane >> 5;
     const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c0 = blockIdx.x * kWgCols, slice = blockIdx.y;
     const int c = min(c0 + 4 * l31, d_in - 4);                   // d_in % 8 == 0: 4 columns inside or the last ones again
     const int chunks = ceil_div(T, kWgChunk);
     const int s_begin = slice * slice_chunks, s_n = min(slice_chunks, chunks - s_begin);
-    const int k0 = s_begin + part * s_n / kWgParts, k1 = s_begin + (part + 1) * s_n / kWgParts;
+    const int k0 = s_begin + part * s_n / PARTS, k1 = s_begin + (part + 1) * s_n / PARTS;
 
     struct Chunk { uint2 x[8]; u32x4 d[3]; };
     auto load = [&](Chunk& f, int ch) {
@@ -358,18 +359,18 @@ __global__ __launch_bounds__(kWgThreads) void gate_bwd_wgrad_kernel(const uint16
     if (kh == 0) s_b[part][l31] = bsum;
     __syncthreads();
     // 16-byte pieces in the order of wpart, the parts added in order
-    for (int p = threadIdx.x; p < kWgCols * kBwdNP / 4; p += kWgThreads) {
+    for (int p = threadIdx.x; p < kWgCols * kBwdNP / 4; p += PARTS * 64) {
         const int col = p / (kBwdNP / 4), piece = p % (kBwdNP / 4);
         const int at = ((col & 3) * 4 + piece / 2) * 64 + (piece & 1) * 32 + col / 4;
         f32x4 v = red[at];
 #pragma unroll
-        for (int w = 1; w < kWgParts; ++w) v += red[w * 16 * 64 + at];
+        for (int w = 1; w < PARTS; ++w) v += red[w * 16 * 64 + at];
         if (c0 + col < d_in) *reinterpret_cast<f32x4*>(wpart + ((size_t)slice * d_in + c0 + col) * kBwdNP + piece * 4) = v;
     }
     if (bias_tile && threadIdx.x < kBwdNP) {
         float v = 0.f;
 #pragma unroll
-        for (int w = 0; w < kWgParts; ++w) v += s_b[w][threadIdx.x];
+        for (int w = 0; w < PARTS; ++w) v += s_b[w][threadIdx.x];
         bpart[slice * kBwdNP + threadIdx.x] = v;
     }
 }
@@ -410,18 +411,27 @@ bool gate_backward_applies(int T, int d_in, int d_out, int N, int r, bool bf16) 
            gemm_dense_splitk_ok(T, d_in, prep_wcat_rows(N, r)) && gemm_dense_splitk_ok(T, d_out, N * r);
 }
 
-// Chunks of 16 tokens per slice: about one workgroup per CU, a chunk or more for each wavefront.
-static int wgrad_slice_chunks(int T, int d_in) {
-    const int chunks = ceil_div(T, kWgChunk), col_tiles = ceil_div(d_in, kWgCols);
-    const int most = ceil_div(chunks, kWgParts), want = ceil_div(256, col_tiles);
-    return ceil_div(chunks, want < most ? want : most);
-}
-
 // The slices a workspace has room for: up to twice as many, in whole blocks of 64 tokens, so that its size does not fall where
 // the number of slices does.
 static int wgrad_slices_reserved(int T, int d_in) {
     const int blocks = ceil_div(T, 64), want = ceil_div(512, ceil_div(d_in, kWgCols));
     return ceil_div(blocks, ceil_div(blocks, want < blocks ? want : blocks));
+}
+
+// One workgroup per CU at most, since a few more take a second round, and 8 slices or, of more than 256 chunks, one for every
+// 32: a slice costs the reduction about 0.1 us.  Four wavefronts to a workgroup, two where a slice has 8 chunks or fewer: the
+// way of more sums through LDS costs more than the longer chains.  Whole gate_backward calls with 64 outputs, us: 5120 inputs
+// on 280 and 240 workgroups, 1000 tokens 38.0 and 31.3, 4096 57.2 and 48.3; 256 inputs in 8, 16 and 64 slices, 4096 tokens
+// 26.8, 26.0, 33.5, 8192 43.1, 40.5, 47.4; 4096 inputs with 8, 4 and 2 wavefronts, 64 tokens 24.3, 22.6, 22.0, 300 25.9, 24.3,
+// 23.8, 1000 31.1, 29.8, 29.3, 4096 44.0, 42.5, 43.1.
+struct WgradPlan { int parts, slice_chunks; };
+static WgradPlan wgrad_plan(int T, int d_in) {
+    const int chunks = ceil_div(T, kWgChunk), col_tiles = ceil_div(d_in, kWgCols);
+    int n = chunks / 32 < 8 ? 8 : chunks / 32 < 32 ? chunks / 32 : 32;
+    for (const int most : {256 / col_tiles, chunks / 4, wgrad_slices_reserved(T, d_in)})
+        if (n > most) n = most;
+    const int slice_chunks = ceil_div(chunks, n < 1 ? 1 : n);
+    return {slice_chunks > 8 ? 4 : 2, slice_chunks};
 }
 
 GateBackwardLayout gate_backward_layout(int T, int d_in, int d_out, int N, int r) {
@@ -444,7 +454,7 @@ GateBackwardLayout gate_backward_layout(int T, int d_in, int d_out, int N, int r
 }
 
 hipError_t gate_bwd_init_kernels() {
-    return ensure_lds_limit(reinterpret_cast<const void*>(&gate_bwd_wgrad_kernel), kWgLds);
+    return ensure_lds_limit(reinterpret_cast<const void*>(&gate_bwd_wgrad_kernel<4>), wgrad_lds(4));
 }
 
 hipError_t launch_gate_backward(const void* x, const void* dy, const void* wcat, const void* B, const float* bias,
@@ -491,12 +501,16 @@ hipError_t launch_gate_backward(const void* x, const void* dy, const void* wcat,
         e = launch_gemm(dy, W_t, T, d_out, d_in, true, ws + L.hx, L.ext, xt, L.ext, dx, 0, nullptr, stream);
         if (e != hipSuccess) return e;
     }
-    const int slice_chunks = wgrad_slice_chunks(T, d_in);
-    const int slices = ceil_div(ceil_div(T, kWgChunk), slice_chunks);
-    if ((e = ensure_lds_limit(reinterpret_cast<const void*>(&gate_bwd_wgrad_kernel), kWgLds)) != hipSuccess) return e;
-    gate_bwd_wgrad_kernel<<<dim3(ceil_div(d_in, kWgCols), slices), kWgThreads, kWgLds, stream>>>(
-        (const uint16_t*)x, (const uint16_t*)dgs, T, d_in, slice_chunks, wpart, bpart);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    const WgradPlan plan = wgrad_plan(T, d_in);
+    const int slices = ceil_div(ceil_div(T, kWgChunk), plan.slice_chunks);
+    auto wgrad = [&](auto kern) {
+        kern<<<dim3(ceil_div(d_in, kWgCols), slices), plan.parts * 64, wgrad_lds(plan.parts), stream>>>(
+            (const uint16_t*)x, (const uint16_t*)dgs, T, d_in, plan.slice_chunks, wpart, bpart);
+        return hipGetLastError();
+    };
+    if (plan.parts == 4 && (e = gate_bwd_init_kernels()) != hipSuccess) return e;
+    e = plan.parts == 4 ? wgrad(gate_bwd_wgrad_kernel<4>) : wgrad(gate_bwd_wgrad_kernel<2>);
+    if (e != hipSuccess) return e;
     const int blocks = (int)ceil_div64((int64_t)d_in * kBwdNP, 256) + 1;
     gate_bwd_reduce_kernel<<<blocks, 256, 0, stream>>>(wpart, bpart, slices, d_in, N, dW_gate, dbias);
     return hipGetLastError();
