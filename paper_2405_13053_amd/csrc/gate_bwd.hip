@@ -193,19 +193,17 @@ __global__ __launch_bounds__(kBwdThreads) void gate_bwd_dlogits_kernel(const Dlo
         if (t >= T) continue;
         if (a.d_logits != nullptr && col < N) a.d_logits[(size_t)t * N + col] = s_dg[lt[i]][col];
     }
-    static_assert(kBwdTokens == 8 && kBwdThreads >= 3 * kBwdNP, "one 16-byte piece per thread: 8 tokens of a term's column");
-    if (threadIdx.x < 3 * NP) {
-        const int term = threadIdx.x / NP, n = threadIdx.x % NP;
-        uint16_t v[8];
+    static_assert(kBwdTokens == 8 && kBwdThreads >= 6 * kBwdNP, "one 8-byte piece per thread: 4 tokens of a term's column");
+    if (threadIdx.x < 6 * NP) {
+        const int half = threadIdx.x & 1, term = threadIdx.x / (2 * NP), n = threadIdx.x / 2 % NP;
+        uint16_t v[4];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const Split3 sp = split3_exact(t0 + j < T && n < N ? s_dg[j][n] : 0.f);
+        for (int j = 0; j < 4; ++j) {
+            const Split3 sp = split3_exact(t0 + half * 4 + j < T && n < N ? s_dg[half * 4 + j][n] : 0.f);
             v[j] = term == 0 ? sp.term[0] : term == 1 ? sp.term[1] : sp.term[2];
         }
-        u32x4 pk;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) pk[j] = (uint32_t)v[2 * j] | (uint32_t)v[2 * j + 1] << 16;
-        *reinterpret_cast<u32x4*>(a.dgs + ((size_t)blockIdx.x * 3 * NP + threadIdx.x) * 8) = pk;
+        *reinterpret_cast<uint2*>(a.dgs + ((size_t)blockIdx.x * 6 * NP + threadIdx.x) * 4) =
+            uint2{(uint32_t)v[0] | (uint32_t)v[1] << 16, (uint32_t)v[2] | (uint32_t)v[3] << 16};
     }
     if (a.hx == nullptr) return;
 
@@ -428,7 +426,7 @@ struct WgradPlan { int parts, slice_chunks; };
 static WgradPlan wgrad_plan(int T, int d_in) {
     const int chunks = ceil_div(T, kWgChunk), col_tiles = ceil_div(d_in, kWgCols);
     int n = chunks / 32 < 8 ? 8 : chunks / 32 < 32 ? chunks / 32 : 32;
-    for (const int most : {256 / col_tiles, chunks / 4, wgrad_slices_reserved(T, d_in)})
+    for (const int most : {256 / col_tiles, ceil_div(chunks, 4), wgrad_slices_reserved(T, d_in)})
         if (n > most) n = most;
     const int slice_chunks = ceil_div(chunks, n < 1 ? 1 : n);
     return {slice_chunks > 8 ? 4 : 2, slice_chunks};
