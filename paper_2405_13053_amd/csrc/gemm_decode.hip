@@ -196,14 +196,17 @@ SplitPlan gemm_decode_plan(int d_in, const int* d_out, int G, int gate_rows) {
         p.per_wg = (int)ceil_div64((int64_t)tiles * p.nk, 256);
         p.S = ceil_div(p.nk - 1, p.per_wg) + 1;   // most runs that nk consecutive units can touch
     }
-    // The tail adds the splits eight at a time, so of narrow outputs (up to 28 row tiles) whole rounds: one round unless its
-    // splits are longer than 8 K steps, two at most.  Whole layers, as many splits as fit and so, 1, 16 and 64 tokens: 4096 ->
-    // 1024 (16 splits, 8) 11.9, 12.7, 15.0 and 11.1, 11.8, 14.1 us; 4096 -> 2048 (13, 8) 13.0, 14.3, 17.8 and 11.5, 12.4, 15.0;
-    // 8192 -> 1024 (23, 8) 15.4, 16.4, 19.2 and 13.8, 14.6, 17.0; 14336 -> 1024 (23, 16) 17.4, 18.8, 21.5 and 16.0, 16.8, 20.1,
-    // with 8 18.1, 19.1, 23.2.
-    if (p.per_wg == 0) {
-        if (p.S > 8 && p.nk <= 64) p.S = 8;
-        else if (p.S > 16) p.S = 16;
+    // The tail adds the splits eight at a time, so of narrow outputs (up to 28 row tiles) one round unless its splits are longer
+    // than 8 K steps, two at most.  Whole layers, as many splits as fit and so, 1, 16 and 64 tokens: 4096 -> 1024 (16 splits, 8)
+    // 11.9, 12.7, 15.0 and 11.1, 11.8, 14.1 us; 4096 -> 2048 (13, 8) 13.0, 14.3, 17.8 and 11.5, 12.4, 15.0; 8192 -> 1024 (23, 8)
+    // 15.4, 16.4, 19.2 and 13.8, 14.6, 17.0; 14336 -> 1024 (23, 16) 17.4, 18.8, 21.5 and 16.0, 16.8, 20.1, with 8 18.1, 19.1,
+    // 23.2.  Where 12 to 16 splits fill the CUs and eight are longer than 6 K steps, few tokens are slower with eight, so as many
+    // as fit: 7360 -> 1400 of rank 16 (16) 13.7, 14.8, 18.6 and with 8 14.6, 15.4, 18.2; 8128 -> 1808 (14) 13.5, 14.6, 19.8 and
+    // 14.1, 14.5, 18.4; 6400 -> 2048 (13) 12.5, 14.3 and 13.3, 13.9; but 7168 -> 2560 (11) 13.8, 15.9 and 13.8, 14.4, 8192 -> 1400
+    // (18) 14.5, 15.8 and 13.5, 14.4.  (The token count does not decide: a token's logits are the same at every decode batch.)
+    if (p.per_wg == 0 && p.S > 8) {
+        if (p.nk > 64) p.S = p.S > 16 ? 16 : p.S;
+        else if (!(p.nk > 48 && p.S >= 12 && p.S <= 16)) p.S = 8;
     }
     return p;
 }

@@ -367,11 +367,16 @@ def test_fp32_routing_does_not_depend_on_the_launches(d_in, d_out, N, r, k):
         assert torch.equal(w, w_ref[:T]), f"T = {T}: weights differ"
 
 
-# row tiles of 128 outputs and of 320 (r = 8), 544 (16) or 320 (7 adapters of 32) rows of Wcat share 256 CUs: 1, 2, 3, 5 and 16 K splits
-@pytest.mark.parametrize("d_in,d_out", [(512, 24584), (512, 13832), (512, 9224), (1280, 5640), (4096, 264)],
-                         ids=["S1", "S2", "S3", "S5", "S16"])
-@pytest.mark.parametrize("N,r,k", [(28, 8, 2), (28, 16, 1), (7, 32, 3)], ids=["r8", "r16", "r32"])
-def test_decode_tail_at_each_split_count(d_in, d_out, N, r, k):
+# row tiles of 128 outputs and of 320 (r = 8), 544 (16) or 320 (7 adapters of 32) rows of Wcat share 256 CUs; up to 8 splits a
+# round of the tail, above 16 never (S: splits for the three adapter sets)
+@pytest.mark.parametrize("d_in,d_out,S", [
+    (512, 24584, (1, 1, 1)), (512, 13832, (2, 2, 2)), (768, 9224, (3, 3, 3)), (1280, 5640, (5, 5, 5)), (4096, 264, (8, 8, 8)),
+    (8384, 264, (16, 16, 16)), (8384, 2056, (12, 11, 12)), (6464, 2056, (12, 8, 12)), (6464, 1416, (8, 15, 8))])
+@pytest.mark.parametrize("adapters", range(3), ids=["r8", "r16", "r32"])
+def test_decode_tail_at_each_split_count(d_in, d_out, S, adapters):
+    N, r, k = [(28, 8, 2), (28, 16, 1), (7, 32, 3)][adapters]
+    regs = {name: written for name, _, _, written in m.workspace_regions(5, d_in, d_out, N, r, k, "bf16", True)}
+    assert regs["splitk"] == S[adapters] * 5 * d_out * 4
     _check_layer(LS(5, d_in, d_out, N, r, k, 2.0, "bf16", "zipf", "tail"), seed=61)
 
 
