@@ -160,9 +160,10 @@ def test_base_gemm_matches_oracle(T, d_in, d_out, dtype):
     assert util.rel_max_err(out, oracle.base(ops["x"], ops["W"])) <= util.tol(shape)
 
 
-# The 16x16x32 kernel at the edges of its K loop (1, 2 and 3 K tiles, one short of and one past an unrolled trip of six,
-# a trip and a remainder) in each of its tile shapes, ragged in both directions.
-@pytest.mark.parametrize("d_in", [64, 128, 192, 448, 512, 576, 1088, 1152])
+# The 16x16x32 kernel at the edges of its K loop in each of its tile shapes, ragged in both directions: 1, 2 and 3 K tiles; the
+# first and the second unrolled trip of six tiles (256x256, entered from 8 and 14 K tiles) and of twelve (192 to 256 rows of
+# 128 columns, from 15 and 27) with none, one and more tiles left.
+@pytest.mark.parametrize("d_in", [64, 128, 192, 448, 512, 576, 832, 896, 960, 1024, 1088, 1152, 1664, 1728, 1792])
 @pytest.mark.parametrize("T,d_out", [(2600, 4104), (1300, 4104), (300, 264), (1100, 4104), (1500, 4104), (1700, 4104), (1700, 5128)],
                          ids=["256x256", "192x128", "128x128", "160x128", "224x128", "256x128", "128x128-two-per-CU"])
 def test_base_gemm_k_loop_edges(T, d_out, d_in):
@@ -526,9 +527,10 @@ def test_dense_route_exact_ties_and_zero_gate():
 
 
 # A bias of -inf masks an adapter; a token whose input is NaN must not disturb the others.  One shape per place that ranks:
-# decode, a few hundred tokens, dense routing, more than 32 adapters, fp32.
+# decode, a few hundred tokens, dense routing, more than 32 adapters, fp32 in two launches, three and one.
 @pytest.mark.parametrize("T,d_in,d_out,N,k,dtype", [(33, 512, 136, 28, 3, "bf16"), (200, 512, 264, 28, 3, "bf16"), (2500, 256, 2056, 28, 3, "bf16"),
-                                                    (300, 256, 136, 64, 8, "bf16"), (40, 256, 136, 64, 3, "f32"), (40, 256, 1288, 12, 8, "f32")])
+                                                    (300, 256, 136, 64, 8, "bf16"), (40, 256, 136, 64, 3, "f32"), (40, 256, 1288, 12, 8, "f32"),
+                                                    (40, 256, 136, 4, 3, "f32"), (40, 128, 136, 8, 3, "f32")])
 def test_masked_adapters_and_a_token_of_nan(T, d_in, d_out, N, k, dtype):
     shape = LS(T, d_in, d_out, N, 8, k, 2.0, dtype)
     ops, dev = util.make_case(shape, seed=57, condition=False)
@@ -565,6 +567,7 @@ GRAPH_SHAPES = [
     LS(400, 1024, 520, 28, 16, 2, 2.0, "bf16", "uniform", "graph-bucketed"),
     # dense routing in front of the fused GEMM (too many output tiles for the split-K form)
     LS(2500, 512, 2056, 28, 8, 2, 2.0, "bf16", "uniform", "graph-dense-route-fused-gemm"),
+    LS(64, 256, 256, 4, 8, 2, 2.0, "f32", "uniform", "graph-fp32-one-launch"),
 ]
 
 
