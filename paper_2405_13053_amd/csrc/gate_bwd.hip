@@ -313,39 +313,74 @@ __global__ __launch_bounds__(PARTS * 64) void gate_bwd_wgrad_kernel(const uint16
         for (int i = 0; i < 16; ++i) acc[f][i] = 0.f;
     float bsum = 0.f;
     const bool bias_tile = blockIdx.x == 0;                      // uniform
-    auto multiply = [&](const Chunk& f) {
+    auto operand = [&](const Chunk& f, int q) {                  // column c + q
+        u32x4 v;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {                            // column c + q
-            u32x4 v;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t even = q < 2 ? f.x[2 * j].x : f.x[2 * j].y, odd = q < 2 ? f.x[2 * j + 1].x : f.x[2 * j + 1].y;
-                v[j] = __builtin_amdgcn_perm(odd, even, q % 2 == 0 ? 0x05040100u : 0x07060302u);
-            }
-#pragma unroll
-            for (int term = 2; term >= 0; --term)
-                acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.d[term]),
-                                                                 __builtin_bit_cast(bf16x8, v), acc[q], 0, 0, 0);
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t even = q < 2 ? f.x[2 * j].x : f.x[2 * j].y, odd = q < 2 ? f.x[2 * j + 1].x : f.x[2 * j + 1].y;
+            v[j] = __builtin_amdgcn_perm(odd, even, q % 2 == 0 ? 0x05040100u : 0x07060302u);
         }
-        if (bias_tile)
+        return __builtin_bit_cast(bf16x8, v);
+    };
+    auto multiply = [&](f32x16& sum, const Chunk& f, int term, bf16x8 xq) {
+        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.d[term]), xq, sum, 0, 0, 0);
+    };
+    auto add_bias = [&](const Chunk& f) {
+        float b[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                bsum += ((bf16_bits_to_float(f.d[2][j] & 0xffffu) + bf16_bits_to_float(f.d[1][j] & 0xffffu)) +
-                         bf16_bits_to_float(f.d[0][j] & 0xffffu)) +
-                        ((bf16_bits_to_float(f.d[2][j] >> 16) + bf16_bits_to_float(f.d[1][j] >> 16)) +
-                         bf16_bits_to_float(f.d[0][j] >> 16));
+        for (int j = 0; j < 4; ++j)
+            b[j] = ((bf16_bits_to_float(f.d[2][j] & 0xffffu) + bf16_bits_to_float(f.d[1][j] & 0xffffu)) +
+                    bf16_bits_to_float(f.d[0][j] & 0xffffu)) +
+                   ((bf16_bits_to_float(f.d[2][j] >> 16) + bf16_bits_to_float(f.d[1][j] >> 16)) +
+                    bf16_bits_to_float(f.d[0][j] >> 16));
+        bsum += (b[0] + b[1]) + (b[2] + b[3]);
     };
     Chunk f[kWgRing];
 #pragma unroll
     for (int u = 0; u < kWgRing; ++u)
         if (k0 + u < k1) load(f[u], k0 + u);
-    for (int ch = k0; ch < k1; ch += kWgRing) {
+    // One rounding of a full-sized sum for each chunk, not three: the small terms come first, or have sums of their own
+    if constexpr (PARTS == 2) {                                  // no more chunks than the ring holds
 #pragma unroll
         for (int u = 0; u < kWgRing; ++u) {
-            if (ch + u >= k1) break;                             // uniform per wavefront
-            multiply(f[u]);
-            if (ch + u + kWgRing < k1) load(f[u], ch + u + kWgRing);
+            if (k0 + u >= k1) break;                             // uniform per wavefront
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const bf16x8 xq = operand(f[u], q);
+                multiply(acc[q], f[u], 2, xq);
+                multiply(acc[q], f[u], 1, xq);
+            }
         }
+#pragma unroll
+        for (int u = 0; u < kWgRing; ++u) {
+            if (k0 + u >= k1) break;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) multiply(acc[q], f[u], 0, operand(f[u], q));
+            if (bias_tile) add_bias(f[u]);
+        }
+    } else {
+        f32x16 low[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) low[q][i] = 0.f;
+        for (int ch = k0; ch < k1; ch += kWgRing) {
+#pragma unroll
+            for (int u = 0; u < kWgRing; ++u) {
+                if (ch + u >= k1) break;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const bf16x8 xq = operand(f[u], q);
+                    multiply(low[q], f[u], 2, xq);
+                    multiply(acc[q], f[u], 0, xq);
+                    multiply(low[q], f[u], 1, xq);
+                }
+                if (bias_tile) add_bias(f[u]);
+                if (ch + u + kWgRing < k1) load(f[u], ch + u + kWgRing);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[q] += low[q];
     }
     // accumulator entry i of lane l: adapter 8*(i/4) + 4*(l/32) + i%4, column c0 + 4 * (l%32) + fragment
 #pragma unroll
@@ -429,7 +464,7 @@ static WgradPlan wgrad_plan(int T, int d_in) {
     for (const int most : {256 / col_tiles, ceil_div(chunks, 4), wgrad_slices_reserved(T, d_in)})
         if (n > most) n = most;
     const int slice_chunks = ceil_div(chunks, n < 1 ? 1 : n);
-    return {slice_chunks > 8 ? 4 : 2, slice_chunks};
+    return {slice_chunks > 2 * kWgRing ? 4 : 2, slice_chunks};
 }
 
 GateBackwardLayout gate_backward_layout(int T, int d_in, int d_out, int N, int r) {
