@@ -32,8 +32,9 @@ __global__ __launch_bounds__(kRowThreads) void gate_logits_f32_kernel(const floa
 // at a time (wave_topk_softmax); the groups a wavefront owns are interleaved so their shuffle
 // latencies overlap.
 //
-// A workgroup of 16 wavefronts owns one bucketing chunk of 64 tokens (4 per wavefront) and also
-// leaves the chunk's adapter histogram for the scatter pass.
+// A workgroup owns one bucketing chunk, 4 tokens per wavefront, and also leaves the chunk's adapter
+// histogram for the scatter pass: 4 wavefronts and 16 tokens up to 2048 tokens, 16 and 64 above
+// (routing_chunk_tokens).
 // ------------------------------------------------------------------------------------------
 constexpr int kTopkTokensPerWave = 4;
 static_assert(kBucketChunkTokens / kTopkTokensPerWave * 64 <= 1024, "one workgroup per bucketing chunk");

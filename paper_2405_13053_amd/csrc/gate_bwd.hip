@@ -46,13 +46,14 @@ struct DlogitsArgs {
     const int32_t* idx_in;   // [T,k] routing of the forward call, or NULL: rank again here
     const float* w_in;       // [T,k]
     const int32_t* labels;   // [T] or NULL
-    bf16_t* dgs;             // d_logits in three bf16 terms, see split3_exact: [blocks of 8 tokens][term][32][8 tokens]
+    bf16_t* dgs;             // d_logits in three bf16 terms, see split3: [blocks of 8 tokens][term][32][8 tokens]
     float* d_logits;         // [T,N] or NULL
     bf16_t* hx;              // [T][ext] extension operand of the input-gradient GEMM, or NULL
     int ext;                 // columns of hx: N*r + 96 rounded up to 64
     int S1, S2, CR, NR, T, N, r, k;
     float scale, beta;
-    // (an even number of token blocks: past T they write zeros); workgroups from token_blocks on write Xt instead (a launch of its own would cost more than its work)
+    // an even number of token blocks (past T they write zeros); workgroups from token_blocks on write Xt instead (a launch of
+    // its own would cost more than its work)
     int token_blocks;
     const uint16_t* A;       // [N, d_in, r]
     const float* W_gate;     // [d_in, N]
@@ -60,10 +61,11 @@ struct DlogitsArgs {
     uint16_t* Xt;            // [d_in][ext]
 };
 
-// The three bf16 terms of an fp32 value, hi + mid + lo == v exactly: its 24 significand bits, 8 to a term (cut, not rounded:
-// the largest values stay finite).  What is not finite is its first term alone.
+// The three bf16 terms of an fp32 value: its 24 significand bits, 8 to a term (cut, not rounded: the largest values stay
+// finite).  hi + mid + lo == v from about 2^-102 up; of smaller values the bits below bf16's smallest normal one may be lost.
+// What is not finite is its first term alone.
 struct Split3 { uint16_t term[3]; };
-__device__ __forceinline__ Split3 split3_exact(float v) {
+__device__ __forceinline__ Split3 split3(float v) {
     const uint32_t hi = __float_as_uint(v) & 0xffff0000u;
     const bool finite = (hi & 0x7f800000u) != 0x7f800000u;
     const float r1 = finite ? v - __uint_as_float(hi) : 0.f;
@@ -199,7 +201,7 @@ __global__ __launch_bounds__(kBwdThreads) void gate_bwd_dlogits_kernel(const Dlo
         uint16_t v[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const Split3 sp = split3_exact(t0 + half * 4 + j < T && n < N ? s_dg[half * 4 + j][n] : 0.f);
+            const Split3 sp = split3(t0 + half * 4 + j < T && n < N ? s_dg[half * 4 + j][n] : 0.f);
             v[j] = term == 0 ? sp.term[0] : term == 1 ? sp.term[1] : sp.term[2];
         }
         *reinterpret_cast<uint2*>(a.dgs + ((size_t)blockIdx.x * 6 * NP + threadIdx.x) * 4) =

@@ -610,7 +610,10 @@ constexpr int kEpiStore = 0, kEpiAccumulate = 1, kEpiPartial = 2, kEpiPartialThr
 // ordinary stores, "nt", "sc1": the fp32 tiles of 300 x 4096 -> 4096 26.35, 25.6, 25.2 us, of 1531 x 4096 -> 1024 of rank
 // 16 38.1, 37.75, 36.7; bf16 outputs: a training step of 4096 tokens 273.1 and 271.0 ("sc1"), 3000 x 5120 -> 5120 from its
 // parts 174.5 and 172.8.  The routing products of a prefill (kEpiPartial, two workgroups per CU at different stages) gain
-// nothing: 4096 tokens 120.9 and 121.7.
+// nothing: 4096 tokens 120.9 and 121.7.  bf16 outputs beside weights that come from HBM, 96 to 4096 tokens, base projections and
+// whole layers of 4096 -> 4096 and 14336, 14336 -> 4096, 5120 -> 5120 and 13824, ordinary and "sc1": 3% faster to 0.7% slower.
+// The ends: 2000 x 4096 -> 4096 54.0 and 52.2, 700 x 4096 -> 14336 with adapters 92.3 and 90.1; 3000 x 4096 -> 14336 256.5
+// and 258.4 (two runs 1.2% apart), 160 x 5120 -> 13824 53.3 and 53.6.
 constexpr int kWriteThrough = 16;
 // Epilogue of the ring kernel.  EPI fixes at compile time which form a kernel carries: with one form the
 // accumulators leave their registers as they are converted (with all three behind run-time branches the compiler
