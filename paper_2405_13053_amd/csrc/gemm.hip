@@ -115,8 +115,8 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_expand_kernel(const Re
 // Skinny batches (decode): one 64-row tile per 64 output columns leaves most CUs idle while W streams
 // from HBM, so K is split over workgroups.  Returns the number of main-K splits (0 = do not split).
 int gemm_splitk_splits(int T, int d_in, int d_out, bool bf16) {
-    if (!bf16 || T < 1 || T > 64 || d_in % kGemmBK != 0) return 0;
-    const int tiles = ceil_div(T, 64) * ceil_div(d_out, 64), nk = d_in / kGemmBK;
+    if (!bf16 || T < 1 || T > 64) return 0;
+    const int tiles = ceil_div(T, 64) * ceil_div(d_out, 64), nk = ceil_div(d_in, kGemmBK);
     if (tiles >= 512 || nk < 8) return 0;
     int S = ceil_div(512, tiles);   // about two workgroups per CU (measured: 384 to 1536 tried)
     if (S > nk / 4) S = nk / 4;
@@ -128,11 +128,11 @@ size_t gemm_splitk_bytes(int T, int d_in, int d_out, bool bf16) {
     return S == 0 ? 0 : (size_t)(S + 1) * T * d_out * sizeof(float);   // +1: the expand extension
 }
 
-// The pipelined kernels need whole K tiles, byte offsets inside x, W and the extension operands that fit 32 bits, and
-// for their staged epilogue an output tile (256 rows at most, fp32 at the widest) whose offsets do too.
+// The pipelined kernels need byte offsets inside x, W and the extension operands that fit 32 bits, and for their staged
+// epilogue an output tile (256 rows at most, fp32 at the widest) whose offsets do too.
 static bool dma_ok(const GemmArgs& a, int BM, int BN) {
     const uint64_t widest = (uint64_t)(a.d_in > a.ext_stride ? a.d_in : a.ext_stride) * 2;
-    return a.d_in % kGemmBK == 0 && ((uint64_t)a.T + BM) * widest < (1ull << 32) &&
+    return ((uint64_t)a.T + BM) * widest < (1ull << 32) &&
            ((uint64_t)a.d_out + BN) * widest < (1ull << 32) && (uint64_t)a.d_out * 4 * 256 < (1ull << 32);
 }
 
@@ -155,7 +155,7 @@ static hipError_t launch_tiles(GemmArgs a, hipStream_t stream) {
                                  : launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, false>, a, smem, 1, stream);
 }
 
-// The same without the ring: any d_in, any size.
+// The same without the ring: any size.
 template <int M>
 static hipError_t launch_plain(GemmArgs a, hipStream_t stream) {
     constexpr int smem = gemm_lds_bytes<M, M>();
@@ -403,7 +403,7 @@ hipError_t launch_gemm(const void* x, const void* W, int T, int d_in, int d_out,
         if (S > 0 && d_in > 0) {
             a.partial = splitk_ws;
             a.splits = S;
-            a.tiles_per_split = ceil_div(d_in / kGemmBK, S);
+            a.tiles_per_split = ceil_div(ceil_div(d_in, kGemmBK), S);
             return launch_skinny(a, stream);
         }
         const int64_t big_tiles = (int64_t)ceil_div(T, 256) * ceil_div(d_out, 256);

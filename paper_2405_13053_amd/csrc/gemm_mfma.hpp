@@ -14,11 +14,11 @@
 // 64 through LDS tiles whose rows are 128 B, their 16-B chunks XOR-swizzled with the row index (see swz) so that a
 // ds_read_b128 pass touches every bank once; W is the MFMA's first operand, so a lane ends up with 4 consecutive output
 // columns of one token row):
-//   gemm_mfma_ring_kernel  d_in % 64 == 0, more than 64 tokens, and every fp32-tile launch: v_mfma_f32_16x16x32_bf16 on a
-//                          ring of LDS slots that global->LDS loads fill two to five K tiles ahead;
-//   gemm_mfma_dma_kernel   d_in % 64 == 0, up to 64 tokens: 64 x 64 tiles, v_mfma_f32_32x32x16_bf16, two slots;
-//   gemm_mfma_kernel       any other d_in, and sizes whose byte offsets pass 32 bits: v_mfma_f32_32x32x16_bf16, tiles
-//                          through registers into two LDS buffers.
+//   gemm_mfma_ring_kernel  more than 64 tokens, and every fp32-tile launch: v_mfma_f32_16x16x32_bf16 on a ring of LDS
+//                          slots that global->LDS loads fill two to five K tiles ahead;
+//   gemm_mfma_dma_kernel   up to 64 tokens: 64 x 64 tiles, v_mfma_f32_32x32x16_bf16, two slots;
+//   gemm_mfma_kernel       sizes whose byte offsets pass 32 bits: v_mfma_f32_32x32x16_bf16, tiles through registers into
+//                          two LDS buffers.
 #pragma once
 #include <type_traits>
 #include <utility>
@@ -238,7 +238,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(const GemmArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Two-slot version for d_in % 64 == 0 and few tokens: the tiles of both operands go from
+// Two-slot version for few tokens: the tiles of both operands go from
 // global memory straight into LDS with 16-byte buffer_load ... lds (no staging registers), the
 // MFMA operand fragments are double-buffered in registers so the ds_reads of k-step s+1 are in
 // flight while the MFMAs of k-step s run, and there is one barrier per 64-wide K tile, placed
@@ -319,6 +319,36 @@ __device__ __forceinline__ void dma_piece(bf16_t* lds_tile, const DmaOperand& o,
     __builtin_amdgcn_raw_ptr_buffer_load_lds(
         o.rsrc, (__attribute__((address_space(3))) void*)(lds_tile + (j * 4 + wave) * 8 * kGemmBK), 16, o.voff,
         (int)(o.piece_step * (uint32_t)j + (uint32_t)ktile * (kGemmBK * 2)), 0, 0);
+}
+
+// The K tiles behind the whole ones: first, where d_in is no multiple of 64, the rest of the main operands' columns (kt < 0),
+// whose chunks past d_in load zeros, then those of the extension.  Both are requested by the same instructions, from
+// the one resource or the other, so that no branch stands between loads and reads of LDS; the whole offset of a piece is
+// in the per-lane operand, which the bounds check covers.  Base projections with tiles through registers for every such
+// d_in, as it was, and so: 512 x 4104 -> 4096 68.5 and 38.1 us, 2000 97.8 and 69.1, 4096 173 and 97.7, 8192 x 4088 -> 4096 336
+// and 195; with 4096 inputs 27.8, 55.0, 91.9 (rows of 8208 bytes straddle the lines of L2, which the lower tiles wait on).
+struct PartTile {
+    int columns;      // d_in % 64
+    uint32_t offset;  // bytes from a row's start to the tile
+    bool mine;        // this lane's chunk holds columns below d_in
+};
+
+__device__ __forceinline__ PartTile part_tile(int d_in, int wave, int lane) {
+    PartTile t;
+    t.columns = d_in % kGemmBK;
+    t.offset = (uint32_t)(d_in / kGemmBK) * (kGemmBK * 2);
+    t.mine = ((lane & 7) ^ (((wave & 1) << 2) | (lane >> 4))) * 8 < t.columns;
+    return t;
+}
+
+__device__ __forceinline__ void dma_piece_behind(bf16_t* lds_tile, const DmaOperand& main, const DmaOperand& ext,
+                                                 const PartTile& t, int kt, int j, int wave) {
+    constexpr uint32_t kOutside = 0xfffffff0u;   // past every matrix: their rows end more than a tile below 2^32
+    const uint32_t in_part = t.mine ? main.voff + main.piece_step * (uint32_t)j + t.offset : kOutside;
+    const uint32_t in_ext = ext.voff + ext.piece_step * (uint32_t)j + (uint32_t)kt * (kGemmBK * 2);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+        kt < 0 ? main.rsrc : ext.rsrc, (__attribute__((address_space(3))) void*)(lds_tile + (j * 4 + wave) * 8 * kGemmBK), 16,
+        kt < 0 ? in_part : in_ext, 0, 0, 0);
 }
 
 // Map a workgroup id to an output tile: ids are dealt round-robin to the 8 XCDs, so each XCD
@@ -468,33 +498,36 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(const GemmArgs a) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.f;
 
-    // this workgroup's share of the contraction: main K tiles [kt0, kt0 + nk_main) and/or the extension
-    int kt0 = 0, nk_main = a.d_in / kGemmBK;
+    // this workgroup's share of the contraction: whole K tiles [kt0, kt0 + nk_main), the partial one, and/or the extension
+    int kt0 = 0, nk_main = a.d_in / kGemmBK, nk_part = a.d_in % kGemmBK != 0 ? 1 : 0;
     int nk_ext = a.ext_k > 0 ? a.ext_stride / kGemmBK : 0;
     if (a.partial != nullptr) {
         const int split = blockIdx.y;
         if (split < a.splits) {
             kt0 = split * a.tiles_per_split;
+            if (nk_main < kt0 || nk_main >= kt0 + a.tiles_per_split) nk_part = 0;
             nk_main = max(0, min(a.tiles_per_split, nk_main - kt0));
             nk_ext = 0;
         } else {
-            nk_main = 0;
+            nk_main = nk_part = 0;
         }
     }
-    const int nk = nk_main + nk_ext;
+    const int nk = nk_main + nk_part + nk_ext;
 
-    // (x, W) feed local tiles [0, nk_main), (hd, Bt) the tiles after them
+    // (x, W) feed local tiles [0, nk_main + nk_part), (hd, Bt) the tiles after them
     const DmaOperand ox = dma_operand(a.x, a.T, a.d_in, m0, wave, lane);
     const DmaOperand ow = dma_operand(a.W, a.d_out, a.d_in, n0, wave, lane);
     const DmaOperand oh = dma_operand(a.hd, nk_ext > 0 ? a.T : 0, a.ext_stride, m0, wave, lane);
     const DmaOperand ob = dma_operand(a.Bt, nk_ext > 0 ? a.d_out : 0, a.ext_stride, n0, wave, lane);
+    const PartTile part = part_tile(a.d_in, wave, lane);
 
     // piece i of local tile `it` (x-like pieces first) into LDS slot `slot`
     auto request_piece = [&](int it, int slot, int i, auto is_ext) {
         bf16_t* xs = smem + slot * kBufElems;
         if constexpr (decltype(is_ext)::value) {
-            if (i < PX) dma_piece(xs, oh, it - nk_main, i, wave);
-            else dma_piece(xs + BM * kGemmBK, ob, it - nk_main, i - PX, wave);
+            const int kt = it - nk_main - nk_part;
+            if (i < PX) dma_piece_behind(xs, ox, oh, part, kt, i, wave);
+            else dma_piece_behind(xs + BM * kGemmBK, ow, ob, part, kt, i - PX, wave);
         } else {
             if (i < PX) dma_piece(xs, ox, kt0 + it, i, wave);
             else dma_piece(xs + BM * kGemmBK, ow, kt0 + it, i - PX, wave);
@@ -529,7 +562,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(const GemmArgs a) {
         mma_frags<MI, NI>(acc, fcur);
         __builtin_amdgcn_sched_barrier(0);
     };
-    // REQ: 0 = tile it+2 is a main tile, 1 = it is an extension tile, 2 = there is none (last two tiles)
+    // REQ: 0 = tile it+2 is a whole main tile, 1 = it is one behind those, 2 = there is none (last two tiles)
     auto tile_step = [&](int it, auto req) {
         constexpr int REQ = decltype(req)::value;
         const bf16_t* xs = smem + (it & 1) * kBufElems;
@@ -848,17 +881,18 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
         a.partial = a_in.seg[e].partial;
     }
 
-    // this workgroup's share of the contraction: main K tiles [kt0, kt0 + nk_main) and/or the extension
-    int kt0 = 0, nk_main = a.d_in / kGemmBK;
+    // this workgroup's share of the contraction: whole K tiles [kt0, kt0 + nk_main), the partial one, and/or the extension
+    int kt0 = 0, nk_main = a.d_in / kGemmBK, nk_part = a.d_in % kGemmBK != 0 ? 1 : 0;
     int nk_ext = a.ext_k > 0 ? a.ext_stride / kGemmBK : 0;
     if (a.partial != nullptr) {
         const int split = blockIdx.y;
         if (split < a.splits) {
             kt0 = split * a.tiles_per_split;
+            if (nk_main < kt0 || nk_main >= kt0 + a.tiles_per_split) nk_part = 0;
             nk_main = max(0, min(a.tiles_per_split, nk_main - kt0));
             nk_ext = 0;
         } else {
-            nk_main = 0;
+            nk_main = nk_part = 0;
         }
     }
     const bool look = LOOK && nk_ext > 0 && a.topk_idx != nullptr;   // uniform
@@ -869,16 +903,17 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
     const DmaOperand ow = dma_operand(a.W, a.d_out, a.d_in, n0, wave, lane);
     const DmaOperand oh = dma_operand(a.hd, nk_ext > 0 ? a.T : 0, a.ext_stride, m0, wave, lane);
     const DmaOperand ob = dma_operand(a.Bt, nk_ext > 0 ? a.d_out : 0, a.ext_stride, n0, wave, lane);
+    const PartTile part = part_tile(a.d_in, wave, lane);
 
     auto xslot = [&](int it) { return smem + (it % D) * kXElems; };
     auto wslot = [&](int it) { return smem + D * kXElems + (it % (D + 1)) * kWElems; };
-    // piece i of the x-like / W-like operand of K tile kt of the main operands or of the extension
+    // piece i of the x-like / W-like operand of whole K tile kt, or of tile kt of those behind the whole ones
     auto request_x = [&](bf16_t* slot, int kt, int i, auto is_ext) {
-        if constexpr (decltype(is_ext)::value) dma_piece(slot, oh, kt, i, wave);
+        if constexpr (decltype(is_ext)::value) dma_piece_behind(slot, ox, oh, part, kt, i, wave);
         else dma_piece(slot, ox, kt, i, wave);
     };
     auto request_w = [&](bf16_t* slot, int kt, int i, auto is_ext) {
-        if constexpr (decltype(is_ext)::value) dma_piece(slot, ob, kt, i, wave);
+        if constexpr (decltype(is_ext)::value) dma_piece_behind(slot, ow, ob, part, kt, i, wave);
         else dma_piece(slot, ow, kt, i, wave);
     };
     auto request_tile = [&](int it, int kt, auto is_ext) {
@@ -903,13 +938,18 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
         mfma_start<MB, NB>(acc);
         if (look) ext_left &= ids.used(a, lane);
     }
-    // the last extension tile may hold data in its first k-step only (28 adapters of rank 8: 224 of 256 columns;
-    // the rest is zero padding): that k-step is all it gets
-    const bool half_last = nk_ext > 0 && ((a.ext_k - 1) % kGemmBK) < kGemmBK / 2 && (ext_left >> (nk_ext - 1) & 1) != 0;
+    // the last tile may hold data in its first k-step only (28 adapters of rank 8: 224 of 256 columns; the rest is zero
+    // padding): that k-step is all it gets
+    bool half_last = nk_ext > 0 && ((a.ext_k - 1) % kGemmBK) < kGemmBK / 2 && (ext_left >> (nk_ext - 1) & 1) != 0;
     nk_ext = __popcll(ext_left);
-    const int nk = nk_main + nk_ext;
-    // tiles are requested in order: the K tile of the extension that comes next
+    if (nk_ext == 0) half_last = nk_part > 0 && part.columns <= kGemmBK / 2;
+    const int nk = nk_main + nk_part + nk_ext;
+    // tiles are requested in order: the one that comes next behind the whole ones, see PartTile
     auto next_ext = [&]() {
+        if (nk_part > 0) {
+            nk_part = 0;
+            return -1;
+        }
         const int e = __ffsll((unsigned long long)ext_left) - 1;
         ext_left &= ext_left - 1;
         return e;
@@ -943,7 +983,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
     // Where tile `it` lies, outside the unrolled main loop: carried along, since the remainders by D and D + 1 sit between
     // two tiles (64 K tiles of 128 x 128, one workgroup per CU, D = 4: 27.2 us with them, 24.5 without)
     int slot_x = 0, slot_w = D * kXElems;
-    // REQ: 0 = tile it+D is a main tile, 1 = it is an extension tile, 2 = there is none (last D tiles)
+    // REQ: 0 = tile it+D is a whole main tile, 1 = it is one behind those, 2 = there is none (last D tiles)
     // PH: `it` in its trip when it is known at compile time (the unrolled main loop: every slot address is then a
     // constant and no address arithmetic sits between two tiles), -1 otherwise
     auto tile_step = [&](int it, auto req, auto ph) __attribute__((always_inline)) {

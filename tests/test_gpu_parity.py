@@ -175,6 +175,27 @@ def test_base_gemm_k_loop_edges(T, d_out, d_in):
     assert float(((out.double() - ref).abs() - 2.0 ** -8 * ref.abs()).max()) <= 1e-4
 
 
+# Widths that leave a partial K tile (1 to 7 chunks of 8 columns; up to 32 columns of it are one k-step), alone and behind 1 to
+# 28 whole tiles, in each tile shape and at up to 64 tokens.  Where a load ran past d_in it would bring the first columns of the
+# next row: one row of x and one of W start with infinities, which may reach that token's and that column's outputs alone.
+@pytest.mark.parametrize("d_in", [8, 32, 40, 56, 72, 136, 184, 232, 456, 520, 1000, 1048, 1112, 1800])
+@pytest.mark.parametrize("T,d_out", [(2600, 4104), (1300, 4104), (300, 264), (1100, 4104), (1500, 4104), (1700, 4104), (1700, 5128),
+                                     (63, 200), (1, 4104)],
+                         ids=["256x256", "192x128", "128x128", "160x128", "224x128", "256x128", "128x128-two-per-CU", "64x64", "one"])
+def test_base_gemm_partial_k_tile(T, d_out, d_in):
+    shape = LS(T, d_in, d_out, 2, 2, 1, 1.0, "bf16")
+    _, dev = util.make_case(shape, seed=37, condition=False)
+    t, c = T // 2, d_out // 2
+    dev["x"][t, :8] = float("inf")
+    dev["W"][c, :8] = float("inf")
+    out = m.base_gemm(dev["x"], dev["W"]).double()
+    ref = dev["x"].double() @ dev["W"].double().t().contiguous()
+    assert not torch.isfinite(out[t]).any() and not torch.isfinite(out[:, c]).any()
+    out[t], out[:, c], ref[t], ref[:, c] = 0.0, 0.0, 0.0, 0.0
+    # one bf16 rounding of an fp32 sum: half an ulp (2^-9 of the value), fp32 summation error far below it
+    assert float(((out - ref).abs() - 2.0 ** -8 * ref.abs()).max()) <= 1e-4
+
+
 # accumulate = 1 in each tile shape: the old output is read, added in fp32 and rounded once; ranks whose last
 # extension K tile is a half (N*r % 64 <= 32) and a whole one
 @pytest.mark.parametrize("N,r", [(28, 8), (7, 8)], ids=["half-tile", "whole-tile"])
