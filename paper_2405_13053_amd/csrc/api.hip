@@ -23,11 +23,10 @@ bool shape_ok(int T, int d_in, int d_out, int N, int r, int k) {
 }
 
 // Decode in two launches (gate logits and every adapter's shrink inside the GEMM's launch, then routing + reduce +
-// expand): the split-K shapes whose adapters also have the Wcat operand.
-bool decode_fused_applies(int T, int d_in, int d_out, int N, int r, bool bf16) {
-    return route_small_applies(T, r, bf16) && gemm_splitk_splits(T, d_in, d_out, bf16) > 0 &&
-           route_dense_possible(d_in, N, r, bf16);
-}
+// expand): whatever the widths.  Four launches (gate logits, top-k with the shrink, split GEMM, reduction), as widths off 64,
+// fewer than 512 inputs and more than 32704 outputs had, and so: 1 token of 4104 -> 4096 24.0 and 15.1 us, 64 27.8 and 20.1,
+// 49 x 320 -> 2920 of rank 16 packed per call 21.6 and 16.9, 1 x 4096 -> 40960 89.5 and 60.5, 64 95.5 and 81.4.
+bool decode_fused_applies(int T, int N, int r, bool bf16) { return route_small_applies(T, r, bf16) && route_dense_possible(N, r, bf16); }
 
 // Mid-sized batches whose 128 x 128 output tiles would leave most CUs idle (a few hundred tokens): the base
 // projection is split along K over workgroups like the routing products (fp32 tiles), and the reduction adds the
@@ -41,7 +40,7 @@ int dense_midsplit_splits(int T, int d_in, int d_out, int N, int r, bool bf16, b
     if (!route_dense_applies(T, d_in, N, r, bf16) || d_out % 8 != 0 || !gemm_dense_splitk_ok(T, d_in, d_out)) return 0;
     const int col_tiles = ceil_div(d_out, 128) + ceil_div(prep_wcat_rows(N, r), 128), fit = gemm_dense_splits(T, d_in, d_out);
     const int S = reserve ? gemm_multi_splits_reserved(T, col_tiles, fit)
-                          : gemm_multi_splits(T, col_tiles, fit, d_in / 64, (int64_t)d_out + prep_wcat_rows(N, r));
+                          : gemm_multi_splits(T, col_tiles, fit, ceil_div(d_in, 64), (int64_t)d_out + prep_wcat_rows(N, r));
     return S >= 2 ? S : 0;
 }
 
@@ -71,7 +70,7 @@ WsLayout ws_layout(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
     L.hdense = take((size_t)T * L.ext_stride * sizeof(uint16_t));
     L.apack = take(shrink_apack_bytes(d_in, N, r, bf16));
     L.hpart = take(shrink_hpart_bytes(T, d_in, r, k, bf16));
-    const bool decode3 = decode_fused_applies(T, d_in, d_out, N, r, bf16);
+    const bool decode3 = decode_fused_applies(T, N, r, bf16);
     const int S_decode = decode3 ? gemm_decode_plan(d_in, &d_out, 1, prep_wcat_rows(N, r)).S : 0;
     size_t splitk = gemm_splitk_bytes(T, d_in, d_out, bf16);   // lora_forward at such a size splits in its own way
     if ((size_t)S_decode * T * d_out * sizeof(float) > splitk) splitk = (size_t)S_decode * T * d_out * sizeof(float);
@@ -95,7 +94,9 @@ WsLayout ws_layout(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
 }
 
 // Packed weights (meteora_pack_weights): the three operand layouts, each 256-byte aligned.
-struct PackLayout { size_t wsplit, apack, btrans, wcat, total; };
+// `least`: what a blob may hold at the least.  Widths that are no multiple of 64 were packed without Wcat once: such a blob, kept
+// in a file, is still taken, and the call packs its operands itself.
+struct PackLayout { size_t wsplit, apack, btrans, wcat, total, least; };
 
 PackLayout pack_layout(int d_in, int d_out, int N, int r, bool bf16) {
     PackLayout P{};
@@ -104,8 +105,9 @@ PackLayout pack_layout(int d_in, int d_out, int N, int r, bool bf16) {
     P.wsplit = take(gate_wsplit_bytes(d_in, N, bf16));
     P.apack = take(shrink_apack_bytes(d_in, N, r, bf16));
     P.btrans = take(prep_btrans_bytes(d_out, N, r, bf16));
-    P.wcat = take(route_dense_possible(d_in, N, r, bf16) ? prep_wcat_bytes(d_in, N, r, bf16) : 0);
+    P.wcat = take(route_dense_possible(N, r, bf16) ? prep_wcat_bytes(d_in, N, r, bf16) : 0);
     P.total = off;
+    P.least = d_in % 64 != 0 ? P.wcat : P.total;
     return P;
 }
 
@@ -255,7 +257,7 @@ int meteora_workspace_regions(int T, int d_in, int d_out, int N, int r, int k, m
     const size_t pairs = (size_t)T * k;
     const int CR = prep_wcat_rows(N, r);
     const bool dense = route_dense_applies(T, d_in, N, r, bf16);
-    const bool decode3 = decode_fused_applies(T, d_in, d_out, N, r, bf16);
+    const bool decode3 = decode_fused_applies(T, N, r, bf16);
     wr("topk_idx", pairs * sizeof(int32_t));
     wr("topk_w", pairs * sizeof(float));
     if (!with_packed) {
@@ -498,7 +500,7 @@ meteora_status meteora_pack_weights(const float* W_gate, const void* A, const vo
     if (P.total == 0) return METEORA_OK;   // this dtype reads the tensors as they are
     if (!packed || !aligned256(packed) || packed_bytes < P.total) return METEORA_ERR_WORKSPACE;
     const bool pw = gate_wsplit_bytes(d_in, N, bf16) > 0, pa = shrink_apack_bytes(d_in, N, r, bf16) > 0;
-    const bool pb = prep_btrans_bytes(d_out, N, r, bf16) > 0, pc = route_dense_possible(d_in, N, r, bf16);
+    const bool pb = prep_btrans_bytes(d_out, N, r, bf16) > 0, pc = route_dense_possible(N, r, bf16);
     METEORA_HIP(launch_prep(W_gate, pw ? at<void>(packed, P.wsplit) : nullptr, A,
                             pa ? at<void>(packed, P.apack) : nullptr, pb ? B : nullptr,
                             pb ? at<void>(packed, P.btrans) : nullptr, pc ? at<void>(packed, P.wcat) : nullptr, d_in,
@@ -522,8 +524,8 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
     const WsLayout L = ws_layout(T, d_in, d_out, N, r, k, bf16);
     if (!ws || !aligned256(ws) || ws_bytes < L.total) return METEORA_ERR_WORKSPACE;
     const PackLayout P = pack_layout(d_in, d_out, N, r, bf16);
-    const bool use_packed = packed != nullptr && P.total > 0;
-    if (use_packed && (!aligned256(packed) || packed_bytes < P.total)) return METEORA_ERR_WORKSPACE;
+    if (packed != nullptr && P.total > 0 && (!aligned256(packed) || packed_bytes < P.least)) return METEORA_ERR_WORKSPACE;
+    const bool use_packed = packed != nullptr && P.total > 0 && packed_bytes >= P.total;
     if (T == 0) return METEORA_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
     int32_t* idx = topk_idx_out ? topk_idx_out : at<int32_t>(ws, L.topk_idx);
@@ -532,7 +534,7 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
     const int tslot = timing_begin_call(st);
     // mid-sized batch: gate logits and the shrink of every adapter in one MFMA launch, selection afterwards
     const bool dense = route_dense_applies(T, d_in, N, r, bf16);
-    const bool decode3 = decode_fused_applies(T, d_in, d_out, N, r, bf16);
+    const bool decode3 = decode_fused_applies(T, N, r, bf16);
     PackedPtrs pk{at<void>(ws, L.wsplit), at<void>(ws, L.apack), at<void>(ws, L.btrans), at<void>(ws, L.wcat)};
     if (use_packed) {
         void* blob = const_cast<void*>(packed);   // read only from here on
@@ -652,11 +654,11 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
 // ---- a group of layers that share x ----------------------------------------------------------------------------
 namespace {
 
-// Fused form: decode-sized batch, every member on the two-launch path with packed weights.
-bool group_fused(const meteora_group_member* m, int G, int T, int d_in, int N, int r, bool bf16) {
-    if (G < 2 || G > kMaxDecodeGroup) return false;
+// Fused form: decode-sized batch, every member with packed weights.
+bool group_fused(const bool* packed, int G, int T, int N, int r, bool bf16) {
+    if (G < 2 || G > kMaxDecodeGroup || !decode_fused_applies(T, N, r, bf16)) return false;
     for (int g = 0; g < G; ++g)
-        if (!m[g].packed || !decode_fused_applies(T, d_in, m[g].d_out, N, r, bf16)) return false;
+        if (!packed[g]) return false;
     return true;
 }
 
@@ -674,7 +676,7 @@ int group_mid_splits(const int* d_out, const bool* packed, int G, int T, int d_i
         tiles += (int64_t)ceil_div(T, 128) * (ceil_div(d_out[g], 128) + ceil_div(cat_rows, 128));
     }
     if (tiles > 320) return 0;   // beyond: member by member (each on the path its own size selects)
-    const int nk = d_in / 64;
+    const int nk = ceil_div(d_in, 64);
     int S = (int)((384 + tiles / 2) / tiles);
     if (S > nk / 4) S = nk / 4;
     if (S > 8) S = 8;
@@ -716,12 +718,11 @@ extern "C" size_t meteora_group_workspace_bytes(const int* d_out, int G, int T, 
     if (dt != METEORA_F32 && dt != METEORA_BF16) return 0;
     const bool bf16 = dt == METEORA_BF16;
     size_t need = 0;
-    bool fused = G >= 2 && G <= kMaxDecodeGroup;
+    const bool fused = G >= 2 && G <= kMaxDecodeGroup && decode_fused_applies(T, N, r, bf16);
     for (int g = 0; g < G; ++g) {
         const size_t one = meteora_workspace_bytes(T, d_in, d_out[g], N, r, k, dt);
         if (one == 0) return 0;
         need = one > need ? one : need;
-        fused = fused && decode_fused_applies(T, d_in, d_out[g], N, r, bf16);
     }
     if (fused) {
         const int gate_rows = prep_wcat_rows(N, r);
@@ -756,7 +757,7 @@ extern "C" meteora_status meteora_linear_forward_group(const void* x, const mete
             (m.topk_idx_out && !aligned16(m.topk_idx_out)) || (m.topk_w_out && !aligned16(m.topk_w_out)))
             return METEORA_ERR_UNSUPPORTED;
         if (m.packed && (!aligned256(m.packed) ||
-                         m.packed_bytes < pack_layout(d_in, m.d_out, N, r, bf16).total))
+                         m.packed_bytes < pack_layout(d_in, m.d_out, N, r, bf16).least))
             return METEORA_ERR_WORKSPACE;
         d_outs[g] = m.d_out;
     }
@@ -765,7 +766,9 @@ extern "C" meteora_status meteora_linear_forward_group(const void* x, const mete
     if (T == 0) return METEORA_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
     bool is_packed[64];
-    for (int g = 0; g < G; ++g) is_packed[g] = members[g].packed != nullptr;
+    for (int g = 0; g < G; ++g)
+        is_packed[g] = members[g].packed != nullptr &&
+                       members[g].packed_bytes >= pack_layout(d_in, members[g].d_out, N, r, bf16).total;
     if (const int S = (G <= kMaxDecodeGroup ? group_mid_splits(d_outs, is_packed, G, T, d_in, N, r, bf16) : 0)) {
         const int cat_rows = prep_wcat_rows(N, r);
         const GroupLayout L = group_layout(d_outs, G, T, d_in, N, r, k, S, cat_rows);
@@ -799,7 +802,7 @@ extern "C" meteora_status meteora_linear_forward_group(const void* x, const mete
         METEORA_HIP(launch_gemm_decode_finish(mem, G, S, T, k, r, st));
         return METEORA_OK;
     }
-    if (!group_fused(members, G, T, d_in, N, r, bf16)) {
+    if (!group_fused(is_packed, G, T, N, r, bf16)) {
         // the same result one layer after the other (they share the workspace, which the stream order allows)
         for (int g = 0; g < G; ++g) {
             const meteora_group_member& m = members[g];

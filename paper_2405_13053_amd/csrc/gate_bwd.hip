@@ -442,7 +442,7 @@ __global__ __launch_bounds__(256) void gate_bwd_reduce_kernel(const float* __res
 
 // ---- host side ----
 bool gate_backward_applies(int T, int d_in, int d_out, int N, int r, bool bf16) {
-    return route_dense_possible(d_in, N, r, bf16) && T >= 1 && T <= kGateBackwardMaxTokens && r <= kMaxRank &&
+    return route_dense_possible(N, r, bf16) && d_in % 64 == 0 && d_out % 64 == 0 && T >= 1 && T <= kGateBackwardMaxTokens && r <= kMaxRank &&
            gemm_dense_splitk_ok(T, d_in, prep_wcat_rows(N, r)) && gemm_dense_splitk_ok(T, d_out, N * r);
 }
 

@@ -203,7 +203,7 @@ static bool dense_small_tiles(int T) { return T <= 4096; }
 
 bool gemm_dense_splitk_ok(int T, int d_in, int rows) {
     const uint64_t widest = (uint64_t)d_in * 2;
-    return d_in % kGemmBK == 0 && rows % 8 == 0 && ((uint64_t)T + 2 * 64) * widest < (1ull << 32) &&
+    return d_in % 8 == 0 && rows % 8 == 0 && ((uint64_t)T + 2 * 64) * widest < (1ull << 32) &&
            ((uint64_t)rows + 5 * 64) * widest < (1ull << 32) && (uint64_t)rows * 4 * 256 < (1ull << 32);
 }
 
@@ -215,7 +215,7 @@ static int dense_split_bounds(int S, int nk) {
 
 int gemm_dense_splits(int T, int d_in, int rows) {
     const bool small = dense_small_tiles(T);
-    const int tiles = ceil_div(T, 128) * ceil_div(rows, small ? 128 : 320), nk = d_in / kGemmBK;
+    const int tiles = ceil_div(T, 128) * ceil_div(rows, small ? 128 : 320), nk = ceil_div(d_in, kGemmBK);
     // 128 x 320 tiles: one workgroup per CU at most, since a few more take a second round (layers of 4096 -> 1024, rank 8, on
     // 282 and 188 workgroups: 12000 x 5120 155.3 and 148.0 us)
     const int S = small ? (384 + tiles / 2) / tiles : 256 / tiles;
@@ -225,7 +225,7 @@ int gemm_dense_splits(int T, int d_in, int rows) {
 int gemm_dense_splits_reserved(int T, int d_in, int rows) {
     if (dense_small_tiles(T)) return gemm_dense_splits(T, d_in, rows);
     const int tiles = ceil_div(T, 128) * ceil_div(rows, 320);
-    return dense_split_bounds((256 + tiles / 2) / tiles, d_in / kGemmBK);
+    return dense_split_bounds((256 + tiles / 2) / tiles, ceil_div(d_in, kGemmBK));
 }
 
 template <int MB, int NB, int D, int EPI>
@@ -242,7 +242,7 @@ hipError_t launch_gemm_dense_splitk(const void* x, const void* Wcat, int T, int 
     a.x = (const bf16_t*)x; a.W = (const bf16_t*)Wcat; a.T = T; a.d_in = d_in; a.d_out = rows;
     a.partial = partial;
     a.splits = gemm_dense_splits(T, d_in, rows);
-    a.tiles_per_split = ceil_div(d_in / kGemmBK, a.splits);
+    a.tiles_per_split = ceil_div(ceil_div(d_in, kGemmBK), a.splits);
     return dense_small_tiles(T) ? launch_dense<4, 4, 2, kEpiPartial>(a, stream) : launch_dense<4, 10, 2, kEpiPartial>(a, stream);
 }
 
@@ -313,7 +313,7 @@ hipError_t launch_gemm_dense_splitk_multi(const void* x, const DenseOperand* ops
     if (S < 1 || n_ops < 1 || n_ops > GemmArgs::kMaxSegments) return hipErrorInvalidValue;
     GemmArgs a{};
     a.x = (const bf16_t*)x; a.T = T; a.d_in = d_in;
-    a.splits = S; a.tiles_per_split = ceil_div(d_in / kGemmBK, S);
+    a.splits = S; a.tiles_per_split = ceil_div(ceil_div(d_in, kGemmBK), S);
     int tile0 = 0;
     int64_t rows = 0;
     for (int i = 0; i < n_ops; ++i) {

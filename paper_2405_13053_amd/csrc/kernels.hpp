@@ -23,7 +23,7 @@ hipError_t bucket_init_scratch();
 // stacked B -> its transpose Bt[d_out, N*r rounded up to 64] (zero-padded) for the GEMM's K-extension.
 // Any pair (W_gate, wsplit) / (A, apack) / (B, btrans) may be NULL to skip it; sizes are gate_wsplit_bytes,
 // shrink_apack_bytes and prep_btrans_bytes (0 = that operand is not packed for this dtype/rank: pass NULL).
-// wcat (optional, needs A, d_in % 64 == 0, r % 8 == 0): Wcat[prep_wcat_rows, d_in] bf16 for the dense routing path,
+// wcat (optional, needs A, r % 8 == 0): Wcat[prep_wcat_rows, d_in] bf16 for the dense routing path,
 // rows = hi | mid | lo terms of the gate columns (padded_adapters(N) rows each), then column q of A_a as row a*r+q.
 // Without W_gate: the rows of A alone.
 size_t prep_btrans_bytes(int d_out, int N, int r, bool bf16);
@@ -54,7 +54,7 @@ hipError_t launch_route_shrink_small(const void* x, const float* partials, int K
                                      int32_t* topk_idx, float* topk_w, void* hdense, int ext_stride,
                                      hipStream_t stream);
 
-// ---- batches of more than 64 tokens (bf16, r % 8 == 0, d_in % 64 == 0, at most 640 rows of Wcat): one MFMA launch
+// ---- batches of more than 64 tokens (bf16, r % 8 == 0, at most 640 rows of Wcat): one MFMA launch
 // computes the split-bf16 gate logits and x * A_i of every adapter as fp32 K-split partials
 // part[splits][T][prep_wcat_rows], then a launch of independent wavefronts adds the splits, ranks (Sec. 3.1, Eq. 3)
 // and writes topk_idx, topk_w and every column of the tokens' rows of hdense.  Replaces launch_gate_logits,
@@ -62,7 +62,7 @@ hipError_t launch_route_shrink_small(const void* x, const float* partials, int K
 // beyond, with up to 320 rows of Wcat always, with more where the products' tiles fill the CUs
 // (route_dense_applies).
 constexpr int kRouteDenseMaxTokens = 8192;
-bool route_dense_possible(int d_in, int N, int r, bool bf16);            // whatever T: is Wcat worth packing
+bool route_dense_possible(int N, int r, bool bf16);   // whatever T: is Wcat worth packing
 bool route_dense_applies(int T, int d_in, int N, int r, bool bf16);
 bool lora_dense_applies(int T, int d_in, int N, int r, int k, bool bf16);   // lora_forward, whose routing is given
 size_t route_dense_part_bytes(int T, int d_in, int N, int r, bool bf16);  // 0 if the path does not apply
@@ -201,7 +201,7 @@ hipError_t launch_route_dense_select_group(const DecodeMember* mem, int G, int S
                                            float inv_temperature, float scale, hipStream_t stream);
 
 // ---- gate gradients (Sec. 3.2, Eq. 4): dW_gate[d_in,N], dbias[N] (optional) and d_logits[T,N] (optional) from
-// x, dy = dL/do, the packed Wcat and B; bf16 shapes of the dense routing path with d_out % 64 == 0.
+// x, dy = dL/do, the packed Wcat and B; bf16 shapes of the dense routing path with d_in and d_out multiples of 64.
 // idx_in / w_in (optional, both or neither): the routing of the forward call; NULL ranks again from the same
 // logits.  labels (optional): per-token adapter label of the classification loss, weight beta; values outside
 // [0, N) give that token no classification part.  ws: gate_backward_layout(...).total bytes.

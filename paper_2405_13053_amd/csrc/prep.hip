@@ -103,7 +103,7 @@ __device__ __forceinline__ void wcat_tile(const float* __restrict__ W_gate, cons
                                           uint16_t* __restrict__ Wcat) {
     constexpr int LD = 66;
     __shared__ uint16_t t[64 * LD];   // t[i][row]
-    const int tiles_i = d_in / 64;
+    const int tiles_i = ceil_div(d_in, 64);
     const int i0 = (tile % tiles_i) * 64, R0 = (tile / tiles_i) * 64;
     // Rows come in groups of 8 that never straddle a region (NP, r and the region starts are multiples of 8): a group
     // of gate rows is 8 consecutive columns j of one term; a group of A rows is columns q0..q0+7 of one adapter,
@@ -114,7 +114,8 @@ __device__ __forceinline__ void wcat_tile(const float* __restrict__ W_gate, cons
         const int Rg = R0 + g * 8, i = i0 + ii;
         union { uint16_t h[8]; uint32_t w[4]; u32x4 v; } p;
         p.v = u32x4{0u, 0u, 0u, 0u};
-        if (Rg < 3 * NP) {
+        if (i >= d_in) {   // behind a ragged width's last column
+        } else if (Rg < 3 * NP) {
             const int term = Rg / NP, j0 = Rg - term * NP;
 #pragma unroll
             for (int jj = 0; jj < 8; ++jj) {
@@ -137,9 +138,9 @@ __device__ __forceinline__ void wcat_tile(const float* __restrict__ W_gate, cons
         union { uint16_t h[16]; u32x4 v[2]; } p;
 #pragma unroll
         for (int jj = 0; jj < 16; ++jj) p.h[jj] = t[(iq + jj) * LD + rr];
-        u32x4* dst = reinterpret_cast<u32x4*>(Wcat + (size_t)(R0 + rr) * d_in + i0 + iq);
-        dst[0] = p.v[0];
-        dst[1] = p.v[1];
+        u32x4* dst = reinterpret_cast<u32x4*>(Wcat + (size_t)(R0 + rr) * d_in + i0 + iq);   // d_in % 8 == 0
+        if (i0 + iq < d_in) dst[0] = p.v[0];
+        if (i0 + iq + 8 < d_in) dst[1] = p.v[1];
     }
 }
 
@@ -177,7 +178,7 @@ size_t prep_btrans_bytes(int d_out, int N, int r, bool bf16) {
 int prep_wcat_rows(int N, int r) { return (int)align_up((size_t)3 * padded_adapters(N) + (size_t)N * r, 8); }
 
 size_t prep_wcat_bytes(int d_in, int N, int r, bool bf16) {
-    return (bf16 && d_in % 64 == 0) ? (size_t)prep_wcat_rows(N, r) * d_in * sizeof(uint16_t) : 0;
+    return bf16 ? (size_t)prep_wcat_rows(N, r) * d_in * sizeof(uint16_t) : 0;
 }
 
 hipError_t launch_prep(const float* W_gate, void* wsplit, const void* A, void* apack, const void* B, void* btrans,
@@ -188,8 +189,8 @@ hipError_t launch_prep(const float* W_gate, void* wsplit, const void* A, void* a
     const int bblocks = (B && btrans) ? (ext_stride / 64) * ceil_div(d_out, 64) : 0;
     const int wblocks = ceil_div(wfrags, 4);
     const int cat_rows = W_gate ? prep_wcat_rows(N, r) : N * r;
-    if (wcat && (!A || d_in % 64 != 0 || r % 8 != 0)) return hipErrorInvalidValue;
-    const int cblocks = wcat ? ceil_div(cat_rows, 64) * (d_in / 64) : 0;
+    if (wcat && (!A || d_in % 8 != 0 || r % 8 != 0)) return hipErrorInvalidValue;
+    const int cblocks = wcat ? ceil_div(cat_rows, 64) * ceil_div(d_in, 64) : 0;
     const int64_t blocks = (int64_t)bblocks + cblocks + wblocks + ceil_div64(afrags, 4);
     if (blocks == 0) return hipSuccess;
     prep_kernel<<<(unsigned)blocks, 256, 0, stream>>>(W_gate, (const bf16_t*)A, d_in, N, r, wblocks, wfrags, afrags,

@@ -156,11 +156,13 @@ hipError_t launch_dense_expand_operand(const float* part, int S, const int32_t* 
     return hipGetLastError();
 }
 
-// Shapes the dense path takes, whatever the batch size (decides whether Wcat is part of the packed weights).
-bool route_dense_possible(int d_in, int N, int r, bool bf16) {
+// Shapes the dense path takes, whatever the batch size (decides whether Wcat is part of the packed weights).  Widths off 64
+// gain as much as the others: 200 x 4104 -> 4096 bucketed 55.8 us, dense 24.9, 512 61.5 and 39.5, 2000 96.3 and 87.4, 8192 277
+// and 261.
+bool route_dense_possible(int N, int r, bool bf16) {
     // up to 640 rows of Wcat (28 adapters of rank 16: 544): measured against the bucketed sequence on 4096 -> 4096,
     // rank 16, the dense forms are faster or equal from T = 8 to 8192 (T = 128: 35 against 55 us)
-    return bf16 && r % 8 == 0 && d_in % 64 == 0 && padded_adapters(N) == kSelNP && prep_wcat_rows(N, r) <= kWcatMaxRows;
+    return bf16 && r % 8 == 0 && padded_adapters(N) == kSelNP && prep_wcat_rows(N, r) <= kWcatMaxRows;
 }
 
 // Measured against the bucketed sequence (gate logits, top-k, scatter, whole-K shrink) on 4096 -> 4096 and
@@ -171,7 +173,7 @@ bool route_dense_possible(int d_in, int N, int r, bool bf16) {
 // of a full K sweep each, 1269 against 1231 us).
 bool route_dense_applies(int T, int d_in, int N, int r, bool bf16) {
     const int CR = prep_wcat_rows(N, r);
-    if (!route_dense_possible(d_in, N, r, bf16) || T <= 64 || !gemm_dense_splitk_ok(T, d_in, CR)) return false;
+    if (!route_dense_possible(N, r, bf16) || T <= 64 || !gemm_dense_splitk_ok(T, d_in, CR)) return false;
     if (T <= kRouteDenseMaxTokens || CR <= 320) return true;
     const int64_t wgs = (int64_t)ceil_div(T, 128) * ceil_div(CR, 320) * gemm_dense_splits(T, d_in, CR);
     return wgs * 10 >= (wgs + 255) / 256 * 256 * 9;   // at least 90% of the CUs' slots over the launch

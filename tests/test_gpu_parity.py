@@ -526,6 +526,33 @@ def test_dense_route_path_matches_oracle_and_bucketed_path(shape):
     assert util.rel_max_err(full, out.to(torch.float64).cpu().numpy()) <= 2 * util.tol(shape)
 
 
+# Widths that are no multiple of 64 (nor of 128, the decode launch's K step) on every launch sequence: inputs of one chunk, layers
+# with fewer K tiles than splits, a partial tile in a split of its own, outputs beyond 256 row tiles.
+@pytest.mark.parametrize("T,d_in,d_out,N,r,k", [
+    (1, 8, 8, 28, 8, 2), (64, 24, 136, 28, 16, 1), (49, 320, 2920, 28, 16, 1), (17, 824, 1848, 7, 32, 3), (5, 72, 33000, 28, 8, 2),
+    (65, 8, 136, 28, 8, 2), (300, 1000, 264, 28, 8, 2), (130, 1032, 136, 28, 16, 2), (200, 4616, 520, 28, 8, 8), (97, 776, 16392, 28, 8, 2),
+    (1100, 1048, 4104, 12, 16, 3), (2500, 136, 2056, 28, 8, 2), (4500, 264, 136, 28, 16, 3), (9000, 72, 264, 28, 8, 1)])
+def test_layer_of_any_width(T, d_in, d_out, N, r, k):
+    _check_layer(LS(T, d_in, d_out, N, r, k, 2.0, "bf16", "zipf", "any-width"), seed=64, rows="all" if T <= 300 else "sample")
+
+
+def test_a_blob_packed_without_the_routing_rows_is_still_taken():
+    """Blobs of widths that are no multiple of 64 once ended in front of Wcat: the call packs its operands itself, the same bits."""
+    for T in (30, 300):
+        shape = LS(T, 520, 264, 28, 8, 2, 2.0, "bf16")
+        _, dev = util.make_case(shape, seed=65)
+        whole = m.pack_weights(dev["W_gate"], dev["A"], dev["B"])
+        short = whole[:-(96 + 28 * 8) * 520 * 2].clone()
+        args = (dev["x"], dev["W"], dev["W_gate"], None, dev["A"], dev["B"], 2, 2.0)
+        assert torch.equal(m.linear_forward(*args, packed=short), m.linear_forward(*args, packed=whole))
+        members = [{"W": dev["W"], "W_gate": dev["W_gate"], "gate_bias": None, "A": dev["A"], "B": dev["B"], "packed": p}
+                   for p in (whole, short)]
+        one, two = m.linear_forward_group(dev["x"], members, 2, 2.0)
+        assert torch.equal(one, two)
+        with pytest.raises(m.MeteoraError):
+            m.linear_forward(*args, packed=short[:-256].clone())
+
+
 def test_dense_route_exact_ties_and_zero_gate():
     """Duplicated gate columns tie exactly: the lower index wins on this path too; a zero gate picks 0..k-1."""
     shape = LS(300, 512, 264, 12, 8, 3, 2.0, "bf16")
