@@ -323,14 +323,13 @@ __device__ __forceinline__ void dma_piece(bf16_t* lds_tile, const DmaOperand& o,
 
 // The K tiles behind the whole ones: first, where d_in is no multiple of 64, the rest of the main operands' columns (kt < 0),
 // whose chunks past d_in load zeros, then those of the extension.  Both are requested by the same instructions, from
-// the one resource or the other, so that no branch stands between loads and reads of LDS; the whole offset of a piece is
-// in the per-lane operand, which the bounds check covers.  Base projections with tiles through registers for every such
+// the one resource or the other, so that no branch stands between loads and reads of LDS.  Base projections with tiles through registers for every such
 // d_in, as it was, and so: 512 x 4104 -> 4096 68.5 and 38.1 us, 2000 97.8 and 69.1, 4096 173 and 97.7, 8192 x 4088 -> 4096 336
 // and 195; with 4096 inputs 27.8, 55.0, 91.9 (rows of 8208 bytes straddle the lines of L2, which the lower tiles wait on).
 struct PartTile {
     int columns;      // d_in % 64
     uint32_t offset;  // bytes from a row's start to the tile
-    bool mine;        // this lane's chunk holds columns below d_in
+    bool mine;        // this lane's chunk holds columns below d_in; if not it asks for what lies behind the matrix's last byte
 };
 
 __device__ __forceinline__ PartTile part_tile(int d_in, int wave, int lane) {
@@ -341,14 +340,15 @@ __device__ __forceinline__ PartTile part_tile(int d_in, int wave, int lane) {
     return t;
 }
 
-__device__ __forceinline__ void dma_piece_behind(bf16_t* lds_tile, const DmaOperand& main, const DmaOperand& ext,
+// main_bytes: those of the main operand's matrix (with a piece's offset still below 2^32, see dma_ok)
+__device__ __forceinline__ void dma_piece_behind(bf16_t* lds_tile, const DmaOperand& main, uint32_t main_bytes, const DmaOperand& ext,
                                                  const PartTile& t, int kt, int j, int wave) {
-    constexpr uint32_t kOutside = 0xfffffff0u;   // past every matrix: their rows end more than a tile below 2^32
-    const uint32_t in_part = t.mine ? main.voff + main.piece_step * (uint32_t)j + t.offset : kOutside;
-    const uint32_t in_ext = ext.voff + ext.piece_step * (uint32_t)j + (uint32_t)kt * (kGemmBK * 2);
+    const uint32_t voff = kt < 0 ? (t.mine ? main.voff : main_bytes) : ext.voff;
+    const uint32_t soff = kt < 0 ? main.piece_step * (uint32_t)j + t.offset
+                                 : ext.piece_step * (uint32_t)j + (uint32_t)kt * (kGemmBK * 2);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(
-        kt < 0 ? main.rsrc : ext.rsrc, (__attribute__((address_space(3))) void*)(lds_tile + (j * 4 + wave) * 8 * kGemmBK), 16,
-        kt < 0 ? in_part : in_ext, 0, 0, 0);
+        kt < 0 ? main.rsrc : ext.rsrc, (__attribute__((address_space(3))) void*)(lds_tile + (j * 4 + wave) * 8 * kGemmBK), 16, voff,
+        (int)soff, 0, 0);
 }
 
 // Map a workgroup id to an output tile: ids are dealt round-robin to the 8 XCDs, so each XCD
@@ -520,14 +520,15 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(const GemmArgs a) {
     const DmaOperand oh = dma_operand(a.hd, nk_ext > 0 ? a.T : 0, a.ext_stride, m0, wave, lane);
     const DmaOperand ob = dma_operand(a.Bt, nk_ext > 0 ? a.d_out : 0, a.ext_stride, n0, wave, lane);
     const PartTile part = part_tile(a.d_in, wave, lane);
+    const uint32_t x_bytes = (uint32_t)a.T * (uint32_t)a.d_in * 2u, w_bytes = (uint32_t)a.d_out * (uint32_t)a.d_in * 2u;
 
     // piece i of local tile `it` (x-like pieces first) into LDS slot `slot`
     auto request_piece = [&](int it, int slot, int i, auto is_ext) {
         bf16_t* xs = smem + slot * kBufElems;
         if constexpr (decltype(is_ext)::value) {
             const int kt = it - nk_main - nk_part;
-            if (i < PX) dma_piece_behind(xs, ox, oh, part, kt, i, wave);
-            else dma_piece_behind(xs + BM * kGemmBK, ow, ob, part, kt, i - PX, wave);
+            if (i < PX) dma_piece_behind(xs, ox, x_bytes, oh, part, kt, i, wave);
+            else dma_piece_behind(xs + BM * kGemmBK, ow, w_bytes, ob, part, kt, i - PX, wave);
         } else {
             if (i < PX) dma_piece(xs, ox, kt0 + it, i, wave);
             else dma_piece(xs + BM * kGemmBK, ow, kt0 + it, i - PX, wave);
@@ -904,16 +905,17 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
     const DmaOperand oh = dma_operand(a.hd, nk_ext > 0 ? a.T : 0, a.ext_stride, m0, wave, lane);
     const DmaOperand ob = dma_operand(a.Bt, nk_ext > 0 ? a.d_out : 0, a.ext_stride, n0, wave, lane);
     const PartTile part = part_tile(a.d_in, wave, lane);
+    const uint32_t x_bytes = (uint32_t)a.T * (uint32_t)a.d_in * 2u, w_bytes = (uint32_t)a.d_out * (uint32_t)a.d_in * 2u;
 
     auto xslot = [&](int it) { return smem + (it % D) * kXElems; };
     auto wslot = [&](int it) { return smem + D * kXElems + (it % (D + 1)) * kWElems; };
     // piece i of the x-like / W-like operand of whole K tile kt, or of tile kt of those behind the whole ones
     auto request_x = [&](bf16_t* slot, int kt, int i, auto is_ext) {
-        if constexpr (decltype(is_ext)::value) dma_piece_behind(slot, ox, oh, part, kt, i, wave);
+        if constexpr (decltype(is_ext)::value) dma_piece_behind(slot, ox, x_bytes, oh, part, kt, i, wave);
         else dma_piece(slot, ox, kt, i, wave);
     };
     auto request_w = [&](bf16_t* slot, int kt, int i, auto is_ext) {
-        if constexpr (decltype(is_ext)::value) dma_piece_behind(slot, ow, ob, part, kt, i, wave);
+        if constexpr (decltype(is_ext)::value) dma_piece_behind(slot, ow, w_bytes, ob, part, kt, i, wave);
         else dma_piece(slot, ow, kt, i, wave);
     };
     auto request_tile = [&](int it, int kt, auto is_ext) {
