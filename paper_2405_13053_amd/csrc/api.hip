@@ -22,26 +22,56 @@ bool shape_ok(int T, int d_in, int d_out, int N, int r, int k) {
     return T >= 0 && d_in >= 1 && d_out >= 1 && N >= 1 && r >= 1 && k >= 1 && k <= N;
 }
 
+// The decode tail reads k * r rows of B for every token, from L2 at about 18 TB/s; beyond some 0.5 to 1.3 GB (the more, the
+// more inputs the other sequences gather for their shrink) the dense operand of every adapter and MFMAs are cheaper.  Top-8 of
+// 64 adapters, tail against bucketed, us: 4096 -> 14336 of rank 32 64 tokens (0.47 GB) 81.6 and 132, of rank 64 40 tokens (0.59) 107
+// and 98, 64 (0.94) 139 and 102; 4096 -> 4096 of rank 64 128 tokens (0.54) 55.8 and 75.6, 256 (1.1) 79.2 and 77.6, of rank 32
+// 300 tokens (0.63) 61.6 and 70.5, 512 (1.1) 83.0 and 68.7; 14336 -> 4096 of rank 32 512 tokens (1.1) 163 and 211.
+bool expand_by_rows_applies(int T, int d_in, int d_out, int r, int k) {
+    return 2.0 * T * k * r * d_out <= (T <= 64 ? 2.6e8 : 4e8) + 6e4 * d_in;
+}
+
 // Decode in two launches (gate logits and every adapter's shrink inside the GEMM's launch, then routing + reduce +
-// expand): whatever the widths.  Four launches (gate logits, top-k with the shrink, split GEMM, reduction), as widths off 64,
-// fewer than 512 inputs and more than 32704 outputs had, and so: 1 token of 4104 -> 4096 24.0 and 15.1 us, 64 27.8 and 20.1,
-// 49 x 320 -> 2920 of rank 16 packed per call 21.6 and 16.9, 1 x 4096 -> 40960 89.5 and 60.5, 64 95.5 and 81.4.
-bool decode_fused_applies(int T, int N, int r, bool bf16) { return route_small_applies(T, r, bf16) && route_dense_possible(N, r, bf16); }
+// expand): whatever the widths and adapters.  Four launches (gate logits, top-k with the shrink, split GEMM, reduction), as
+// widths off 64, fewer than 512 inputs and more than 32704 outputs had, and so: 1 token of 4104 -> 4096 24.0 and 15.1 us, 64 27.8
+// and 20.1, 49 x 320 -> 2920 of rank 16 packed per call 21.6 and 16.9, 1 x 4096 -> 40960 89.5 and 60.5, 64 95.5 and 81.4.
+// 64 adapters of rank 32, top-4 and top-8, 4096 -> 4096, 1 token 61.3 and 89.1 against 23.2 and 33.7, 64 tokens 66.5 and 95.4
+// against 29.8 and 39.6, though 2240 more rows are streamed; 28 adapters of rank 12, 40.2 and 45.0 against 15.3 and 19.2.
+bool decode_fused_applies(int T, int d_in, int d_out, int r, int k, bool bf16) {
+    return bf16 && T <= 64 && expand_by_rows_applies(T, d_in, d_out, r, k);
+}
 
 // Mid-sized batches whose 128 x 128 output tiles would leave most CUs idle (a few hundred tokens): the base
 // projection is split along K over workgroups like the routing products (fp32 tiles), and the reduction adds the
 // LoRA expand, as for decode.  Returns the number of K splits, 0 = the fused GEMM runs instead.
 // `reserve`: as many as a workspace has room for.
-int dense_midsplit_splits(int T, int d_in, int d_out, int N, int r, bool bf16, bool reserve = false) {
+int dense_midsplit_splits(int T, int d_in, int d_out, int N, int r, int k, bool bf16, bool reserve = false) {
     // measured on 4096 -> 4096, 4096 -> 14336 and 14336 -> 4096, T = 65 ... 2048: the split form wins as long as the
     // projection can still be cut into at least two K splits (see gemm_multi_splits for how many) (19.0 against 56.1 us
     // at T = 65, 36.1 against 60.1 at T = 512, 45.6 against 48.7 at T = 704, 47.6 against 48.8 at T = 768 for
     // 4096 -> 4096; 43.3 against 47.6 at T = 160 for 4096 -> 14336; 107 against 131 at T = 704 for 14336 -> 4096)
-    if (!route_dense_applies(T, d_in, N, r, bf16) || d_out % 8 != 0 || !gemm_dense_splitk_ok(T, d_in, d_out)) return 0;
-    const int col_tiles = ceil_div(d_out, 128) + ceil_div(prep_wcat_rows(N, r), 128), fit = gemm_dense_splits(T, d_in, d_out);
+    // Above 640 rows of Wcat the bucketed sequence is the other choice: 64 adapters of rank 32, top-4, 4096 -> 4096 T = 65 29.2
+    // against 60.5, 200 36.6 against 61.7, 512 58.2 against 63.6; 14336 -> 4096 top-8 T = 300 123 against 170; but not with two
+    // workgroups per CU (4096 -> 14336 T = 65 91.0 against 84.9, 128 143 against 95.7).
+    const int CR = prep_wcat_rows(N, r);
+    if (!bf16 || T <= 64 || !gemm_dense_splitk_ok(T, d_in, CR) || !gemm_dense_splitk_ok(T, d_in, d_out)) return 0;
+    const int col_tiles = ceil_div(d_out, 128) + ceil_div(CR, 128), fit = gemm_dense_splits(T, d_in, d_out);
+    if (CR > kWcatMaxRows && (2 * ceil_div(T, 256) * col_tiles > 256 || !expand_by_rows_applies(T, d_in, d_out, r, k))) return 0;
     const int S = reserve ? gemm_multi_splits_reserved(T, col_tiles, fit)
-                          : gemm_multi_splits(T, col_tiles, fit, ceil_div(d_in, 64), (int64_t)d_out + prep_wcat_rows(N, r));
+                          : gemm_multi_splits(T, col_tiles, fit, ceil_div(d_in, 64), (int64_t)d_out + CR);
     return S >= 2 ? S : 0;
+}
+
+// The most (token, K split) pairs that a batch of up to T tokens has in that form: a workspace holds the smaller batches too.  The
+// splits that fit change at multiples of 128 tokens, and at two row tiles' worth per column tile there are none left.
+int64_t midsplit_pairs_reserved(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
+    int64_t most = 0;
+    const int last = 256 * 128 / (ceil_div(d_out, 128) + ceil_div(prep_wcat_rows(N, r), 128));
+    for (int t = T < last ? T : last; t > 64; t = (t - 1) / 128 * 128) {
+        const int64_t pairs = (int64_t)dense_midsplit_splits(t, d_in, d_out, N, r, k, bf16, true) * t;
+        most = pairs > most ? pairs : most;
+    }
+    return most;
 }
 
 bool shape_supported(int T, int d_in, int d_out, int N, int r, int k) {
@@ -68,34 +98,35 @@ WsLayout ws_layout(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
     L.topk_w = take(pairs * sizeof(float));
     L.h32 = take(pairs * r * sizeof(float));
     L.hdense = take((size_t)T * L.ext_stride * sizeof(uint16_t));
-    L.apack = take(shrink_apack_bytes(d_in, N, r, bf16));
+    // A packed for the bucketed sequence, or Wcat: a call reads the one or the other
+    const size_t apack = shrink_apack_bytes(d_in, N, r, bf16), wcat = prep_wcat_bytes(d_in, N, r, bf16);
+    L.apack = L.wcat = take(apack > wcat ? apack : wcat);
     L.hpart = take(shrink_hpart_bytes(T, d_in, r, k, bf16));
-    const bool decode3 = decode_fused_applies(T, N, r, bf16);
-    const int S_decode = decode3 ? gemm_decode_plan(d_in, &d_out, 1, prep_wcat_rows(N, r)).S : 0;
-    size_t splitk = gemm_splitk_bytes(T, d_in, d_out, bf16);   // lora_forward at such a size splits in its own way
-    if ((size_t)S_decode * T * d_out * sizeof(float) > splitk) splitk = (size_t)S_decode * T * d_out * sizeof(float);
-    L.splitk = take(splitk);
+    // Decode-sized calls take splitk and gpart, larger ones spart and dpart; the latter have room for every smaller batch
+    const int CR = prep_wcat_rows(N, r), Td = T < 64 ? T : 64;
+    const size_t pairs_decode = bf16 ? (size_t)gemm_decode_plan(d_in, &d_out, 1, CR).S * Td : 0;
+    size_t tiles = pairs_decode * d_out * sizeof(float), products = pairs_decode * CR * sizeof(float);
+    auto most = [](size_t a, size_t b) { return a > b ? a : b; };
+    tiles = most(tiles, gemm_splitk_bytes(Td, d_in, d_out, bf16));   // lora_forward at such a size splits in its own way
+    if (T > 64) {
+        const size_t mid = (size_t)midsplit_pairs_reserved(T, d_in, d_out, N, r, k, bf16);
+        tiles = most(tiles, mid * d_out * sizeof(float));
+        // the routing products come in the K splits of the launch that writes them: the products launch's own count, or
+        // that of the split base projection when both share one launch (which may be the larger of the two)
+        products = most(products, most(mid * CR * sizeof(float), route_dense_part_bytes(T, d_in, N, r, bf16)));
+    }
+    L.splitk = take(T <= 64 ? tiles : 0);
     L.btrans = take(prep_btrans_bytes(d_out, N, r, bf16));
-    const bool dense = route_dense_applies(T, d_in, N, r, bf16);
-    L.wcat = take(dense || decode3 ? prep_wcat_bytes(d_in, N, r, bf16) : 0);
-    // the routing products come in the K splits of the launch that writes them: the products launch's own count, or
-    // that of the split base projection when both share one launch (which may be the larger of the two)
-    const int S_mid = dense_midsplit_splits(T, d_in, d_out, N, r, bf16, true);
-    size_t dpart = S_mid > 0 ? (size_t)S_mid * T * prep_wcat_rows(N, r) * sizeof(float)
-                             : route_dense_part_bytes(T, d_in, N, r, bf16);
-    // lora_forward at such a size: the adapters' rows alone, in the splits their own launch takes
-    const size_t lora = lora_dense_applies(T, d_in, N, r, k, bf16)
-                            ? (size_t)gemm_dense_splits_reserved(T, d_in, N * r) * T * N * r * sizeof(float) : 0;
-    L.dpart = take(lora > dpart ? lora : dpart);
-    L.gpart = take((size_t)S_decode * T * prep_wcat_rows(N, r) * sizeof(float));
-    L.spart = take((size_t)S_mid * T * d_out * sizeof(float));
+    L.dpart = take(T > 64 ? products : 0);
+    L.gpart = take(T <= 64 ? products : 0);
+    L.spart = take(T > 64 ? tiles : 0);
     L.total = off;
     return L;
 }
 
 // Packed weights (meteora_pack_weights): the three operand layouts, each 256-byte aligned.
-// `least`: what a blob may hold at the least.  Widths that are no multiple of 64 were packed without Wcat once: such a blob, kept
-// in a file, is still taken, and the call packs its operands itself.
+// `least`: what a blob may hold at the least.  Wcat once belonged only to widths that are multiples of 64, ranks that are multiples
+// of 8, up to 32 adapters and 640 rows: a blob without it, kept in a file, is still taken, and the call packs its operands itself.
 struct PackLayout { size_t wsplit, apack, btrans, wcat, total, least; };
 
 PackLayout pack_layout(int d_in, int d_out, int N, int r, bool bf16) {
@@ -105,9 +136,9 @@ PackLayout pack_layout(int d_in, int d_out, int N, int r, bool bf16) {
     P.wsplit = take(gate_wsplit_bytes(d_in, N, bf16));
     P.apack = take(shrink_apack_bytes(d_in, N, r, bf16));
     P.btrans = take(prep_btrans_bytes(d_out, N, r, bf16));
-    P.wcat = take(route_dense_possible(N, r, bf16) ? prep_wcat_bytes(d_in, N, r, bf16) : 0);
+    P.wcat = take(prep_wcat_bytes(d_in, N, r, bf16));
     P.total = off;
-    P.least = d_in % 64 != 0 ? P.wcat : P.total;
+    P.least = d_in % 64 == 0 && r % 8 == 0 && N <= 32 && prep_wcat_rows(N, r) <= kWcatMaxRows ? P.total : P.wcat;
     return P;
 }
 
@@ -243,11 +274,11 @@ int meteora_workspace_regions(int T, int d_in, int d_out, int N, int r, int k, m
     const bool bf16 = dt == METEORA_BF16;
     const WsLayout L = ws_layout(T, d_in, d_out, N, r, k, bf16);
     struct Region { const char* name; size_t off, written; };
-    Region R[19] = {{"wsplit", L.wsplit, 0}, {"partials", L.partials, 0}, {"chunk_counts", L.chunk_counts, 0},
+    Region R[18] = {{"wsplit", L.wsplit, 0}, {"partials", L.partials, 0}, {"chunk_counts", L.chunk_counts, 0},
                     {"counts", L.counts, 0}, {"offsets", L.offsets, 0}, {"bucket_tok", L.bucket_tok, 0},
                     {"bucket_slot", L.bucket_slot, 0}, {"topk_idx", L.topk_idx, 0}, {"topk_w", L.topk_w, 0},
                     {"h32", L.h32, 0}, {"hdense", L.hdense, 0}, {"apack", L.apack, 0}, {"hpart", L.hpart, 0},
-                    {"splitk", L.splitk, 0}, {"btrans", L.btrans, 0}, {"wcat", L.wcat, 0}, {"dpart", L.dpart, 0},
+                    {"splitk", L.splitk, 0}, {"btrans", L.btrans, 0}, {"dpart", L.dpart, 0},
                     {"gpart", L.gpart, 0}, {"spart", L.spart, 0}};
     auto wr = [&](const char* name, size_t bytes) {
         for (Region& g : R)
@@ -256,25 +287,24 @@ int meteora_workspace_regions(int T, int d_in, int d_out, int N, int r, int k, m
     const int NP = padded_adapters(N);
     const size_t pairs = (size_t)T * k;
     const int CR = prep_wcat_rows(N, r);
-    const bool dense = route_dense_applies(T, d_in, N, r, bf16);
-    const bool decode3 = decode_fused_applies(T, N, r, bf16);
+    const int S_mid = dense_midsplit_splits(T, d_in, d_out, N, r, k, bf16);
+    const bool dense = S_mid > 0 || route_dense_applies(T, d_in, N, r, bf16);
+    const bool decode3 = decode_fused_applies(T, d_in, d_out, r, k, bf16);
     wr("topk_idx", pairs * sizeof(int32_t));
     wr("topk_w", pairs * sizeof(float));
     if (!with_packed) {
         if (!dense && !decode3) { wr("wsplit", gate_wsplit_bytes(d_in, N, bf16)); wr("apack", shrink_apack_bytes(d_in, N, r, bf16)); }
-        if (!decode3 && !(dense && dense_midsplit_splits(T, d_in, d_out, N, r, bf16) > 0))
-            wr("btrans", prep_btrans_bytes(d_out, N, r, bf16));
-        if (dense || decode3) wr("wcat", prep_wcat_bytes(d_in, N, r, bf16));
+        if (!decode3 && S_mid == 0) wr("btrans", prep_btrans_bytes(d_out, N, r, bf16));
+        if (dense || decode3) wr("apack", prep_wcat_bytes(d_in, N, r, bf16));   // Wcat in its place
     }
     if (decode3) {
         const int S = gemm_decode_plan(d_in, &d_out, 1, CR).S;
         wr("splitk", (size_t)S * T * d_out * sizeof(float));
         wr("gpart", (size_t)S * T * CR * sizeof(float));
     } else if (dense) {
-        if (const int S = dense_midsplit_splits(T, d_in, d_out, N, r, bf16)) {
-            wr("spart", (size_t)S * T * d_out * sizeof(float));
-            wr("dpart", (size_t)S * T * CR * sizeof(float));
-            if (!decode_tail_applies(r)) wr("h32", pairs * r * sizeof(float));
+        if (S_mid > 0) {
+            wr("spart", (size_t)S_mid * T * d_out * sizeof(float));
+            wr("dpart", (size_t)S_mid * T * CR * sizeof(float));
         } else {
             wr("dpart", (size_t)gemm_dense_splits(T, d_in, CR) * T * CR * sizeof(float));
             wr("hdense", (size_t)T * L.ext_stride * sizeof(uint16_t));
@@ -285,20 +315,15 @@ int meteora_workspace_regions(int T, int d_in, int d_out, int N, int r, int k, m
         wr("partials", (size_t)gate_kslices(d_in, bf16) * T * NP * sizeof(float));
         const bool fused = gemm_fuses_expand(bf16);
         if (fused) wr("hdense", (size_t)T * L.ext_stride * sizeof(uint16_t));
-        if (route_small_applies(T, r, bf16)) {
-            const int S = gemm_splitk_splits(T, d_in, d_out, bf16);
-            if (S > 0) wr("splitk", (size_t)(S + 1) * T * d_out * sizeof(float));
-        } else {
-            wr("chunk_counts", (size_t)routing_chunks(T) * N * sizeof(int32_t));
-            wr("counts", (size_t)N * sizeof(int32_t));
-            wr("offsets", (size_t)(N + 1) * sizeof(int32_t));
-            wr("bucket_tok", pairs * sizeof(int32_t));
-            wr("bucket_slot", pairs * sizeof(int32_t));
-            wr("hpart", shrink_hpart_bytes(T, d_in, r, k, bf16));
-            if (!fused) wr("h32", pairs * r * sizeof(float));
-            const int S = gemm_splitk_splits(T, d_in, d_out, bf16);
-            if (fused && S > 0) wr("splitk", (size_t)(S + 1) * T * d_out * sizeof(float));
-        }
+        wr("chunk_counts", (size_t)routing_chunks(T) * N * sizeof(int32_t));
+        wr("counts", (size_t)N * sizeof(int32_t));
+        wr("offsets", (size_t)(N + 1) * sizeof(int32_t));
+        wr("bucket_tok", pairs * sizeof(int32_t));
+        wr("bucket_slot", pairs * sizeof(int32_t));
+        wr("hpart", shrink_hpart_bytes(T, d_in, r, k, bf16));
+        if (!fused) wr("h32", pairs * r * sizeof(float));
+        const int S = gemm_splitk_splits(T, d_in, d_out, bf16);
+        if (fused && S > 0) wr("splitk", (size_t)(S + 1) * T * d_out * sizeof(float));
     }
     const int n = (int)(sizeof(R) / sizeof(R[0]));
     for (int i = 0; i < n && i < max_regions; ++i) {
@@ -500,7 +525,7 @@ meteora_status meteora_pack_weights(const float* W_gate, const void* A, const vo
     if (P.total == 0) return METEORA_OK;   // this dtype reads the tensors as they are
     if (!packed || !aligned256(packed) || packed_bytes < P.total) return METEORA_ERR_WORKSPACE;
     const bool pw = gate_wsplit_bytes(d_in, N, bf16) > 0, pa = shrink_apack_bytes(d_in, N, r, bf16) > 0;
-    const bool pb = prep_btrans_bytes(d_out, N, r, bf16) > 0, pc = route_dense_possible(N, r, bf16);
+    const bool pb = prep_btrans_bytes(d_out, N, r, bf16) > 0, pc = prep_wcat_bytes(d_in, N, r, bf16) > 0;
     METEORA_HIP(launch_prep(W_gate, pw ? at<void>(packed, P.wsplit) : nullptr, A,
                             pa ? at<void>(packed, P.apack) : nullptr, pb ? B : nullptr,
                             pb ? at<void>(packed, P.btrans) : nullptr, pc ? at<void>(packed, P.wcat) : nullptr, d_in,
@@ -533,8 +558,9 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
     float* partials = at<float>(ws, L.partials);
     const int tslot = timing_begin_call(st);
     // mid-sized batch: gate logits and the shrink of every adapter in one MFMA launch, selection afterwards
-    const bool dense = route_dense_applies(T, d_in, N, r, bf16);
-    const bool decode3 = decode_fused_applies(T, N, r, bf16);
+    const int S_mid = dense_midsplit_splits(T, d_in, d_out, N, r, k, bf16);
+    const bool dense = S_mid > 0 || route_dense_applies(T, d_in, N, r, bf16);
+    const bool decode3 = decode_fused_applies(T, d_in, d_out, r, k, bf16);
     PackedPtrs pk{at<void>(ws, L.wsplit), at<void>(ws, L.apack), at<void>(ws, L.btrans), at<void>(ws, L.wcat)};
     if (use_packed) {
         void* blob = const_cast<void*>(packed);   // read only from here on
@@ -545,16 +571,15 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
         StageScope sc(ST_PREP, st, tslot);
         const bool pw = !dense && !decode3 && gate_wsplit_bytes(d_in, N, bf16) > 0;
         const bool pa = !dense && !decode3 && shrink_apack_bytes(d_in, N, r, bf16) > 0;
-        const bool mid = dense && dense_midsplit_splits(T, d_in, d_out, N, r, bf16) > 0;   // reads B as it is, like decode
-        const bool pb = !decode3 && !mid && prep_btrans_bytes(d_out, N, r, bf16) > 0;
+        const bool pb = !decode3 && S_mid == 0 && prep_btrans_bytes(d_out, N, r, bf16) > 0;
         METEORA_HIP(launch_prep(W_gate, pw ? pk.wsplit : nullptr, A, pa ? pk.apack : nullptr, pb ? B : nullptr,
                                 pb ? pk.btrans : nullptr, dense || decode3 ? pk.wcat : nullptr, d_in, d_out, N, r, st));
+        // pb: a few hundred tokens and decode read B as it is
     }
     if (decode3) {
         // decode-sized batch: the launch that streams W also computes the gate logits; then top-k, softmax and the
         // shrink of the selected adapters token by token; then the split-K reduction, which adds the expand
-        const DecodeMember mem{W, pk.wcat, gate_bias, A, B, d_out, at<float>(ws, L.splitk), at<float>(ws, L.gpart),
-                               at<float>(ws, L.h32), idx, w, out};
+        const DecodeMember mem{W, pk.wcat, gate_bias, B, d_out, at<float>(ws, L.splitk), at<float>(ws, L.gpart), idx, w, out};
         const int gate_rows = prep_wcat_rows(N, r);   // the gate terms and every adapter's shrink columns
         const SplitPlan plan = gemm_decode_plan(d_in, &d_out, 1, gate_rows);
         {
@@ -568,29 +593,18 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
     }
     if (dense) {
         float* dpart = at<float>(ws, L.dpart);
-        if (const int S = dense_midsplit_splits(T, d_in, d_out, N, r, bf16)) {
-            // few output tiles: x * W^T and x * Wcat^T as fp32 K-split tiles of one launch, selection, then the
-            // reduction with the expand (the decode sequence with 128 x 128 tiles and the dense selection)
-            float* hs = at<float>(ws, L.h32);
-            DecodeMember mem{W, nullptr, gate_bias, A, B, d_out, at<float>(ws, L.spart), dpart, hs, idx, w, out};
+        if (S_mid > 0) {
+            // few output tiles: x * W^T and x * Wcat^T as fp32 K-split tiles of one launch, then selection, reduction and expand
+            // in another, as for decode
+            const DecodeMember mem{W, nullptr, gate_bias, B, d_out, at<float>(ws, L.spart), dpart, idx, w, out};
             {
                 StageScope sc(ST_GEMM, st, tslot);
                 const DenseOperand two[2] = {{W, d_out, mem.partial}, {pk.wcat, prep_wcat_rows(N, r), dpart}};
-                METEORA_HIP(launch_gemm_dense_splitk_multi(x, two, 2, S, T, d_in, st));
+                METEORA_HIP(launch_gemm_dense_splitk_multi(x, two, 2, S_mid, T, d_in, st));
             }
-            if (decode_tail_applies(r)) {   // selection, reduction and expand in one launch, as for decode
-                StageScope sc(ST_SHRINK, st, tslot);
-                METEORA_HIP(launch_decode_tail_group(&mem, 1, SplitPlan{S, 0, 0}, T, N, r, k, prep_wcat_rows(N, r), inv_temperature,
-                                                     scale, st));
-                return METEORA_OK;
-            }
-            {
-                StageScope sc(ST_GATE_TOPK, st, tslot);
-                METEORA_HIP(launch_route_dense_select(dpart, gate_bias, T, d_in, N, r, k, inv_temperature, scale, idx, w, nullptr,
-                                                      L.ext_stride, st, hs, S));
-            }
-            StageScope sc(ST_EXPAND, st, tslot);
-            METEORA_HIP(launch_gemm_decode_finish(&mem, 1, S, T, k, r, st));
+            StageScope sc(ST_SHRINK, st, tslot);
+            METEORA_HIP(launch_decode_tail_group(&mem, 1, SplitPlan{S_mid, 0, 0}, T, N, r, k, prep_wcat_rows(N, r), inv_temperature,
+                                                 scale, st));
             return METEORA_OK;
         }
         {
@@ -628,19 +642,6 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
         StageScope sc(ST_GATE_LOGITS, st, tslot);
         METEORA_HIP(launch_gate_logits(x, W_gate, T, d_in, N, bf16, pk.wsplit, partials, st));
     }
-    if (route_small_applies(T, r, bf16)) {
-        // decode-sized batch: top-k, softmax and the shrink of the selected adapters in one launch, then the GEMM
-        {
-            StageScope sc(ST_SHRINK, st, tslot);
-            METEORA_HIP(launch_route_shrink_small(x, partials, gate_kslices(d_in, bf16), gate_bias, A, T, d_in, N, r,
-                                                  k, inv_temperature, scale, idx, w, at<void>(ws, L.hdense), L.ext_stride, st));
-        }
-        StageScope sc(ST_GEMM, st, tslot);
-        METEORA_HIP(launch_gemm(x, W, T, d_in, d_out, bf16, at<void>(ws, L.hdense), L.ext_stride, pk.btrans, N * r,
-                                out, 0, gemm_splitk_bytes(T, d_in, d_out, bf16) > 0 ? at<float>(ws, L.splitk) : nullptr,
-                                st));
-        return METEORA_OK;
-    }
     {
         StageScope sc(ST_GATE_TOPK, st, tslot);
         METEORA_HIP(launch_gate_topk(partials, gate_kslices(d_in, bf16), gate_bias, T, N, k, inv_temperature, idx, w,
@@ -655,24 +656,24 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
 namespace {
 
 // Fused form: decode-sized batch, every member with packed weights.
-bool group_fused(const bool* packed, int G, int T, int N, int r, bool bf16) {
-    if (G < 2 || G > kMaxDecodeGroup || !decode_fused_applies(T, N, r, bf16)) return false;
+bool group_fused(const int* d_out, const bool* packed, int G, int T, int d_in, int r, int k, bool bf16) {
+    if (G < 2 || G > kMaxDecodeGroup) return false;
     for (int g = 0; g < G; ++g)
-        if (!packed[g]) return false;
+        if (!packed[g] || !decode_fused_applies(T, d_in, d_out[g], r, k, bf16)) return false;
     return true;
 }
 
-// Second fused form: a few hundred tokens, every member on the dense routing path with packed weights, few output
-// tiles in all: the projections and routing products of all members as K-split tiles of one launch, one selection
-// launch, one reduction with the expands.  Returns the number of K splits (`reserve`: as many as a workspace has room for), 0
+// Second fused form: a few hundred tokens, every member with packed weights, few output tiles in all: the projections and
+// routing products of all members as K-split tiles of one launch, one launch with the selections and expands.  Returns the number of K splits (`reserve`: as many as a workspace has room for), 0
 // = not this form.
-int group_mid_splits(const int* d_out, const bool* packed, int G, int T, int d_in, int N, int r, bool bf16,
+int group_mid_splits(const int* d_out, const bool* packed, int G, int T, int d_in, int N, int r, int k, bool bf16,
                      bool reserve = false) {
-    if (G < 2 || G > kMaxDecodeGroup || !route_dense_applies(T, d_in, N, r, bf16)) return 0;
     const int cat_rows = prep_wcat_rows(N, r);
+    if (G < 2 || G > kMaxDecodeGroup || !bf16 || T <= 64 || !gemm_dense_splitk_ok(T, d_in, cat_rows)) return 0;
     int64_t tiles = 0;
     for (int g = 0; g < G; ++g) {
         if (!packed[g] || d_out[g] % 8 != 0 || !gemm_dense_splitk_ok(T, d_in, d_out[g])) return 0;
+        if (cat_rows > kWcatMaxRows && !expand_by_rows_applies(T, d_in, d_out[g], r, k)) return 0;
         tiles += (int64_t)ceil_div(T, 128) * (ceil_div(d_out[g], 128) + ceil_div(cat_rows, 128));
     }
     if (tiles > 320) return 0;   // beyond: member by member (each on the path its own size selects)
@@ -690,10 +691,9 @@ int group_mid_splits(const int* d_out, const bool* packed, int G, int T, int d_i
     return S < 1 ? 1 : S;
 }
 
-struct GroupLayout { size_t partial[kMaxDecodeGroup], gpart[kMaxDecodeGroup], hs[kMaxDecodeGroup], idx[kMaxDecodeGroup],
-                            w[kMaxDecodeGroup], total; int S; };
+struct GroupLayout { size_t partial[kMaxDecodeGroup], gpart[kMaxDecodeGroup], idx[kMaxDecodeGroup], w[kMaxDecodeGroup], total; int S; };
 
-// gate_rows: columns of gpart per member (the gate terms for decode, every row of Wcat for the second form)
+// gate_rows: columns of gpart per member, every row of Wcat
 GroupLayout group_layout(const int* d_out, int G, int T, int d_in, int N, int r, int k, int S, int gate_rows) {
     GroupLayout L{};
     size_t off = 0;
@@ -702,7 +702,6 @@ GroupLayout group_layout(const int* d_out, int G, int T, int d_in, int N, int r,
     for (int g = 0; g < G; ++g) {
         L.partial[g] = take((size_t)L.S * T * d_out[g] * sizeof(float));
         L.gpart[g] = take((size_t)L.S * T * gate_rows * sizeof(float));
-        L.hs[g] = take((size_t)T * k * r * sizeof(float));
         L.idx[g] = take((size_t)T * k * sizeof(int32_t));
         L.w[g] = take((size_t)T * k * sizeof(float));
     }
@@ -718,24 +717,22 @@ extern "C" size_t meteora_group_workspace_bytes(const int* d_out, int G, int T, 
     if (dt != METEORA_F32 && dt != METEORA_BF16) return 0;
     const bool bf16 = dt == METEORA_BF16;
     size_t need = 0;
-    const bool fused = G >= 2 && G <= kMaxDecodeGroup && decode_fused_applies(T, N, r, bf16);
     for (int g = 0; g < G; ++g) {
         const size_t one = meteora_workspace_bytes(T, d_in, d_out[g], N, r, k, dt);
         if (one == 0) return 0;
         need = one > need ? one : need;
     }
-    if (fused) {
-        const int gate_rows = prep_wcat_rows(N, r);
-        const size_t f = group_layout(d_out, G, T, d_in, N, r, k, gemm_decode_plan(d_in, d_out, G, gate_rows).S,
-                                      gate_rows).total + 256;
-        need = f > need ? f : need;
-    }
-    if (G >= 2 && G <= kMaxDecodeGroup) {
-        bool all_packed[kMaxDecodeGroup] = {true, true, true, true};   // sized as if packed: the larger need
-        if (const int S = group_mid_splits(d_out, all_packed, G, T, d_in, N, r, bf16, true)) {
-            const size_t f = group_layout(d_out, G, T, d_in, N, r, k, S, prep_wcat_rows(N, r)).total + 256;
+    if (bf16 && G >= 2 && G <= kMaxDecodeGroup) {   // sized as if packed, the larger need, and for every smaller batch
+        const int gate_rows = prep_wcat_rows(N, r), Td = T < 64 ? T : 64;
+        auto fused = [&](int t, int S) {
+            const size_t f = group_layout(d_out, G, t, d_in, N, r, k, S, gate_rows).total + 256;
             need = f > need ? f : need;
-        }
+        };
+        fused(Td, gemm_decode_plan(d_in, d_out, G, gate_rows).S);
+        const bool all_packed[kMaxDecodeGroup] = {true, true, true, true};
+        // at most 320 tiles of 128 rows; the splits that fit change at multiples of 128 tokens
+        for (int t = T < 128 * 320 / (2 * G) ? T : 128 * 320 / (2 * G); t > 64; t = (t - 1) / 128 * 128)
+            if (const int S = group_mid_splits(d_out, all_packed, G, t, d_in, N, r, k, bf16, true)) fused(t, S);
     }
     return need;
 }
@@ -769,7 +766,7 @@ extern "C" meteora_status meteora_linear_forward_group(const void* x, const mete
     for (int g = 0; g < G; ++g)
         is_packed[g] = members[g].packed != nullptr &&
                        members[g].packed_bytes >= pack_layout(d_in, members[g].d_out, N, r, bf16).total;
-    if (const int S = (G <= kMaxDecodeGroup ? group_mid_splits(d_outs, is_packed, G, T, d_in, N, r, bf16) : 0)) {
+    if (const int S = (G <= kMaxDecodeGroup ? group_mid_splits(d_outs, is_packed, G, T, d_in, N, r, k, bf16) : 0)) {
         const int cat_rows = prep_wcat_rows(N, r);
         const GroupLayout L = group_layout(d_outs, G, T, d_in, N, r, k, S, cat_rows);
         DecodeMember mem[kMaxDecodeGroup];
@@ -777,8 +774,8 @@ extern "C" meteora_status meteora_linear_forward_group(const void* x, const mete
         for (int g = 0; g < G; ++g) {
             const meteora_group_member& m = members[g];
             const PackLayout P = pack_layout(d_in, m.d_out, N, r, bf16);
-            mem[g] = DecodeMember{m.W, at<void>(const_cast<void*>(m.packed), P.wcat), m.gate_bias, m.A, m.B, m.d_out,
-                                  at<float>(ws, L.partial[g]), at<float>(ws, L.gpart[g]), at<float>(ws, L.hs[g]),
+            mem[g] = DecodeMember{m.W, at<void>(const_cast<void*>(m.packed), P.wcat), m.gate_bias, m.B, m.d_out,
+                                  at<float>(ws, L.partial[g]), at<float>(ws, L.gpart[g]),
                                   m.topk_idx_out ? m.topk_idx_out : at<int32_t>(ws, L.idx[g]),
                                   m.topk_w_out ? m.topk_w_out : at<float>(ws, L.w[g]), m.out};
             ops[2 * g] = {mem[g].W, m.d_out, mem[g].partial};
@@ -789,20 +786,11 @@ extern "C" meteora_status meteora_linear_forward_group(const void* x, const mete
             StageScope sc(ST_GEMM, st, tslot);
             METEORA_HIP(launch_gemm_dense_splitk_multi(x, ops, 2 * G, S, T, d_in, st));
         }
-        if (decode_tail_applies(r)) {
-            StageScope sc(ST_SHRINK, st, tslot);
-            METEORA_HIP(launch_decode_tail_group(mem, G, SplitPlan{S, 0, 0}, T, N, r, k, cat_rows, inv_temperature, scale, st));
-            return METEORA_OK;
-        }
-        {
-            StageScope sc(ST_GATE_TOPK, st, tslot);
-            METEORA_HIP(launch_route_dense_select_group(mem, G, S, T, N, r, k, inv_temperature, scale, st));
-        }
-        StageScope sc(ST_EXPAND, st, tslot);
-        METEORA_HIP(launch_gemm_decode_finish(mem, G, S, T, k, r, st));
+        StageScope sc(ST_SHRINK, st, tslot);
+        METEORA_HIP(launch_decode_tail_group(mem, G, SplitPlan{S, 0, 0}, T, N, r, k, cat_rows, inv_temperature, scale, st));
         return METEORA_OK;
     }
-    if (!group_fused(is_packed, G, T, N, r, bf16)) {
+    if (!group_fused(d_outs, is_packed, G, T, d_in, r, k, bf16)) {
         // the same result one layer after the other (they share the workspace, which the stream order allows)
         for (int g = 0; g < G; ++g) {
             const meteora_group_member& m = members[g];
@@ -820,8 +808,8 @@ extern "C" meteora_status meteora_linear_forward_group(const void* x, const mete
     for (int g = 0; g < G; ++g) {
         const meteora_group_member& m = members[g];
         const PackLayout P = pack_layout(d_in, m.d_out, N, r, bf16);
-        mem[g] = DecodeMember{m.W, at<void>(const_cast<void*>(m.packed), P.wcat), m.gate_bias, m.A, m.B, m.d_out,
-                              at<float>(ws, L.partial[g]), at<float>(ws, L.gpart[g]), at<float>(ws, L.hs[g]),
+        mem[g] = DecodeMember{m.W, at<void>(const_cast<void*>(m.packed), P.wcat), m.gate_bias, m.B, m.d_out,
+                              at<float>(ws, L.partial[g]), at<float>(ws, L.gpart[g]),
                               m.topk_idx_out ? m.topk_idx_out : at<int32_t>(ws, L.idx[g]),
                               m.topk_w_out ? m.topk_w_out : at<float>(ws, L.w[g]), m.out};
     }
@@ -885,7 +873,7 @@ meteora_status meteora_gate_backward(const void* x, const void* dy, const float*
         const WsLayout F = ws_layout(T, d_in, d_out, N, r, k, bf16);
         if (!aligned256(forward_ws) || forward_ws_bytes < F.total) return METEORA_ERR_WORKSPACE;
         part_x = reinterpret_cast<const float*>(static_cast<const char*>(forward_ws) + F.dpart);
-        part_x_splits = dense_midsplit_splits(T, d_in, d_out, N, r, bf16);   // 0: the products launch's own split count
+        part_x_splits = dense_midsplit_splits(T, d_in, d_out, N, r, k, bf16);   // 0: the products launch's own split count
     }
     const hipError_t e = launch_gate_backward(x, dy, wcat, B, gate_bias, topk_idx, topk_w, labels, beta, T, d_in, d_out,
                                               N, r, k, scale, dW_gate, dbias, d_logits, part_x, part_x_splits, A, W_gate, W_t, dx,

@@ -41,5 +41,7 @@ __host__ __device__ constexpr size_t align_up(size_t v, size_t a) { return (v + 
 
 // Number of logit columns the gate kernels carry: N padded to 32 or 64.
 __host__ __device__ constexpr int padded_adapters(int N) { return N <= 32 ? 32 : 64; }
+// Rows of Wcat (columns of the dense products) per adapter: its rank in whole eights.
+__host__ __device__ constexpr int wcat_rank(int r) { return (r + 7) / 8 * 8; }
 
 }  // namespace meteora

@@ -442,15 +442,15 @@ __global__ __launch_bounds__(256) void gate_bwd_reduce_kernel(const float* __res
 
 // ---- host side ----
 bool gate_backward_applies(int T, int d_in, int d_out, int N, int r, bool bf16) {
-    return route_dense_possible(N, r, bf16) && d_in % 64 == 0 && d_out % 64 == 0 && T >= 1 && T <= kGateBackwardMaxTokens && r <= kMaxRank &&
+    return bf16 && N <= kBwdNP && r % 8 == 0 && prep_wcat_rows(N, r) <= kWcatMaxRows && d_in % 64 == 0 && d_out % 64 == 0 &&
+           T >= 1 && T <= kGateBackwardMaxTokens && r <= kMaxRank &&
            gemm_dense_splitk_ok(T, d_in, prep_wcat_rows(N, r)) && gemm_dense_splitk_ok(T, d_out, N * r);
 }
 
-// The slices a workspace has room for: up to twice as many, in whole blocks of 64 tokens, so that its size does not fall where
-// the number of slices does.
+// The slices a workspace has room for: never fewer for more tokens, as the number in use is.
 static int wgrad_slices_reserved(int T, int d_in) {
     const int blocks = ceil_div(T, 64), want = ceil_div(512, ceil_div(d_in, kWgCols));
-    return ceil_div(blocks, ceil_div(blocks, want < blocks ? want : blocks));
+    return want < blocks ? want : blocks;
 }
 
 // One workgroup per CU at most, since a few more take a second round, and 8 slices or, of more than 256 chunks, one for every
@@ -463,7 +463,7 @@ struct WgradPlan { int parts, slice_chunks; };
 static WgradPlan wgrad_plan(int T, int d_in) {
     const int chunks = ceil_div(T, kWgChunk), col_tiles = ceil_div(d_in, kWgCols);
     int n = chunks / 32 < 8 ? 8 : chunks / 32 < 32 ? chunks / 32 : 32;
-    for (const int most : {256 / col_tiles, ceil_div(chunks, 4), wgrad_slices_reserved(T, d_in)})
+    for (const int most : {256 / col_tiles, ceil_div(chunks, 4)})
         if (n > most) n = most;
     const int slice_chunks = ceil_div(chunks, n < 1 ? 1 : n);
     return {slice_chunks > 2 * kWgRing ? 4 : 2, slice_chunks};
@@ -474,8 +474,8 @@ GateBackwardLayout gate_backward_layout(int T, int d_in, int d_out, int N, int r
     const int CR = prep_wcat_rows(N, r), NR = N * r;
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off = align_up(off + bytes, 256); return o; };
-    L.part_x = take((size_t)gemm_dense_splits_reserved(T, d_in, CR) * T * CR * sizeof(float));
-    L.part_dy = take((size_t)gemm_dense_splits_reserved(T, d_out, NR) * T * NR * sizeof(float));
+    L.part_x = take((size_t)gemm_dense_pairs_reserved(T, d_in, CR) * CR * sizeof(float));
+    L.part_dy = take((size_t)gemm_dense_pairs_reserved(T, d_out, NR) * NR * sizeof(float));
     // whole pairs of 8-token blocks, 3072 bytes each: less than 192 T + 3072
     L.dgs = take((size_t)T * 192 + 3072);
     const int slices = wgrad_slices_reserved(T, d_in);

@@ -37,81 +37,6 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(const float* __
     *dst = pk;
 }
 
-// Decode: the fixed-order sum of the split-K tiles plus the LoRA expand of Eq. 2 from the fp32 shrink outputs,
-//   out[t, c] = bf16( sum_s partial[s][t][c] + sum_slot sum_q hs[t][slot][q] * B[idx[t][slot]][q][c] ),
-// hs = scale * w * h.  A thread owns 8 consecutive columns of one token: B rows are read as 16-byte pieces,
-// coalesced across the threads of a token.
-struct ReduceExpandArgs {
-    struct Member {
-        const float* partial;   // [S][T][d_out]
-        const float* hs;        // [T,k,r]
-        const int32_t* idx;     // [T,k]
-        const bf16_t* B;        // [N,r,d_out]
-        bf16_t* out;            // [T,d_out]
-        int d_out, block0;      // first workgroup of this member
-    } m[kMaxDecodeGroup];
-    int G;
-};
-
-__global__ __launch_bounds__(256) void gemm_splitk_reduce_expand_kernel(const ReduceExpandArgs ra, int nsplit, int T,
-                                                                        int k, int r) {
-    int g = 0;
-    for (int i = 1; i < ra.G; ++i)
-        if ((int)blockIdx.x >= ra.m[i].block0) g = i;   // uniform
-    const float* __restrict__ partial = ra.m[g].partial;
-    const float* __restrict__ hs = ra.m[g].hs;
-    const int32_t* __restrict__ idx = ra.m[g].idx;
-    const bf16_t* __restrict__ B = ra.m[g].B;
-    bf16_t* __restrict__ out = ra.m[g].out;
-    const int d_out = ra.m[g].d_out;
-    const int c8 = d_out / 8;
-    const size_t i = (size_t)(blockIdx.x - ra.m[g].block0) * 256 + threadIdx.x;
-    if (i >= (size_t)T * c8) return;
-    const int t = (int)(i / c8), c = (int)(i - (size_t)t * c8) * 8;
-    f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
-    for (int s0 = 0; s0 < nsplit; s0 += 8) {   // tiles in order, 8 tiles' loads in flight
-        f32x4 v0[8], v1[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const float* src = partial + ((size_t)min(s0 + u, nsplit - 1) * T + t) * d_out + c;
-            v0[u] = *reinterpret_cast<const f32x4*>(src);
-            v1[u] = *reinterpret_cast<const f32x4*>(src + 4);
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (s0 + u < nsplit) { lo += v0[u]; hi += v1[u]; }
-    }
-    for (int slot = 0; slot < k; ++slot) {
-        const int a = idx[(size_t)t * k + slot];
-        const float* h = hs + ((size_t)t * k + slot) * r;
-        const bf16_t* Ba = B + (size_t)a * r * d_out + c;
-        for (int q0 = 0; q0 < r; q0 += 8) {   // r % 8 == 0; 8 rows of B in flight
-            u32x4 b[8];
-            float hv[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                b[u] = *reinterpret_cast<const u32x4*>(Ba + (size_t)(q0 + u) * d_out);
-                hv[u] = h[q0 + u];
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                lo[0] = fmaf(hv[u], bf16_bits_to_float(b[u][0] & 0xffffu), lo[0]);
-                lo[1] = fmaf(hv[u], bf16_bits_to_float(b[u][0] >> 16), lo[1]);
-                lo[2] = fmaf(hv[u], bf16_bits_to_float(b[u][1] & 0xffffu), lo[2]);
-                lo[3] = fmaf(hv[u], bf16_bits_to_float(b[u][1] >> 16), lo[3]);
-                hi[0] = fmaf(hv[u], bf16_bits_to_float(b[u][2] & 0xffffu), hi[0]);
-                hi[1] = fmaf(hv[u], bf16_bits_to_float(b[u][2] >> 16), hi[1]);
-                hi[2] = fmaf(hv[u], bf16_bits_to_float(b[u][3] & 0xffffu), hi[2]);
-                hi[3] = fmaf(hv[u], bf16_bits_to_float(b[u][3] >> 16), hi[3]);
-            }
-        }
-    }
-    u32x4 pk;
-    pk[0] = pack_bf16x2(lo[0], lo[1]); pk[1] = pack_bf16x2(lo[2], lo[3]);
-    pk[2] = pack_bf16x2(hi[0], hi[1]); pk[3] = pack_bf16x2(hi[2], hi[3]);
-    reinterpret_cast<u32x4*>(out)[i] = pk;
-}
-
 // Skinny batches (decode): one 64-row tile per 64 output columns leaves most CUs idle while W streams
 // from HBM, so K is split over workgroups.  Returns the number of main-K splits (0 = do not split).
 int gemm_splitk_splits(int T, int d_in, int d_out, bool bf16) {
@@ -222,10 +147,13 @@ int gemm_dense_splits(int T, int d_in, int rows) {
     return dense_split_bounds(S, nk);
 }
 
-int gemm_dense_splits_reserved(int T, int d_in, int rows) {
-    if (dense_small_tiles(T)) return gemm_dense_splits(T, d_in, rows);
-    const int tiles = ceil_div(T, 128) * ceil_div(rows, 320);
-    return dense_split_bounds((256 + tiles / 2) / tiles, ceil_div(d_in, kGemmBK));
+int64_t gemm_dense_pairs_reserved(int T, int d_in, int rows) {
+    const int64_t most = dense_split_bounds(8, ceil_div(d_in, kGemmBK));
+    auto bound = [&](int64_t t, int64_t pairs) { return pairs > most * t ? most * t : pairs > t ? pairs : t; };
+    const int64_t t = T < 4096 ? T : 4096;
+    const int64_t few = bound(t, ceil_div(384 * 128, ceil_div(rows, 128)) + (t + 1) / 2);   // S <= 384 / tiles + 1/2
+    const int64_t many = T > 4096 ? bound(T, ceil_div(256 * 128, ceil_div(rows, 320))) : 0;
+    return few > many ? few : many;
 }
 
 template <int MB, int NB, int D, int EPI>
@@ -329,21 +257,6 @@ hipError_t launch_gemm_dense_splitk_multi(const void* x, const DenseOperand* ops
     const bool two = T <= 128 && tile0 * S > 256;   // two per CU
     return rows * d_in * 2 <= kWriteThroughWeights ? launch_multi_tiles<kEpiPartialThrough>(a, two, stream)
                                                    : launch_multi_tiles<kEpiPartial>(a, two, stream);
-}
-
-hipError_t launch_gemm_decode_finish(const DecodeMember* mem, int G, int S, int T, int k, int r,
-                                     hipStream_t stream) {
-    if (S <= 0 || r % 8 != 0 || G < 1 || G > kMaxDecodeGroup) return hipErrorInvalidValue;
-    ReduceExpandArgs ra{};
-    unsigned blocks = 0;
-    for (int g = 0; g < G; ++g) {
-        ra.m[g] = {mem[g].partial, mem[g].hs, mem[g].idx, (const bf16_t*)mem[g].B, (bf16_t*)mem[g].out, mem[g].d_out,
-                   (int)blocks};
-        blocks += (unsigned)(((size_t)T * mem[g].d_out / 8 + 255) / 256);
-    }
-    ra.G = G;
-    gemm_splitk_reduce_expand_kernel<<<blocks, 256, 0, stream>>>(ra, S, T, k, r);
-    return hipGetLastError();
 }
 
 bool gemm_fuses_expand(bool bf16) { return bf16; }

@@ -23,8 +23,9 @@ hipError_t bucket_init_scratch();
 // stacked B -> its transpose Bt[d_out, N*r rounded up to 64] (zero-padded) for the GEMM's K-extension.
 // Any pair (W_gate, wsplit) / (A, apack) / (B, btrans) may be NULL to skip it; sizes are gate_wsplit_bytes,
 // shrink_apack_bytes and prep_btrans_bytes (0 = that operand is not packed for this dtype/rank: pass NULL).
-// wcat (optional, needs A, r % 8 == 0): Wcat[prep_wcat_rows, d_in] bf16 for the dense routing path,
-// rows = hi | mid | lo terms of the gate columns (padded_adapters(N) rows each), then column q of A_a as row a*r+q.
+// wcat (optional, needs A): Wcat[prep_wcat_rows, d_in] bf16 for the dense routing path,
+// rows = hi | mid | lo terms of the gate columns (padded_adapters(N) rows each), then column q of A_a as row
+// a*wcat_rank(r)+q (rows q >= r zero).
 // Without W_gate: the rows of A alone.
 size_t prep_btrans_bytes(int d_out, int N, int r, bool bf16);
 int prep_wcat_rows(int N, int r);
@@ -44,49 +45,35 @@ hipError_t launch_gate_topk(const float* partials, int KS, const float* bias, in
                             float inv_temperature, int32_t* topk_idx, float* topk_w, float* logits,
                             int32_t* chunk_counts, hipStream_t stream);
 
-// ---- small batches (T <= 64, bf16, r in {8, 16, 32}): top-k + softmax and the shrink of the selected
-// adapters in one launch, one workgroup per token; consumes launch_gate_logits' partials and writes
-// topk_idx, topk_w and every column of the token's row of hdense.  Replaces launch_gate_topk,
-// launch_bucket and launch_shrink for the whole-layer call (shapes the two-launch decode form below does not take).
-bool route_small_applies(int T, int r, bool bf16);
-hipError_t launch_route_shrink_small(const void* x, const float* partials, int KS, const float* bias, const void* A,
-                                     int T, int d_in, int N, int r, int k, float inv_temperature, float scale,
-                                     int32_t* topk_idx, float* topk_w, void* hdense, int ext_stride,
-                                     hipStream_t stream);
-
-// ---- batches of more than 64 tokens (bf16, r % 8 == 0, at most 640 rows of Wcat): one MFMA launch
+// ---- batches of more than 64 tokens (bf16, at most 640 rows of Wcat): one MFMA launch
 // computes the split-bf16 gate logits and x * A_i of every adapter as fp32 K-split partials
 // part[splits][T][prep_wcat_rows], then a launch of independent wavefronts adds the splits, ranks (Sec. 3.1, Eq. 3)
 // and writes topk_idx, topk_w and every column of the tokens' rows of hdense.  Replaces launch_gate_logits,
 // launch_gate_topk, launch_bucket and launch_shrink for the whole-layer call.  Up to kRouteDenseMaxTokens always;
 // beyond, with up to 320 rows of Wcat always, with more where the products' tiles fill the CUs
 // (route_dense_applies).
-constexpr int kRouteDenseMaxTokens = 8192;
-bool route_dense_possible(int N, int r, bool bf16);   // whatever T: is Wcat worth packing
+constexpr int kRouteDenseMaxTokens = 8192, kWcatMaxRows = 640;
 bool route_dense_applies(int T, int d_in, int N, int r, bool bf16);
 bool lora_dense_applies(int T, int d_in, int N, int r, int k, bool bf16);   // lora_forward, whose routing is given
-size_t route_dense_part_bytes(int T, int d_in, int N, int r, bool bf16);  // 0 if the path does not apply
+size_t route_dense_part_bytes(int T, int d_in, int N, int r, bool bf16);  // what the products of any batch of up to T tokens take
 hipError_t launch_route_dense_products(const void* x, const void* wcat, int T, int d_in, int N, int r, float* part,
                                        hipStream_t stream);
-// the expand operand for a routing that is given: part[S][T][N*r] = x * A_i of every adapter
+// the expand operand for a routing that is given (r % 8 == 0): part[S][T][N*r] = x * A_i of every adapter
 hipError_t launch_dense_expand_operand(const float* part, int S, const int32_t* topk_idx, const float* topk_w, int T,
                                        int N, int r, int k, float scale, void* hdense, int ext_stride,
                                        hipStream_t stream);
 hipError_t launch_route_dense_select(const float* part, const float* bias, int T, int d_in, int N, int r, int k,
                                      float inv_temperature, float scale, int32_t* topk_idx, float* topk_w,
-                                     void* hdense, int ext_stride, hipStream_t stream, float* hs = nullptr,
-                                     int splits = 0);
-// hs (optional): also write hs[T,k,r] = scale * w * h in fp32 (the operand of launch_gemm_decode_finish); hdense may
-// then be NULL.  splits (optional): the number of K splits in `part` if it is not launch_route_dense_products' own.
+                                     void* hdense, int ext_stride, hipStream_t stream);
 // the GEMM behind launch_route_dense_products: partial[split][T][rows] = x * Wcat^T over the split's K range
 bool gemm_dense_splitk_ok(int T, int d_in, int rows);
 int gemm_dense_splits(int T, int d_in, int rows);
 // few-tile split-K launches over several matrices (col_tiles: the 128-column tiles of all of them, rows: their rows): S
 // capped to one workgroup per CU, or for few tokens to two, and of what that leaves the number that costs the least
 int gemm_multi_splits(int T, int col_tiles, int S, int nk, int64_t rows);
-// What a workspace reserves: as many splits as fit.  The two above come and go with the token count; a workspace for the
-// largest batch has to hold the smaller ones, and with these its size falls at few of them.
-int gemm_dense_splits_reserved(int T, int d_in, int rows);
+// What a workspace reserves: the two above come and go with the token count, and a workspace for the largest batch holds the
+// smaller ones.  Bound of tokens times splits of the products of any batch of up to T tokens, and the splits that fit.
+int64_t gemm_dense_pairs_reserved(int T, int d_in, int rows);
 int gemm_multi_splits_reserved(int T, int col_tiles, int S);
 hipError_t launch_gemm_dense_splitk(const void* x, const void* Wcat, int T, int d_in, int rows, float* partial,
                                     hipStream_t stream);
@@ -156,26 +143,24 @@ hipError_t launch_layer_f32(const float* x, const float* W, const float* W_gate,
                             float scale, int32_t* topk_idx, float* topk_w, float* out, hipStream_t stream);
 bool f32_expand_apart(int d_out, int r, int k);   // the expand is a launch of its own and h is used
 
-// ---- decode-sized batches in two launches (T <= 64, bf16, r in {8, 16, 32}, Wcat packed), for one layer or for a
-// group of up to kMaxDecodeGroup layers that share x (q/k/v, gate/up):
+// ---- decode-sized batches in two launches (T <= 64, bf16, Wcat packed), for one layer or for a group of up to
+// kMaxDecodeGroup layers that share x (q/k/v, gate/up):
 // launch_gemm_decode_main: the main K splits of x * W_g^T as fp32 tiles partial_g[S][T][d_out_g], and in the same
 //   launch x * Wcat_g^T (gate_rows = prep_wcat_rows(N, r): the gate terms and every adapter's shrink columns) as
 //   gpartial_g[S][T][gate_rows]; S and the splits of every row tile follow from gemm_decode_plan(...);
 // launch_decode_tail_group (route_small.hip): top-k, softmax -> idx_g, w_g, and
 //   out_g = bf16(sum of the S tiles in order + sum_slot (scale * w * h from the shrink tiles) * B_g[idx_g]).
-// launch_gemm_decode_finish: the reduction with the expand alone, from hs_g[T,k,r] = scale * w * h (the few-tile
-//   form of mid-sized batches below).
+// Batches of a few hundred tokens with few output tiles end in the same tail, behind launch_gemm_dense_splitk_multi over every
+// W_g and Wcat_g.
 constexpr int kMaxDecodeGroup = 4;
 struct DecodeMember {
     const void* W;        // [d_out, d_in]
     const void* wg3;      // Wcat
     const float* bias;    // gate bias or NULL
-    const void* A;        // [N, d_in, r]
     const void* B;        // [N, r, d_out]
     int d_out;
     float* partial;       // [S][T][d_out]
     float* gpartial;      // [S][T][gate_rows]
-    float* hs;            // [T,k,r]
     int32_t* idx;         // [T,k]
     float* w;             // [T,k]
     void* out;            // [T,d_out]
@@ -191,17 +176,11 @@ struct SplitPlan {
 SplitPlan gemm_decode_plan(int d_in, const int* d_out, int G, int gate_rows);
 hipError_t launch_gemm_decode_main(const void* x, const DecodeMember* mem, int G, int gate_rows, const SplitPlan& plan,
                                    int T, int d_in, hipStream_t stream);
-hipError_t launch_gemm_decode_finish(const DecodeMember* mem, int G, int S, int T, int k, int r, hipStream_t stream);
-bool decode_tail_applies(int r);   // ranks the tail's kernel is built for
 hipError_t launch_decode_tail_group(const DecodeMember* mem, int G, const SplitPlan& plan, int T, int N, int r, int k, int gate_rows,
                                     float inv_temperature, float scale, hipStream_t stream);
-// The same three launches for batches of a few hundred tokens with few output tiles: launch_gemm_dense_splitk_multi over
-// every W_g and Wcat_g (gpartial_g then holds [S][T][prep_wcat_rows]), this selection for all members, the finish above.
-hipError_t launch_route_dense_select_group(const DecodeMember* mem, int G, int S, int T, int N, int r, int k,
-                                           float inv_temperature, float scale, hipStream_t stream);
 
 // ---- gate gradients (Sec. 3.2, Eq. 4): dW_gate[d_in,N], dbias[N] (optional) and d_logits[T,N] (optional) from
-// x, dy = dL/do, the packed Wcat and B; bf16 shapes of the dense routing path with d_in and d_out multiples of 64.
+// x, dy = dL/do, the packed Wcat and B; bf16, N <= 32, r % 8 == 0, at most 640 rows of Wcat, d_in and d_out multiples of 64.
 // idx_in / w_in (optional, both or neither): the routing of the forward call; NULL ranks again from the same
 // logits.  labels (optional): per-token adapter label of the classification loss, weight beta; values outside
 // [0, N) give that token no classification part.  ws: gate_backward_layout(...).total bytes.

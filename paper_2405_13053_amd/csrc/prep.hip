@@ -4,8 +4,9 @@
 //   - stacked LoRA A[N, d_in, r] (Sec. 3.3) -> fragments with the rank padded to 32 columns;
 //   - stacked LoRA B[N, r, d_out] viewed as [N*r, d_out] -> its transpose Bt[d_out, ext_stride]
 //     (columns >= N*r zero), the layout the GEMM's K-extension streams like W.
-//   - for the dense routing path, Wcat[3*NP + N*r, d_in]: the three gate terms and every column of every
-//     A_i as rows contiguous along d_in, the layout the GEMM kernel streams like W.
+//   - for the dense routing path, Wcat[3*NP + N*RP, d_in]: the three gate terms and every column of every
+//     A_i (RP: its rank in whole eights, the columns past r zero) as rows contiguous along d_in, the layout the GEMM
+//     kernel streams like W.
 // All run in ONE launch (disjoint workgroup ranges); a wavefront writes one fragment, a workgroup
 // one 64x64 tile of a transpose.
 #include "common.hpp"
@@ -96,7 +97,7 @@ __device__ __forceinline__ void btrans_tile(const uint16_t* __restrict__ B, int 
 }
 
 // tile (ti, tr) of Wcat[rows, d_in]: row R = term*NP + j (term 0..2 = hi, mid, lo of W_gate[:, j]; zero for
-// j >= N), then row 3*NP + a*r + q = A[a][:, q], then zero rows up to `rows`.  Sources are read along the
+// j >= N), then row 3*NP + a*RP + q = A[a][:, q] (zero for q >= r), RP = r in whole eights.  Sources are read along the
 // row index (contiguous in W_gate and, per adapter, in A), transposed through LDS, stored along d_in.
 __device__ __forceinline__ void wcat_tile(const float* __restrict__ W_gate, const uint16_t* __restrict__ A, int d_in,
                                           int N, int NP, int r, int rows, int tile, int tid,
@@ -104,8 +105,8 @@ __device__ __forceinline__ void wcat_tile(const float* __restrict__ W_gate, cons
     constexpr int LD = 66;
     __shared__ uint16_t t[64 * LD];   // t[i][row]
     const int tiles_i = ceil_div(d_in, 64);
-    const int i0 = (tile % tiles_i) * 64, R0 = (tile / tiles_i) * 64;
-    // Rows come in groups of 8 that never straddle a region (NP, r and the region starts are multiples of 8): a group
+    const int i0 = (tile % tiles_i) * 64, R0 = (tile / tiles_i) * 64, RP = wcat_rank(r);
+    // Rows come in groups of 8 that never straddle a region (NP, RP and the region starts are multiples of 8): a group
     // of gate rows is 8 consecutive columns j of one term; a group of A rows is columns q0..q0+7 of one adapter,
     // one 16-byte load per i, consecutive threads along i so that a wavefront reads 1 KB of A contiguously.
     // All index arithmetic is per group, i.e. uniform across the 64 threads that share it.
@@ -125,9 +126,16 @@ __device__ __forceinline__ void wcat_tile(const float* __restrict__ W_gate, cons
                     p.h[jj] = term == 0 ? h : (term == 1 ? m : l);
                 }
             }
-        } else if (Rg < 3 * NP + N * r) {
-            const int c = Rg - 3 * NP, a = c / r, q0 = c - a * r;
-            p.v = *reinterpret_cast<const u32x4*>(A + ((size_t)a * d_in + i) * r + q0);
+        } else if (Rg < 3 * NP + N * RP) {
+            const int c = Rg - 3 * NP, a = c / RP, q0 = c - a * RP;
+            const uint16_t* src = A + ((size_t)a * d_in + i) * r + q0;
+            if (RP == r) {   // uniform
+                p.v = *reinterpret_cast<const u32x4*>(src);
+            } else {
+#pragma unroll
+                for (int jj = 0; jj < 8; ++jj)
+                    if (q0 + jj < r) p.h[jj] = src[jj];
+            }
         }
         uint32_t* dst = reinterpret_cast<uint32_t*>(&t[ii * LD + g * 8]);
         dst[0] = p.w[0]; dst[1] = p.w[1]; dst[2] = p.w[2]; dst[3] = p.w[3];
@@ -175,7 +183,7 @@ size_t prep_btrans_bytes(int d_out, int N, int r, bool bf16) {
     return bf16 ? (size_t)d_out * align_up((size_t)N * r, 64) * sizeof(uint16_t) : 0;
 }
 
-int prep_wcat_rows(int N, int r) { return (int)align_up((size_t)3 * padded_adapters(N) + (size_t)N * r, 8); }
+int prep_wcat_rows(int N, int r) { return 3 * padded_adapters(N) + N * wcat_rank(r); }
 
 size_t prep_wcat_bytes(int d_in, int N, int r, bool bf16) {
     return bf16 ? (size_t)prep_wcat_rows(N, r) * d_in * sizeof(uint16_t) : 0;
@@ -188,8 +196,8 @@ hipError_t launch_prep(const float* W_gate, void* wsplit, const void* A, void* a
     const int ext_stride = (int)align_up((size_t)N * r, 64);
     const int bblocks = (B && btrans) ? (ext_stride / 64) * ceil_div(d_out, 64) : 0;
     const int wblocks = ceil_div(wfrags, 4);
-    const int cat_rows = W_gate ? prep_wcat_rows(N, r) : N * r;
-    if (wcat && (!A || d_in % 8 != 0 || r % 8 != 0)) return hipErrorInvalidValue;
+    const int cat_rows = W_gate ? prep_wcat_rows(N, r) : N * wcat_rank(r);
+    if (wcat && (!A || d_in % 8 != 0)) return hipErrorInvalidValue;
     const int cblocks = wcat ? ceil_div(cat_rows, 64) * ceil_div(d_in, 64) : 0;
     const int64_t blocks = (int64_t)bblocks + cblocks + wblocks + ceil_div64(afrags, 4);
     if (blocks == 0) return hipSuccess;

@@ -99,6 +99,18 @@ def test_a_backward_workspace_for_more_tokens_holds_fewer(d_in, d_out, r, fewer,
     assert size(fewer) <= size(more)
 
 
+@pytest.mark.parametrize("d_in,d_out", [(4096, 4096), (4096, 1024), (1024, 1024), (14336, 4096), (520, 8200), (136, 136)])
+@pytest.mark.parametrize("N,r", [(28, 8), (28, 16), (28, 12), (64, 32), (64, 8), (5, 5)])
+def test_the_size_of_a_workspace_never_falls(d_in, d_out, N, r):
+    """On either side of every multiple of 64 tokens, where the paths and their K splits change."""
+    Ts = [t + d for t in [*range(64, 4400, 64), 8192, 12000, 16384] for d in (-1, 0, 1)]
+    for size in (lambda T: m.workspace_bytes(T, d_in, d_out, N, r, 2, "bf16"),
+                 lambda T: m.group_workspace_bytes((d_out, 264, d_out), T, d_in, N, r, 2, "bf16"),
+                 lambda T: m.gate_backward_workspace_bytes(T, d_in, d_out, N, r, 2, "bf16")):
+        sizes = [size(T) for T in Ts]
+        assert sizes == sorted(sizes)
+
+
 @pytest.mark.parametrize("T", [65, 96, 128])
 @pytest.mark.parametrize("d_out", [16008, 16384, 18432, 19584])
 def test_wide_layers_of_up_to_128_tokens_split_along_k(T, d_out):

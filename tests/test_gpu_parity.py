@@ -536,13 +536,57 @@ def test_layer_of_any_width(T, d_in, d_out, N, r, k):
     _check_layer(LS(T, d_in, d_out, N, r, k, 2.0, "bf16", "zipf", "any-width"), seed=64, rows="all" if T <= 300 else "sample")
 
 
-def test_a_blob_packed_without_the_routing_rows_is_still_taken():
-    """Blobs of widths that are no multiple of 64 once ended in front of Wcat: the call packs its operands itself, the same bits."""
+# More than 32 adapters and ranks that are no multiple of 8 or no power of two on every launch sequence: decode with 1 to 16
+# splits (equal ones, and runs that cut the gate rows' two tiles in different places), a few hundred tokens, dense routing,
+# bucketed.  (Rank 1 with all three adapters: the expand operand and the output are rounded to bf16, 2^-9 each; with rank 1 and
+# one adapter a single rounded factor of up to 28 meets sampled outputs of up to 20, 3.98e-3 * 28 / 20 = 5.6e-3 of the largest.)
+@pytest.mark.parametrize("N,r,k", [(64, 32, 8), (33, 8, 2), (28, 12, 2), (5, 5, 3), (64, 64, 4), (40, 20, 3), (3, 1, 3), (28, 24, 2)])
+@pytest.mark.parametrize("T,d_in,d_out", [(1, 136, 8), (3, 4096, 264), (64, 1024, 776), (17, 512, 11008), (5, 8384, 136),
+                                          (65, 512, 264), (130, 1032, 16392), (300, 512, 2056), (1300, 320, 2056)])
+def test_layer_with_any_adapters(N, r, k, T, d_in, d_out):
+    _check_layer(LS(T, d_in, d_out, N, r, k, 2.0, "bf16", "zipf", "any-adapters"), seed=66, rows="all" if T <= 17 else "sample")
+
+
+# So many rows of B per token that the dense operand and MFMAs are cheaper than the tail: decode-sized, a few hundred tokens, a group
+# with one such member.
+@pytest.mark.parametrize("T,d_in,d_out", [(64, 128, 8200), (300, 512, 2056)])
+def test_layer_with_many_ranks_per_token(T, d_in, d_out):
+    shape = LS(T, d_in, d_out, 64, 64, 8, 0.5, "bf16", "uniform", "many-ranks")
+    _check_layer(shape, seed=68, rows="sample")
+    shapes, all_ops, members, x, rows = _group_case(T, d_in, (d_out, 136), 64, 64, 8, "uniform", seed=69)
+    for mb in members:
+        mb["packed"] = m.pack_weights(mb["W_gate"], mb["A"], mb["B"])
+    for mb, out in zip(members, m.linear_forward_group(x, members, 8, 0.5)):
+        alone = m.linear_forward(x, mb["W"], mb["W_gate"], mb["gate_bias"], mb["A"], mb["B"], 8, 0.5, packed=mb["packed"])
+        assert util.rel_max_err(out[rows], alone[rows].to(torch.float64).cpu().numpy()) <= 2 * util.tol(shape)
+
+
+@pytest.mark.parametrize("T", [9, 200])
+def test_padding_of_a_rank_reads_no_other_adapter(T):
+    """28 adapters of rank 12, infinities in every adapter but two: tokens that chose only those two see none of them.  (Decode
+    and the few-tile form; the fused GEMM multiplies every adapter of a used K tile.)"""
+    shape = LS(T, 1024, 264, 28, 12, 2, 2.0, "bf16")
+    ops, dev = util.make_case(shape, seed=67, condition=False)
+    bias = torch.full((28,), -1e4, device="cuda")
+    bias[7] = bias[20] = 0.0
+    clean = m.linear_forward(dev["x"], dev["W"], dev["W_gate"], bias, dev["A"], dev["B"], 2, 2.0)
+    others = torch.ones(28, dtype=torch.bool, device="cuda")
+    others[7] = others[20] = False
+    dev["B"][others] = float("inf")
+    dev["A"][others] = 0.0     # their shrink is finite: the dense products are of every adapter
+    out, idx, _ = m.linear_forward(dev["x"], dev["W"], dev["W_gate"], bias, dev["A"], dev["B"], 2, 2.0, return_routing=True)
+    assert sorted(set(_np(idx).ravel().tolist())) == [7, 20]
+    assert torch.equal(out, clean)
+
+
+@pytest.mark.parametrize("d_in,N,r", [(520, 28, 8), (512, 28, 12), (512, 64, 8)], ids=["width", "rank", "adapters"])
+def test_a_blob_packed_without_the_routing_rows_is_still_taken(d_in, N, r):
+    """Blobs that once ended in front of Wcat: the call packs its operands itself, the same bits."""
     for T in (30, 300):
-        shape = LS(T, 520, 264, 28, 8, 2, 2.0, "bf16")
+        shape = LS(T, d_in, 264, N, r, 2, 2.0, "bf16")
         _, dev = util.make_case(shape, seed=65)
         whole = m.pack_weights(dev["W_gate"], dev["A"], dev["B"])
-        short = whole[:-(96 + 28 * 8) * 520 * 2].clone()
+        short = whole[:-(3 * (32 if N <= 32 else 64) + N * ((r + 7) // 8 * 8)) * d_in * 2].clone()
         args = (dev["x"], dev["W"], dev["W_gate"], None, dev["A"], dev["B"], 2, 2.0)
         assert torch.equal(m.linear_forward(*args, packed=short), m.linear_forward(*args, packed=whole))
         members = [{"W": dev["W"], "W_gate": dev["W_gate"], "gate_bias": None, "A": dev["A"], "B": dev["B"], "packed": p}
