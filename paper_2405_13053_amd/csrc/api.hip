@@ -55,7 +55,7 @@ int dense_midsplit_splits(int T, int d_in, int d_out, int N, int r, int k, bool 
     // workgroups per CU (4096 -> 14336 T = 65 91.0 against 84.9, 128 143 against 95.7).
     const int CR = prep_wcat_rows(N, r);
     if (!bf16 || T <= 64 || !gemm_dense_splitk_ok(T, d_in, CR) || !gemm_dense_splitk_ok(T, d_in, d_out)) return 0;
-    const int col_tiles = ceil_div(d_out, 128) + ceil_div(CR, 128), fit = gemm_dense_splits(T, d_in, d_out);
+    const int col_tiles = ceil_div(d_out, 128) + ceil_div(CR, 128), fit = gemm_multi_fit(T, d_in, d_out);
     if (CR > kWcatMaxRows && (2 * ceil_div(T, 256) * col_tiles > 256 || !expand_by_rows_applies(T, d_in, d_out, r, k))) return 0;
     const int S = reserve ? gemm_multi_splits_reserved(T, col_tiles, fit)
                           : gemm_multi_splits(T, col_tiles, fit, ceil_div(d_in, 64), (int64_t)d_out + CR);

@@ -121,16 +121,20 @@ static hipError_t launch_skinny(GemmArgs a, hipStream_t stream) {
 // Dense routing operand: partial[split][T][rows] = x[T, K-range of split] * Wcat[rows, same K]^T in fp32,
 // no reduction (the select kernel adds the splits in order).
 // ------------------------------------------------------------------------------------------
-// Up to 4096 tokens: 128 x 128 tiles, two workgroups per CU (one computes while the other waits for its
-// loads), about 384 workgroups; above: 128 x 320 tiles (x is read once), one workgroup per CU.  Both with
-// the two-deep ring.  Measured on T = 4096 and 8192, d_in = 4096 and 14336.
-static bool dense_small_tiles(int T) { return T <= 4096; }
-
-bool gemm_dense_splitk_ok(int T, int d_in, int rows) {
-    const uint64_t widest = (uint64_t)d_in * 2;
-    return d_in % 8 == 0 && rows % 8 == 0 && ((uint64_t)T + 2 * 64) * widest < (1ull << 32) &&
-           ((uint64_t)rows + 5 * 64) * widest < (1ull << 32) && (uint64_t)rows * 4 * 256 < (1ull << 32);
-}
+// Bound by the CU's port to L2 (a K tile of 128 x 160 is 37 KB and 640 cycles of MFMAs) and by the fp32 tiles.  One workgroup per CU:
+//   - 128 x 160 tiles, a ring of three: 320 and 544 rows of Wcat fill them, and they are dealt evenly, where 128 x 128 tiles, two
+//     to a CU, left half of the CUs with one of the 384 workgroups (and half of the third column tile of 320 rows empty).
+//     While they make two K splits or more.
+//   - beyond 2048 tokens, where x is read again for every column tile: the narrowest tile of up to 320 columns that takes the
+//     rows in as few column tiles as 320 does (544 rows: 288).
+// and otherwise, as where K ends the splits before the CUs are full, 128 x 128 tiles, two workgroups per CU.
+// Whole calls, 128 x 128 up to 4096 tokens and 128 x 320 above with ordinary stores, as it was, and so (written through, see kWriteThrough;
+// with ordinary stores), us: layers of rank 8, 4096 -> 4096 1000 tokens 49.3, 48.4 (48.0), 4096 117.6, 116.0 (117.9), 5000 181.6,
+// 176.4 (176.3), 8192 227.2, 221.8 (223.1); 3000 x 5120 -> 5120 144.1, 136.0 (137.5), 4096 x 14336 -> 1024 193.7, 183.0
+// (183.0); of rank 16 4096 x 4096 -> 4096 132.2, 127.1 (127.0), 16384 x 14336 -> 1024 584.6, 567.2 (567.3); lora_forward of rank 8
+// 3000 x 5120 -> 1024 32.2, 29.8 (31.1), 8000 x 4096 -> 1024 42.7, 40.0 (40.9); a training step of 4096 x 4096 -> 4096 266.9,
+// 262.1 (263.9).  128 x 160 with one split loses: 6000 tokens of rank 16 215 against 211.
+struct DenseTile { int nb, splits; };   // columns in blocks of 32
 
 static int dense_split_bounds(int S, int nk) {
     if (S > nk / 4) S = nk / 4;                // at least 4 K tiles per split
@@ -138,22 +142,41 @@ static int dense_split_bounds(int S, int nk) {
     return S < 1 ? 1 : S;
 }
 
-int gemm_dense_splits(int T, int d_in, int rows) {
-    const bool small = dense_small_tiles(T);
-    const int tiles = ceil_div(T, 128) * ceil_div(rows, small ? 128 : 320), nk = ceil_div(d_in, kGemmBK);
-    // 128 x 320 tiles: one workgroup per CU at most, since a few more take a second round (layers of 4096 -> 1024, rank 8, on
-    // 282 and 188 workgroups: 12000 x 5120 155.3 and 148.0 us)
-    const int S = small ? (384 + tiles / 2) / tiles : 256 / tiles;
-    return dense_split_bounds(S, nk);
+static int dense_wide_blocks(int rows) { return ceil_div(ceil_div(rows, ceil_div(rows, 320)), 32); }
+
+static DenseTile dense_tile(int T, int d_in, int rows) {
+    const int nk = ceil_div(d_in, kGemmBK), row_tiles = ceil_div(T, 128), four = ceil_div(rows, 128), five = ceil_div(rows, 160);
+    auto fits = [&](int tiles) { return dense_split_bounds(256 / tiles, nk) == dense_split_bounds(256 / tiles, 32); };   // K does not bind
+    if (five * 160 <= four * 128 && 2 * row_tiles * five <= 256 && fits(row_tiles * five))
+        return {5, dense_split_bounds(256 / (row_tiles * five), nk)};
+    const int nb = dense_wide_blocks(rows), tiles = row_tiles * ceil_div(rows, 32 * nb);
+    if (nb > 4 && (T > 4096 || (T > 2048 && fits(tiles)))) return {nb, dense_split_bounds(256 / tiles, nk)};
+    return {4, dense_split_bounds((384 + row_tiles * four / 2) / (row_tiles * four), nk)};
+}
+
+bool gemm_dense_splitk_ok(int T, int d_in, int rows) {
+    const uint64_t widest = (uint64_t)d_in * 2;
+    return d_in % 8 == 0 && rows % 8 == 0 && ((uint64_t)T + 2 * 64) * widest < (1ull << 32) &&
+           ((uint64_t)rows + 5 * 64) * widest < (1ull << 32) && (uint64_t)rows * 4 * 256 < (1ull << 32);
+}
+
+int gemm_dense_splits(int T, int d_in, int rows) { return dense_tile(T, d_in, rows).splits; }
+
+// The K splits that few-tile launches start from (see gemm_multi_splits)
+int gemm_multi_fit(int T, int d_in, int rows) {
+    const int tiles = ceil_div(T, 128) * ceil_div(rows, T <= 4096 ? 128 : 320);
+    return dense_split_bounds(T <= 4096 ? (384 + tiles / 2) / tiles : 256 / tiles, ceil_div(d_in, kGemmBK));
 }
 
 int64_t gemm_dense_pairs_reserved(int T, int d_in, int rows) {
-    const int64_t most = dense_split_bounds(8, ceil_div(d_in, kGemmBK));
-    auto bound = [&](int64_t t, int64_t pairs) { return pairs > most * t ? most * t : pairs > t ? pairs : t; };
-    const int64_t t = T < 4096 ? T : 4096;
-    const int64_t few = bound(t, ceil_div(384 * 128, ceil_div(rows, 128)) + (t + 1) / 2);   // S <= 384 / tiles + 1/2
-    const int64_t many = T > 4096 ? bound(T, ceil_div(256 * 128, ceil_div(rows, 320))) : 0;
-    return few > many ? few : many;
+    // splits times tokens of each form of dense_tile, as bounds that grow with the tokens: 256 / tiles, 384 / tiles + 1/2
+    const int64_t most = (int64_t)dense_split_bounds(8, ceil_div(d_in, kGemmBK)) * T;
+    const int wide = dense_wide_blocks(rows), few = wide <= 4 || T < 4096 ? T : 4096;
+    int64_t pairs = T;
+    for (const int64_t form : {256 * 128 / ceil_div(rows, 160), 256 * 128 / ceil_div(rows, 32 * wide),
+                               ceil_div(384 * 128, ceil_div(rows, 128)) + (few + 1) / 2})
+        if (form > pairs) pairs = form;
+    return pairs < most ? pairs : most;
 }
 
 template <int MB, int NB, int D, int EPI>
@@ -169,9 +192,18 @@ hipError_t launch_gemm_dense_splitk(const void* x, const void* Wcat, int T, int 
     GemmArgs a{};
     a.x = (const bf16_t*)x; a.W = (const bf16_t*)Wcat; a.T = T; a.d_in = d_in; a.d_out = rows;
     a.partial = partial;
-    a.splits = gemm_dense_splits(T, d_in, rows);
+    const DenseTile tile = dense_tile(T, d_in, rows);
+    a.splits = tile.splits;
     a.tiles_per_split = ceil_div(ceil_div(d_in, kGemmBK), a.splits);
-    return dense_small_tiles(T) ? launch_dense<4, 4, 2, kEpiPartial>(a, stream) : launch_dense<4, 10, 2, kEpiPartial>(a, stream);
+    switch (tile.nb) {
+        case 4: return launch_dense<4, 4, 2, kEpiPartial>(a, stream);
+        case 5: return launch_dense<4, 5, 3, kEpiPartialThrough>(a, stream);
+        case 6: return launch_dense<4, 6, 3, kEpiPartialThrough>(a, stream);
+        case 7: return launch_dense<4, 7, 3, kEpiPartialThrough>(a, stream);
+        case 8: return launch_dense<4, 8, 2, kEpiPartialThrough>(a, stream);
+        case 9: return launch_dense<4, 9, 2, kEpiPartialThrough>(a, stream);
+        default: return launch_dense<4, 10, 2, kEpiPartialThrough>(a, stream);
+    }
 }
 
 // Several matrices in one split-K launch (few-tile batches): ops[i].partial[s][T][rows_i] = x * W_i^T over the K
@@ -283,7 +315,12 @@ hipError_t gemm_init_kernels() {
     METEORA_TILES(5, 4, 4);
     METEORA_TILES(4, 4, 3);
     METEORA_TILES(4, 4, 2);
-    METEORA_RING(4, 10, 2, kEpiPartial, false);
+    METEORA_RING(4, 10, 2, kEpiPartialThrough, false);
+    METEORA_RING(4, 5, 3, kEpiPartialThrough, false);
+    METEORA_RING(4, 6, 3, kEpiPartialThrough, false);
+    METEORA_RING(4, 7, 3, kEpiPartialThrough, false);
+    METEORA_RING(4, 8, 2, kEpiPartialThrough, false);
+    METEORA_RING(4, 9, 2, kEpiPartialThrough, false);
 #define METEORA_PARTIAL(MB, NB, D)                   \
     METEORA_RING(MB, NB, D, kEpiPartial, false);     \
     METEORA_RING(MB, NB, D, kEpiPartialThrough, false)

@@ -643,7 +643,7 @@ constexpr int kEpiStore = 0, kEpiAccumulate = 1, kEpiPartial = 2, kEpiPartialThr
 // lines left in the L2 are only written back when the launch is over, and the next one waits for that.  Whole calls,
 // ordinary stores, "nt", "sc1": the fp32 tiles of 300 x 4096 -> 4096 26.35, 25.6, 25.2 us, of 1531 x 4096 -> 1024 of rank
 // 16 38.1, 37.75, 36.7; bf16 outputs: a training step of 4096 tokens 273.1 and 271.0 ("sc1"), 3000 x 5120 -> 5120 from its
-// parts 174.5 and 172.8.  The routing products of a prefill (kEpiPartial, two workgroups per CU at different stages) gain
+// parts 174.5 and 172.8.  The routing products on 128 x 128 tiles (kEpiPartial, two workgroups per CU at different stages) gain
 // nothing: 4096 tokens 120.9 and 121.7.  bf16 outputs beside weights that come from HBM, 96 to 4096 tokens, base projections and
 // whole layers of 4096 -> 4096 and 14336, 14336 -> 4096, 5120 -> 5120 and 13824, ordinary and "sc1": 3% faster to 0.7% slower.
 // The ends: 2000 x 4096 -> 4096 54.0 and 52.2, 700 x 4096 -> 14336 with adapters 92.3 and 90.1; 3000 x 4096 -> 14336 256.5
@@ -790,9 +790,9 @@ __device__ __forceinline__ void mfma_start(f32x4 (&acc)[MB][NB]) {
 #pragma unroll
     for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < NB; ni += 2) {
-            acc[mi][ni] = acc[mi][ni + 1] = f32x4{0.f, 0.f, 0.f, 0.f};
-            asm volatile("" : "+a"(acc[mi][ni]), "+a"(acc[mi][ni + 1]));
+        for (int ni = 0; ni < NB; ++ni) {
+            acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+            asm volatile("" : "+a"(acc[mi][ni]));
         }
     asm volatile("s_nop 1" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
@@ -812,33 +812,49 @@ __device__ __forceinline__ void mfma_results(f32x4 (&acc)[MB][NB]) {
 #pragma unroll
     for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < NB; ni += 2) asm volatile("" : "+a"(acc[mi][ni]), "+a"(acc[mi][ni + 1]));
+        for (int ni = 0; ni < NB; ++ni) asm volatile("" : "+a"(acc[mi][ni]));
     __builtin_amdgcn_sched_barrier(0);
 }
 
 // Order of the MB x NB products of a k-step: 2 x 2 micro-blocks, each a cycle, walked as a snake, so that one operand
-// register changes from one MFMA to the next (0.5% less time than sweeping whole rows).  An odd last row is swept.
+// register changes from one MFMA to the next (0.5% less time than sweeping whole rows).  An odd last row is swept; with an odd
+// number of columns rows and columns change places.
+template <int R, int C>
+__host__ __device__ constexpr int snake_row(int k) {
+    return k >= R / 2 * 2 * C ? R - 1 : (k / (2 * C)) * 2 + ((k >> 1) & 1);
+}
+template <int R, int C>
+__host__ __device__ constexpr int snake_col(int k) {
+    if (k >= R / 2 * 2 * C) return k - R / 2 * 2 * C;
+    const int col = (k >> 2) % (C / 2), in = k & 3;
+    return (((k / (2 * C)) & 1) ? C / 2 - 1 - col : col) * 2 + ((in == 1 || in == 2) ? 1 : 0);
+}
 template <int MB, int NB>
 __host__ __device__ constexpr int order_mi(int k) {
-    return k >= MB / 2 * 2 * NB ? MB - 1 : (k / (2 * NB)) * 2 + ((k >> 1) & 1);
+    if constexpr (NB % 2 == 0) return snake_row<MB, NB>(k);
+    else return snake_col<NB, MB>(k);
 }
 template <int MB, int NB>
 __host__ __device__ constexpr int order_ni(int k) {
-    if (k >= MB / 2 * 2 * NB) return k - MB / 2 * 2 * NB;
-    const int col = (k >> 2) % (NB / 2), in = k & 3;
-    return (((k / (2 * NB)) & 1) ? NB / 2 - 1 - col : col) * 2 + ((in == 1 || in == 2) ? 1 : 0);
+    if constexpr (NB % 2 == 0) return snake_col<MB, NB>(k);
+    else return snake_row<NB, MB>(k);
 }
 
-// Fragment number i in the order the MFMAs need them: x 0, x 1, every W fragment, the other x fragments.
+// Fragment number i in the order the MFMAs need them: two of the operand that is walked in pairs (x; W with an odd NB), every
+// one of the other, the rest of the first.
 template <int MB, int NB>
 __device__ __forceinline__ void load_frag16(Frags16<MB, NB>& f, const bf16_t* xs, const bf16_t* wsm, int wm, int wn, int l15,
                                             int kq, int ks, int i) {
-    if (i >= 2 && i < 2 + NB) {
-        const int n = i - 2, row = wn + n * 16 + l15;
+    constexpr bool XPAIRS = NB % 2 == 0;
+    constexpr int OTHER = XPAIRS ? NB : MB;
+    const bool other = i >= 2 && i < 2 + OTHER;
+    const int n = other ? i - 2 : i < 2 ? i : i - OTHER;
+    if (other == XPAIRS) {
+        const int row = wn + n * 16 + l15;
         f.w[n] = *reinterpret_cast<const bf16x8*>(wsm + row * kGemmBK + swz(row, ks * 4 + kq) * 8);
     } else {
-        const int m = i < 2 ? i : i - NB, row = wm + m * 16 + l15;
-        f.x[m] = *reinterpret_cast<const bf16x8*>(xs + row * kGemmBK + swz(row, ks * 4 + kq) * 8);
+        const int row = wm + n * 16 + l15;
+        f.x[n] = *reinterpret_cast<const bf16x8*>(xs + row * kGemmBK + swz(row, ks * 4 + kq) * 8);
     }
 }
 
@@ -854,7 +870,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
     GemmArgs a = a_in;
     constexpr int BM = MB * 32, BN = NB * 32;   // 2 x 2 wavefronts of MB x NB blocks of 16 x 16
     constexpr int PX = BM / 32, PW = BN / 32;   // pieces per wavefront per tile
-    static_assert(NB % 2 == 0 && D >= 2 && (D - 1) * (PX + PW) < 64, "whole 2 x 2 micro-blocks; vmcnt holds 6 bits");
+    static_assert((NB % 2 == 0 || MB % 2 == 0) && D >= 2 && (D - 1) * (PX + PW) < 64, "whole 2 x 2 micro-blocks; vmcnt holds 6 bits");
     constexpr int NR = MB + NB, NM = MB * NB;   // fragment reads and MFMAs per k-step
     // MFMAs per fragment read: k-step 0's reads (of k-step 1) end early, since the barrier waits for them; k-step 1's
     // (of the next tile) are spread over all of it

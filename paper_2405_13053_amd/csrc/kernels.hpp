@@ -68,6 +68,7 @@ hipError_t launch_route_dense_select(const float* part, const float* bias, int T
 // the GEMM behind launch_route_dense_products: partial[split][T][rows] = x * Wcat^T over the split's K range
 bool gemm_dense_splitk_ok(int T, int d_in, int rows);
 int gemm_dense_splits(int T, int d_in, int rows);
+int gemm_multi_fit(int T, int d_in, int rows);
 // few-tile split-K launches over several matrices (col_tiles: the 128-column tiles of all of them, rows: their rows): S
 // capped to one workgroup per CU, or for few tokens to two, and of what that leaves the number that costs the least
 int gemm_multi_splits(int T, int col_tiles, int S, int nk, int64_t rows);

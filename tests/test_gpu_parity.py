@@ -597,6 +597,16 @@ def test_a_blob_packed_without_the_routing_rows_is_still_taken(d_in, N, r):
             m.linear_forward(*args, packed=short[:-256].clone())
 
 
+# The routing products in each of their tile widths: 128 x 160 (320, 288 and 544 rows of Wcat, one of the last tile's columns ragged)
+# with 8, 4 and 2 splits, and beside it with too few inputs for that; 192 to 320 columns for many tokens; partial K tiles.
+@pytest.mark.parametrize("T,d_in,d_out,N,r,k", [
+    (1100, 2056, 2056, 28, 8, 2), (4000, 1024, 776, 28, 8, 2), (3000, 1096, 1032, 12, 16, 3), (2500, 1032, 1032, 28, 16, 2),
+    (4100, 512, 520, 28, 8, 2), (4000, 512, 776, 28, 8, 2), (2300, 1032, 776, 16, 8, 2), (4500, 264, 136, 12, 8, 2),
+    (4500, 264, 136, 16, 8, 2), (4500, 264, 136, 20, 8, 1), (4500, 264, 136, 28, 16, 2), (8400, 136, 264, 28, 8, 2), (8400, 136, 264, 30, 16, 8)])
+def test_routing_products_in_each_tile_width(T, d_in, d_out, N, r, k):
+    _check_layer(LS(T, d_in, d_out, N, r, k, 2.0, "bf16", "zipf", "products"), seed=70, rows="sample")
+
+
 def test_dense_route_exact_ties_and_zero_gate():
     """Duplicated gate columns tie exactly: the lower index wins on this path too; a zero gate picks 0..k-1."""
     shape = LS(300, 512, 264, 12, 8, 3, 2.0, "bf16")
