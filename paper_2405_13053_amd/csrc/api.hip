@@ -4,6 +4,8 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
+
 #include "../../include/meteora.h"
 #include "common.hpp"
 #include "kernels.hpp"
@@ -29,6 +31,10 @@ bool shape_ok(int T, int d_in, int d_out, int N, int r, int k) {
 // 300 tokens (0.63) 61.6 and 70.5, 512 (1.1) 83.0 and 68.7; 14336 -> 4096 of rank 32 512 tokens (1.1) 163 and 211.
 bool expand_by_rows_applies(int T, int d_in, int d_out, int r, int k) {
     return 2.0 * T * k * r * d_out <= (T <= 64 ? 2.6e8 : 4e8) + 6e4 * d_in;
+}
+// the largest batch of more than 64 tokens it takes (or fewer: none)
+int expand_by_rows_tokens(int d_in, int d_out, int r, int k) {
+    return (int)std::min((4e8 + 6e4 * d_in) / (2.0 * k * r * d_out), 1e9);
 }
 
 // Decode in two launches (gate logits and every adapter's shrink inside the GEMM's launch, then routing + reduce +
@@ -66,7 +72,8 @@ int dense_midsplit_splits(int T, int d_in, int d_out, int N, int r, int k, bool 
 // splits that fit change at multiples of 128 tokens, and at two row tiles' worth per column tile there are none left.
 int64_t midsplit_pairs_reserved(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
     int64_t most = 0;
-    const int last = 256 * 128 / (ceil_div(d_out, 128) + ceil_div(prep_wcat_rows(N, r), 128));
+    int last = 256 * 128 / (ceil_div(d_out, 128) + ceil_div(prep_wcat_rows(N, r), 128));
+    if (prep_wcat_rows(N, r) > kWcatMaxRows) last = std::min(last, expand_by_rows_tokens(d_in, d_out, r, k));
     for (int t = T < last ? T : last; t > 64; t = (t - 1) / 128 * 128) {
         const int64_t pairs = (int64_t)dense_midsplit_splits(t, d_in, d_out, N, r, k, bf16, true) * t;
         most = pairs > most ? pairs : most;
@@ -731,7 +738,9 @@ extern "C" size_t meteora_group_workspace_bytes(const int* d_out, int G, int T, 
         fused(Td, gemm_decode_plan(d_in, d_out, G, gate_rows).S);
         const bool all_packed[kMaxDecodeGroup] = {true, true, true, true};
         // at most 320 tiles of 128 rows; the splits that fit change at multiples of 128 tokens
-        for (int t = T < 128 * 320 / (2 * G) ? T : 128 * 320 / (2 * G); t > 64; t = (t - 1) / 128 * 128)
+        int last = std::min(T, 128 * 320 / (2 * G));
+        for (int g = 0; g < G && gate_rows > kWcatMaxRows; ++g) last = std::min(last, expand_by_rows_tokens(d_in, d_out[g], r, k));
+        for (int t = last; t > 64; t = (t - 1) / 128 * 128)
             if (const int S = group_mid_splits(d_out, all_packed, G, t, d_in, N, r, k, bf16, true)) fused(t, S);
     }
     return need;

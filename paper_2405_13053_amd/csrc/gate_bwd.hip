@@ -484,6 +484,7 @@ GateBackwardLayout gate_backward_layout(int T, int d_in, int d_out, int N, int r
     L.ext = (int)align_up((size_t)NR + 3 * kBwdNP, 64);
     L.hx = take((size_t)T * L.ext * sizeof(uint16_t));
     L.xt = take((size_t)d_in * L.ext * sizeof(uint16_t));
+    L.dxpart = take(gemm_few_tile_bytes(T, d_out, d_in));
     L.total = off;
     return L;
 }
@@ -533,7 +534,10 @@ hipError_t launch_gate_backward(const void* x, const void* dy, const void* wcat,
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (dx != nullptr) {
         // dx = dy * W_t^T continued over hx * Xt^T: the forward's GEMM with d_in and d_out swapped
-        e = launch_gemm(dy, W_t, T, d_out, d_in, true, ws + L.hx, L.ext, xt, L.ext, dx, 0, nullptr, stream);
+        float* dxpart = reinterpret_cast<float*>(ws + L.dxpart);
+        e = gemm_few_tile_splits(T, d_out, d_in) > 0
+                ? launch_gemm_few_tiles(dy, W_t, T, d_out, d_in, ws + L.hx, L.ext, xt, L.ext, dx, dxpart, stream)
+                : launch_gemm(dy, W_t, T, d_out, d_in, true, ws + L.hx, L.ext, xt, L.ext, dx, 0, T <= 64 ? dxpart : nullptr, stream);
         if (e != hipSuccess) return e;
     }
     const WgradPlan plan = wgrad_plan(T, d_in);

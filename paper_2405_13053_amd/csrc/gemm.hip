@@ -15,10 +15,17 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(const float* __
     const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n8) return;
     f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s < nsplit; ++s) {
-        const float* src = partial + (size_t)s * T * d_out + i * 8;
-        lo += *reinterpret_cast<const f32x4*>(src);
-        hi += *reinterpret_cast<const f32x4*>(src + 4);
+    for (int s0 = 0; s0 < nsplit; s0 += 4) {   // tiles in order, four tiles' loads in flight
+        f32x4 v0[4], v1[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float* src = partial + (size_t)min(s0 + u, nsplit - 1) * T * d_out + i * 8;
+            v0[u] = *reinterpret_cast<const f32x4*>(src);
+            v1[u] = *reinterpret_cast<const f32x4*>(src + 4);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (s0 + u < nsplit) { lo += v0[u]; hi += v1[u]; }
     }
     u32x4* dst = reinterpret_cast<u32x4*>(out) + i;
     if (accumulate) {
@@ -292,6 +299,52 @@ hipError_t launch_gemm_dense_splitk_multi(const void* x, const DenseOperand* ops
 }
 
 bool gemm_fuses_expand(bool bf16) { return bf16; }
+
+// The input gradient of a few hundred tokens: few output tiles and a long contraction, so K is split as in the few-tile layers,
+// the extension going with the last split, and a second launch adds the tiles and rounds once.  Where the model of gemm_multi_splits
+// says so, a launch being 4.5 us: a short contraction, or enough tiles for one sweep, lose (training steps, one sweep and
+// split: 1000 x 4096 -> 1024 62 and 72 us, 800 x 4096 -> 4096 105 and 113).  Training steps with the input gradient, one sweep
+// and so: 64 x 4096 -> 14336 220 and 105 us, 300 x 4096 -> 4096 78.5 and 70.2, 375 x 5120 -> 13824 267 and 208, 512 x 4096 ->
+// 14336 250 and 191, 2000 x 1024 -> 14336 241 and 195.
+int gemm_few_tile_splits(int T, int d_in, int d_out) {
+    const int col_tiles = ceil_div(d_out, 128), nk = ceil_div(d_in, kGemmBK), row_tiles = 256 / col_tiles;
+    if (T <= 64 || row_tiles < 1 || !gemm_dense_splitk_ok(T, d_in, d_out)) return 0;
+    const int S = gemm_multi_splits(T, col_tiles, gemm_multi_fit(T, d_in, d_out), nk, d_out);
+    if (S < 2) return 0;
+    auto tile_us = [](int blocks) { return 0.2f + 0.07f * (float)(blocks < 4 ? 4 : blocks); };
+    const float one = tile_us(ceil_div(ceil_div(T, row_tiles), 32)) * (float)nk;   // launch_gemm's tiles
+    const float split = tile_us(gemm_multi_row_blocks(T)) * (float)ceil_div(nk, S) + 0.45e-6f * 4.f * (float)T * (float)d_out * (float)S;
+    return split + 4.5f < one ? S : 0;
+}
+
+size_t gemm_few_tile_bytes(int T, int d_in, int d_out) {
+    int64_t pairs = 0;   // tokens times splits of any batch of up to T tokens: what fits changes at multiples of 128
+    const int last = 256 * 128 / ceil_div(d_out, 128);
+    for (int t = T < last ? T : last; t > 64; t = (t - 1) / 128 * 128) {
+        const int64_t p = (int64_t)gemm_multi_splits_reserved(t, ceil_div(d_out, 128), gemm_multi_fit(t, d_in, d_out)) * t;
+        pairs = p > pairs ? p : pairs;
+    }
+    const size_t few = gemm_splitk_bytes(T < 64 ? T : 64, d_in, d_out, true), many = (size_t)pairs * d_out * sizeof(float);
+    return few > many ? few : many;
+}
+
+hipError_t launch_gemm_few_tiles(const void* x, const void* W, int T, int d_in, int d_out, const void* hdense, int ext_stride,
+                                 const void* Bt, int ext_k, void* out, float* partial, hipStream_t stream) {
+    const int S = gemm_few_tile_splits(T, d_in, d_out);
+    GemmArgs a{};
+    a.x = (const bf16_t*)x; a.W = (const bf16_t*)W; a.hd = (const bf16_t*)hdense; a.Bt = (const bf16_t*)Bt;
+    a.T = T; a.d_in = d_in; a.d_out = d_out; a.ext_k = ext_k; a.ext_stride = ext_stride;
+    a.partial = partial; a.splits = S; a.tiles_n = ceil_div(d_out, 128);
+    if (S < 2 || ext_stride % kGemmBK != 0 || ext_stride < ext_k || !dma_ok(a, 256, 128)) return hipErrorInvalidValue;
+    a.tiles_per_split = ceil_div(ceil_div(d_in, kGemmBK), S);
+    const bool two = T <= 128 && a.tiles_n * S > 256;
+    const hipError_t e = (int64_t)d_out * d_in * 2 <= kWriteThroughWeights ? launch_multi_tiles<kEpiPartialThrough>(a, two, stream)
+                                                                           : launch_multi_tiles<kEpiPartial>(a, two, stream);
+    if (e != hipSuccess) return e;
+    const size_t n8 = (size_t)T * d_out / 8;
+    gemm_splitk_reduce_kernel<<<(unsigned)((n8 + 255) / 256), 256, 0, stream>>>(partial, S, T, d_out, (bf16_t*)out, 0);
+    return hipGetLastError();
+}
 
 // every kernel of this file that a launcher above may start with more than the default dynamic LDS
 hipError_t gemm_init_kernels() {

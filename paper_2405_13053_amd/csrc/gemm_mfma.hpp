@@ -62,8 +62,9 @@ struct GemmArgs {
     int topk, rank;
     int accumulate;       // 1: add previous contents of out
     int tiles_m, tiles_n;
-    // split-K (skinny batches): blockIdx.y = split; split s < splits takes K tiles [s*tiles_per_split, ...),
-    // split == splits (only if ext_k > 0) takes the expand extension; fp32 tiles go to partial[split][T][d_out]
+    // split-K (skinny batches): blockIdx.y = split; split s < splits takes K tiles [s*tiles_per_split, ...), and the expand
+    // extension (if ext_k > 0) is the last split's too in the ring kernel, split == splits in the two-slot one; fp32 tiles go
+    // to partial[split][T][d_out]
     float* partial;       // nullptr: no split, the kernel writes `out` itself
     int splits, tiles_per_split;
     // few-tile batches (fp32 tiles of the ring kernel only): the column tiles of one launch may belong to
@@ -902,15 +903,10 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
     int kt0 = 0, nk_main = a.d_in / kGemmBK, nk_part = a.d_in % kGemmBK != 0 ? 1 : 0;
     int nk_ext = a.ext_k > 0 ? a.ext_stride / kGemmBK : 0;
     if (a.partial != nullptr) {
-        const int split = blockIdx.y;
-        if (split < a.splits) {
-            kt0 = split * a.tiles_per_split;
-            if (nk_main < kt0 || nk_main >= kt0 + a.tiles_per_split) nk_part = 0;
-            nk_main = max(0, min(a.tiles_per_split, nk_main - kt0));
-            nk_ext = 0;
-        } else {
-            nk_main = nk_part = 0;
-        }
+        kt0 = (int)blockIdx.y * a.tiles_per_split;
+        if (nk_main < kt0 || nk_main >= kt0 + a.tiles_per_split) nk_part = 0;
+        nk_main = max(0, min(a.tiles_per_split, nk_main - kt0));
+        if ((int)blockIdx.y != a.splits - 1) nk_ext = 0;
     }
     const bool look = LOOK && nk_ext > 0 && a.topk_idx != nullptr;   // uniform
     ExtIds<BM> ids;

@@ -190,7 +190,7 @@ hipError_t launch_decode_tail_group(const DecodeMember* mem, int G, const SplitP
 // dx (optional, bf16 [T, d_in]): the input gradient; needs A, W_gate and W_t = the base weight transposed,
 // [d_in, d_out].
 constexpr int kGateBackwardMaxTokens = 65536;
-struct GateBackwardLayout { size_t part_x, part_dy, dgs, wpart, bpart, hx, xt, total; int ext; };
+struct GateBackwardLayout { size_t part_x, part_dy, dgs, wpart, bpart, hx, xt, dxpart, total; int ext; };
 bool gate_backward_applies(int T, int d_in, int d_out, int N, int r, bool bf16);
 GateBackwardLayout gate_backward_layout(int T, int d_in, int d_out, int N, int r);
 hipError_t launch_gate_backward(const void* x, const void* dy, const void* wcat, const void* B, const float* bias,
@@ -211,6 +211,12 @@ bool gemm_fuses_expand(bool bf16);
 // topk_idx[T,k], r (optional): the routing that hdense was made from; K tiles of the extension that are zero for all
 // tokens of an output tile are left out.
 size_t gemm_splitk_bytes(int T, int d_in, int d_out, bool bf16);
+// bf16, more than 64 tokens with few output tiles: K splits of a launch of fp32 tiles and one that adds them (0: launch_gemm), and
+// the scratch that any batch of up to T tokens takes (launch_gemm's splitk_ws up to 64)
+int gemm_few_tile_splits(int T, int d_in, int d_out);
+size_t gemm_few_tile_bytes(int T, int d_in, int d_out);
+hipError_t launch_gemm_few_tiles(const void* x, const void* W, int T, int d_in, int d_out, const void* hdense, int ext_stride,
+                                 const void* Bt, int ext_k, void* out, float* partial, hipStream_t stream);
 hipError_t launch_gemm(const void* x, const void* W, int T, int d_in, int d_out, bool bf16,
                        const void* hdense, int ext_stride, const void* Bt, int ext_k,
                        void* out, int accumulate, float* splitk_ws, hipStream_t stream,

@@ -64,7 +64,19 @@ def test_gate_backward_matches_oracle(shape, beta):
     assert float(dl.sum(dim=1).abs().max()) <= 1e-5 * max(1.0, float(dl.abs().max()))
 
 
-@pytest.mark.parametrize("shape", BACKWARD_SHAPES, ids=lambda s: s.name)
+# The input gradient with its contraction (d_out) split: 64 tokens on the two-slot kernel, two and more splits on each tile height,
+# two workgroups per CU, the extension behind a last split that is shorter than the others.
+SPLIT_DX_SHAPES = [
+    LS(64, 256, 2048, 28, 8, 2, 2.0, "bf16", "zipf", "T=64-two-slot"),
+    LS(65, 256, 4096, 28, 8, 2, 2.0, "bf16", "uniform", "T=65-96-rows"),
+    LS(128, 16640, 4096, 5, 8, 1, 2.0, "bf16", "uniform", "T=128-two-per-CU"),
+    LS(150, 512, 4160, 28, 16, 2, 2.0, "bf16", "zipf", "T=150-short-last-split"),
+    LS(300, 1024, 4096, 28, 8, 2, 2.0, "bf16", "uniform", "T=300-160-rows"),
+    LS(450, 1024, 4096, 7, 32, 3, 2.0, "bf16", "zipf", "T=450-256-rows"),
+]
+
+
+@pytest.mark.parametrize("shape", BACKWARD_SHAPES + SPLIT_DX_SHAPES, ids=lambda s: s.name)
 def test_gate_backward_input_gradient_matches_oracle(shape):
     """dx (bf16 storage, fp32 accumulation: the forward's output bar, 5e-3 of the largest entry) with a
     classification weight large enough that the gate term is a visible part of it; the other outputs are the
