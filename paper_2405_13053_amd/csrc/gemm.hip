@@ -140,7 +140,9 @@ static hipError_t launch_skinny(GemmArgs a, hipStream_t stream) {
 // 176.4 (176.3), 8192 227.2, 221.8 (223.1); 3000 x 5120 -> 5120 144.1, 136.0 (137.5), 4096 x 14336 -> 1024 193.7, 183.0
 // (183.0); of rank 16 4096 x 4096 -> 4096 132.2, 127.1 (127.0), 16384 x 14336 -> 1024 584.6, 567.2 (567.3); lora_forward of rank 8
 // 3000 x 5120 -> 1024 32.2, 29.8 (31.1), 8000 x 4096 -> 1024 42.7, 40.0 (40.9); a training step of 4096 x 4096 -> 4096 266.9,
-// 262.1 (263.9).  128 x 160 with one split loses: 6000 tokens of rank 16 215 against 211.
+// 262.1 (263.9).  128 x 160 with one split loses: 6000 tokens of rank 16 215 against 211; and where the contraction is long beside the
+// fp32 tiles that 320 columns need for their extra splits: 5000 x 14336 -> 1024 198 against 195, 8192 x 14336 -> 4096 696 against 692;
+// with 6144 inputs 8192 tokens 130 against 137.
 struct DenseTile { int nb, splits; };   // columns in blocks of 32
 
 static int dense_split_bounds(int S, int nk) {
@@ -154,7 +156,7 @@ static int dense_wide_blocks(int rows) { return ceil_div(ceil_div(rows, ceil_div
 static DenseTile dense_tile(int T, int d_in, int rows) {
     const int nk = ceil_div(d_in, kGemmBK), row_tiles = ceil_div(T, 128), four = ceil_div(rows, 128), five = ceil_div(rows, 160);
     auto fits = [&](int tiles) { return dense_split_bounds(256 / tiles, nk) == dense_split_bounds(256 / tiles, 32); };   // K does not bind
-    if (five * 160 <= four * 128 && 2 * row_tiles * five <= 256 && fits(row_tiles * five))
+    if (five * 160 <= four * 128 && 2 * row_tiles * five <= 256 && (T <= 4096 || nk <= 96) && fits(row_tiles * five))
         return {5, dense_split_bounds(256 / (row_tiles * five), nk)};
     const int nb = dense_wide_blocks(rows), tiles = row_tiles * ceil_div(rows, 32 * nb);
     if (nb > 4 && (T > 4096 || (T > 2048 && fits(tiles)))) return {nb, dense_split_bounds(256 / tiles, nk)};
