@@ -292,6 +292,8 @@ struct GateRows {
 // as there, so that a token's routing is the same in gate_topk, in the launches of the larger layers and here.  The rows
 // of x and W_gate that belong to w's parts pass through LDS (`staged`, this wavefront's own: no barrier); a lane takes a part
 // (two or four adjacent ones where N leaves fewer than 4 columns) of 4 tokens and 4 columns.
+// TOK tokens at a time: four take more than 128 registers.
+template <int TOK>
 __device__ __forceinline__ void gate_rows_f32(const __amdgpu_buffer_rsrc_t xr, const __amdgpu_buffer_rsrc_t gr, int m0, int T,
                                               int d_in, int N, int w, int lane, float* staged,
                                               float (&gate)[16][kF32LayerAdapters + 4]) {
@@ -334,36 +336,38 @@ __device__ __forceinline__ void gate_rows_f32(const __amdgpu_buffer_rsrc_t xr, c
     const int first = g.mine > 16 ? pl * local : pl & (g.mine - 1);
     const int c0 = (pl >> g.mine_log2) * 4;
 #pragma unroll 1
-    for (int t0 = (lane >> 4) * 4, half = 0; half < 2; ++half, t0 += 2) {   // two tokens at a time: 128 registers at most
-        f32x4 sum[2], held[2];
+    for (int t0 = (lane >> 4) * 4, left = 4; left > 0; left -= TOK, t0 += TOK) {
+        f32x4 sum[TOK], held[TOK];
 #pragma unroll 1
         for (int n = 0; n < local; ++n) {
-            f32x4 a[4][2];   // [chain][token]
+            f32x4 a[4][TOK];   // [chain][token]
 #pragma unroll
-            for (int u = 0; u < 4; ++u) a[u][0] = a[u][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int t = 0; t < TOK; ++t) a[u][t] = f32x4{0.f, 0.f, 0.f, 0.f};
             const float* xl = xs + t0 * g.x_row + first + n;
             const float* wl = ws + (first + n) * g.stride + c0;
             for (int m = 0; m < g.M; m += 4) {
                 f32x4 wq[4];
-                float xq[4][2];
+                float xq[4][TOK];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int at = min(m + u, g.M - 1) << g.mine_log2;
                     wq[u] = *reinterpret_cast<const f32x4*>(wl + (at << g.stride_log2));
-                    xq[u][0] = xl[at];
-                    xq[u][1] = xl[g.x_row + at];
+#pragma unroll
+                    for (int t = 0; t < TOK; ++t) xq[u][t] = xl[t * g.x_row + at];
                 }
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     if (m + u >= g.M) break;   // uniform
 #pragma unroll
-                    for (int t = 0; t < 2; ++t)
+                    for (int t = 0; t < TOK; ++t)
 #pragma unroll
                         for (int j = 0; j < 4; ++j) a[u][t][j] = fmaf(xq[u][t], wq[u][j], a[u][t][j]);
                 }
             }
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {   // the lane's parts in pairs, then pairs of pairs
+            for (int t = 0; t < TOK; ++t) {   // the lane's parts in pairs, then pairs of pairs
                 const f32x4 v = (a[0][t] + a[1][t]) + (a[2][t] + a[3][t]);
                 if (n == 0) sum[t] = v;
                 else if (n == 1) sum[t] = sum[t] + v;
@@ -375,7 +379,7 @@ __device__ __forceinline__ void gate_rows_f32(const __amdgpu_buffer_rsrc_t xr, c
         // its sum in all lanes of a group, so that a mirrored lane is as good as the one across)
         auto across = [&](auto ctrl) {
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+            for (int t = 0; t < TOK; ++t)
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
                     sum[t][j] += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, (float)sum[t][j]),
@@ -386,19 +390,23 @@ __device__ __forceinline__ void gate_rows_f32(const __amdgpu_buffer_rsrc_t xr, c
         if (g.mine >= 8) across(std::integral_constant<int, 0x141>{});    // row_half_mirror
         if (g.mine >= 16) across(std::integral_constant<int, 0x140>{});   // row_mirror
         if ((pl & (g.mine - 1)) == 0) {
-            *reinterpret_cast<f32x4*>(&gate[t0][c0]) = sum[0];
-            *reinterpret_cast<f32x4*>(&gate[t0 + 1][c0]) = sum[1];
+#pragma unroll
+            for (int t = 0; t < TOK; ++t) *reinterpret_cast<f32x4*>(&gate[t0 + t][c0]) = sum[t];
         }
     }
 }
 
-template <int EB>
-__global__ __launch_bounds__(kF32LayerThreads, EB == 2 ? 4 : 2) void layer_f32_kernel(
+// ALONE: at most one workgroup per CU (256 tiles, and always with four blocks of adapter columns, see layer_f32_applies), which then
+// has twice the registers: a fourth K step in flight and four tokens of the gate at a time.  GPU alone, two tokens and 128 registers as for
+// two workgroups, and so: 64 x 256 -> 256, 4 adapters of rank 8 8.06 and 7.99 us, 64 x 512 -> 512 10.07 and 9.81, 8 adapters 64 x 168
+// -> 256 8.36 and 8.03, 13 of rank 4 64 x 128 -> 256 9.78 and 9.17.
+template <int EB, bool ALONE>
+__global__ __launch_bounds__(kF32LayerThreads, EB == 2 && !ALONE ? 4 : 2) void layer_f32_kernel(
     const float* __restrict__ x, const float* __restrict__ W, const float* __restrict__ W_gate,
     const float* __restrict__ bias, const float* __restrict__ A, const float* __restrict__ B, int T, int d_in, int d_out,
     int N, int r, int k, float inv_temperature, float scale, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
     float* __restrict__ out) {
-    constexpr int TN = 16, C = (1 + EB) * 16, AHEAD = EB == 2 ? 3 : 4;
+    constexpr int TN = 16, C = (1 + EB) * 16, AHEAD = EB == 2 && !ALONE ? 3 : 4;
     __shared__ __attribute__((aligned(16))) float red[4][16][C + 4];
     __shared__ __attribute__((aligned(16))) float gate[4][16][kF32LayerAdapters + 4];   // gate_row's sums per wavefront
     __shared__ int sel_idx[16][kMaxTopK];
@@ -422,7 +430,7 @@ __global__ __launch_bounds__(kF32LayerThreads, EB == 2 ? 4 : 2) void layer_f32_k
     const __amdgpu_buffer_rsrc_t xr = resource(x, T * ld), wr = resource(W, d_out * ld), gr = resource(W_gate, ld * N),
                                  ar = resource(A, (uint32_t)NR * ld);
     if (wave >= 4) {
-        gate_rows_f32(xr, gr, m0, T, d_in, N, wave - 4, lane, staged + (wave - 4) * GateRows(d_in, N).wave_floats(),
+        gate_rows_f32<ALONE ? 4 : 2>(xr, gr, m0, T, d_in, N, wave - 4, lane, staged + (wave - 4) * GateRows(d_in, N).wave_floats(),
                       gate[wave - 4]);
     } else {
         const int s0 = wave * steps / 4, s1 = (wave + 1) * steps / 4;
@@ -580,7 +588,8 @@ hipError_t launch_layer_f32(const float* x, const float* W, const float* W_gate,
                                                                  inv_temperature, scale, topk_idx, topk_w, out);
         return hipGetLastError();
     };
-    return N * r <= 32 ? go(layer_f32_kernel<2>) : go(layer_f32_kernel<4>);
+    if (N * r > 32) return go(layer_f32_kernel<4, true>);
+    return tiles <= 256 ? go(layer_f32_kernel<2, true>) : go(layer_f32_kernel<2, false>);
 }
 
 }  // namespace meteora

@@ -398,6 +398,11 @@ def test_fp32_layer_in_one_launch(T, d_in, d_out, N, r, k):
 
 
 # fp32 routing is one sum in one order, whichever launches run: gate_topk, the layer in one launch, the layer in two or three
+@pytest.mark.parametrize("T,d_in,d_out,N,r,k", [(129, 40, 520, 4, 8, 2), (512, 256, 256, 4, 8, 2), (256, 248, 256, 4, 8, 4)])
+def test_fp32_layer_in_one_launch_around_one_workgroup_per_cu(T, d_in, d_out, N, r, k):
+    _check_layer(LS(T, d_in, d_out, N, r, k, 2.0, "f32", "uniform", "f32-two-per-CU"), seed=71)
+
+
 @pytest.mark.parametrize("d_in,d_out,N,r,k", [
     (256, 256, 4, 8, 2), (8, 8, 1, 1, 1), (256, 256, 16, 2, 8), (72, 264, 16, 4, 3), (512, 8, 4, 8, 1), (328, 136, 2, 16, 2),
     (64, 904, 7, 8, 3), (168, 40, 1, 64, 1), (248, 40, 11, 2, 4), (200, 64, 3, 8, 3), (128, 256, 16, 2, 2), (256, 264, 1, 32, 1),
