@@ -442,10 +442,7 @@ static meteora_status run_lora(const void* x, const void* W, const void* A, cons
                                   pk.apack, at<float>(ws, L.hpart), fused ? nullptr : h32,
                                   fused ? at<void>(ws, L.hdense) : nullptr, L.ext_stride, st));
     }
-    if (W == nullptr && bf16 && expand_dense_applies(T, d_out, N * r, L.ext_stride)) {
-        StageScope sc(ST_EXPAND, st, tslot);
-        METEORA_HIP(launch_expand_dense(at<void>(ws, L.hdense), L.ext_stride, B, N * r, T, d_out, out, accumulate, st));
-    } else if (fused) {
+    if (fused) {
         // base projection (if W is given) and LoRA expand in one MFMA kernel, one rounding of the output
         StageScope sc(ST_GEMM, st, tslot);
         METEORA_HIP(launch_gemm(x, W, T, W ? d_in : 0, d_out, bf16, at<void>(ws, L.hdense), L.ext_stride,
@@ -473,31 +470,27 @@ meteora_status meteora_lora_forward(const void* x, const void* A, const void* B,
     const WsLayout L = ws_layout(T, d_in, d_out, N, r, k, bf16);
     if (!ws || !aligned256(ws) || ws_bytes < L.total) return METEORA_ERR_WORKSPACE;
     if (T == 0) return METEORA_OK;
-    const bool direct = bf16 && expand_dense_applies(T, d_out, N * r, L.ext_stride);   // reads B as it is
     if (lora_dense_applies(T, d_in, N, r, k, bf16)) {
         // x * A_i of every adapter in one MFMA launch, then the selected columns as the expand operand: three short
         // launches fewer than bucket lists and grouped shrink, and x is read in order
         hipStream_t st = static_cast<hipStream_t>(stream);
         const int tslot = timing_begin_call(st);
         float* part = at<float>(ws, L.dpart);
-        METEORA_HIP(launch_prep(nullptr, nullptr, A, nullptr, direct ? nullptr : B, at<void>(ws, L.btrans), at<void>(ws, L.wcat),
-                                d_in, d_out, N, r, st));
+        METEORA_HIP(launch_prep(nullptr, nullptr, A, nullptr, B, at<void>(ws, L.btrans), at<void>(ws, L.wcat), d_in, d_out,
+                                N, r, st));
         {
             StageScope sc(ST_SHRINK, st, tslot);
             METEORA_HIP(launch_gemm_dense_splitk(x, at<void>(ws, L.wcat), T, d_in, N * r, part, st));
             METEORA_HIP(launch_dense_expand_operand(part, gemm_dense_splits(T, d_in, N * r), topk_idx, topk_w, T, N, r, k,
                                                     scale, at<void>(ws, L.hdense), L.ext_stride, st));
         }
-        StageScope sc(ST_EXPAND, st, tslot);
-        if (direct)
-            METEORA_HIP(launch_expand_dense(at<void>(ws, L.hdense), L.ext_stride, B, N * r, T, d_out, out, accumulate, st));
-        else
-            METEORA_HIP(launch_gemm(x, nullptr, T, 0, d_out, bf16, at<void>(ws, L.hdense), L.ext_stride, at<void>(ws, L.btrans),
-                                    N * r, out, accumulate, nullptr, st, topk_idx, k, r));
+        StageScope sc(ST_GEMM, st, tslot);
+        METEORA_HIP(launch_gemm(x, nullptr, T, 0, d_out, bf16, at<void>(ws, L.hdense), L.ext_stride, at<void>(ws, L.btrans),
+                                N * r, out, accumulate, nullptr, st, topk_idx, k, r));
         return METEORA_OK;
     }
     {
-        const bool pa = shrink_apack_bytes(d_in, N, r, bf16) > 0, pb = !direct && prep_btrans_bytes(d_out, N, r, bf16) > 0;
+        const bool pa = shrink_apack_bytes(d_in, N, r, bf16) > 0, pb = prep_btrans_bytes(d_out, N, r, bf16) > 0;
         METEORA_HIP(launch_prep(nullptr, nullptr, pa ? A : nullptr, pa ? at<void>(ws, L.apack) : nullptr,
                                 pb ? B : nullptr, pb ? at<void>(ws, L.btrans) : nullptr, nullptr, d_in, d_out, N, r,
                                 static_cast<hipStream_t>(stream)));

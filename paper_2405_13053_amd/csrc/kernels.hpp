@@ -17,7 +17,6 @@ hipError_t gemm_decode_init_kernels();
 hipError_t gate_init_kernels();
 hipError_t shrink_init_kernels();
 hipError_t gate_bwd_init_kernels();
-hipError_t expand_init_kernels();
 hipError_t bucket_init_scratch();
 
 // ---- weight repacking, one launch: W_gate -> split bf16 fragments (bf16 gate), A -> MFMA fragments,
@@ -132,12 +131,6 @@ hipError_t launch_shrink(const void* x, const void* A, const int32_t* topk_idx, 
 hipError_t launch_expand(const float* h32, const void* B, const int32_t* topk_idx, const float* topk_w,
                          int T, int d_out, int N, int r, int k, float scale, bool bf16, void* out,
                          int accumulate, hipStream_t stream);
-
-// bf16, the expand alone from the dense operand hdense[T, ext_stride] (ext_k columns in use, at most 256), B as it is stored:
-// out (+)= hdense * B viewed as [ext_k, d_out].  Where it does not apply, launch_gemm with d_in = 0 and B packed does the same.
-bool expand_dense_applies(int T, int d_out, int ext_k, int ext_stride);
-hipError_t launch_expand_dense(const void* hdense, int ext_stride, const void* B, int ext_k, int T, int d_out, void* out,
-                               int accumulate, hipStream_t stream);
 
 // ---- fp32 storage (layer_f32.hip): the base projection, and the rest of the layer onto it
 hipError_t launch_gemm_f32(const float* x, const float* W, int T, int d_in, int d_out, float* out, hipStream_t stream);

@@ -45,8 +45,6 @@ hipError_t init_kernels() {
     if (e != hipSuccess) return e;
     e = gemm_decode_init_kernels();
     if (e != hipSuccess) return e;
-    e = expand_init_kernels();
-    if (e != hipSuccess) return e;
     e = gate_init_kernels();
     if (e != hipSuccess) return e;
     e = shrink_init_kernels();

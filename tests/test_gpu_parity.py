@@ -211,31 +211,6 @@ def test_lora_accumulate_in_each_tile_shape(T, d_out, N, r):
     assert util.rel_max_err(out, old.double().cpu().numpy() + ref) <= util.tol(shape)
 
 
-# The expand alone on wide outputs: one row to many groups of 32 rows, a slab of which 8 columns are left, 1 to 8 K steps with the last
-# one partly used, ranks whose columns straddle steps, an adapter nobody chose whose B is infinite.  (Rank 1 with all three
-# adapters: one factor and the output are each rounded to bf16, 2^-8 at the most, which a single product shows in full.)
-@pytest.mark.parametrize("T,d_out,N,r,k", [(65, 4104, 28, 8, 2), (97, 4096, 3, 1, 3), (2600, 4360, 16, 16, 3), (300, 14344, 4, 8, 2),
-                                           (7000, 4096, 20, 12, 2), (1025, 5120, 32, 8, 1)])
-@pytest.mark.parametrize("accumulate", [False, True])
-def test_lora_with_wide_outputs(T, d_out, N, r, k, accumulate):
-    shape = LS(T, 64, d_out, N, r, k, 2.0, "bf16")
-    ops, dev = util.make_case(shape, seed=38, condition=False)
-    rng = np.random.default_rng(9)
-    idx = np.argsort(rng.random((T, N)), 1)[:, :k].astype(np.int32)
-    w = rng.uniform(0.2, 0.8, (T, k)).astype(np.float32)
-    if N * r >= 128:                       # the last adapter and, in its K step, the three before it: nobody's
-        idx = np.argsort(rng.random((T, N - 4)), 1)[:, :k].astype(np.int32)
-        dev["B"][N - 1] = float("inf")
-    old = torch.randn((T, d_out), device="cuda", generator=torch.Generator(device="cuda").manual_seed(6)).bfloat16()
-    out = m.lora_forward(dev["x"], dev["A"], dev["B"], torch.from_numpy(idx).cuda(), torch.from_numpy(w).cuda(), 2.0,
-                         out=old.clone(), accumulate=accumulate)
-    rows = np.unique(np.concatenate([np.arange(0, T, 37), np.arange(max(0, T - 40), T)]))
-    ref = oracle.lora_delta(ops["x"][rows], ops["A"], ops["B"], idx[rows], w[rows].astype(np.float64), 2.0)
-    if accumulate:
-        ref = ref + old.double().cpu().numpy()[rows]
-    assert util.rel_max_err(out[torch.from_numpy(rows).cuda()], ref) <= util.tol(shape)
-
-
 # Routing that leaves most of the expand's K tiles (64 columns of N*r) empty: the first or last tile alone, tiles far
 # apart, a rank that straddles tiles, and in the second half of the tokens other adapters than in the first.
 @pytest.mark.parametrize("N,r,used", [(28, 8, (27,)), (28, 8, (0, 9)), (64, 32, (3, 40, 63)), (9, 24, (2, 5)), (28, 16, (4,))])
@@ -568,8 +543,8 @@ def test_layer_of_any_width(T, d_in, d_out, N, r, k):
 
 # More than 32 adapters and ranks that are no multiple of 8 or no power of two on every launch sequence: decode with 1 to 16
 # splits (equal ones, and runs that cut the gate rows' two tiles in different places), a few hundred tokens, dense routing,
-# bucketed.  (Rank 1 with all three adapters: one factor of the expand and the output are each rounded to bf16, 2^-8 at the most, and
-# with a single product both show in full: 5.6e-3 of the largest sampled output.)
+# bucketed.  (Rank 1 with all three adapters: the expand operand and the output are rounded to bf16, 2^-9 each; with rank 1 and
+# one adapter a single rounded factor of up to 28 meets sampled outputs of up to 20, 3.98e-3 * 28 / 20 = 5.6e-3 of the largest.)
 @pytest.mark.parametrize("N,r,k", [(64, 32, 8), (33, 8, 2), (28, 12, 2), (5, 5, 3), (64, 64, 4), (40, 20, 3), (3, 1, 3), (28, 24, 2)])
 @pytest.mark.parametrize("T,d_in,d_out", [(1, 136, 8), (3, 4096, 264), (64, 1024, 776), (17, 512, 11008), (5, 8384, 136),
                                           (65, 512, 264), (130, 1032, 16392), (300, 512, 2056), (1300, 320, 2056)])
