@@ -76,15 +76,19 @@ static hipError_t launch_ring(K kern, const GemmArgs& a, int lds_bytes, int spli
     return hipGetLastError();
 }
 
+// Nothing behind the whole K tiles: kBehindNone.  Splits of K share one kernel, also where only the last of them has more.
+static bool whole_tiles(const GemmArgs& a) { return a.d_in % kGemmBK == 0 && a.ext_k == 0; }
+
 // One workgroup per (MB*32) x (NB*32) output tile; the output is written, or added to, by the kernel itself.
 template <int MB, int NB, int D>
 static hipError_t launch_tiles(GemmArgs a, hipStream_t stream) {
     a.tiles_m = ceil_div(a.T, MB * 32);
     a.tiles_n = ceil_div(a.d_out, NB * 32);
     constexpr int smem = gemm_ring_lds_bytes<MB, NB, D>();
-    if (a.accumulate) return launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiAccumulate, true>, a, smem, 1, stream);
-    return a.topk_idx != nullptr ? launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, true>, a, smem, 1, stream)
-                                 : launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, false>, a, smem, 1, stream);
+    if (a.accumulate) return launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiAccumulate, kBehindLook>, a, smem, 1, stream);
+    if (a.topk_idx != nullptr) return launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, kBehindLook>, a, smem, 1, stream);
+    return whole_tiles(a) ? launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, kBehindNone>, a, smem, 1, stream)
+                          : launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, kBehindAny>, a, smem, 1, stream);
 }
 
 // The same without the ring: any size.
@@ -192,7 +196,9 @@ template <int MB, int NB, int D, int EPI>
 static hipError_t launch_dense(GemmArgs a, hipStream_t stream) {   // fp32 split-K tiles; tiles_n is the caller's
     a.tiles_m = ceil_div(a.T, MB * 32);
     if (a.tiles_n == 0) a.tiles_n = ceil_div(a.d_out, NB * 32);
-    return launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, EPI, false>, a, gemm_ring_lds_bytes<MB, NB, D>(), a.splits, stream);
+    constexpr int smem = gemm_ring_lds_bytes<MB, NB, D>();
+    return whole_tiles(a) ? launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, EPI, kBehindNone>, a, smem, a.splits, stream)
+                          : launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, EPI, kBehindAny>, a, smem, a.splits, stream);
 }
 
 hipError_t launch_gemm_dense_splitk(const void* x, const void* Wcat, int T, int d_in, int rows, float* partial,
@@ -358,11 +364,14 @@ hipError_t gemm_init_kernels() {
     lim(&gemm_mfma_kernel<2, 2>, gemm_lds_bytes<2, 2>());
     lim(&gemm_mfma_kernel<1, 1>, gemm_lds_bytes<1, 1>());
     lim(&gemm_mfma_dma_kernel<1, 1>, gemm_lds_bytes<1, 1>());
-#define METEORA_RING(MB, NB, D, EPI, LOOK) lim(&gemm_mfma_ring_kernel<MB, NB, D, EPI, LOOK>, gemm_ring_lds_bytes<MB, NB, D>())
-#define METEORA_TILES(MB, NB, D)                   \
-    METEORA_RING(MB, NB, D, kEpiStore, false);     \
-    METEORA_RING(MB, NB, D, kEpiStore, true);      \
-    METEORA_RING(MB, NB, D, kEpiAccumulate, true)
+#define METEORA_RING(MB, NB, D, EPI, BEHIND) lim(&gemm_mfma_ring_kernel<MB, NB, D, EPI, BEHIND>, gemm_ring_lds_bytes<MB, NB, D>())
+#define METEORA_BOTH(MB, NB, D, EPI)              \
+    METEORA_RING(MB, NB, D, EPI, kBehindNone);    \
+    METEORA_RING(MB, NB, D, EPI, kBehindAny)
+#define METEORA_TILES(MB, NB, D)                       \
+    METEORA_BOTH(MB, NB, D, kEpiStore);                \
+    METEORA_RING(MB, NB, D, kEpiStore, kBehindLook);   \
+    METEORA_RING(MB, NB, D, kEpiAccumulate, kBehindLook)
     METEORA_TILES(8, 8, 2);
     METEORA_TILES(8, 4, 3);
     METEORA_TILES(7, 4, 3);
@@ -370,15 +379,15 @@ hipError_t gemm_init_kernels() {
     METEORA_TILES(5, 4, 4);
     METEORA_TILES(4, 4, 3);
     METEORA_TILES(4, 4, 2);
-    METEORA_RING(4, 10, 2, kEpiPartialThrough, false);
-    METEORA_RING(4, 5, 3, kEpiPartialThrough, false);
-    METEORA_RING(4, 6, 3, kEpiPartialThrough, false);
-    METEORA_RING(4, 7, 3, kEpiPartialThrough, false);
-    METEORA_RING(4, 8, 2, kEpiPartialThrough, false);
-    METEORA_RING(4, 9, 2, kEpiPartialThrough, false);
-#define METEORA_PARTIAL(MB, NB, D)                   \
-    METEORA_RING(MB, NB, D, kEpiPartial, false);     \
-    METEORA_RING(MB, NB, D, kEpiPartialThrough, false)
+    METEORA_BOTH(4, 10, 2, kEpiPartialThrough);
+    METEORA_BOTH(4, 5, 3, kEpiPartialThrough);
+    METEORA_BOTH(4, 6, 3, kEpiPartialThrough);
+    METEORA_BOTH(4, 7, 3, kEpiPartialThrough);
+    METEORA_BOTH(4, 8, 2, kEpiPartialThrough);
+    METEORA_BOTH(4, 9, 2, kEpiPartialThrough);
+#define METEORA_PARTIAL(MB, NB, D)           \
+    METEORA_BOTH(MB, NB, D, kEpiPartial);    \
+    METEORA_BOTH(MB, NB, D, kEpiPartialThrough)
     METEORA_PARTIAL(4, 4, 2);
     METEORA_PARTIAL(3, 4, 2);
     METEORA_PARTIAL(3, 4, 5);
@@ -389,6 +398,7 @@ hipError_t gemm_init_kernels() {
     METEORA_PARTIAL(8, 4, 3);
 #undef METEORA_PARTIAL
 #undef METEORA_TILES
+#undef METEORA_BOTH
 #undef METEORA_RING
     return e;
 }

@@ -864,11 +864,17 @@ __device__ __forceinline__ void for_each_phase(std::integer_sequence<int, PH...>
     (f(std::integral_constant<int, PH>{}), ...);
 }
 
-// LOOK: whether the kernel looks for empty tiles of the extension.  The base projection and the backward pass have a
-// kernel without: the code alone, not run, costs a short call with cold weights 0.8 us (65 x 1024 -> 4096 11.5 against 10.6).
-template <int MB, int NB, int D, int EPI, bool LOOK>
+// BEHIND: which K tiles there may be behind the whole ones of the main operands: none, any (see PartTile), or any, and the kernel
+// looks for empty tiles of the extension.  Code that is not run costs a short call with cold weights 0.8 us (65 x 1024 -> 4096 11.5
+// with the look against 10.6), and two more buffer resources and the tests of what there is cost the others 0.3 to 0.5% and more:
+// whole calls, any and none, 300 x 4096 -> 4096 25.1 and 24.7 us, 1531 x 4096 -> 1024 of rank 16 37.2 and 36.4, 3000 x 5120 -> 5120
+// from its parts 170.4 and 169.1, a training step of 4096 x 4096 -> 4096 263.9 and 261.7.
+constexpr int kBehindNone = 0, kBehindAny = 1, kBehindLook = 2;
+
+template <int MB, int NB, int D, int EPI, int BEHIND>
 __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in) {
     GemmArgs a = a_in;
+    constexpr bool LOOK = BEHIND == kBehindLook, ANY = BEHIND != kBehindNone;
     constexpr int BM = MB * 32, BN = NB * 32;   // 2 x 2 wavefronts of MB x NB blocks of 16 x 16
     constexpr int PX = BM / 32, PW = BN / 32;   // pieces per wavefront per tile
     static_assert((NB % 2 == 0 || MB % 2 == 0) && D >= 2 && (D - 1) * (PX + PW) < 64, "whole 2 x 2 micro-blocks; vmcnt holds 6 bits");
@@ -900,8 +906,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
     }
 
     // this workgroup's share of the contraction: whole K tiles [kt0, kt0 + nk_main), the partial one, and/or the extension
-    int kt0 = 0, nk_main = a.d_in / kGemmBK, nk_part = a.d_in % kGemmBK != 0 ? 1 : 0;
-    int nk_ext = a.ext_k > 0 ? a.ext_stride / kGemmBK : 0;
+    int kt0 = 0, nk_main = a.d_in / kGemmBK, nk_part = ANY && a.d_in % kGemmBK != 0 ? 1 : 0;
+    int nk_ext = ANY && a.ext_k > 0 ? a.ext_stride / kGemmBK : 0;
     if (a.partial != nullptr) {
         kt0 = (int)blockIdx.y * a.tiles_per_split;
         if (nk_main < kt0 || nk_main >= kt0 + a.tiles_per_split) nk_part = 0;
@@ -970,7 +976,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
     };
 #pragma unroll
     for (int t = 0; t < D; ++t)
-        if (t >= nk_main && t < nk) request_tile(t, next_ext(), std::true_type{});
+        if (ANY && t >= nk_main && t < nk) request_tile(t, next_ext(), std::true_type{});
 
     Frags16<MB, NB> f0, f1;
     // tile t is needed next: the loads of at most `left` tiles, requested after it, may still be in flight
@@ -1079,7 +1085,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
     if (idle) {
         for (; it < nk - (half_last ? 1 : 0); ++it) {
             if (it + D < nk) {
-                const bool ext = it + D >= nk_main;
+                const bool ext = ANY && it + D >= nk_main;
                 const int kt = ext ? next_ext() : kt0 + it + D;
 #pragma unroll
                 for (int i = 0; i < PW; ++i) {
@@ -1112,7 +1118,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
         slot_w = (int)(wslot(it) - smem);
     }
     for (; it + D < nk_main; ++it) tile_step(it, Req0{}, Rt{});
-    for (; it + D < nk; ++it) tile_step(it, std::integral_constant<int, 1>{}, Rt{});
+    if constexpr (ANY)
+        for (; it + D < nk; ++it) tile_step(it, std::integral_constant<int, 1>{}, Rt{});
     for (; it < nk - (half_last ? 1 : 0); ++it) tile_step(it, std::integral_constant<int, 2>{}, Rt{});
     if (half_last && !idle) {   // read, behind the barrier, in the previous step's last phase
         mfmas(f0, 0, NM);
