@@ -9,7 +9,7 @@ namespace meteora {
 
 namespace {
 constexpr int kMaxDevices = 64;
-constexpr int kMaxKernels = 64;
+constexpr int kMaxKernels = 128;   // those that gemm_init_kernels and the others list: about 90
 struct LdsEntry { const void* kernel; uint64_t done; };   // bit d: the limit is set on device d
 LdsEntry g_lds[kMaxKernels];
 int g_lds_count = 0;
