@@ -38,13 +38,13 @@ int expand_by_rows_tokens(int d_in, int d_out, int r, int k) {
 }
 
 // Decode in two launches (gate logits and every adapter's shrink inside the GEMM's launch, then routing + reduce +
-// expand): whatever the widths and adapters.  Four launches (gate logits, top-k with the shrink, split GEMM, reduction), as
+// expand): whatever the widths (below 8 million inputs) and adapters.  Four launches (gate logits, top-k with the shrink, split GEMM, reduction), as
 // widths off 64, fewer than 512 inputs and more than 32704 outputs had, and so: 1 token of 4104 -> 4096 24.0 and 15.1 us, 64 27.8
 // and 20.1, 49 x 320 -> 2920 of rank 16 packed per call 21.6 and 16.9, 1 x 4096 -> 40960 89.5 and 60.5, 64 95.5 and 81.4.
 // 64 adapters of rank 32, top-4 and top-8, 4096 -> 4096, 1 token 61.3 and 89.1 against 23.2 and 33.7, 64 tokens 66.5 and 95.4
 // against 29.8 and 39.6, though 2240 more rows are streamed; 28 adapters of rank 12, 40.2 and 45.0 against 15.3 and 19.2.
 bool decode_fused_applies(int T, int d_in, int d_out, int r, int k, bool bf16) {
-    return bf16 && T <= 64 && expand_by_rows_applies(T, d_in, d_out, r, k);
+    return bf16 && T <= 64 && gemm_decode_ok(d_in) && expand_by_rows_applies(T, d_in, d_out, r, k);
 }
 
 // Mid-sized batches whose 128 x 128 output tiles would leave most CUs idle (a few hundred tokens): the base
@@ -60,7 +60,7 @@ int dense_midsplit_splits(int T, int d_in, int d_out, int N, int r, int k, bool 
     // against 60.5, 200 36.6 against 61.7, 512 58.2 against 63.6; 14336 -> 4096 top-8 T = 300 123 against 170; but not with two
     // workgroups per CU (4096 -> 14336 T = 65 91.0 against 84.9, 128 143 against 95.7).
     const int CR = prep_wcat_rows(N, r);
-    if (!bf16 || T <= 64 || !gemm_dense_splitk_ok(T, d_in, CR) || !gemm_dense_splitk_ok(T, d_in, d_out)) return 0;
+    if (!bf16 || T <= 64 || !gemm_multi_ok(T, d_in, CR) || !gemm_multi_ok(T, d_in, d_out)) return 0;
     const int col_tiles = ceil_div(d_out, 128) + ceil_div(CR, 128), fit = gemm_multi_fit(T, d_in, d_out);
     if (CR > kWcatMaxRows && (2 * ceil_div(T, 256) * col_tiles > 256 || !expand_by_rows_applies(T, d_in, d_out, r, k))) return 0;
     const int S = reserve ? gemm_multi_splits_reserved(T, col_tiles, fit)
@@ -676,10 +676,10 @@ bool group_fused(const int* d_out, const bool* packed, int G, int T, int d_in, i
 int group_mid_splits(const int* d_out, const bool* packed, int G, int T, int d_in, int N, int r, int k, bool bf16,
                      bool reserve = false) {
     const int cat_rows = prep_wcat_rows(N, r);
-    if (G < 2 || G > kMaxDecodeGroup || !bf16 || T <= 64 || !gemm_dense_splitk_ok(T, d_in, cat_rows)) return 0;
+    if (G < 2 || G > kMaxDecodeGroup || !bf16 || T <= 64 || !gemm_multi_ok(T, d_in, cat_rows)) return 0;
     int64_t tiles = 0;
     for (int g = 0; g < G; ++g) {
-        if (!packed[g] || d_out[g] % 8 != 0 || !gemm_dense_splitk_ok(T, d_in, d_out[g])) return 0;
+        if (!packed[g] || d_out[g] % 8 != 0 || !gemm_multi_ok(T, d_in, d_out[g])) return 0;
         if (cat_rows > kWcatMaxRows && !expand_by_rows_applies(T, d_in, d_out[g], r, k)) return 0;
         tiles += (int64_t)ceil_div(T, 128) * (ceil_div(d_out[g], 128) + ceil_div(cat_rows, 128));
     }

@@ -173,6 +173,11 @@ bool gemm_dense_splitk_ok(int T, int d_in, int rows) {
            ((uint64_t)rows + 5 * 64) * widest < (1ull << 32) && (uint64_t)rows * 4 * 256 < (1ull << 32);
 }
 
+// the same for tiles of up to 256 rows (launch_gemm_dense_splitk_multi, launch_gemm_few_tiles)
+bool gemm_multi_ok(int T, int d_in, int rows) {
+    return gemm_dense_splitk_ok(T, d_in, rows) && ((uint64_t)T + 256) * ((uint64_t)d_in * 2) < (1ull << 32);
+}
+
 int gemm_dense_splits(int T, int d_in, int rows) { return dense_tile(T, d_in, rows).splits; }
 
 // The K splits that few-tile launches start from (see gemm_multi_splits)
@@ -292,7 +297,7 @@ hipError_t launch_gemm_dense_splitk_multi(const void* x, const DenseOperand* ops
     int tile0 = 0;
     int64_t rows = 0;
     for (int i = 0; i < n_ops; ++i) {
-        if (!gemm_dense_splitk_ok(T, d_in, ops[i].rows)) return hipErrorInvalidValue;
+        if (!gemm_multi_ok(T, d_in, ops[i].rows)) return hipErrorInvalidValue;
         a.seg[i] = {(const bf16_t*)ops[i].W, ops[i].partial, ops[i].rows, tile0};
         tile0 += ceil_div(ops[i].rows, 128);
         rows += ops[i].rows;
@@ -300,7 +305,6 @@ hipError_t launch_gemm_dense_splitk_multi(const void* x, const DenseOperand* ops
     a.nseg = n_ops;
     a.W = a.seg[0].W; a.d_out = a.seg[0].rows; a.partial = a.seg[0].partial;   // replaced per workgroup
     a.tiles_n = tile0;
-    if (((uint64_t)T + 256) * ((uint64_t)d_in * 2) >= (1ull << 32)) return hipErrorInvalidValue;
     const bool two = T <= 128 && tile0 * S > 256;   // two per CU
     return rows * d_in * 2 <= kWriteThroughWeights ? launch_multi_tiles<kEpiPartialThrough>(a, two, stream)
                                                    : launch_multi_tiles<kEpiPartial>(a, two, stream);
@@ -316,7 +320,7 @@ bool gemm_fuses_expand(bool bf16) { return bf16; }
 // 14336 250 and 191, 2000 x 1024 -> 14336 241 and 195.
 int gemm_few_tile_splits(int T, int d_in, int d_out) {
     const int col_tiles = ceil_div(d_out, 128), nk = ceil_div(d_in, kGemmBK), row_tiles = 256 / col_tiles;
-    if (T <= 64 || row_tiles < 1 || !gemm_dense_splitk_ok(T, d_in, d_out)) return 0;
+    if (T <= 64 || row_tiles < 1 || !gemm_multi_ok(T, d_in, d_out)) return 0;
     const int S = gemm_multi_splits(T, col_tiles, gemm_multi_fit(T, d_in, d_out), nk, d_out);
     if (S < 2) return 0;
     auto tile_us = [](int blocks) { return 0.2f + 0.07f * (float)(blocks < 4 ? 4 : blocks); };

@@ -211,10 +211,13 @@ SplitPlan gemm_decode_plan(int d_in, const int* d_out, int G, int gate_rows) {
     return p;
 }
 
+// the offsets inside a row tile of W, and of the rows and columns outside it (kOutside), fit
+bool gemm_decode_ok(int d_in) { return (uint64_t)kStreamRows * d_in * 2 < (1ull << 31); }
+
 hipError_t launch_gemm_decode_main(const void* x, const DecodeMember* mem, int G, int gate_rows, const SplitPlan& plan,
                                    int T, int d_in, hipStream_t stream) {
     if (gate_rows % 8 != 0 || G < 1 || G > kMaxDecodeGroup || T < 1 || T > 64 || d_in % 8 != 0 || plan.S < 1 ||
-        plan.nk != ceil_div(d_in, kStreamK) || (uint64_t)kStreamRows * d_in * 2 >= (1ull << 31))
+        plan.nk != ceil_div(d_in, kStreamK) || !gemm_decode_ok(d_in))
         return hipErrorInvalidValue;
     StreamArgs a{};
     a.x = (const bf16_t*)x; a.T = T; a.d_in = d_in; a.nk = plan.nk; a.plan = plan;

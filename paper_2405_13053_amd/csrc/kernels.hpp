@@ -67,6 +67,7 @@ hipError_t launch_route_dense_select(const float* part, const float* bias, int T
                                      void* hdense, int ext_stride, hipStream_t stream);
 // the GEMM behind launch_route_dense_products: partial[split][T][rows] = x * Wcat^T over the split's K range
 bool gemm_dense_splitk_ok(int T, int d_in, int rows);
+bool gemm_multi_ok(int T, int d_in, int rows);
 int gemm_dense_splits(int T, int d_in, int rows);
 int gemm_multi_fit(int T, int d_in, int rows);
 // few-tile split-K launches over several matrices (col_tiles: the 128-column tiles of all of them, rows: their rows): S
@@ -174,6 +175,7 @@ constexpr int kSplitRows = 128;
 struct SplitPlan {
     int S, nk, per_wg;
 };
+bool gemm_decode_ok(int d_in);
 SplitPlan gemm_decode_plan(int d_in, const int* d_out, int G, int gate_rows);
 hipError_t launch_gemm_decode_main(const void* x, const DecodeMember* mem, int G, int gate_rows, const SplitPlan& plan,
                                    int T, int d_in, hipStream_t stream);

@@ -111,6 +111,14 @@ def test_the_size_of_a_workspace_never_falls(d_in, d_out, N, r):
         assert sizes == sorted(sizes)
 
 
+@pytest.mark.parametrize("T,d_in,region,taken", [(1, 8388600, "gpart", True), (1, 8388608, "gpart", False), (64, 8388616, "gpart", False),
+                                                 (600, 2508600, "spart", True), (600, 2508752, "spart", False)])
+def test_contractions_beyond_32_bit_offsets_keep_the_general_sequence(T, d_in, region, taken):
+    """The two-launch forms address a row tile of W in 31 bits (decode) and x with 256 rows more in 32 (few tiles)."""
+    regs = {n: w for n, _, _, w in m.workspace_regions(T, d_in, 8, 2, 4, 1, "bf16", True)}
+    assert (regs[region] > 0) == taken
+
+
 @pytest.mark.parametrize("T", [65, 96, 128])
 @pytest.mark.parametrize("d_out", [16008, 16384, 18432, 19584])
 def test_wide_layers_of_up_to_128_tokens_split_along_k(T, d_out):
