@@ -91,6 +91,16 @@ static hipError_t launch_tiles(GemmArgs a, hipStream_t stream) {
                           : launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, kBehindAny>, a, smem, 1, stream);
 }
 
+// Few tiles and no extension: base projections of few tokens.
+template <int MB, int NB, int D>
+static hipError_t launch_small_tiles(GemmArgs a, hipStream_t stream) {
+    a.tiles_m = ceil_div(a.T, MB * 32);
+    a.tiles_n = ceil_div(a.d_out, NB * 32);
+    constexpr int smem = gemm_ring_lds_bytes<MB, NB, D>();
+    return whole_tiles(a) ? launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, kBehindNone>, a, smem, 1, stream)
+                          : launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, kBehindAny>, a, smem, 1, stream);
+}
+
 // The same without the ring: any size.
 template <int M>
 static hipError_t launch_plain(GemmArgs a, hipStream_t stream) {
@@ -383,6 +393,9 @@ hipError_t gemm_init_kernels() {
     METEORA_TILES(5, 4, 4);
     METEORA_TILES(4, 4, 3);
     METEORA_TILES(4, 4, 2);
+    METEORA_BOTH(2, 2, 5, kEpiStore);
+    METEORA_BOTH(3, 2, 5, kEpiStore);
+    METEORA_BOTH(4, 2, 4, kEpiStore);
     METEORA_BOTH(4, 10, 2, kEpiPartialThrough);
     METEORA_BOTH(4, 5, 3, kEpiPartialThrough);
     METEORA_BOTH(4, 6, 3, kEpiPartialThrough);
@@ -424,6 +437,19 @@ hipError_t launch_gemm(const void* x, const void* W, int T, int d_in, int d_out,
             a.splits = S;
             a.tiles_per_split = ceil_div(ceil_div(d_in, kGemmBK), S);
             return launch_skinny(a, stream);
+        }
+        // A base projection of few tokens (no extension, and no workspace to split K in): tiles of 64 columns, as low as one per CU
+        // allows, 64 to 128 rows.  It is bound by how many CUs stream W and by the bytes they have in flight: against 64 x 64 tiles
+        // with two slots up to 64 tokens and 128 x 128 above, W not in any cache, 1, 64, 96 and 300 tokens: 4096 -> 4096 45.0, 45.5,
+        // 35.1, 30.2 and 15.5, 21.2, 17.7, 19.0 us; 14336 -> 4096 151, 152, 129, 104 and 48.1, 70.2, 57.2, 59.0; 4096 -> 1024 28.0, 28.3,
+        // 24.2, 28.0 and 11.7, 12.6, 12.6, 12.6; 5120 -> 13824 58.3, 58.8, 59.9 and 25.5, 36.2, 45.0.  128-row tiles only: 200 x 5120 ->
+        // 5120 38.0, and 24.8 with 96 rows; rings as deep as LDS allows (9, 7, 6): 1 us slower at most sizes.
+        const int row_tiles_64 = 256 / ceil_div(d_out, 64);
+        if (a.ext_k == 0 && !accumulate && row_tiles_64 > 0 && dma_ok(a, 128, 64)) {
+            const int blocks = ceil_div(ceil_div(T, row_tiles_64), 32);
+            if (blocks <= 2) return launch_small_tiles<2, 2, 5>(a, stream);
+            if (blocks == 3) return launch_small_tiles<3, 2, 5>(a, stream);
+            if (blocks == 4) return launch_small_tiles<4, 2, 4>(a, stream);
         }
         const int64_t big_tiles = (int64_t)ceil_div(T, 256) * ceil_div(d_out, 256);
         // 256 x 256 tiles once they fill most of the 256 CUs; below that 128 x 128 tiles keep more CUs busy

@@ -196,6 +196,19 @@ def test_base_gemm_partial_k_tile(T, d_out, d_in):
     assert float(((out - ref).abs() - 2.0 ** -8 * ref.abs()).max()) <= 1e-4
 
 
+# Base projections of few tokens, tiles of 64 columns: each height at its least and largest batch, ragged in both directions, with
+# fewer K tiles than the ring is deep, as many, one more, and partial ones; and the next batch, which takes 128 columns.
+@pytest.mark.parametrize("d_in", [8, 64, 256, 320, 328, 384, 1000])
+@pytest.mark.parametrize("T,d_out", [(1, 8), (16, 16384), (64, 4104), (192, 4104), (193, 4104), (288, 4104), (289, 4104), (384, 4104),
+                                     (385, 4104), (1, 16392), (2048, 72)])
+def test_base_gemm_of_few_tokens(T, d_out, d_in):
+    _, dev = util.make_case(LS(T, d_in, d_out, 2, 2, 1, 1.0, "bf16"), seed=38, condition=False)
+    out = m.base_gemm(dev["x"], dev["W"])
+    ref = dev["x"].double() @ dev["W"].double().t().contiguous()
+    # one bf16 rounding of an fp32 sum: half an ulp (2^-9 of the value), fp32 summation error far below it
+    assert float(((out.double() - ref).abs() - 2.0 ** -8 * ref.abs()).max()) <= 1e-4
+
+
 # accumulate = 1 in each tile shape: the old output is read, added in fp32 and rounded once; ranks whose last
 # extension K tile is a half (N*r % 64 <= 32) and a whole one
 @pytest.mark.parametrize("N,r", [(28, 8), (7, 8)], ids=["half-tile", "whole-tile"])
