@@ -14,9 +14,10 @@
 // 64 through LDS tiles whose rows are 128 B, their 16-B chunks XOR-swizzled with the row index (see swz) so that a
 // ds_read_b128 pass touches every bank once; W is the MFMA's first operand, so a lane ends up with 4 consecutive output
 // columns of one token row):
-//   gemm_mfma_ring_kernel  more than 64 tokens, and every fp32-tile launch: v_mfma_f32_16x16x32_bf16 on a ring of LDS
-//                          slots that global->LDS loads fill two to five K tiles ahead;
-//   gemm_mfma_dma_kernel   up to 64 tokens: 64 x 64 tiles, v_mfma_f32_32x32x16_bf16, two slots;
+//   gemm_mfma_ring_kernel  more than 64 tokens, base projections of up to 16384 outputs, and every fp32-tile launch of more than
+//                          64: v_mfma_f32_16x16x32_bf16 on a ring of LDS slots that global->LDS loads fill two to five K
+//                          tiles ahead;
+//   gemm_mfma_dma_kernel   otherwise up to 64 tokens: 64 x 64 tiles, v_mfma_f32_32x32x16_bf16, two slots;
 //   gemm_mfma_kernel       sizes whose byte offsets pass 32 bits: v_mfma_f32_32x32x16_bf16, tiles through registers into
 //                          two LDS buffers.
 #pragma once
