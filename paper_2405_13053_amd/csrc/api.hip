@@ -43,8 +43,14 @@ int expand_by_rows_tokens(int d_in, int d_out, int r, int k) {
 // and 20.1, 49 x 320 -> 2920 of rank 16 packed per call 21.6 and 16.9, 1 x 4096 -> 40960 89.5 and 60.5, 64 95.5 and 81.4.
 // 64 adapters of rank 32, top-4 and top-8, 4096 -> 4096, 1 token 61.3 and 89.1 against 23.2 and 33.7, 64 tokens 66.5 and 95.4
 // against 29.8 and 39.6, though 2240 more rows are streamed; 28 adapters of rank 12, 40.2 and 45.0 against 15.3 and 19.2.
-bool decode_fused_applies(int T, int d_in, int d_out, int r, int k, bool bf16) {
-    return bf16 && T <= 64 && gemm_decode_ok(d_in) && expand_by_rows_applies(T, d_in, d_out, r, k);
+// The token count does not decide, so that a token is routed by the same sums in every decode batch: the rows of B that 64 tokens
+// read do (64 adapters of rank 64, top-8, 4096 -> 14336, tail and bucketed, 1 token 65 and 90, 30 tokens 87 and 97, 64 139 and 102).
+// Ranks 8, 16 and 32 of up to 640 rows of Wcat, at most 256 rows of B per token, take the tail whatever the outputs: 28 adapters of
+// rank 16, top-8, 64 tokens, bucketed and tail 512 -> 28672 46.0 and 39.0, 4096 -> 32704 107 and 86; 17 of rank 32 4096 -> 32704 32
+// tokens 104 and 83, 64 110 and 109, 512 -> 32704 1 token 49 and 34, 32 45 and 47, 64 50 and 71.
+bool decode_fused_applies(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
+    if (!bf16 || T > 64 || !gemm_decode_ok(d_in)) return false;
+    return ((r == 8 || r == 16 || r == 32) && prep_wcat_rows(N, r) <= kWcatMaxRows) || expand_by_rows_applies(64, d_in, d_out, r, k);
 }
 
 // Mid-sized batches whose 128 x 128 output tiles would leave most CUs idle (a few hundred tokens): the base
@@ -296,7 +302,7 @@ int meteora_workspace_regions(int T, int d_in, int d_out, int N, int r, int k, m
     const int CR = prep_wcat_rows(N, r);
     const int S_mid = dense_midsplit_splits(T, d_in, d_out, N, r, k, bf16);
     const bool dense = S_mid > 0 || route_dense_applies(T, d_in, N, r, bf16);
-    const bool decode3 = decode_fused_applies(T, d_in, d_out, r, k, bf16);
+    const bool decode3 = decode_fused_applies(T, d_in, d_out, N, r, k, bf16);
     wr("topk_idx", pairs * sizeof(int32_t));
     wr("topk_w", pairs * sizeof(float));
     if (!with_packed) {
@@ -567,7 +573,7 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
     // mid-sized batch: gate logits and the shrink of every adapter in one MFMA launch, selection afterwards
     const int S_mid = dense_midsplit_splits(T, d_in, d_out, N, r, k, bf16);
     const bool dense = S_mid > 0 || route_dense_applies(T, d_in, N, r, bf16);
-    const bool decode3 = decode_fused_applies(T, d_in, d_out, r, k, bf16);
+    const bool decode3 = decode_fused_applies(T, d_in, d_out, N, r, k, bf16);
     PackedPtrs pk{at<void>(ws, L.wsplit), at<void>(ws, L.apack), at<void>(ws, L.btrans), at<void>(ws, L.wcat)};
     if (use_packed) {
         void* blob = const_cast<void*>(packed);   // read only from here on
@@ -663,10 +669,10 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
 namespace {
 
 // Fused form: decode-sized batch, every member with packed weights.
-bool group_fused(const int* d_out, const bool* packed, int G, int T, int d_in, int r, int k, bool bf16) {
+bool group_fused(const int* d_out, const bool* packed, int G, int T, int d_in, int N, int r, int k, bool bf16) {
     if (G < 2 || G > kMaxDecodeGroup) return false;
     for (int g = 0; g < G; ++g)
-        if (!packed[g] || !decode_fused_applies(T, d_in, d_out[g], r, k, bf16)) return false;
+        if (!packed[g] || !decode_fused_applies(T, d_in, d_out[g], N, r, k, bf16)) return false;
     return true;
 }
 
@@ -799,7 +805,7 @@ extern "C" meteora_status meteora_linear_forward_group(const void* x, const mete
         METEORA_HIP(launch_decode_tail_group(mem, G, SplitPlan{S, 0, 0}, T, N, r, k, cat_rows, inv_temperature, scale, st));
         return METEORA_OK;
     }
-    if (!group_fused(d_outs, is_packed, G, T, d_in, r, k, bf16)) {
+    if (!group_fused(d_outs, is_packed, G, T, d_in, N, r, k, bf16)) {
         // the same result one layer after the other (they share the workspace, which the stream order allows)
         for (int g = 0; g < G; ++g) {
             const meteora_group_member& m = members[g];
