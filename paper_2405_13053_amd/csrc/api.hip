@@ -47,7 +47,7 @@ int expand_by_rows_tokens(int d_in, int d_out, int r, int k) {
 // read do (64 adapters of rank 64, top-8, 4096 -> 14336, tail and bucketed, 1 token 65 and 90, 30 tokens 87 and 97, 64 139 and 102).
 // Ranks 8, 16 and 32 of up to 640 rows of Wcat, at most 256 rows of B per token, take the tail whatever the outputs: 28 adapters of
 // rank 16, top-8, 64 tokens, bucketed and tail 512 -> 28672 46.0 and 39.0, 4096 -> 32704 107 and 86; 17 of rank 32 4096 -> 32704 32
-// tokens 104 and 83, 64 110 and 109, 512 -> 32704 1 token 49 and 34, 32 45 and 47, 64 50 and 71.
+// tokens 104 and 83, 64 110 and 109, 512 -> 32704 45 and 47, 50 and 71.
 bool decode_fused_applies(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
     if (!bf16 || T > 64 || !gemm_decode_ok(d_in)) return false;
     return ((r == 8 || r == 16 || r == 32) && prep_wcat_rows(N, r) <= kWcatMaxRows) || expand_by_rows_applies(64, d_in, d_out, r, k);
