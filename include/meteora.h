@@ -198,9 +198,14 @@ meteora_status meteora_linear_forward(const void* x, const void* W, const float*
  *                          of repacking into the workspace.  `packed` = NULL behaves as
  *                          meteora_linear_forward.  The results are bit-identical.
  *                          W_gate, A and B are still required and must be the tensors the
- *                          blob was packed from: some paths (fp32, decode-sized batches)
- *                          read them directly.
- * Errors: METEORA_ERR_WORKSPACE if packed_bytes is smaller than meteora_packed_bytes.
+ *                          blob was packed from: some paths read them directly (fp32 all three;
+ *                          decode-sized batches and a few hundred tokens B).
+ * Errors: METEORA_ERR_WORKSPACE if packed_bytes is smaller than meteora_packed_bytes.  One smaller size
+ * is taken by the forward calls: for d_in % 64 != 0, r % 8 != 0, N > 32 or 3*32 + N*r > 640 the blob once ended in
+ * front of its last operand, the matrix of gate terms and adapter columns, (3*NP + N*R) * d_in * 2 bytes
+ * (NP = 32 or 64 >= N, R = r rounded up to a multiple of 8).  A blob kept from then, or cut there, gives the same
+ * results; a call that reads that matrix packs it into the workspace every time (batches of any other size
+ * read what the blob holds), and a group with such a member runs member by member.
  */
 size_t meteora_packed_bytes(int d_in, int d_out, int N, int r, meteora_dtype dt);
 

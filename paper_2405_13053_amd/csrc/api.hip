@@ -139,7 +139,7 @@ WsLayout ws_layout(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
 
 // Packed weights (meteora_pack_weights): the three operand layouts, each 256-byte aligned.
 // `least`: what a blob may hold at the least.  Wcat once belonged only to widths that are multiples of 64, ranks that are multiples
-// of 8, up to 32 adapters and 640 rows: a blob without it, kept in a file, is still taken, and the call packs its operands itself.
+// of 8, up to 32 adapters and 640 rows: a blob without it, kept in a file, is still taken, and a call that reads Wcat packs that itself.
 struct PackLayout { size_t wsplit, apack, btrans, wcat, total, least; };
 
 PackLayout pack_layout(int d_in, int d_out, int N, int r, bool bf16) {
@@ -563,7 +563,7 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
     if (!ws || !aligned256(ws) || ws_bytes < L.total) return METEORA_ERR_WORKSPACE;
     const PackLayout P = pack_layout(d_in, d_out, N, r, bf16);
     if (packed != nullptr && P.total > 0 && (!aligned256(packed) || packed_bytes < P.least)) return METEORA_ERR_WORKSPACE;
-    const bool use_packed = packed != nullptr && P.total > 0 && packed_bytes >= P.total;
+    const bool use_packed = packed != nullptr && P.total > 0, has_wcat = use_packed && packed_bytes >= P.total;
     if (T == 0) return METEORA_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
     int32_t* idx = topk_idx_out ? topk_idx_out : at<int32_t>(ws, L.topk_idx);
@@ -578,16 +578,18 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
     if (use_packed) {
         void* blob = const_cast<void*>(packed);   // read only from here on
         pk = PackedPtrs{at<void>(blob, P.wsplit), at<void>(blob, P.apack), at<void>(blob, P.btrans),
-                        at<void>(blob, P.wcat)};
-    } else {
-        // only the operands this batch size reads are packed
+                        has_wcat ? at<void>(blob, P.wcat) : pk.wcat};
+    }
+    // only the operands that this batch size reads and the blob does not hold are packed (a few hundred tokens and decode read B
+    // as it is)
+    const bool pw = !use_packed && !dense && !decode3 && gate_wsplit_bytes(d_in, N, bf16) > 0;
+    const bool pa = !use_packed && !dense && !decode3 && shrink_apack_bytes(d_in, N, r, bf16) > 0;
+    const bool pb = !use_packed && !decode3 && S_mid == 0 && prep_btrans_bytes(d_out, N, r, bf16) > 0;
+    const bool pc = !has_wcat && (dense || decode3);
+    if (!use_packed || pc) {
         StageScope sc(ST_PREP, st, tslot);
-        const bool pw = !dense && !decode3 && gate_wsplit_bytes(d_in, N, bf16) > 0;
-        const bool pa = !dense && !decode3 && shrink_apack_bytes(d_in, N, r, bf16) > 0;
-        const bool pb = !decode3 && S_mid == 0 && prep_btrans_bytes(d_out, N, r, bf16) > 0;
         METEORA_HIP(launch_prep(W_gate, pw ? pk.wsplit : nullptr, A, pa ? pk.apack : nullptr, pb ? B : nullptr,
-                                pb ? pk.btrans : nullptr, dense || decode3 ? pk.wcat : nullptr, d_in, d_out, N, r, st));
-        // pb: a few hundred tokens and decode read B as it is
+                                pb ? pk.btrans : nullptr, pc ? pk.wcat : nullptr, d_in, d_out, N, r, st));
     }
     if (decode3) {
         // decode-sized batch: the launch that streams W also computes the gate logits; then top-k, softmax and the

@@ -599,7 +599,7 @@ def test_padding_of_a_rank_reads_no_other_adapter(T):
 
 @pytest.mark.parametrize("d_in,N,r", [(520, 28, 8), (512, 28, 12), (512, 64, 8)], ids=["width", "rank", "adapters"])
 def test_a_blob_packed_without_the_routing_rows_is_still_taken(d_in, N, r):
-    """Blobs that once ended in front of Wcat: the call packs its operands itself, the same bits."""
+    """Blobs that once ended in front of Wcat: a call that reads it packs it itself, the same bits."""
     for T in (30, 300):
         shape = LS(T, d_in, 264, N, r, 2, 2.0, "bf16")
         _, dev = util.make_case(shape, seed=65)
@@ -613,6 +613,24 @@ def test_a_blob_packed_without_the_routing_rows_is_still_taken(d_in, N, r):
         assert torch.equal(one, two)
         with pytest.raises(m.MeteoraError):
             m.linear_forward(*args, packed=short[:-256].clone())
+
+
+def test_what_a_blob_without_the_routing_rows_holds_is_not_packed_again():
+    """64 adapters of rank 32: a call of many tokens reads the other operands alone and writes none of them into its workspace; a
+    few tokens take Wcat from there, and nothing else."""
+    bf, (d_in, d_out, N, r, k) = torch.bfloat16, (320, 2056, 64, 32, 4)
+    for T, packs in ((1300, ()), (30, ("apack",))):
+        shape = LS(T, d_in, d_out, N, r, k, 2.0, "bf16")
+        _, dev = util.make_case(shape, seed=72, condition=False)
+        whole = m.pack_weights(dev["W_gate"], dev["A"], dev["B"])
+        short = whole[:-(3 * 64 + N * r) * d_in * 2].clone()
+        ws = torch.full((m.workspace_bytes(T, d_in, d_out, N, r, k, bf),), 0xa5, dtype=torch.uint8, device="cuda")
+        args = (dev["x"], dev["W"], dev["W_gate"], None, dev["A"], dev["B"], k, 2.0)
+        assert torch.equal(m.linear_forward(*args, packed=short, ws=ws), m.linear_forward(*args, packed=whole))
+        regs = {n: (o, s) for n, o, s, _ in m.workspace_regions(T, d_in, d_out, N, r, k, bf, True)}
+        for name in ("wsplit", "apack", "btrans"):
+            o, s = regs[name]
+            assert bool((ws[o:o + s] != 0xa5).any()) == (name in packs), name
 
 
 # The routing products in each of their tile widths: 128 x 160 (320, 288 and 544 rows of Wcat, one of the last tile's columns ragged)
