@@ -78,9 +78,9 @@ meteora_status meteora_init(int device);
 
 /*
  * Scratch bytes needed by meteora_gate_topk, meteora_bucket_tokens,
- * meteora_lora_forward and meteora_linear_forward for this problem size (the
- * maximum over the four; entry points that take no d_out or r accept the
- * value computed with any legal d_out, r, e.g. 8 and 1).
+ * meteora_lora_forward and meteora_linear_forward for this problem size and for
+ * any smaller T (the maximum over the four; entry points that take no d_out or
+ * r accept the value computed with any legal d_out, r, e.g. 8 and 1).
  * Host only, no HIP call.  Returns 0 for arguments outside the limits.
  */
 size_t meteora_workspace_bytes(int T, int d_in, int d_out, int N, int r, int k, meteora_dtype dt);

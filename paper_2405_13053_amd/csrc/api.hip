@@ -56,8 +56,7 @@ bool decode_fused_applies(int T, int d_in, int d_out, int N, int r, int k, bool 
 // Mid-sized batches whose 128 x 128 output tiles would leave most CUs idle (a few hundred tokens): the base
 // projection is split along K over workgroups like the routing products (fp32 tiles), and the reduction adds the
 // LoRA expand, as for decode.  Returns the number of K splits, 0 = the fused GEMM runs instead.
-// `reserve`: as many as a workspace has room for.
-int dense_midsplit_splits(int T, int d_in, int d_out, int N, int r, int k, bool bf16, bool reserve = false) {
+int dense_midsplit_splits(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
     // measured on 4096 -> 4096, 4096 -> 14336 and 14336 -> 4096, T = 65 ... 2048: the split form wins as long as the
     // projection can still be cut into at least two K splits (see gemm_multi_splits for how many) (19.0 against 56.1 us
     // at T = 65, 36.1 against 60.1 at T = 512, 45.6 against 48.7 at T = 704, 47.6 against 48.8 at T = 768 for
@@ -69,22 +68,21 @@ int dense_midsplit_splits(int T, int d_in, int d_out, int N, int r, int k, bool 
     if (!bf16 || T <= 64 || !gemm_multi_ok(T, d_in, CR) || !gemm_multi_ok(T, d_in, d_out)) return 0;
     const int col_tiles = ceil_div(d_out, 128) + ceil_div(CR, 128), fit = gemm_multi_fit(T, d_in, d_out);
     if (CR > kWcatMaxRows && (2 * ceil_div(T, 256) * col_tiles > 256 || !expand_by_rows_applies(T, d_in, d_out, r, k))) return 0;
-    const int S = reserve ? gemm_multi_splits_reserved(T, col_tiles, fit)
-                          : gemm_multi_splits(T, col_tiles, fit, ceil_div(d_in, 64), (int64_t)d_out + CR);
+    const int S = gemm_multi_splits(T, col_tiles, fit, ceil_div(d_in, 64), (int64_t)d_out + CR);
     return S >= 2 ? S : 0;
 }
 
-// The most (token, K split) pairs that a batch of up to T tokens has in that form: a workspace holds the smaller batches too.  The
-// splits that fit change at multiples of 128 tokens, and at two row tiles' worth per column tile there are none left.
-int64_t midsplit_pairs_reserved(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
-    int64_t most = 0;
-    int last = 256 * 128 / (ceil_div(d_out, 128) + ceil_div(prep_wcat_rows(N, r), 128));
-    if (prep_wcat_rows(N, r) > kWcatMaxRows) last = std::min(last, expand_by_rows_tokens(d_in, d_out, r, k));
-    for (int t = T < last ? T : last; t > 64; t = (t - 1) / 128 * 128) {
-        const int64_t pairs = (int64_t)dense_midsplit_splits(t, d_in, d_out, N, r, k, bf16, true) * t;
-        most = pairs > most ? pairs : most;
-    }
-    return most;
+// Which sequence of launches a call of meteora_linear_forward runs.  S: its K splits (decode, few tiles, dense products).
+enum class Form { kDecode, kFewTiles, kDense, kBucketed, kF32 };
+struct LayerForm { Form form; int S; };
+
+LayerForm layer_form(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
+    if (!bf16) return {Form::kF32, 0};
+    const int CR = prep_wcat_rows(N, r);
+    if (decode_fused_applies(T, d_in, d_out, N, r, k, bf16)) return {Form::kDecode, gemm_decode_plan(d_in, &d_out, 1, CR).S};
+    if (const int S = dense_midsplit_splits(T, d_in, d_out, N, r, k, bf16)) return {Form::kFewTiles, S};
+    if (route_dense_applies(T, d_in, N, r, bf16)) return {Form::kDense, gemm_dense_splits(T, d_in, CR)};
+    return {Form::kBucketed, 0};
 }
 
 bool shape_supported(int T, int d_in, int d_out, int N, int r, int k) {
@@ -92,49 +90,95 @@ bool shape_supported(int T, int d_in, int d_out, int N, int r, int k) {
            (int64_t)T * k < (int64_t)INT32_MAX && (int64_t)T * (int64_t)(d_in > d_out ? d_in : d_out) < ((int64_t)1 << 40);
 }
 
-WsLayout ws_layout(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
+// The regions that one call writes, one behind the other; those of other forms are empty.  pairs: tokens times K splits.
+WsLayout ws_carve(Form form, int64_t pairs, int T, int d_in, int d_out, int N, int r, int k, bool lora) {
     WsLayout L{};
     size_t off = 0;
-    auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
-    const int NP = padded_adapters(N);
-    const size_t pairs = (size_t)T * k;
+    auto take = [&](bool used, size_t bytes) { size_t o = off; off = align_up(off + (used ? bytes : 0), 256); return o; };
+    const bool bf16 = form != Form::kF32, routes = !lora;
+    const bool decode = form == Form::kDecode, few = form == Form::kFewTiles, dense = form == Form::kDense;
+    const bool bucketed = form == Form::kBucketed, lists = bucketed || (lora && !bf16), expand = dense || bucketed;
+    const size_t slots = (size_t)T * k, CR = lora ? (size_t)N * wcat_rank(r) : prep_wcat_rows(N, r);
     L.ext_stride = (int)align_up((size_t)N * r, 64);
-    L.wsplit = take(gate_wsplit_bytes(d_in, N, bf16));
-    L.partials = take((size_t)gate_kslices(d_in, bf16) * T * NP * sizeof(float));
-    L.chunk_counts = take((size_t)bucket_chunks(T) * N * sizeof(int32_t));
-    take((size_t)routing_chunks_extra(T) * N * sizeof(int32_t));   // of chunk_counts
-    L.counts = take((size_t)N * sizeof(int32_t));
-    L.offsets = take((size_t)(N + 1) * sizeof(int32_t));
-    L.bucket_tok = take(pairs * sizeof(int32_t));
-    L.bucket_slot = take(pairs * sizeof(int32_t));
-    L.topk_idx = take(pairs * sizeof(int32_t));
-    L.topk_w = take(pairs * sizeof(float));
-    L.h32 = take(pairs * r * sizeof(float));
-    L.hdense = take((size_t)T * L.ext_stride * sizeof(uint16_t));
+    L.wsplit = take(bucketed && routes, gate_wsplit_bytes(d_in, N, bf16));
+    L.partials = take(bucketed && routes, (size_t)gate_kslices(d_in, bf16) * T * padded_adapters(N) * sizeof(float));
+    L.chunk_counts = take(lists, (size_t)(bucket_chunks(T) + routing_chunks_extra(T)) * N * sizeof(int32_t));
+    L.counts = take(lists, (size_t)N * sizeof(int32_t));
+    L.offsets = take(lists, (size_t)(N + 1) * sizeof(int32_t));
+    L.bucket_tok = take(lists, slots * sizeof(int32_t));
+    L.bucket_slot = take(lists, slots * sizeof(int32_t));
+    L.topk_idx = take(routes, slots * sizeof(int32_t));
+    L.topk_w = take(routes, slots * sizeof(float));
+    L.h32 = take(!bf16, slots * r * sizeof(float));
+    L.hdense = take(expand, (size_t)T * L.ext_stride * sizeof(uint16_t));
     // A packed for the bucketed sequence, or Wcat: a call reads the one or the other
-    const size_t apack = shrink_apack_bytes(d_in, N, r, bf16), wcat = prep_wcat_bytes(d_in, N, r, bf16);
-    L.apack = L.wcat = take(apack > wcat ? apack : wcat);
-    L.hpart = take(shrink_hpart_bytes(T, d_in, r, k, bf16));
-    // Decode-sized calls take splitk and gpart, larger ones spart and dpart; the latter have room for every smaller batch
-    const int CR = prep_wcat_rows(N, r), Td = T < 64 ? T : 64;
-    const size_t pairs_decode = bf16 ? (size_t)gemm_decode_plan(d_in, &d_out, 1, CR).S * Td : 0;
-    size_t tiles = pairs_decode * d_out * sizeof(float), products = pairs_decode * CR * sizeof(float);
-    auto most = [](size_t a, size_t b) { return a > b ? a : b; };
-    tiles = most(tiles, gemm_splitk_bytes(Td, d_in, d_out, bf16));   // lora_forward at such a size splits in its own way
-    if (T > 64) {
-        const size_t mid = (size_t)midsplit_pairs_reserved(T, d_in, d_out, N, r, k, bf16);
-        tiles = most(tiles, mid * d_out * sizeof(float));
-        // the routing products come in the K splits of the launch that writes them: the products launch's own count, or
-        // that of the split base projection when both share one launch (which may be the larger of the two)
-        products = most(products, most(mid * CR * sizeof(float), route_dense_part_bytes(T, d_in, N, r, bf16)));
-    }
-    L.splitk = take(T <= 64 ? tiles : 0);
-    L.btrans = take(prep_btrans_bytes(d_out, N, r, bf16));
-    L.dpart = take(T > 64 ? products : 0);
-    L.gpart = take(T <= 64 ? products : 0);
-    L.spart = take(T > 64 ? tiles : 0);
+    L.apack = L.wcat = take(bf16, bucketed ? shrink_apack_bytes(d_in, N, r, bf16) : CR * d_in * sizeof(uint16_t));
+    L.hpart = take(bucketed, shrink_hpart_bytes(T, d_in, r, k, bf16));
+    L.splitk = take(decode || (bucketed && routes), decode ? (size_t)pairs * d_out * sizeof(float) : gemm_splitk_bytes(T, d_in, d_out, bf16));
+    L.btrans = take(expand, prep_btrans_bytes(d_out, N, r, bf16));
+    L.dpart = take(few || dense, (size_t)pairs * CR * sizeof(float));
+    L.gpart = take(decode, (size_t)pairs * CR * sizeof(float));
+    L.spart = take(few, (size_t)pairs * d_out * sizeof(float));
     L.total = off;
     return L;
+}
+
+WsLayout ws_layout(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {   // of meteora_linear_forward
+    const LayerForm f = layer_form(T, d_in, d_out, N, r, k, bf16);
+    return ws_carve(f.form, (int64_t)f.S * T, T, d_in, d_out, N, r, k, false);
+}
+
+WsLayout lora_layout(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {   // of meteora_lora_forward
+    if (!bf16) return ws_carve(Form::kF32, 0, T, d_in, d_out, N, r, k, true);
+    if (!lora_dense_applies(T, d_in, N, r, k, bf16)) return ws_carve(Form::kBucketed, 0, T, d_in, d_out, N, r, k, true);
+    return ws_carve(Form::kDense, (int64_t)gemm_dense_splits(T, d_in, N * r) * T, T, d_in, d_out, N, r, k, true);
+}
+
+// meteora_gate_topk: the split gate weight, then the partial logits
+size_t gate_ws_bytes(int T, int d_in, int N, bool bf16) {
+    return align_up(gate_wsplit_bytes(d_in, N, bf16), 256) +
+           align_up((size_t)gate_kslices(d_in, bf16) * T * padded_adapters(N) * sizeof(float), 256);
+}
+
+// What the entry points that share a workspace write of it, the largest of them, for a batch of T tokens.  linear: what
+// meteora_linear_forward does (ws_layout)
+size_t ws_written(size_t linear, int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
+    return std::max({linear, lora_layout(T, d_in, d_out, N, r, k, bf16).total, gate_ws_bytes(T, d_in, N, bf16),
+                     (size_t)bucket_chunks(T) * N * sizeof(int32_t)});
+}
+size_t ws_written(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
+    return ws_written(ws_layout(T, d_in, d_out, N, r, k, bf16).total, T, d_in, d_out, N, r, k, bf16);
+}
+
+// and for any batch of up to T, since a program allocates for its largest.  Every form as it is for the largest batch that takes it,
+// with the most (token, K split) pairs that any smaller one has: the splits fall where the tokens grow.
+size_t ws_reserved(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
+    size_t need = std::max(ws_written(T, d_in, d_out, N, r, k, bf16), ws_written(std::min(T, 64), d_in, d_out, N, r, k, bf16));
+    if (!bf16 || T <= 64) return need;
+    auto add = [&](Form f, int64_t pairs, int t, bool lora) {
+        need = std::max(need, ws_carve(f, pairs, t, d_in, d_out, N, r, k, lora).total);
+    };
+    const int CR = prep_wcat_rows(N, r), NR = N * r;
+    // few tiles: the splits change downwards inside 32 tokens only; with more than 256 tiles of 128 rows there are none
+    int last = std::min(T, 256 * 128 / (ceil_div(d_out, 128) + ceil_div(CR, 128)));
+    if (CR > kWcatMaxRows) last = std::min(last, expand_by_rows_tokens(d_in, d_out, r, k));
+    int64_t pairs = 0;
+    int takes = 0;
+    for (int t = 64; t < last; t += 32)
+        if (const int S = dense_midsplit_splits(t + 1, d_in, d_out, N, r, k, bf16)) {
+            takes = std::min(t + 32, last);
+            pairs = std::max(pairs, (int64_t)S * takes);
+        }
+    if (takes > 0) add(Form::kFewTiles, pairs, takes, false);
+    const bool products = CR <= kWcatMaxRows;
+    if (products) add(Form::kDense, gemm_dense_pairs_reserved(T, d_in, CR), T, false);
+    if (!products || T > kRouteDenseMaxTokens || !gemm_dense_splitk_ok(T, d_in, CR)) add(Form::kBucketed, 0, T, false);
+    if (products && r % 8 == 0) {
+        const int most = NR <= 256 ? (k >= 2 ? T : std::min(T, 4096)) : std::min(T, 1024);   // see lora_dense_applies
+        add(Form::kDense, gemm_dense_pairs_reserved(most, d_in, NR), most, true);
+    }
+    add(Form::kBucketed, 0, T, true);
+    return need;
 }
 
 // Packed weights (meteora_pack_weights): the three operand layouts, each 256-byte aligned.
@@ -273,7 +317,7 @@ const char* meteora_status_string(meteora_status s) {
 size_t meteora_workspace_bytes(int T, int d_in, int d_out, int N, int r, int k, meteora_dtype dt) {
     if (!shape_ok(T, d_in, d_out, N, r, k) || !shape_supported(T, d_in, d_out, N, r, k)) return 0;
     if (dt != METEORA_F32 && dt != METEORA_BF16) return 0;
-    return ws_layout(T, d_in, d_out, N, r, k, dt == METEORA_BF16).total + 256;
+    return ws_reserved(T, d_in, d_out, N, r, k, dt == METEORA_BF16) + 256;
 }
 
 // Host-only audit of the workspace carving of meteora_linear_forward(_packed): for every region, where it starts,
@@ -361,15 +405,13 @@ meteora_status meteora_gate_topk(const void* x, const float* W_gate, const float
         (logits && !aligned16(logits)) || (gate_bias && !aligned4(gate_bias)))
         return METEORA_ERR_UNSUPPORTED;
     const bool bf16 = dt == METEORA_BF16;
-    const WsLayout L = ws_layout(T, d_in, 8, N, 1, k, bf16);
-    if (!ws || !aligned256(ws) || ws_bytes < L.chunk_counts) return METEORA_ERR_WORKSPACE;
+    if (!ws || !aligned256(ws) || ws_bytes < gate_ws_bytes(T, d_in, N, bf16)) return METEORA_ERR_WORKSPACE;
     if (T == 0) return METEORA_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    float* partials = at<float>(ws, L.partials);
+    float* partials = at<float>(ws, align_up(gate_wsplit_bytes(d_in, N, bf16), 256));
     if (gate_wsplit_bytes(d_in, N, bf16) > 0)
-        METEORA_HIP(launch_prep(W_gate, at<void>(ws, L.wsplit), nullptr, nullptr, nullptr, nullptr, nullptr, d_in, 8, N,
-                                1, st));
-    METEORA_HIP(launch_gate_logits(x, W_gate, T, d_in, N, bf16, at<void>(ws, L.wsplit), partials, st));
+        METEORA_HIP(launch_prep(W_gate, ws, nullptr, nullptr, nullptr, nullptr, nullptr, d_in, 8, N, 1, st));
+    METEORA_HIP(launch_gate_logits(x, W_gate, T, d_in, N, bf16, ws, partials, st));
     METEORA_HIP(launch_gate_topk(partials, gate_kslices(d_in, bf16), gate_bias, T, N, k, inv_temperature,
                                  topk_idx, topk_w, logits, nullptr, st));
     return METEORA_OK;
@@ -473,8 +515,8 @@ meteora_status meteora_lora_forward(const void* x, const void* A, const void* B,
     if (s != METEORA_OK) return s;
     if (!aligned16(topk_idx) || !aligned16(topk_w)) return METEORA_ERR_UNSUPPORTED;
     const bool bf16 = dt == METEORA_BF16;
-    const WsLayout L = ws_layout(T, d_in, d_out, N, r, k, bf16);
-    if (!ws || !aligned256(ws) || ws_bytes < L.total) return METEORA_ERR_WORKSPACE;
+    const WsLayout L = lora_layout(T, d_in, d_out, N, r, k, bf16);
+    if (!ws || !aligned256(ws) || ws_bytes < ws_written(T, d_in, d_out, N, r, k, bf16)) return METEORA_ERR_WORKSPACE;
     if (T == 0) return METEORA_OK;
     if (lora_dense_applies(T, d_in, N, r, k, bf16)) {
         // x * A_i of every adapter in one MFMA launch, then the selected columns as the expand operand: three short
@@ -559,8 +601,9 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
         (topk_idx_out && !aligned16(topk_idx_out)) || (topk_w_out && !aligned16(topk_w_out)))
         return METEORA_ERR_UNSUPPORTED;
     const bool bf16 = dt == METEORA_BF16;
-    const WsLayout L = ws_layout(T, d_in, d_out, N, r, k, bf16);
-    if (!ws || !aligned256(ws) || ws_bytes < L.total) return METEORA_ERR_WORKSPACE;
+    const LayerForm form = layer_form(T, d_in, d_out, N, r, k, bf16);
+    const WsLayout L = ws_carve(form.form, (int64_t)form.S * T, T, d_in, d_out, N, r, k, false);
+    if (!ws || !aligned256(ws) || ws_bytes < ws_written(L.total, T, d_in, d_out, N, r, k, bf16)) return METEORA_ERR_WORKSPACE;
     const PackLayout P = pack_layout(d_in, d_out, N, r, bf16);
     if (packed != nullptr && P.total > 0 && (!aligned256(packed) || packed_bytes < P.least)) return METEORA_ERR_WORKSPACE;
     const bool use_packed = packed != nullptr && P.total > 0, has_wcat = use_packed && packed_bytes >= P.total;
@@ -571,9 +614,8 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
     float* partials = at<float>(ws, L.partials);
     const int tslot = timing_begin_call(st);
     // mid-sized batch: gate logits and the shrink of every adapter in one MFMA launch, selection afterwards
-    const int S_mid = dense_midsplit_splits(T, d_in, d_out, N, r, k, bf16);
-    const bool dense = S_mid > 0 || route_dense_applies(T, d_in, N, r, bf16);
-    const bool decode3 = decode_fused_applies(T, d_in, d_out, N, r, k, bf16);
+    const int S_mid = form.form == Form::kFewTiles ? form.S : 0;
+    const bool dense = S_mid > 0 || form.form == Form::kDense, decode3 = form.form == Form::kDecode;
     PackedPtrs pk{at<void>(ws, L.wsplit), at<void>(ws, L.apack), at<void>(ws, L.btrans), at<void>(ws, L.wcat)};
     if (use_packed) {
         void* blob = const_cast<void*>(packed);   // read only from here on
@@ -679,10 +721,9 @@ bool group_fused(const int* d_out, const bool* packed, int G, int T, int d_in, i
 }
 
 // Second fused form: a few hundred tokens, every member with packed weights, few output tiles in all: the projections and
-// routing products of all members as K-split tiles of one launch, one launch with the selections and expands.  Returns the number of K splits (`reserve`: as many as a workspace has room for), 0
-// = not this form.
-int group_mid_splits(const int* d_out, const bool* packed, int G, int T, int d_in, int N, int r, int k, bool bf16,
-                     bool reserve = false) {
+// routing products of all members as K-split tiles of one launch, one launch with the selections and expands.  Returns the
+// number of K splits, 0 = not this form.
+int group_mid_splits(const int* d_out, const bool* packed, int G, int T, int d_in, int N, int r, int k, bool bf16) {
     const int cat_rows = prep_wcat_rows(N, r);
     if (G < 2 || G > kMaxDecodeGroup || !bf16 || T <= 64 || !gemm_multi_ok(T, d_in, cat_rows)) return 0;
     int64_t tiles = 0;
@@ -702,7 +743,7 @@ int group_mid_splits(const int* d_out, const bool* packed, int G, int T, int d_i
         col_tiles += ceil_div(d_out[g], 128) + ceil_div(cat_rows, 128);
         rows += d_out[g] + cat_rows;
     }
-    S = reserve ? gemm_multi_splits_reserved(T, col_tiles, S) : gemm_multi_splits(T, col_tiles, S, nk, rows);
+    S = gemm_multi_splits(T, col_tiles, S, nk, rows);
     return S < 1 ? 1 : S;
 }
 
@@ -743,13 +784,16 @@ extern "C" size_t meteora_group_workspace_bytes(const int* d_out, int G, int T, 
             const size_t f = group_layout(d_out, G, t, d_in, N, r, k, S, gate_rows).total + 256;
             need = f > need ? f : need;
         };
-        fused(Td, gemm_decode_plan(d_in, d_out, G, gate_rows).S);
         const bool all_packed[kMaxDecodeGroup] = {true, true, true, true};
-        // at most 320 tiles of 128 rows; the splits that fit change at multiples of 128 tokens
+        if (group_fused(d_out, all_packed, G, Td, d_in, N, r, k, bf16)) fused(Td, gemm_decode_plan(d_in, d_out, G, gate_rows).S);
+        // at most 320 tiles of 128 rows; the splits change downwards inside 32 tokens only
         int last = std::min(T, 128 * 320 / (2 * G));
         for (int g = 0; g < G && gate_rows > kWcatMaxRows; ++g) last = std::min(last, expand_by_rows_tokens(d_in, d_out[g], r, k));
-        for (int t = last; t > 64; t = (t - 1) / 128 * 128)
-            if (const int S = group_mid_splits(d_out, all_packed, G, t, d_in, N, r, k, bf16, true)) fused(t, S);
+        for (int t = 64; t < last; t += 32) {
+            const int S = group_mid_splits(d_out, all_packed, G, t + 1, d_in, N, r, k, bf16);
+            if (S == 0) break;
+            fused(std::min(t + 32, last), S);
+        }
     }
     return need;
 }
@@ -775,17 +819,21 @@ extern "C" meteora_status meteora_linear_forward_group(const void* x, const mete
             return METEORA_ERR_WORKSPACE;
         d_outs[g] = m.d_out;
     }
-    if (!ws || !aligned256(ws) || ws_bytes < meteora_group_workspace_bytes(d_outs, G, T, d_in, N, r, k, dt))
-        return METEORA_ERR_WORKSPACE;
-    if (T == 0) return METEORA_OK;
-    hipStream_t st = static_cast<hipStream_t>(stream);
     bool is_packed[64];
     for (int g = 0; g < G; ++g)
         is_packed[g] = members[g].packed != nullptr &&
                        members[g].packed_bytes >= pack_layout(d_in, members[g].d_out, N, r, bf16).total;
-    if (const int S = (G <= kMaxDecodeGroup ? group_mid_splits(d_outs, is_packed, G, T, d_in, N, r, k, bf16) : 0)) {
-        const int cat_rows = prep_wcat_rows(N, r);
-        const GroupLayout L = group_layout(d_outs, G, T, d_in, N, r, k, S, cat_rows);
+    const int gate_rows = prep_wcat_rows(N, r);
+    const int S_mid = T > 0 ? group_mid_splits(d_outs, is_packed, G, T, d_in, N, r, k, bf16) : 0;
+    const bool decode = S_mid == 0 && T > 0 && group_fused(d_outs, is_packed, G, T, d_in, N, r, k, bf16);
+    const SplitPlan plan = decode ? gemm_decode_plan(d_in, d_outs, G, gate_rows) : SplitPlan{S_mid, 0, 0};
+    const GroupLayout L = S_mid > 0 || decode ? group_layout(d_outs, G, T, d_in, N, r, k, plan.S, gate_rows) : GroupLayout{};
+    size_t need = L.total;
+    for (int g = 0; g < G && !decode && S_mid == 0; ++g) need = std::max(need, ws_written(T, d_in, d_outs[g], N, r, k, bf16));
+    if (!ws || !aligned256(ws) || ws_bytes < need) return METEORA_ERR_WORKSPACE;
+    if (T == 0) return METEORA_OK;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (S_mid > 0) {
         DecodeMember mem[kMaxDecodeGroup];
         DenseOperand ops[2 * kMaxDecodeGroup];
         for (int g = 0; g < G; ++g) {
@@ -796,18 +844,18 @@ extern "C" meteora_status meteora_linear_forward_group(const void* x, const mete
                                   m.topk_idx_out ? m.topk_idx_out : at<int32_t>(ws, L.idx[g]),
                                   m.topk_w_out ? m.topk_w_out : at<float>(ws, L.w[g]), m.out};
             ops[2 * g] = {mem[g].W, m.d_out, mem[g].partial};
-            ops[2 * g + 1] = {mem[g].wg3, cat_rows, mem[g].gpartial};
+            ops[2 * g + 1] = {mem[g].wg3, gate_rows, mem[g].gpartial};
         }
         const int tslot = timing_begin_call(st);
         {
             StageScope sc(ST_GEMM, st, tslot);
-            METEORA_HIP(launch_gemm_dense_splitk_multi(x, ops, 2 * G, S, T, d_in, st));
+            METEORA_HIP(launch_gemm_dense_splitk_multi(x, ops, 2 * G, S_mid, T, d_in, st));
         }
         StageScope sc(ST_SHRINK, st, tslot);
-        METEORA_HIP(launch_decode_tail_group(mem, G, SplitPlan{S, 0, 0}, T, N, r, k, cat_rows, inv_temperature, scale, st));
+        METEORA_HIP(launch_decode_tail_group(mem, G, plan, T, N, r, k, gate_rows, inv_temperature, scale, st));
         return METEORA_OK;
     }
-    if (!group_fused(d_outs, is_packed, G, T, d_in, N, r, k, bf16)) {
+    if (!decode) {
         // the same result one layer after the other (they share the workspace, which the stream order allows)
         for (int g = 0; g < G; ++g) {
             const meteora_group_member& m = members[g];
@@ -818,9 +866,6 @@ extern "C" meteora_status meteora_linear_forward_group(const void* x, const mete
         }
         return METEORA_OK;
     }
-    const int gate_rows = prep_wcat_rows(N, r);
-    const SplitPlan plan = gemm_decode_plan(d_in, d_outs, G, gate_rows);
-    const GroupLayout L = group_layout(d_outs, G, T, d_in, N, r, k, plan.S, gate_rows);
     DecodeMember mem[kMaxDecodeGroup];
     for (int g = 0; g < G; ++g) {
         const meteora_group_member& m = members[g];
@@ -854,7 +899,7 @@ meteora_status meteora_linear_forward(const void* x, const void* W, const float*
 size_t meteora_gate_backward_workspace_bytes(int T, int d_in, int d_out, int N, int r, int k, meteora_dtype dt) {
     if (!shape_ok(T, d_in, d_out, N, r, k) || !shape_supported(T, d_in, d_out, N, r, k) || T < 1) return 0;
     if (!gate_backward_applies(T, d_in, d_out, N, r, dt == METEORA_BF16)) return 0;
-    return gate_backward_layout(T, d_in, d_out, N, r).total;
+    return gate_backward_layout(T, d_in, d_out, N, r, true, true).total;
 }
 
 meteora_status meteora_gate_backward(const void* x, const void* dy, const float* gate_bias, const void* B,
@@ -880,7 +925,7 @@ meteora_status meteora_gate_backward(const void* x, const void* dy, const float*
         return METEORA_ERR_UNSUPPORTED;
     const PackLayout P = pack_layout(d_in, d_out, N, r, bf16);
     if (!aligned256(packed) || packed_bytes < P.total) return METEORA_ERR_WORKSPACE;
-    const GateBackwardLayout L = gate_backward_layout(T, d_in, d_out, N, r);
+    const GateBackwardLayout L = gate_backward_layout(T, d_in, d_out, N, r, dx != nullptr, false);
     if (!ws || !aligned256(ws) || ws_bytes < L.total) return METEORA_ERR_WORKSPACE;
     const void* wcat = static_cast<const char*>(packed) + P.wcat;
     // the forward call of a mid-sized batch leaves x * Wcat^T in its workspace: take it instead of computing it again

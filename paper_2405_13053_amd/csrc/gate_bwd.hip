@@ -447,44 +447,53 @@ bool gate_backward_applies(int T, int d_in, int d_out, int N, int r, bool bf16) 
            gemm_dense_splitk_ok(T, d_in, prep_wcat_rows(N, r)) && gemm_dense_splitk_ok(T, d_out, N * r);
 }
 
-// The slices a workspace has room for: never fewer for more tokens, as the number in use is.
-static int wgrad_slices_reserved(int T, int d_in) {
-    const int blocks = ceil_div(T, 64), want = ceil_div(512, ceil_div(d_in, kWgCols));
-    return want < blocks ? want : blocks;
-}
-
 // One workgroup per CU at most, since a few more take a second round, and 8 slices or, of more than 256 chunks, one for every
 // 32: a slice costs the reduction about 0.1 us.  Four wavefronts to a workgroup, two where a slice has 8 chunks or fewer: the
 // way of more sums through LDS costs more than the longer chains.  Whole gate_backward calls with 64 outputs, us: 5120 inputs
 // on 280 and 240 workgroups, 1000 tokens 38.0 and 31.3, 4096 57.2 and 48.3; 256 inputs in 8, 16 and 64 slices, 4096 tokens
 // 26.8, 26.0, 33.5, 8192 43.1, 40.5, 47.4; 4096 inputs with 8, 4 and 2 wavefronts, 64 tokens 24.3, 22.6, 22.0, 300 25.9, 24.3,
 // 23.8, 1000 31.1, 29.8, 29.3, 4096 44.0, 42.5, 43.1.
-struct WgradPlan { int parts, slice_chunks; };
+// most_slices never falls with more tokens, as the slices in use do: it is what a workspace has room for.
+struct WgradPlan { int parts, slice_chunks, most_slices; };
 static WgradPlan wgrad_plan(int T, int d_in) {
     const int chunks = ceil_div(T, kWgChunk), col_tiles = ceil_div(d_in, kWgCols);
     int n = chunks / 32 < 8 ? 8 : chunks / 32 < 32 ? chunks / 32 : 32;
     for (const int most : {256 / col_tiles, ceil_div(chunks, 4)})
         if (n > most) n = most;
-    const int slice_chunks = ceil_div(chunks, n < 1 ? 1 : n);
-    return {slice_chunks > 2 * kWgRing ? 4 : 2, slice_chunks};
+    if (n < 1) n = 1;
+    const int slice_chunks = ceil_div(chunks, n);
+    return {slice_chunks > 2 * kWgRing ? 4 : 2, slice_chunks, n};
 }
 
-GateBackwardLayout gate_backward_layout(int T, int d_in, int d_out, int N, int r) {
+// One after the other in the same place: the products until the kernel of d_logits has read them, the input gradient's K splits, the
+// weight gradient's slices.  reserve: room for any batch of up to T tokens, else what a call of T tokens writes (dx: with the input
+// gradient).
+GateBackwardLayout gate_backward_layout(int T, int d_in, int d_out, int N, int r, bool dx, bool reserve) {
     GateBackwardLayout L{};
     const int CR = prep_wcat_rows(N, r), NR = N * r;
-    size_t off = 0;
+    size_t off = 0, shared = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off = align_up(off + bytes, 256); return o; };
-    L.part_x = take((size_t)gemm_dense_pairs_reserved(T, d_in, CR) * CR * sizeof(float));
-    L.part_dy = take((size_t)gemm_dense_pairs_reserved(T, d_out, NR) * NR * sizeof(float));
-    // whole pairs of 8-token blocks, 3072 bytes each: less than 192 T + 3072
-    L.dgs = take((size_t)T * 192 + 3072);
-    const int slices = wgrad_slices_reserved(T, d_in);
+    auto again = [&]() { shared = off > shared ? off : shared; off = 0; };
+    auto pairs = [&](int K, int rows) {
+        return reserve ? (size_t)gemm_dense_pairs_reserved(T, K, rows) : (size_t)gemm_dense_splits(T, K, rows) * T;
+    };
+    L.part_x = take(pairs(d_in, CR) * CR * sizeof(float));
+    L.part_dy = take(pairs(d_out, NR) * NR * sizeof(float));
+    again();
+    if (reserve) L.dxpart = take(gemm_few_tile_bytes(T, d_out, d_in));
+    else if (const int S = dx ? gemm_few_tile_splits(T, d_out, d_in) : 0) L.dxpart = take((size_t)S * T * d_in * sizeof(float));
+    else L.dxpart = take(dx ? gemm_splitk_bytes(T, d_out, d_in, true) : 0);
+    again();
+    const int slices = wgrad_plan(T, d_in).most_slices;
     L.wpart = take((size_t)slices * d_in * kBwdNP * sizeof(float));
     L.bpart = take((size_t)slices * kBwdNP * sizeof(float));
+    again();
+    off = shared;
+    // whole pairs of 8-token blocks, 3072 bytes each: less than 192 T + 3072
+    L.dgs = take((size_t)T * 192 + 3072);
     L.ext = (int)align_up((size_t)NR + 3 * kBwdNP, 64);
-    L.hx = take((size_t)T * L.ext * sizeof(uint16_t));
-    L.xt = take((size_t)d_in * L.ext * sizeof(uint16_t));
-    L.dxpart = take(gemm_few_tile_bytes(T, d_out, d_in));
+    L.hx = take(dx || reserve ? (size_t)T * L.ext * sizeof(uint16_t) : 0);
+    L.xt = take(dx || reserve ? (size_t)d_in * L.ext * sizeof(uint16_t) : 0);
     L.total = off;
     return L;
 }
@@ -501,7 +510,7 @@ hipError_t launch_gate_backward(const void* x, const void* dy, const void* wcat,
     if ((dx != nullptr) && (!A || !W_gate || !W_t)) return hipErrorInvalidValue;
     if (!gate_backward_applies(T, d_in, d_out, N, r, true) || k < 1 || k > kMaxTopK || k > N)
         return hipErrorInvalidValue;
-    const GateBackwardLayout L = gate_backward_layout(T, d_in, d_out, N, r);
+    const GateBackwardLayout L = gate_backward_layout(T, d_in, d_out, N, r, dx != nullptr, false);
     const int CR = prep_wcat_rows(N, r), NR = N * r;
     const float* part_x = part_x_given != nullptr ? part_x_given : reinterpret_cast<float*>(ws + L.part_x);
     float* part_dy = reinterpret_cast<float*>(ws + L.part_dy);

@@ -197,14 +197,13 @@ int gemm_multi_fit(int T, int d_in, int rows) {
 }
 
 int64_t gemm_dense_pairs_reserved(int T, int d_in, int rows) {
-    // splits times tokens of each form of dense_tile, as bounds that grow with the tokens: 256 / tiles, 384 / tiles + 1/2
-    const int64_t most = (int64_t)dense_split_bounds(8, ceil_div(d_in, kGemmBK)) * T;
-    const int wide = dense_wide_blocks(rows), few = wide <= 4 || T < 4096 ? T : 4096;
-    int64_t pairs = T;
-    for (const int64_t form : {256 * 128 / ceil_div(rows, 160), 256 * 128 / ceil_div(rows, 32 * wide),
-                               ceil_div(384 * 128, ceil_div(rows, 128)) + (few + 1) / 2})
-        if (form > pairs) pairs = form;
-    return pairs < most ? pairs : most;
+    // the splits change at multiples of 128 tokens; above 384 row tiles there is one
+    int64_t pairs = (int64_t)gemm_dense_splits(T, d_in, rows) * T;
+    for (int t = 128; t < T && t <= 384 * 128; t += 128) {
+        const int64_t p = (int64_t)gemm_dense_splits(t, d_in, rows) * t;
+        if (p > pairs) pairs = p;
+    }
+    return pairs;
 }
 
 template <int MB, int NB, int D, int EPI>
@@ -259,15 +258,10 @@ static int gemm_multi_row_blocks(int T) {
 // 18.9, 200 x 1024 -> 4096 19.4 and 17.7, 96 x 4096 -> 4096 18.7 and 18.2; 1531 x 1024 -> 1024 20.1 and 21.1.
 static int multi_cap(int T, int col_tiles) { return 256 / (ceil_div(T, 256) * (col_tiles > 0 ? col_tiles : 1)); }   // 256 CUs
 
-int gemm_multi_splits_reserved(int T, int col_tiles, int S) {
+int gemm_multi_splits(int T, int col_tiles, int S, int nk, int64_t rows) {
     const int cap = multi_cap(T, col_tiles);
     if (T <= 128 && cap < 2 && S >= 3) return S;
-    return S > cap ? (cap > 0 ? cap : 1) : S;
-}
-
-int gemm_multi_splits(int T, int col_tiles, int S, int nk, int64_t rows) {
-    if (T <= 128 && multi_cap(T, col_tiles) < 2 && S >= 3) return S;
-    S = gemm_multi_splits_reserved(T, col_tiles, S);
+    if (S > cap) S = cap > 0 ? cap : 1;
     const float per_tile = 0.2f + 0.07f * (float)gemm_multi_row_blocks(T), per_split = 0.45e-6f * 4.f * (float)T * (float)rows;
     int best = S;
     float least = 0.f;
@@ -340,11 +334,12 @@ int gemm_few_tile_splits(int T, int d_in, int d_out) {
 }
 
 size_t gemm_few_tile_bytes(int T, int d_in, int d_out) {
-    int64_t pairs = 0;   // tokens times splits of any batch of up to T tokens: what fits changes at multiples of 128
-    const int last = 256 * 128 / ceil_div(d_out, 128);
-    for (int t = T < last ? T : last; t > 64; t = (t - 1) / 128 * 128) {
-        const int64_t p = (int64_t)gemm_multi_splits_reserved(t, ceil_div(d_out, 128), gemm_multi_fit(t, d_in, d_out)) * t;
-        pairs = p > pairs ? p : pairs;
+    int64_t pairs = 0;   // tokens times splits of any batch of up to T tokens: the splits change downwards inside 32 tokens only
+    const int col_tiles = ceil_div(d_out, 128), most = 256 * 128 / col_tiles, last = T < most ? T : most;
+    for (int t = 64; t < last; t += 32) {
+        const int S = gemm_multi_splits(t + 1, col_tiles, gemm_multi_fit(t + 1, d_in, d_out), ceil_div(d_in, kGemmBK), d_out);
+        const int64_t p = S < 2 ? 0 : (int64_t)S * (t + 32 < last ? t + 32 : last);
+        if (p > pairs) pairs = p;
     }
     const size_t few = gemm_splitk_bytes(T < 64 ? T : 64, d_in, d_out, true), many = (size_t)pairs * d_out * sizeof(float);
     return few > many ? few : many;

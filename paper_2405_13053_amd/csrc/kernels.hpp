@@ -55,7 +55,6 @@ hipError_t launch_gate_topk(const float* partials, int KS, const float* bias, in
 constexpr int kRouteDenseMaxTokens = 8192, kWcatMaxRows = 640;
 bool route_dense_applies(int T, int d_in, int N, int r, bool bf16);
 bool lora_dense_applies(int T, int d_in, int N, int r, int k, bool bf16);   // lora_forward, whose routing is given
-size_t route_dense_part_bytes(int T, int d_in, int N, int r, bool bf16);  // what the products of any batch of up to T tokens take
 hipError_t launch_route_dense_products(const void* x, const void* wcat, int T, int d_in, int N, int r, float* part,
                                        hipStream_t stream);
 // the expand operand for a routing that is given (r % 8 == 0): part[S][T][N*r] = x * A_i of every adapter
@@ -73,10 +72,9 @@ int gemm_multi_fit(int T, int d_in, int rows);
 // few-tile split-K launches over several matrices (col_tiles: the 128-column tiles of all of them, rows: their rows): S
 // capped to one workgroup per CU, or for few tokens to two, and of what that leaves the number that costs the least
 int gemm_multi_splits(int T, int col_tiles, int S, int nk, int64_t rows);
-// What a workspace reserves: the two above come and go with the token count, and a workspace for the largest batch holds the
-// smaller ones.  Bound of tokens times splits of the products of any batch of up to T tokens, and the splits that fit.
+// What a workspace reserves: the splits come and go with the token count, and a workspace for the largest batch holds the smaller
+// ones.  The most tokens times splits that the products of any batch of up to T tokens have.
 int64_t gemm_dense_pairs_reserved(int T, int d_in, int rows);
-int gemm_multi_splits_reserved(int T, int col_tiles, int S);
 hipError_t launch_gemm_dense_splitk(const void* x, const void* Wcat, int T, int d_in, int rows, float* partial,
                                     hipStream_t stream);
 
@@ -194,7 +192,7 @@ hipError_t launch_decode_tail_group(const DecodeMember* mem, int G, const SplitP
 constexpr int kGateBackwardMaxTokens = 65536;
 struct GateBackwardLayout { size_t part_x, part_dy, dgs, wpart, bpart, hx, xt, dxpart, total; int ext; };
 bool gate_backward_applies(int T, int d_in, int d_out, int N, int r, bool bf16);
-GateBackwardLayout gate_backward_layout(int T, int d_in, int d_out, int N, int r);
+GateBackwardLayout gate_backward_layout(int T, int d_in, int d_out, int N, int r, bool dx, bool reserve);
 hipError_t launch_gate_backward(const void* x, const void* dy, const void* wcat, const void* B, const float* bias,
                                 const int32_t* idx_in, const float* w_in, const int32_t* labels, float beta, int T,
                                 int d_in, int d_out, int N, int r, int k, float scale, float* dW_gate, float* dbias,

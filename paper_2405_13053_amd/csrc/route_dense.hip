@@ -202,14 +202,6 @@ bool lora_dense_applies(int T, int d_in, int N, int r, int k, bool bf16) {
     return r % 8 == 0 && route_dense_applies(T, d_in, N, r, bf16) && (N * r <= 256 ? T <= 4096 || k >= 2 : T <= 1024);
 }
 
-size_t route_dense_part_bytes(int T, int d_in, int N, int r, bool bf16) {
-    const int CR = prep_wcat_rows(N, r);
-    if (!bf16 || CR > kWcatMaxRows || T <= 64) return 0;
-    const size_t all = (size_t)gemm_dense_pairs_reserved(T, d_in, CR) * CR;
-    const size_t lora = (size_t)gemm_dense_pairs_reserved(T, d_in, N * wcat_rank(r)) * N * wcat_rank(r);   // lora_forward: no gate rows
-    return (all > lora ? all : lora) * sizeof(float);
-}
-
 hipError_t launch_route_dense_products(const void* x, const void* wcat, int T, int d_in, int N, int r, float* part,
                                        hipStream_t stream) {
     return launch_gemm_dense_splitk(x, wcat, T, d_in, prep_wcat_rows(N, r), part, stream);

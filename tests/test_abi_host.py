@@ -92,6 +92,21 @@ def test_a_workspace_for_more_tokens_holds_fewer(d_in, d_out, N, r, k, Ts):
     assert sizes == sorted(sizes)
 
 
+@pytest.mark.parametrize("T,d_in,d_out,r,layer,train", [(4096, 4096, 4096, 8, 43.7, 57.5), (2000, 4096, 4096, 8, 37.7, 47.5),
+                                                        (300, 4096, 4096, 8, 30.4, 27.5), (8192, 4096, 14336, 8, 64.0, 72.0)])
+def test_a_workspace_reserves_what_calls_write(T, d_in, d_out, r, layer, train):
+    """In MB: what one call of any batch of up to T tokens writes, not the largest of each region over all of them (86.1 and 119.3
+    MB for the first)."""
+    assert m.workspace_bytes(T, d_in, d_out, 28, r, 2, "bf16") <= layer * 1e6
+    assert m.gate_backward_workspace_bytes(T, d_in, d_out, 28, r, 2, "bf16") <= train * 1e6
+    group = m.group_workspace_bytes((d_out, 1024, 1024), T, d_in, 28, r, 2, "bf16")
+    assert group <= max(layer, 46.3) * 1e6
+    # the largest of what the calls of that many and fewer tokens write, beside the routing and the packed operands
+    written = max(sum(w for _, _, _, w in m.workspace_regions(t, d_in, d_out, 28, r, 2, "bf16", False))
+                  for t in (1, 64, 96, 160, 256, 300, 512, 704, 768, 1024, 2048, 4096, 8192) if t <= T)
+    assert written <= m.workspace_bytes(T, d_in, d_out, 28, r, 2, "bf16") <= 1.35 * written
+
+
 @pytest.mark.parametrize("d_in,d_out,r,fewer,more", [(4096, 4096, 8, 2049, 2177), (5120, 5120, 8, 2030, 2177),
                                                      (4096, 1024, 16, 1174, 1281)])
 def test_a_backward_workspace_for_more_tokens_holds_fewer(d_in, d_out, r, fewer, more):
