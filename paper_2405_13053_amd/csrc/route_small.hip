@@ -54,6 +54,8 @@ constexpr int kTailThreads = 64;
 // U: K splits whose loads are in flight.  The loads of a round are unconditional, those past the last split repeat it, so U
 // follows the number of splits of the launch.  Whole calls with eight always, and so: 300 x 4096 -> 4096 (three splits) 26.6
 // and 26.1 us, 1531 x 4096 -> 1024 rank 16 (three) 38.4 and 37.7, 64 x 5120 -> 13824 (two) 36.6 and 36.2.
+// Ranks off 8, 16, 32 and 64 have two of them, since one and two splits with four in flight lose 0.1 to 0.3 us: rank 12, four always and
+// so, 1 x 4096 -> 1024 (eight splits) 12.6 and 11.9, 8384 -> 264 (16) 15.5 and 14.2, 200 x 4096 -> 4096 top-8 (six) 37.1 and 36.2.
 // R8: a slot's shrink values take 8 * R8 lanes.  NP: N padded to 32 or 64.  WHOLE: the rank is 8 * R8; otherwise it is less, and
 // the rows of B past it are left out.
 template <int R8, int U, int NP, bool WHOLE>
@@ -214,7 +216,7 @@ hipError_t launch_decode_tail_group(const DecodeMember* mem, int G, const SplitP
     };
     auto by_splits = [&](auto r8, auto np) {
         constexpr int R8 = decltype(r8)::value, NP = decltype(np)::value;
-        if (r != 8 * R8) return go(decode_tail_kernel<R8, 4, NP, false>);
+        if (r != 8 * R8) return plan.S <= 4 ? go(decode_tail_kernel<R8, 4, NP, false>) : go(decode_tail_kernel<R8, 8, NP, false>);
         if (plan.S == 1) return go(decode_tail_kernel<R8, 1, NP, true>);
         if (plan.S == 2) return go(decode_tail_kernel<R8, 2, NP, true>);
         if (plan.S <= 4) return go(decode_tail_kernel<R8, 4, NP, true>);
