@@ -64,13 +64,18 @@ def test_gate_backward_matches_oracle(shape, beta):
     assert float(dl.sum(dim=1).abs().max()) <= 1e-5 * max(1.0, float(dl.abs().max()))
 
 
-# The input gradient with its contraction (d_out) split: 64 tokens on the two-slot kernel, two and more splits on each tile height,
-# two workgroups per CU, the extension behind a last split that is shorter than the others.
+# The input gradient with its contraction (d_out) split: 64 tokens on the two-slot kernel, then each height of the split tiles (96 to
+# 256 rows in steps of 32), 96 and 128 rows with one and with two workgroups per CU, the extension behind a last split that is as long
+# as the others or shorter.
 SPLIT_DX_SHAPES = [
     LS(64, 256, 2048, 28, 8, 2, 2.0, "bf16", "zipf", "T=64-two-slot"),
     LS(65, 256, 4096, 28, 8, 2, 2.0, "bf16", "uniform", "T=65-96-rows"),
     LS(128, 16640, 4096, 5, 8, 1, 2.0, "bf16", "uniform", "T=128-two-per-CU"),
+    LS(80, 16640, 4096, 5, 8, 1, 2.0, "bf16", "uniform", "T=80-two-per-CU"),
+    LS(110, 512, 4160, 28, 8, 2, 2.0, "bf16", "uniform", "T=110-128-rows"),
     LS(150, 512, 4160, 28, 16, 2, 2.0, "bf16", "zipf", "T=150-short-last-split"),
+    LS(180, 512, 4160, 28, 8, 2, 2.0, "bf16", "uniform", "T=180-192-rows"),
+    LS(210, 512, 4160, 7, 32, 3, 2.0, "bf16", "zipf", "T=210-224-rows"),
     LS(300, 1024, 4096, 28, 8, 2, 2.0, "bf16", "uniform", "T=300-160-rows"),
     LS(450, 1024, 4096, 7, 32, 3, 2.0, "bf16", "zipf", "T=450-256-rows"),
 ]

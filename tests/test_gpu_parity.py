@@ -370,10 +370,30 @@ def test_linear_forward_matches_oracle(shape):
     _check_layer(shape, seed=41)
 
 
-# bucketed sequence (more than 32 adapters): chunks of 16 tokens up to 2048 tokens, of 64 above; up to 8 K slices and more
-@pytest.mark.parametrize("T,d_in,N,k", [(65, 136, 64, 8), (95, 4616, 33, 3), (2047, 72, 64, 4), (2048, 136, 40, 1), (2049, 136, 64, 4)])
-def test_bucketing_chunk_sizes(T, d_in, N, k):
-    _check_layer(LS(T, d_in, 136, N, 8, k, 2.0, "bf16", "zipf", "chunks"), seed=63, rows="sample")
+def _sequence(T, d_in, d_out, N, r, k, dtype="bf16"):
+    """Which launches a layer call takes, from what they write."""
+    regs = {name for name, _, _, written in m.workspace_regions(T, d_in, d_out, N, r, k, dtype, True) if written > 0}
+    if dtype == "f32":
+        return "fp32"
+    return next(name for region, name in (("gpart", "decode"), ("spart", "few-tile"), ("dpart", "dense"), ("partials", "bucketed"))
+                if region in regs)
+
+
+# bucketed sequence (more than 640 rows of Wcat, and more than a few output tiles, too few inputs for two K splits or too many rows of
+# B): chunks of 16 tokens up to 2048 tokens, of 64 above; one K slice of 512 inputs and ten
+@pytest.mark.parametrize("T,d_in,d_out,N,r,k", [
+    (65, 136, 136, 64, 8, 8), (2047, 72, 136, 64, 8, 4), (2048, 136, 136, 64, 8, 4), (2049, 136, 136, 64, 8, 4),
+    (1600, 4616, 136, 64, 32, 3), (95, 4616, 7048, 64, 64, 8), (30, 4616, 8264, 64, 64, 8)])
+def test_bucketing_chunk_sizes(T, d_in, d_out, N, r, k):
+    assert _sequence(T, d_in, d_out, N, r, k) == "bucketed"
+    _check_layer(LS(T, d_in, d_out, N, r, k, 2.0 if r == 8 else 0.5, "bf16", "zipf", "chunks"), seed=63, rows="sample")
+
+
+# as many adapters, but few tiles, or up to 640 rows of Wcat
+@pytest.mark.parametrize("T,d_in,N,k,sequence", [(95, 4616, 33, 3, "few-tile"), (2048, 136, 40, 1, "dense")])
+def test_more_than_32_adapters_without_lists(T, d_in, N, k, sequence):
+    assert _sequence(T, d_in, 136, N, 8, k) == sequence
+    _check_layer(LS(T, d_in, 136, N, 8, k, 2.0, "bf16", "zipf", "no-lists"), seed=63, rows="sample")
 
 
 # fp32 layers with few adapters in one launch: tiles of 16 tokens and 16 columns, K in steps of 16 over four wavefronts
@@ -385,12 +405,13 @@ def test_fp32_layer_in_one_launch(T, d_in, d_out, N, r, k):
     _check_layer(LS(T, d_in, d_out, N, r, k, 2.0, "f32", "zipf", "f32-one-launch"), seed=62)
 
 
-# fp32 routing is one sum in one order, whichever launches run: gate_topk, the layer in one launch, the layer in two or three
+# two workgroups per CU, and at most one, have a kernel each
 @pytest.mark.parametrize("T,d_in,d_out,N,r,k", [(129, 40, 520, 4, 8, 2), (512, 256, 256, 4, 8, 2), (256, 248, 256, 4, 8, 4)])
 def test_fp32_layer_in_one_launch_around_one_workgroup_per_cu(T, d_in, d_out, N, r, k):
     _check_layer(LS(T, d_in, d_out, N, r, k, 2.0, "f32", "uniform", "f32-two-per-CU"), seed=71)
 
 
+# fp32 routing is one sum in one order, whichever launches run: gate_topk, the layer in one launch, the layer in two or three
 @pytest.mark.parametrize("d_in,d_out,N,r,k", [
     (256, 256, 4, 8, 2), (8, 8, 1, 1, 1), (256, 256, 16, 2, 8), (72, 264, 16, 4, 3), (512, 8, 4, 8, 1), (328, 136, 2, 16, 2),
     (64, 904, 7, 8, 3), (168, 40, 1, 64, 1), (248, 40, 11, 2, 4), (200, 64, 3, 8, 3), (128, 256, 16, 2, 2), (256, 264, 1, 32, 1),
@@ -545,10 +566,12 @@ def test_dense_route_path_matches_oracle_and_bucketed_path(shape):
 
 
 # Widths that are no multiple of 64 (nor of 128, the decode launch's K step) on every launch sequence: inputs of one chunk, layers
-# with fewer K tiles than splits, a partial tile in a split of its own, outputs beyond 256 row tiles.
+# with fewer K tiles than splits, a partial tile in a split of its own, outputs beyond 256 row tiles, each height of the few-tile form's
+# tiles (96 to 256 rows in steps of 32; 96 and 128 also with two workgroups per CU).
 @pytest.mark.parametrize("T,d_in,d_out,N,r,k", [
     (1, 8, 8, 28, 8, 2), (64, 24, 136, 28, 16, 1), (49, 320, 2920, 28, 16, 1), (17, 824, 1848, 7, 32, 3), (5, 72, 33000, 28, 8, 2),
     (65, 8, 136, 28, 8, 2), (300, 1000, 264, 28, 8, 2), (130, 1032, 136, 28, 16, 2), (200, 4616, 520, 28, 8, 8), (97, 776, 16392, 28, 8, 2),
+    (80, 776, 16392, 28, 8, 2), (66, 1032, 264, 28, 8, 2), (110, 1032, 264, 28, 16, 2), (180, 584, 264, 28, 8, 2), (450, 1096, 520, 28, 8, 2),
     (1100, 1048, 4104, 12, 16, 3), (2500, 136, 2056, 28, 8, 2), (4500, 264, 136, 28, 16, 3), (9000, 72, 264, 28, 8, 1)])
 def test_layer_of_any_width(T, d_in, d_out, N, r, k):
     _check_layer(LS(T, d_in, d_out, N, r, k, 2.0, "bf16", "zipf", "any-width"), seed=64, rows="all" if T <= 300 else "sample")
@@ -701,8 +724,9 @@ def test_masked_adapters_and_a_token_of_nan(T, d_in, d_out, N, k, dtype):
 
 GRAPH_SHAPES = [
     LS(33, 1024, 520, 28, 8, 2, 2.0, "bf16", "uniform", "graph-decode"),
-    LS(333, 1024, 520, 28, 8, 2, 2.0, "bf16", "zipf", "graph-dense-route"),
-    LS(400, 1024, 520, 28, 16, 2, 2.0, "bf16", "uniform", "graph-bucketed"),
+    LS(333, 1024, 520, 28, 8, 2, 2.0, "bf16", "zipf", "graph-few-tile"),
+    LS(400, 1024, 520, 28, 16, 2, 2.0, "bf16", "uniform", "graph-few-tile-r16"),
+    LS(1300, 320, 2056, 64, 32, 4, 0.5, "bf16", "zipf", "graph-bucketed"),
     # dense routing in front of the fused GEMM (too many output tiles for the split-K form)
     LS(2500, 512, 2056, 28, 8, 2, 2.0, "bf16", "uniform", "graph-dense-route-fused-gemm"),
     LS(64, 256, 256, 4, 8, 2, 2.0, "f32", "uniform", "graph-fp32-one-launch"),
@@ -772,6 +796,7 @@ def test_many_tokens_small_layer_sampled_rows(r, N, path):
     bucketed path (1094 bucketing chunks, whole-K shrink), rank 8 through the dense routing products (320 rows of
     Wcat: every batch size), rank 16 through whichever of the two the tile count of the products selects."""
     shape = LS(70000, 256, 264, N, r, 2, 2.0, "bf16", "zipf", f"T=70000-{path}")
+    assert path == "rank16" or _sequence(70000, 256, 264, N, r, 2) == path
     _check_layer(shape, seed=49, rows="sample")
 
 
@@ -803,7 +828,7 @@ def _group_case(T, d_in, d_outs, N, r, k, routing, seed):
     (33, 512, (8200, 4104, 3080), 28, 8, 2, "uniform", True),    # 132 row tiles: runs that go on from member to member
     (5, 512, (16392, 8200, 8200), 28, 16, 2, "zipf", True),      # 274: runs longer than a row tile, two Wcat tiles cut
     (33, 1024, (520, 136), 28, 8, 2, "uniform", False),          # not packed: member by member
-    (300, 512, (256, 264), 28, 8, 2, "uniform", True),           # a few hundred tokens: three launches with 128-row tiles
+    (300, 512, (256, 264), 28, 8, 2, "uniform", True),           # a few hundred tokens: two launches with 160-row tiles
     (16, 512, (264,), 28, 8, 2, "zipf", True),                   # a group of one is the single-layer call
     (128, 1024, (520, 136, 136), 28, 8, 2, "uniform", True),     # q/k/v-like at T = 128
     (200, 1024, (776, 776), 12, 16, 3, "zipf", True),            # gate/up-like, r = 16, bias, ragged token tile
@@ -834,14 +859,21 @@ def test_group_call_matches_oracle_and_single_calls(T, d_in, d_outs, N, r, k, ro
 
 # ------------------------------------------------ temperature (App. A.6) and the top-1 strategy (App. A.1)
 # one shape per launch sequence of the whole-layer call: decode (two launches), a few hundred tokens with the
-# projection split along K, dense routing in front of the fused GEMM, bucketed (rank 12 is no multiple of 8), fp32
+# projection split along K, dense routing in front of the fused GEMM, bucketed (2240 rows of Wcat), fp32
 SEQUENCE_SHAPES = [
     LS(48, 1024, 520, 28, 8, 2, 2.0, "bf16", "uniform", "decode"),
-    LS(200, 1024, 1096, 28, 8, 2, 2.0, "bf16", "zipf", "mid-split"),
-    LS(2500, 512, 2056, 28, 8, 2, 2.0, "bf16", "uniform", "dense-route"),
-    LS(700, 512, 264, 28, 12, 2, 2.0, "bf16", "zipf", "bucketed"),
+    LS(200, 1024, 1096, 28, 8, 2, 2.0, "bf16", "zipf", "few-tile"),
+    LS(700, 512, 264, 28, 12, 2, 2.0, "bf16", "zipf", "few-tile-r12"),
+    LS(2500, 512, 2056, 28, 8, 2, 2.0, "bf16", "uniform", "dense"),
+    LS(1300, 320, 2056, 64, 32, 4, 0.5, "bf16", "zipf", "bucketed"),
     LS(90, 264, 136, 6, 8, 2, 2.0, "f32", "uniform", "fp32"),
 ]
+
+
+@pytest.mark.parametrize("shape", SEQUENCE_SHAPES, ids=lambda s: s.name)
+def test_each_sequence_shape_takes_its_sequence(shape):
+    for k in (1, shape.k):   # top-1 and what the temperature is tested with
+        assert shape.name.startswith(_sequence(shape.T, shape.d_in, shape.d_out, shape.N, shape.r, k, shape.dtype))
 
 
 @pytest.mark.parametrize("tau", [15.0, 20.0, 30.0])
