@@ -465,32 +465,29 @@ static WgradPlan wgrad_plan(int T, int d_in) {
     return {slice_chunks > 2 * kWgRing ? 4 : 2, slice_chunks, n};
 }
 
-// One after the other in the same place: the products until the kernel of d_logits has read them, the input gradient's K splits, the
-// weight gradient's slices.  reserve: room for any batch of up to T tokens, else what a call of T tokens writes (dx: with the input
-// gradient).
+// One after the other in the same place: the products until the kernel of d_logits has read them, and the input gradient's K splits.
+// (The weight gradient's slices have one of their own: behind the products the launch that adds them took 3.6 us, so 2.5, 600 x 2048.)
+// reserve: room for any batch of up to T tokens, else what a call of T tokens writes (dx: with the input gradient).
 GateBackwardLayout gate_backward_layout(int T, int d_in, int d_out, int N, int r, bool dx, bool reserve) {
     GateBackwardLayout L{};
     const int CR = prep_wcat_rows(N, r), NR = N * r;
-    size_t off = 0, shared = 0;
+    size_t off = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off = align_up(off + bytes, 256); return o; };
-    auto again = [&]() { shared = off > shared ? off : shared; off = 0; };
     auto pairs = [&](int K, int rows) {
         return reserve ? (size_t)gemm_dense_pairs_reserved(T, K, rows) : (size_t)gemm_dense_splits(T, K, rows) * T;
     };
-    L.part_x = take(pairs(d_in, CR) * CR * sizeof(float));
+    size_t dx_bytes = 0;
+    if (reserve) dx_bytes = gemm_few_tile_bytes(T, d_out, d_in);
+    else if (const int S = dx ? gemm_few_tile_splits(T, d_out, d_in) : 0) dx_bytes = (size_t)S * T * d_in * sizeof(float);
+    else if (dx) dx_bytes = gemm_splitk_bytes(T, d_out, d_in, true);
+    L.dxpart = L.part_x = take(pairs(d_in, CR) * CR * sizeof(float));
     L.part_dy = take(pairs(d_out, NR) * NR * sizeof(float));
-    again();
-    if (reserve) L.dxpart = take(gemm_few_tile_bytes(T, d_out, d_in));
-    else if (const int S = dx ? gemm_few_tile_splits(T, d_out, d_in) : 0) L.dxpart = take((size_t)S * T * d_in * sizeof(float));
-    else L.dxpart = take(dx ? gemm_splitk_bytes(T, d_out, d_in, true) : 0);
-    again();
+    if (off < dx_bytes) off = align_up(dx_bytes, 256);
+    // whole pairs of 8-token blocks, 3072 bytes each: less than 192 T + 3072
+    L.dgs = take((size_t)T * 192 + 3072);
     const int slices = wgrad_plan(T, d_in).most_slices;
     L.wpart = take((size_t)slices * d_in * kBwdNP * sizeof(float));
     L.bpart = take((size_t)slices * kBwdNP * sizeof(float));
-    again();
-    off = shared;
-    // whole pairs of 8-token blocks, 3072 bytes each: less than 192 T + 3072
-    L.dgs = take((size_t)T * 192 + 3072);
     L.ext = (int)align_up((size_t)NR + 3 * kBwdNP, 64);
     L.hx = take(dx || reserve ? (size_t)T * L.ext * sizeof(uint16_t) : 0);
     L.xt = take(dx || reserve ? (size_t)d_in * L.ext * sizeof(uint16_t) : 0);
