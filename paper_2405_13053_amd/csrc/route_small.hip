@@ -160,9 +160,14 @@ __global__ __launch_bounds__(kTailThreads) void decode_tail_kernel(int T, int N,
         for (int j = 0; j < ngroups; ++j) {   // (slot, 8 rows) pieces; the next piece's loads go out before this one's FMAs
             u32x4 bnext[8];
             const bool more = j + 1 < ngroups;
-            const int e0 = slot * RL + q0, rows = WHOLE ? 8 : r - q0;
-            q0 += 8;
-            if (q0 >= r) { q0 = 0; ++slot; }
+            const int e0 = WHOLE ? j * 8 : slot * RL + q0, rows = WHOLE ? 8 : r - q0;
+            if constexpr (WHOLE) {
+                slot = (j + 1) / R8;
+                q0 = (j + 1) % R8 * 8;
+            } else {
+                q0 += 8;
+                if (q0 >= r) { q0 = 0; ++slot; }
+            }
             if (more) load_rows(s0 + slot, q0, bnext);
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
