@@ -76,8 +76,9 @@ static hipError_t launch_ring(K kern, const GemmArgs& a, int lds_bytes, int spli
     return hipGetLastError();
 }
 
+static bool ragged(const GemmArgs& a) { return a.d_in % kGemmBK != 0; }
 // Nothing behind the whole K tiles: kBehindNone.  Splits of K share one kernel, also where only the last of them has more.
-static bool whole_tiles(const GemmArgs& a) { return a.d_in % kGemmBK == 0 && a.ext_k == 0; }
+static bool whole_tiles(const GemmArgs& a) { return !ragged(a) && a.ext_k == 0; }
 
 // One workgroup per (MB*32) x (NB*32) output tile; the output is written, or added to, by the kernel itself.
 template <int MB, int NB, int D>
@@ -85,10 +86,16 @@ static hipError_t launch_tiles(GemmArgs a, hipStream_t stream) {
     a.tiles_m = ceil_div(a.T, MB * 32);
     a.tiles_n = ceil_div(a.d_out, NB * 32);
     constexpr int smem = gemm_ring_lds_bytes<MB, NB, D>();
-    if (a.accumulate) return launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiAccumulate, kBehindLook>, a, smem, 1, stream);
-    if (a.topk_idx != nullptr) return launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, kBehindLook>, a, smem, 1, stream);
-    return whole_tiles(a) ? launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, kBehindNone>, a, smem, 1, stream)
-                          : launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, kBehindAny>, a, smem, 1, stream);
+    if (a.accumulate) {   // an expand alone
+        if (ragged(a)) return hipErrorInvalidValue;
+        return launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiAccumulate, kBehindExtLook>, a, smem, 1, stream);
+    }
+    if (a.ext_k == 0)
+        return ragged(a) ? launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, kBehindPart>, a, smem, 1, stream)
+                         : launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, kBehindNone>, a, smem, 1, stream);
+    if (ragged(a)) return launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, kBehindAnyLook>, a, smem, 1, stream);
+    return a.topk_idx != nullptr ? launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, kBehindExtLook>, a, smem, 1, stream)
+                                 : launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, kBehindExt>, a, smem, 1, stream);
 }
 
 // Few tiles and no extension: base projections of few tokens.
@@ -97,8 +104,8 @@ static hipError_t launch_small_tiles(GemmArgs a, hipStream_t stream) {
     a.tiles_m = ceil_div(a.T, MB * 32);
     a.tiles_n = ceil_div(a.d_out, NB * 32);
     constexpr int smem = gemm_ring_lds_bytes<MB, NB, D>();
-    return whole_tiles(a) ? launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, kBehindNone>, a, smem, 1, stream)
-                          : launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, kBehindAny>, a, smem, 1, stream);
+    return ragged(a) ? launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, kBehindPart>, a, smem, 1, stream)
+                     : launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, kEpiStore, kBehindNone>, a, smem, 1, stream);
 }
 
 // The same without the ring: any size.
@@ -117,21 +124,22 @@ static hipError_t launch_plain(GemmArgs a, hipStream_t stream) {
 static hipError_t launch_skinny(GemmArgs a, hipStream_t stream) {
     constexpr int smem = gemm_lds_bytes<1, 1>();
     hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(&gemm_mfma_kernel<1, 1>), smem);
-    if (e == hipSuccess) e = ensure_lds_limit(reinterpret_cast<const void*>(&gemm_mfma_dma_kernel<1, 1>), smem);
+    const auto dma_kernel = ragged(a) ? &gemm_mfma_dma_kernel<1, 1, true> : &gemm_mfma_dma_kernel<1, 1, false>;
+    if (e == hipSuccess) e = ensure_lds_limit(reinterpret_cast<const void*>(dma_kernel), smem);
     if (e != hipSuccess) return e;
     a.tiles_m = ceil_div(a.T, 64);
     a.tiles_n = ceil_div(a.d_out, 64);
     const bool dma = dma_ok(a, 64, 64);
     if (dma && a.partial != nullptr) {
         const int nsplit = a.splits + (a.ext_k > 0 ? 1 : 0);
-        gemm_mfma_dma_kernel<1, 1><<<dim3(a.tiles_m * a.tiles_n, nsplit), 256, smem, stream>>>(a);
+        dma_kernel<<<dim3(a.tiles_m * a.tiles_n, nsplit), 256, smem, stream>>>(a);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         const size_t n8 = (size_t)a.T * a.d_out / 8;
         gemm_splitk_reduce_kernel<<<(unsigned)((n8 + 255) / 256), 256, 0, stream>>>(a.partial, nsplit, a.T, a.d_out,
                                                                                    a.out, a.accumulate);
     } else if (dma) {
-        gemm_mfma_dma_kernel<1, 1><<<a.tiles_m * a.tiles_n, 256, smem, stream>>>(a);
+        dma_kernel<<<a.tiles_m * a.tiles_n, 256, smem, stream>>>(a);
     } else {
         gemm_mfma_kernel<1, 1><<<a.tiles_m * a.tiles_n, 256, smem, stream>>>(a);
     }
@@ -206,13 +214,14 @@ int64_t gemm_dense_pairs_reserved(int T, int d_in, int rows) {
     return pairs;
 }
 
-template <int MB, int NB, int D, int EPI>
-static hipError_t launch_dense(GemmArgs a, hipStream_t stream) {   // fp32 split-K tiles; tiles_n is the caller's
+// fp32 split-K tiles; tiles_n is the caller's.  MORE: what there may be behind the whole K tiles
+template <int MB, int NB, int D, int EPI, int MORE = kBehindPart>
+static hipError_t launch_dense(GemmArgs a, hipStream_t stream) {
     a.tiles_m = ceil_div(a.T, MB * 32);
     if (a.tiles_n == 0) a.tiles_n = ceil_div(a.d_out, NB * 32);
     constexpr int smem = gemm_ring_lds_bytes<MB, NB, D>();
     return whole_tiles(a) ? launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, EPI, kBehindNone>, a, smem, a.splits, stream)
-                          : launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, EPI, kBehindAny>, a, smem, a.splits, stream);
+                          : launch_ring(&gemm_mfma_ring_kernel<MB, NB, D, EPI, MORE>, a, smem, a.splits, stream);
 }
 
 hipError_t launch_gemm_dense_splitk(const void* x, const void* Wcat, int T, int d_in, int rows, float* partial,
@@ -225,7 +234,7 @@ hipError_t launch_gemm_dense_splitk(const void* x, const void* Wcat, int T, int 
     a.splits = tile.splits;
     a.tiles_per_split = ceil_div(ceil_div(d_in, kGemmBK), a.splits);
     switch (tile.nb) {
-        case 4: return launch_dense<4, 4, 2, kEpiPartial>(a, stream);
+        case 4: return launch_dense<4, 4, 2, kEpiPartial, kBehindAny>(a, stream);   // one kernel with the few tiles of launch_multi_tiles
         case 5: return launch_dense<4, 5, 3, kEpiPartialThrough>(a, stream);
         case 6: return launch_dense<4, 6, 3, kEpiPartialThrough>(a, stream);
         case 7: return launch_dense<4, 7, 3, kEpiPartialThrough>(a, stream);
@@ -281,14 +290,14 @@ constexpr int64_t kWriteThroughWeights = 48 << 20;
 
 template <int EPI>
 static hipError_t launch_multi_tiles(const GemmArgs& a, bool two, hipStream_t stream) {
-    if (two) return a.T <= 96 ? launch_dense<3, 4, 2, EPI>(a, stream) : launch_dense<4, 4, 2, EPI>(a, stream);
+    if (two) return a.T <= 96 ? launch_dense<3, 4, 2, EPI, kBehindAny>(a, stream) : launch_dense<4, 4, 2, EPI, kBehindAny>(a, stream);
     switch (gemm_multi_row_blocks(a.T)) {
-        case 3: return launch_dense<3, 4, 5, EPI>(a, stream);
-        case 4: return launch_dense<4, 4, 4, EPI>(a, stream);
-        case 5: return launch_dense<5, 4, 4, EPI>(a, stream);
-        case 6: return launch_dense<6, 4, 3, EPI>(a, stream);
-        case 7: return launch_dense<7, 4, 3, EPI>(a, stream);
-        default: return launch_dense<8, 4, 3, EPI>(a, stream);
+        case 3: return launch_dense<3, 4, 5, EPI, kBehindAny>(a, stream);
+        case 4: return launch_dense<4, 4, 4, EPI, kBehindAny>(a, stream);
+        case 5: return launch_dense<5, 4, 4, EPI, kBehindAny>(a, stream);
+        case 6: return launch_dense<6, 4, 3, EPI, kBehindAny>(a, stream);
+        case 7: return launch_dense<7, 4, 3, EPI, kBehindAny>(a, stream);
+        default: return launch_dense<8, 4, 3, EPI, kBehindAny>(a, stream);
     }
 }
 
@@ -372,15 +381,18 @@ hipError_t gemm_init_kernels() {
     lim(&gemm_mfma_kernel<4, 4>, gemm_lds_bytes<4, 4>());
     lim(&gemm_mfma_kernel<2, 2>, gemm_lds_bytes<2, 2>());
     lim(&gemm_mfma_kernel<1, 1>, gemm_lds_bytes<1, 1>());
-    lim(&gemm_mfma_dma_kernel<1, 1>, gemm_lds_bytes<1, 1>());
+    lim(&gemm_mfma_dma_kernel<1, 1, false>, gemm_lds_bytes<1, 1>());
+    lim(&gemm_mfma_dma_kernel<1, 1, true>, gemm_lds_bytes<1, 1>());
 #define METEORA_RING(MB, NB, D, EPI, BEHIND) lim(&gemm_mfma_ring_kernel<MB, NB, D, EPI, BEHIND>, gemm_ring_lds_bytes<MB, NB, D>())
 #define METEORA_BOTH(MB, NB, D, EPI)              \
     METEORA_RING(MB, NB, D, EPI, kBehindNone);    \
-    METEORA_RING(MB, NB, D, EPI, kBehindAny)
-#define METEORA_TILES(MB, NB, D)                       \
-    METEORA_BOTH(MB, NB, D, kEpiStore);                \
-    METEORA_RING(MB, NB, D, kEpiStore, kBehindLook);   \
-    METEORA_RING(MB, NB, D, kEpiAccumulate, kBehindLook)
+    METEORA_RING(MB, NB, D, EPI, kBehindPart)
+#define METEORA_TILES(MB, NB, D)                          \
+    METEORA_BOTH(MB, NB, D, kEpiStore);                   \
+    METEORA_RING(MB, NB, D, kEpiStore, kBehindExt);       \
+    METEORA_RING(MB, NB, D, kEpiStore, kBehindExtLook);   \
+    METEORA_RING(MB, NB, D, kEpiStore, kBehindAnyLook);   \
+    METEORA_RING(MB, NB, D, kEpiAccumulate, kBehindExtLook)
     METEORA_TILES(8, 8, 2);
     METEORA_TILES(8, 4, 3);
     METEORA_TILES(7, 4, 3);
@@ -397,9 +409,11 @@ hipError_t gemm_init_kernels() {
     METEORA_BOTH(4, 7, 3, kEpiPartialThrough);
     METEORA_BOTH(4, 8, 2, kEpiPartialThrough);
     METEORA_BOTH(4, 9, 2, kEpiPartialThrough);
-#define METEORA_PARTIAL(MB, NB, D)           \
-    METEORA_BOTH(MB, NB, D, kEpiPartial);    \
-    METEORA_BOTH(MB, NB, D, kEpiPartialThrough)
+#define METEORA_PARTIAL(MB, NB, D)                          \
+    METEORA_RING(MB, NB, D, kEpiPartial, kBehindNone);         \
+    METEORA_RING(MB, NB, D, kEpiPartial, kBehindAny);          \
+    METEORA_RING(MB, NB, D, kEpiPartialThrough, kBehindNone);  \
+    METEORA_RING(MB, NB, D, kEpiPartialThrough, kBehindAny)
     METEORA_PARTIAL(4, 4, 2);
     METEORA_PARTIAL(3, 4, 2);
     METEORA_PARTIAL(3, 4, 5);

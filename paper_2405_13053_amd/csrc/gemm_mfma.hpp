@@ -342,15 +342,21 @@ __device__ __forceinline__ PartTile part_tile(int d_in, int wave, int lane) {
     return t;
 }
 
-// main_bytes: those of the main operand's matrix (with a piece's offset still below 2^32, see dma_ok)
+// main_bytes: those of the main operand's matrix (with a piece's offset still below 2^32, see dma_ok).  PART, EXT: which there may be.
+template <bool PART, bool EXT>
 __device__ __forceinline__ void dma_piece_behind(bf16_t* lds_tile, const DmaOperand& main, uint32_t main_bytes, const DmaOperand& ext,
                                                  const PartTile& t, int kt, int j, int wave) {
-    const uint32_t voff = kt < 0 ? (t.mine ? main.voff : main_bytes) : ext.voff;
-    const uint32_t soff = kt < 0 ? main.piece_step * (uint32_t)j + t.offset
-                                 : ext.piece_step * (uint32_t)j + (uint32_t)kt * (kGemmBK * 2);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(
-        kt < 0 ? main.rsrc : ext.rsrc, (__attribute__((address_space(3))) void*)(lds_tile + (j * 4 + wave) * 8 * kGemmBK), 16, voff,
-        (int)soff, 0, 0);
+    if constexpr (!PART) {
+        dma_piece(lds_tile, ext, kt, j, wave);
+    } else {
+        const bool of_main = !EXT || kt < 0;
+        const uint32_t voff = of_main ? (t.mine ? main.voff : main_bytes) : ext.voff;
+        const uint32_t soff = of_main ? main.piece_step * (uint32_t)j + t.offset
+                                      : ext.piece_step * (uint32_t)j + (uint32_t)kt * (kGemmBK * 2);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            of_main ? main.rsrc : ext.rsrc, (__attribute__((address_space(3))) void*)(lds_tile + (j * 4 + wave) * 8 * kGemmBK), 16,
+            voff, (int)soff, 0, 0);
+    }
 }
 
 // Map a workgroup id to an output tile: ids are dealt round-robin to the 8 XCDs, so each XCD
@@ -476,7 +482,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x16 (&acc)[M
     }
 }
 
-template <int MI, int NI>
+// PART: the inputs may end in a partial K tile
+template <int MI, int NI, bool PART>
 __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(const GemmArgs a) {
     constexpr int BM = MI * 64, BN = NI * 64;
     constexpr int PX = BM / 32, PW = BN / 32;   // pieces per wavefront per tile
@@ -501,7 +508,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(const GemmArgs a) {
             for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.f;
 
     // this workgroup's share of the contraction: whole K tiles [kt0, kt0 + nk_main), the partial one, and/or the extension
-    int kt0 = 0, nk_main = a.d_in / kGemmBK, nk_part = a.d_in % kGemmBK != 0 ? 1 : 0;
+    int kt0 = 0, nk_main = a.d_in / kGemmBK, nk_part = PART && a.d_in % kGemmBK != 0 ? 1 : 0;
     int nk_ext = a.ext_k > 0 ? a.ext_stride / kGemmBK : 0;
     if (a.partial != nullptr) {
         const int split = blockIdx.y;
@@ -529,8 +536,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(const GemmArgs a) {
         bf16_t* xs = smem + slot * kBufElems;
         if constexpr (decltype(is_ext)::value) {
             const int kt = it - nk_main - nk_part;
-            if (i < PX) dma_piece_behind(xs, ox, x_bytes, oh, part, kt, i, wave);
-            else dma_piece_behind(xs + BM * kGemmBK, ow, w_bytes, ob, part, kt, i - PX, wave);
+            if (i < PX) dma_piece_behind<PART, true>(xs, ox, x_bytes, oh, part, kt, i, wave);
+            else dma_piece_behind<PART, true>(xs + BM * kGemmBK, ow, w_bytes, ob, part, kt, i - PX, wave);
         } else {
             if (i < PX) dma_piece(xs, ox, kt0 + it, i, wave);
             else dma_piece(xs + BM * kGemmBK, ow, kt0 + it, i - PX, wave);
@@ -865,17 +872,19 @@ __device__ __forceinline__ void for_each_phase(std::integer_sequence<int, PH...>
     (f(std::integral_constant<int, PH>{}), ...);
 }
 
-// BEHIND: which K tiles there may be behind the whole ones of the main operands: none, any (see PartTile), or any, and the kernel
-// looks for empty tiles of the extension.  Code that is not run costs a short call with cold weights 0.8 us (65 x 1024 -> 4096 11.5
-// with the look against 10.6), and two more buffer resources and the tests of what there is cost the others 0.3 to 0.5% and more:
-// whole calls, any and none, 300 x 4096 -> 4096 25.1 and 24.7 us, 1531 x 4096 -> 1024 of rank 16 37.2 and 36.4, 3000 x 5120 -> 5120
-// from its parts 170.4 and 169.1, a training step of 4096 x 4096 -> 4096 263.9 and 261.7.
-constexpr int kBehindNone = 0, kBehindAny = 1, kBehindLook = 2;
+// BEHIND: which K tiles there may be behind the whole ones of the main operands: the partial one (see PartTile), those of the
+// extension, and whether the kernel looks for empty ones among these.  Code that is not run costs a short call with cold weights 0.8 us
+// (65 x 1024 -> 4096 11.5 with the look against 10.6), and two more buffer resources and the tests of what there is cost the others 0.3 to
+// 0.5% and more: whole calls, any and none, 300 x 4096 -> 4096 25.1 and 24.7 us, 1531 x 4096 -> 1024 of rank 16 37.2 and 36.4, 3000 x
+// 5120 -> 5120 from its parts 170.4 and 169.1, a training step of 4096 x 4096 -> 4096 263.9 and 261.7.  Calls that are mostly extension
+// feel the choice between its operands and the partial tile's in every request, with it and without: 1846 x 512 -> 856, 64 adapters of rank
+// 32 (8 K tiles and 32 of the extension) 53.9 and 51.2, 137 x 256 -> 4096 40.7 and 40.1, lora_forward of 40 x 624 -> 5120 20.8 and 20.6.
+constexpr int kBehindNone = 0, kBehindPart = 1, kBehindExt = 2, kBehindAny = 3, kBehindExtLook = 6, kBehindAnyLook = 7;
 
 template <int MB, int NB, int D, int EPI, int BEHIND>
 __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in) {
     GemmArgs a = a_in;
-    constexpr bool LOOK = BEHIND == kBehindLook, ANY = BEHIND != kBehindNone;
+    constexpr bool PART = (BEHIND & 1) != 0, EXT = (BEHIND & 2) != 0, LOOK = (BEHIND & 4) != 0, ANY = BEHIND != kBehindNone;
     constexpr int BM = MB * 32, BN = NB * 32;   // 2 x 2 wavefronts of MB x NB blocks of 16 x 16
     constexpr int PX = BM / 32, PW = BN / 32;   // pieces per wavefront per tile
     static_assert((NB % 2 == 0 || MB % 2 == 0) && D >= 2 && (D - 1) * (PX + PW) < 64, "whole 2 x 2 micro-blocks; vmcnt holds 6 bits");
@@ -907,8 +916,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
     }
 
     // this workgroup's share of the contraction: whole K tiles [kt0, kt0 + nk_main), the partial one, and/or the extension
-    int kt0 = 0, nk_main = a.d_in / kGemmBK, nk_part = ANY && a.d_in % kGemmBK != 0 ? 1 : 0;
-    int nk_ext = ANY && a.ext_k > 0 ? a.ext_stride / kGemmBK : 0;
+    int kt0 = 0, nk_main = a.d_in / kGemmBK, nk_part = PART && a.d_in % kGemmBK != 0 ? 1 : 0;
+    int nk_ext = EXT && a.ext_k > 0 ? a.ext_stride / kGemmBK : 0;
     if (a.partial != nullptr) {
         kt0 = (int)blockIdx.y * a.tiles_per_split;
         if (nk_main < kt0 || nk_main >= kt0 + a.tiles_per_split) nk_part = 0;
@@ -930,11 +939,11 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
     auto wslot = [&](int it) { return smem + D * kXElems + (it % (D + 1)) * kWElems; };
     // piece i of the x-like / W-like operand of whole K tile kt, or of tile kt of those behind the whole ones
     auto request_x = [&](bf16_t* slot, int kt, int i, auto is_ext) {
-        if constexpr (decltype(is_ext)::value) dma_piece_behind(slot, ox, x_bytes, oh, part, kt, i, wave);
+        if constexpr (decltype(is_ext)::value) dma_piece_behind<PART, EXT>(slot, ox, x_bytes, oh, part, kt, i, wave);
         else dma_piece(slot, ox, kt, i, wave);
     };
     auto request_w = [&](bf16_t* slot, int kt, int i, auto is_ext) {
-        if constexpr (decltype(is_ext)::value) dma_piece_behind(slot, ow, w_bytes, ob, part, kt, i, wave);
+        if constexpr (decltype(is_ext)::value) dma_piece_behind<PART, EXT>(slot, ow, w_bytes, ob, part, kt, i, wave);
         else dma_piece(slot, ow, kt, i, wave);
     };
     auto request_tile = [&](int it, int kt, auto is_ext) {
@@ -963,11 +972,11 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
     // padding): that k-step is all it gets
     bool half_last = nk_ext > 0 && ((a.ext_k - 1) % kGemmBK) < kGemmBK / 2 && (ext_left >> (nk_ext - 1) & 1) != 0;
     nk_ext = __popcll(ext_left);
-    if (nk_ext == 0) half_last = nk_part > 0 && part.columns <= kGemmBK / 2;
+    if (PART && nk_ext == 0) half_last = nk_part > 0 && part.columns <= kGemmBK / 2;
     const int nk = nk_main + nk_part + nk_ext;
     // tiles are requested in order: the one that comes next behind the whole ones, see PartTile
     auto next_ext = [&]() {
-        if (nk_part > 0) {
+        if (PART && nk_part > 0) {
             nk_part = 0;
             return -1;
         }
