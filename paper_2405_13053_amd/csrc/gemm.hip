@@ -156,7 +156,11 @@ static hipError_t launch_skinny(GemmArgs a, hipStream_t stream) {
 //     While they make two K splits or more.
 //   - beyond 2048 tokens, where x is read again for every column tile: the narrowest tile of up to 320 columns that takes the
 //     rows in as few column tiles as 320 does (544 rows: 288).
-// and otherwise, as where K ends the splits before the CUs are full, 128 x 128 tiles, two workgroups per CU.
+// and otherwise, as where K ends the splits before the CUs are full, 128 x 128 tiles, two workgroups per CU.  So also while those are few
+// (up to 176, or 256 of up to four K tiles) and their splits are shorter than 16 K tiles: a narrower tile is through its K tiles sooner, and
+// more CUs work on it.  Gradients of the gate alone, 320 rows, 128 x 128 and 128 x 160: 2048 inputs 450 tokens 23.2 and 25.3, 1200 28.3 and
+// 29.7, 1500 31.1 and 28.8; 4096 inputs 300 tokens 25.0 and 25.6, 1200 31.7 and 30.6; 6144 inputs 800 31.4 and 32.0, 1000 33.2 and 31.4;
+// 14336 inputs 65 tokens 34.3 and 33.2.
 // Whole calls, 128 x 128 up to 4096 tokens and 128 x 320 above with ordinary stores, as it was, and so (written through, see kWriteThrough;
 // with ordinary stores), us: layers of rank 8, 4096 -> 4096 1000 tokens 49.3, 48.4 (48.0), 4096 117.6, 116.0 (117.9), 5000 181.6,
 // 176.4 (176.3), 8192 227.2, 221.8 (223.1); 3000 x 5120 -> 5120 144.1, 136.0 (137.5), 4096 x 14336 -> 1024 193.7, 183.0
@@ -177,12 +181,15 @@ static int dense_wide_blocks(int rows) { return ceil_div(ceil_div(rows, ceil_div
 
 static DenseTile dense_tile(int T, int d_in, int rows) {
     const int nk = ceil_div(d_in, kGemmBK), row_tiles = ceil_div(T, 128), four = ceil_div(rows, 128), five = ceil_div(rows, 160);
+    const DenseTile narrow = {4, dense_split_bounds((384 + row_tiles * four / 2) / (row_tiles * four), nk)};
+    const int part = ceil_div(nk, narrow.splits);
+    if (part < 16 && row_tiles * four * narrow.splits <= (part <= 4 ? 256 : 176)) return narrow;
     auto fits = [&](int tiles) { return dense_split_bounds(256 / tiles, nk) == dense_split_bounds(256 / tiles, 32); };   // K does not bind
     if (five * 160 <= four * 128 && 2 * row_tiles * five <= 256 && (T <= 4096 || nk <= 96) && fits(row_tiles * five))
         return {5, dense_split_bounds(256 / (row_tiles * five), nk)};
     const int nb = dense_wide_blocks(rows), tiles = row_tiles * ceil_div(rows, 32 * nb);
     if (nb > 4 && (T > 4096 || (T > 2048 && fits(tiles)))) return {nb, dense_split_bounds(256 / tiles, nk)};
-    return {4, dense_split_bounds((384 + row_tiles * four / 2) / (row_tiles * four), nk)};
+    return narrow;
 }
 
 bool gemm_dense_splitk_ok(int T, int d_in, int rows) {
