@@ -231,7 +231,7 @@ meteora_status meteora_linear_forward_packed(const void* x, const void* W, const
  * split-K sums may run in another order).  For decode-sized batches (T <= 64) and for batches of a few
  * hundred tokens whose members have few output tiles in all (at most 320 tiles of 128 x 128, routing
  * products included), with bf16, packed weights and at most 4 members, the whole group runs in two
- * (decode) or three launches instead of that many per layer; otherwise the members run one after the other.
+ * launches instead of that many per layer; otherwise the members run one after the other.
  *   members  host array of G descriptors; every pointer in it is a device pointer with the meaning and
  *            alignment it has in meteora_linear_forward_packed (packed may be NULL: that member is then
  *            repacked into the workspace on every call, and the group runs member by member).
@@ -282,9 +282,10 @@ meteora_status meteora_linear_forward_group(const void* x, const meteora_group_m
  * these three may be NULL.  The gate term is computed from two-term bf16 splits (about 2^-16 of its size).
  * `packed` is the blob of meteora_pack_weights for these adapters; B is the stacked [N,r,d_out] tensor.
  * forward_ws (optional): the workspace in which meteora_linear_forward(_packed) ran on this same x, these
- * adapters and the same T, d_in, d_out, N, r, k, dt, not written to since.  For 64 < T <= 8192 that call leaves
- * its products of x with the packed gate and A operands there and they are read instead of being computed
- * again (one launch less); for other T the argument is ignored.  The caller vouches for the contents.
+ * adapters and the same T, d_in, d_out, N, r, k, dt, not written to since.  For T > 64 (beyond 8192 tokens where
+ * the call takes its dense routing products) it leaves its products of x with the packed gate and A operands there and
+ * they are read instead of being computed again (one launch less); otherwise the argument is ignored.  The caller vouches
+ * for the contents.
  * Limits: dt == METEORA_BF16, N <= 32, r % 8 == 0, d_in % 64 == 0, d_out % 64 == 0, 3*32 + N*r <= 640,
  * T <= 65536; otherwise METEORA_ERR_UNSUPPORTED (meteora_gate_backward_workspace_bytes returns 0).
  * All pointers but the host-side scalars are device memory; ws as for the other entry points.

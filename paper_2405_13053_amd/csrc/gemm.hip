@@ -459,7 +459,9 @@ hipError_t launch_gemm(const void* x, const void* W, int T, int d_in, int d_out,
         // with two slots up to 64 tokens and 128 x 128 above, W not in any cache, 1, 64, 96 and 300 tokens: 4096 -> 4096 45.0, 45.5,
         // 35.1, 30.2 and 15.5, 21.2, 17.7, 19.0 us; 14336 -> 4096 151, 152, 129, 104 and 48.1, 70.2, 57.2, 59.0; 4096 -> 1024 28.0, 28.3,
         // 24.2, 28.0 and 11.7, 12.6, 12.6, 12.6; 5120 -> 13824 58.3, 58.8, 59.9 and 25.5, 36.2, 45.0.  128-row tiles only: 200 x 5120 ->
-        // 5120 38.0, and 24.8 with 96 rows; rings as deep as LDS allows (9, 7, 6): 1 us slower at most sizes.
+        // 5120 38.0, and 24.8 with 96 rows; rings as deep as LDS allows (9, 7, 6): 1 us slower at most sizes.  Short contractions and W in
+        // cache gain too or are level (280 sizes of 64 to 4096 inputs, GPU alone): 200 x 128 -> 1024 4.1 and 3.2 cold, 4.1 and 3.1 warm,
+        // 96 x 512 -> 4096 7.9 and 5.1, 6.0 and 4.4, 1 x 256 -> 1024 3.4 and 3.5 warm.
         const int row_tiles_64 = 256 / ceil_div(d_out, 64);
         if (a.ext_k == 0 && !accumulate && row_tiles_64 > 0 && dma_ok(a, 128, 64)) {
             const int blocks = ceil_div(ceil_div(T, row_tiles_64), 32);

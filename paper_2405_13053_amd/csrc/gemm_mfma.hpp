@@ -1087,8 +1087,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_ring_kernel(const GemmArgs a_in
     };
     using Req0 = std::integral_constant<int, 0>;
     using Rt = std::integral_constant<int, -1>;
-    // A wavefront whose whole piece of the tile lies past the matrix (ragged last tile row or column: the third
-    // 128-column tile of the 320 routing products is half empty) moves its share of the operand tiles and keeps the
+    // A wavefront whose whole piece of the tile lies past the matrix (ragged last tile row or column: of few tokens the third
+    // 128-column tile of 320 routing products is half empty) moves its share of the operand tiles and keeps the
     // barriers, one per K tile like the others, and skips the fragment reads and the MFMAs.
     const bool idle = n0 + wn >= a.d_out || m0 + wm >= a.T;   // uniform per wavefront
     int it = 0;
