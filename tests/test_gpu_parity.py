@@ -370,6 +370,20 @@ def test_linear_forward_matches_oracle(shape):
     _check_layer(shape, seed=41)
 
 
+# adapters in chunks of tokens: 16 up to 2048 tokens, 64 above (33 adapters of a few tiles, and 40 of up to 640 rows of Wcat, without lists)
+@pytest.mark.parametrize("T,d_in,N,k", [(65, 136, 64, 8), (95, 4616, 33, 3), (2047, 72, 64, 4), (2048, 136, 40, 1), (2049, 136, 64, 4)])
+def test_bucketing_chunk_sizes(T, d_in, N, k):
+    _check_layer(LS(T, d_in, 136, N, 8, k, 2.0, "bf16", "zipf", "chunks"), seed=63, rows="sample")
+
+
+# bucketed sequence (more than 640 rows of Wcat, and more than a few output tiles, too few inputs for two K splits or too many rows of
+# B) at the same chunk sizes, and with more than one K slice of 512 inputs
+@pytest.mark.parametrize("T,d_in,d_out,N,r,k", [
+    (2048, 136, 136, 64, 8, 4), (1600, 4616, 136, 64, 32, 3), (95, 4616, 7048, 64, 64, 8), (30, 4616, 8264, 64, 64, 8)])
+def test_bucketed_sequence(T, d_in, d_out, N, r, k):
+    _check_layer(LS(T, d_in, d_out, N, r, k, 2.0 if r == 8 else 0.5, "bf16", "zipf", "chunks"), seed=63, rows="sample")
+
+
 def _sequence(T, d_in, d_out, N, r, k, dtype="bf16"):
     """Which launches a layer call takes, from what they write."""
     regs = {name for name, _, _, written in m.workspace_regions(T, d_in, d_out, N, r, k, dtype, True) if written > 0}
@@ -379,21 +393,17 @@ def _sequence(T, d_in, d_out, N, r, k, dtype="bf16"):
                 if region in regs)
 
 
-# bucketed sequence (more than 640 rows of Wcat, and more than a few output tiles, too few inputs for two K splits or too many rows of
-# B): chunks of 16 tokens up to 2048 tokens, of 64 above; one K slice of 512 inputs and ten
-@pytest.mark.parametrize("T,d_in,d_out,N,r,k", [
-    (65, 136, 136, 64, 8, 8), (2047, 72, 136, 64, 8, 4), (2048, 136, 136, 64, 8, 4), (2049, 136, 136, 64, 8, 4),
-    (1600, 4616, 136, 64, 32, 3), (95, 4616, 7048, 64, 64, 8), (30, 4616, 8264, 64, 64, 8)])
-def test_bucketing_chunk_sizes(T, d_in, d_out, N, r, k):
-    assert _sequence(T, d_in, d_out, N, r, k) == "bucketed"
-    _check_layer(LS(T, d_in, d_out, N, r, k, 2.0 if r == 8 else 0.5, "bf16", "zipf", "chunks"), seed=63, rows="sample")
-
-
-# as many adapters, but few tiles, or up to 640 rows of Wcat
-@pytest.mark.parametrize("T,d_in,N,k,sequence", [(95, 4616, 33, 3, "few-tile"), (2048, 136, 40, 1, "dense")])
-def test_more_than_32_adapters_without_lists(T, d_in, N, k, sequence):
-    assert _sequence(T, d_in, 136, N, 8, k) == sequence
-    _check_layer(LS(T, d_in, 136, N, 8, k, 2.0, "bf16", "zipf", "no-lists"), seed=63, rows="sample")
+# what the tests of a sequence run, here and below
+@pytest.mark.parametrize("sequence,shapes", [
+    ("decode", [(48, 1024, 520, 28, 8, 2), (48, 1024, 520, 28, 8, 1), (33, 1024, 520, 28, 8, 2)]),
+    ("few-tile", [(200, 1024, 1096, 28, 8, 2), (200, 1024, 1096, 28, 8, 1), (700, 512, 264, 28, 12, 2), (700, 512, 264, 28, 12, 1),
+                  (333, 1024, 520, 28, 8, 2), (400, 1024, 520, 28, 16, 2), (95, 4616, 136, 33, 8, 3)]),
+    ("dense", [(2500, 512, 2056, 28, 8, 2), (2500, 512, 2056, 28, 8, 1), (2048, 136, 136, 40, 8, 1), (70000, 256, 264, 28, 8, 2)]),
+    ("bucketed", [(1300, 320, 2056, 64, 32, 4), (1300, 320, 2056, 64, 32, 1), (65, 136, 136, 64, 8, 8), (2047, 72, 136, 64, 8, 4),
+                  (2048, 136, 136, 64, 8, 4), (2049, 136, 136, 64, 8, 4), (1600, 4616, 136, 64, 32, 3), (95, 4616, 7048, 64, 64, 8),
+                  (30, 4616, 8264, 64, 64, 8), (70000, 256, 264, 28, 12, 2)])])
+def test_each_shape_takes_its_sequence(sequence, shapes):
+    assert [_sequence(*s) for s in shapes] == [sequence] * len(shapes)
 
 
 # fp32 layers with few adapters in one launch: tiles of 16 tokens and 16 columns, K in steps of 16 over four wavefronts
@@ -724,11 +734,12 @@ def test_masked_adapters_and_a_token_of_nan(T, d_in, d_out, N, k, dtype):
 
 GRAPH_SHAPES = [
     LS(33, 1024, 520, 28, 8, 2, 2.0, "bf16", "uniform", "graph-decode"),
-    LS(333, 1024, 520, 28, 8, 2, 2.0, "bf16", "zipf", "graph-few-tile"),
-    LS(400, 1024, 520, 28, 16, 2, 2.0, "bf16", "uniform", "graph-few-tile-r16"),
-    LS(1300, 320, 2056, 64, 32, 4, 0.5, "bf16", "zipf", "graph-bucketed"),
+    LS(333, 1024, 520, 28, 8, 2, 2.0, "bf16", "zipf", "graph-dense-route"),
+    LS(400, 1024, 520, 28, 16, 2, 2.0, "bf16", "uniform", "graph-bucketed"),
     # dense routing in front of the fused GEMM (too many output tiles for the split-K form)
     LS(2500, 512, 2056, 28, 8, 2, 2.0, "bf16", "uniform", "graph-dense-route-fused-gemm"),
+    # the bucketed sequence (the two of 333 and 400 tokens are of the few-tile form)
+    LS(1300, 320, 2056, 64, 32, 4, 0.5, "bf16", "zipf", "graph-lists"),
     LS(64, 256, 256, 4, 8, 2, 2.0, "f32", "uniform", "graph-fp32-one-launch"),
 ]
 
@@ -796,7 +807,6 @@ def test_many_tokens_small_layer_sampled_rows(r, N, path):
     bucketed path (1094 bucketing chunks, whole-K shrink), rank 8 through the dense routing products (320 rows of
     Wcat: every batch size), rank 16 through whichever of the two the tile count of the products selects."""
     shape = LS(70000, 256, 264, N, r, 2, 2.0, "bf16", "zipf", f"T=70000-{path}")
-    assert path == "rank16" or _sequence(70000, 256, 264, N, r, 2) == path
     _check_layer(shape, seed=49, rows="sample")
 
 
@@ -859,21 +869,16 @@ def test_group_call_matches_oracle_and_single_calls(T, d_in, d_outs, N, r, k, ro
 
 # ------------------------------------------------ temperature (App. A.6) and the top-1 strategy (App. A.1)
 # one shape per launch sequence of the whole-layer call: decode (two launches), a few hundred tokens with the
-# projection split along K, dense routing in front of the fused GEMM, bucketed (2240 rows of Wcat), fp32
+# projection split along K, dense routing in front of the fused GEMM, the few-tile form again with rank 12, bucketed (2240 rows of
+# Wcat), fp32
 SEQUENCE_SHAPES = [
     LS(48, 1024, 520, 28, 8, 2, 2.0, "bf16", "uniform", "decode"),
-    LS(200, 1024, 1096, 28, 8, 2, 2.0, "bf16", "zipf", "few-tile"),
-    LS(700, 512, 264, 28, 12, 2, 2.0, "bf16", "zipf", "few-tile-r12"),
-    LS(2500, 512, 2056, 28, 8, 2, 2.0, "bf16", "uniform", "dense"),
-    LS(1300, 320, 2056, 64, 32, 4, 0.5, "bf16", "zipf", "bucketed"),
+    LS(200, 1024, 1096, 28, 8, 2, 2.0, "bf16", "zipf", "mid-split"),
+    LS(2500, 512, 2056, 28, 8, 2, 2.0, "bf16", "uniform", "dense-route"),
+    LS(700, 512, 264, 28, 12, 2, 2.0, "bf16", "zipf", "bucketed"),
+    LS(1300, 320, 2056, 64, 32, 4, 0.5, "bf16", "zipf", "lists"),
     LS(90, 264, 136, 6, 8, 2, 2.0, "f32", "uniform", "fp32"),
 ]
-
-
-@pytest.mark.parametrize("shape", SEQUENCE_SHAPES, ids=lambda s: s.name)
-def test_each_sequence_shape_takes_its_sequence(shape):
-    for k in (1, shape.k):   # top-1 and what the temperature is tested with
-        assert shape.name.startswith(_sequence(shape.T, shape.d_in, shape.d_out, shape.N, shape.r, k, shape.dtype))
 
 
 @pytest.mark.parametrize("tau", [15.0, 20.0, 30.0])
