@@ -24,9 +24,11 @@ struct FinishGroup {
         bf16_t* out;            // [T, d_out]
         int d_out;
         int tile0, gate_tile0;  // first row tile of its W and of its Wcat in the launch that wrote the K splits
+        int chunk0;             // first of its stretches of kTailThreads * 8 columns; of members not there: past the last one
     } m[kMaxDecodeGroup];
     SplitPlan plan;
-    int chunks;                 // stretches of kTailThreads * 8 columns per row of the widest member
+    int chunks;                 // per_xcd: stretches of all members; else those of the widest
+    int per_xcd;                // (stretch, token) pairs of an XCD, 0: member by member, the stretches of a token side by side
 };
 
 // K splits of row tile g of the launch (see SplitPlan)
@@ -51,6 +53,14 @@ __device__ __forceinline__ int split_count(const SplitPlan& p, int g) {
 // one wavefront per workgroup (measured: 64, 128 and 256 threads per workgroup time the same)
 constexpr int kTailThreads = 64;
 
+// A wavefront reads its stretch of k * r rows of B.  Workgroup ids are dealt round-robin to the XCDs, so with a token's stretches side
+// by side every XCD reads all of B where their number is odd, a half or a quarter where it is even: where that is more than
+// an XCD's L2 holds, and where members of a group differ in width, an XCD gets stretches of its own instead, one after the other
+// for all tokens.  Whole calls, side by side and so, us: 64 adapters of rank 32, top-4, 190 x 5120 -> 13824 142 and 96, twice 286
+// and 194, 300 x 2048 -> 5504 twice 146 and 98; 28 of rank 8 64 x 5120 -> 13824 36.0 and 34.6; q, k, v of 300 tokens 4096 inputs 37.5
+// and 33.5.  With less (1368 -> 1072, three stretches of which the last is short) 300 to 1000 tokens lose 2 to 4%.
+constexpr int64_t kTailL2Bytes = 4 << 20;
+
 // U: K splits whose loads are in flight.  The loads of a round are unconditional, those past the last split repeat it, so U
 // follows the number of splits of the launch.  Whole calls with eight always, and so: 300 x 4096 -> 4096 (three splits) 26.6
 // and 26.1 us, 1531 x 4096 -> 1024 rank 16 (three) 38.4 and 37.7, 64 x 5120 -> 13824 (two) 36.6 and 36.2.
@@ -66,12 +76,24 @@ __global__ __launch_bounds__(kTailThreads) void decode_tail_kernel(int T, int N,
     constexpr int SLOTS = 64 / RL;   // slots whose shrink values a wavefront holds at a time, one value per lane
     const int r = WHOLE ? RL : rank, groups = WHOLE ? R8 : (r + 7) / 8;   // groups of 8 rows of B per slot
     const int lane = threadIdx.x & 63;
-    const int chunk = blockIdx.x % fg.chunks;
-    int t = blockIdx.x / fg.chunks;
-    const int member = t / T;
-    t -= member * T;
+    int chunk, t, member = 0;
+    if (__builtin_expect(fg.per_xcd == 0, 1)) {   // uniform
+        chunk = blockIdx.x % fg.chunks;
+        t = blockIdx.x / fg.chunks;
+        if (t >= T) {
+            member = t / T;
+            t -= member * T;
+        }
+    } else {   // the token runs fastest, in eight equal parts
+        const int pair = (int)(blockIdx.x % 8) * fg.per_xcd + (int)(blockIdx.x / 8);
+        if (pair >= fg.chunks * T) return;
+        chunk = pair / T;
+        t = pair - chunk * T;
+#pragma unroll
+        for (int g = 1; g < kMaxDecodeGroup; ++g) member += chunk >= fg.m[g].chunk0 ? 1 : 0;
+        chunk -= fg.m[member].chunk0;
+    }
     const int d_out = fg.m[member].d_out, c8 = d_out / 8, S = fg.plan.S;
-    if (chunk * kTailThreads >= c8) return;   // a narrower member of the group: nothing in this stretch
     const int gi = chunk * kTailThreads + threadIdx.x;
     const bool active = gi < c8;              // lanes past the row's end work on its last columns and do not store
     const int c = (active ? gi : c8 - 1) * 8;
@@ -203,18 +225,23 @@ hipError_t launch_decode_tail_group(const DecodeMember* mem, int G, const SplitP
         return hipErrorInvalidValue;
     RouteGroup rg{};
     FinishGroup fg{};
-    int widest = 0, tiles = 0;
+    int tiles = 0, chunks = 0, widest = 0;
     for (int g = 0; g < G; ++g) {
         if (mem[g].d_out % 8 != 0 || mem[g].d_out < 8) return hipErrorInvalidValue;
         rg.m[g] = {mem[g].gpartial, mem[g].bias, mem[g].idx, mem[g].w};
         fg.m[g] = {mem[g].partial, (const bf16_t*)mem[g].B, (bf16_t*)mem[g].out, mem[g].d_out, tiles,
-                   tiles + ceil_div(mem[g].d_out, kSplitRows)};
+                   tiles + ceil_div(mem[g].d_out, kSplitRows), chunks};
         tiles += ceil_div(mem[g].d_out, kSplitRows) + ceil_div(gate_rows, kSplitRows);
-        widest = mem[g].d_out > widest ? mem[g].d_out : widest;
+        const int stretches = ceil_div(mem[g].d_out / 8, kTailThreads);
+        chunks += stretches;
+        widest = stretches > widest ? stretches : widest;
     }
+    for (int g = G; g < kMaxDecodeGroup; ++g) fg.m[g].chunk0 = chunks;
     fg.plan = plan;
-    fg.chunks = ceil_div(widest / 8, kTailThreads);
-    const unsigned grid = (unsigned)G * T * fg.chunks;
+    const bool apart = chunks != G * widest || (int64_t)chunks * kTailThreads * 8 * N * r * 2 > kTailL2Bytes;
+    fg.per_xcd = apart ? ceil_div(chunks * T, 8) : 0;
+    fg.chunks = fg.per_xcd > 0 ? chunks : widest;
+    const unsigned grid = fg.per_xcd > 0 ? (unsigned)fg.per_xcd * 8 : (unsigned)G * T * widest;
     auto go = [&](auto kern) {
         kern<<<grid, kTailThreads, 0, stream>>>(T, N, gate_rows, k, r, inv_temperature, scale, rg, fg);
         return hipGetLastError();

@@ -867,6 +867,16 @@ def test_group_call_matches_oracle_and_single_calls(T, d_in, d_outs, N, r, k, ro
         assert util.rel_max_err(out, single.to(torch.float64).cpu().numpy()) <= 2 * util.tol(sh)
 
 
+# The tail's stretches of 512 columns, dealt to the XCDs where B is more than 4 MB: pairs of stretch and token that are no multiple of
+# eight, fewer than eight, a short last stretch; both sides of 4 MB (18 and 19 stretches of 28 adapters of rank 8).
+@pytest.mark.parametrize("T,d_in,d_out,N,r,k", [
+    (1, 64, 2056, 64, 32, 4), (7, 136, 2056, 64, 32, 4), (64, 72, 2048, 64, 32, 2), (97, 1032, 2056, 64, 32, 2), (3, 64, 1032, 60, 36, 3),
+    (1, 64, 520, 64, 64, 2), (5, 64, 9216, 28, 8, 2), (5, 64, 9224, 28, 8, 2), (70, 1024, 9224, 28, 8, 2), (1, 520, 16392, 28, 16, 8)])
+def test_stretches_of_the_tail_by_xcd(T, d_in, d_out, N, r, k):
+    assert _sequence(T, d_in, d_out, N, r, k) == ("decode" if T <= 64 else "few-tile")
+    _check_layer(LS(T, d_in, d_out, N, r, k, 0.5 if r > 16 else 2.0, "bf16", "zipf", "stretches"), seed=74)
+
+
 # ------------------------------------------------ temperature (App. A.6) and the top-1 strategy (App. A.1)
 # one shape per launch sequence of the whole-layer call: decode (two launches), a few hundred tokens with the
 # projection split along K, dense routing in front of the fused GEMM, the few-tile form again with rank 12, bucketed (2240 rows of
