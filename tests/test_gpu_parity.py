@@ -867,6 +867,34 @@ def test_group_call_matches_oracle_and_single_calls(T, d_in, d_outs, N, r, k, ro
         assert util.rel_max_err(out, single.to(torch.float64).cpu().numpy()) <= 2 * util.tol(sh)
 
 
+# 64 adapters, 2048 -> 14336 twice: 260 column tiles and more.  The two-launch form lays out fp32 tiles and routing alone, which 24 MB
+# hold; member by member the expand operands need more, and the outputs are those of the single calls bit for bit.
+@pytest.mark.parametrize("T,k,r,two_launches", [(65, 4, 32, True), (120, 4, 32, True), (65, 8, 32, False), (68, 8, 32, False)])
+def test_a_group_of_more_tiles_than_CUs(T, k, r, two_launches):
+    d_in, d_out, N, bf = 2048, 14336, 64, torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(73)
+    rand = lambda std, *shape: torch.randn(*shape, generator=g, device="cuda") * std
+    x, members = rand(1.0, T, d_in).to(bf), []
+    for _ in range(2):
+        mb = {"W": rand(d_in ** -0.5, d_out, d_in).to(bf), "W_gate": rand(d_in ** -0.5, d_in, N), "gate_bias": None,
+              "A": rand(d_in ** -0.5, N, d_in, r).to(bf), "B": rand(r ** -0.5, N, r, d_out).to(bf)}
+        members.append(dict(mb, packed=m.pack_weights(mb["W_gate"], mb["A"], mb["B"])))
+    small = torch.empty(24 << 20, dtype=torch.uint8, device="cuda")
+    if two_launches:
+        res = m.linear_forward_group(x, members, k, 0.5, ws=small, return_routing=True)
+    else:
+        with pytest.raises(m.MeteoraError):
+            m.linear_forward_group(x, members, k, 0.5, ws=small)
+        res = m.linear_forward_group(x, members, k, 0.5, return_routing=True)
+    for mb, (out, idx, w) in zip(members, res):
+        ref, idx1, w1 = m.linear_forward(x, mb["W"], mb["W_gate"], None, mb["A"], mb["B"], k, 0.5, return_routing=True, packed=mb["packed"])
+        assert torch.equal(idx, idx1)
+        if two_launches:   # one rounding of an fp32 sum each, the single call rounds s * w * h to bf16 as well
+            assert util.rel_max_err(out, ref.to(torch.float64).cpu().numpy()) <= 2e-2
+        else:
+            assert torch.equal(out, ref) and torch.equal(w, w1)
+
+
 # The tail's stretches of 512 columns, dealt to the XCDs where B is more than 4 MB: pairs of stretch and token that are no multiple of
 # eight, fewer than eight, a short last stretch; both sides of 4 MB (18 and 19 stretches of 28 adapters of rank 8).
 @pytest.mark.parametrize("T,d_in,d_out,N,r,k", [
