@@ -24,10 +24,10 @@ bool shape_ok(int T, int d_in, int d_out, int N, int r, int k) {
     return T >= 0 && d_in >= 1 && d_out >= 1 && N >= 1 && r >= 1 && k >= 1 && k <= N;
 }
 
-// The decode tail reads k * r rows of B for every token, from L2 at about 18 TB/s; beyond some 0.5 to 1.3 GB (the more, the
+// The decode tail reads k * r rows of B for every token, from L2; beyond some 0.5 to 1.3 GB (the more, the
 // more inputs the other sequences gather for their shrink) the dense operand of every adapter and MFMAs are cheaper.  Top-8 of
-// 64 adapters, tail against bucketed, us: 4096 -> 14336 of rank 32 64 tokens (0.47 GB) 81.6 and 132, of rank 64 40 tokens (0.59) 107
-// and 98, 64 (0.94) 139 and 102; 4096 -> 4096 of rank 64 128 tokens (0.54) 55.8 and 75.6, 256 (1.1) 79.2 and 77.6, of rank 32
+// 64 adapters, tail against bucketed, us: 4096 -> 14336 of rank 32 64 tokens (0.47 GB) 68 and 78, of rank 64 40 tokens (0.59) 96
+// and 98, 64 (0.94) 124 and 102; 4096 -> 4096 of rank 64 128 tokens (0.54) 55.8 and 75.6, 256 (1.1) 79.2 and 77.6, of rank 32
 // 300 tokens (0.63) 61.6 and 70.5, 512 (1.1) 83.0 and 68.7; 14336 -> 4096 of rank 32 512 tokens (1.1) 163 and 211.
 bool expand_by_rows_applies(int T, int d_in, int d_out, int r, int k) {
     return 2.0 * T * k * r * d_out <= (T <= 64 ? 2.6e8 : 4e8) + 6e4 * d_in;
@@ -44,13 +44,16 @@ int expand_by_rows_tokens(int d_in, int d_out, int r, int k) {
 // 64 adapters of rank 32, top-4 and top-8, 4096 -> 4096, 1 token 61.3 and 89.1 against 23.2 and 33.7, 64 tokens 66.5 and 95.4
 // against 29.8 and 39.6, though 2240 more rows are streamed; 28 adapters of rank 12, 40.2 and 45.0 against 15.3 and 19.2.
 // The token count does not decide, so that a token is routed by the same sums in every decode batch: the rows of B that 64 tokens
-// read do (64 adapters of rank 64, top-8, 4096 -> 14336, tail and bucketed, 1 token 65 and 90, 30 tokens 87 and 97, 64 139 and 102).
-// Ranks 8, 16 and 32 of up to 640 rows of Wcat, at most 256 rows of B per token, take the tail whatever the outputs: 28 adapters of
-// rank 16, top-8, 64 tokens, bucketed and tail 512 -> 28672 46.0 and 39.0, 4096 -> 32704 107 and 86; 17 of rank 32 4096 -> 32704 32
-// tokens 104 and 83, 64 110 and 109, 512 -> 32704 45 and 47, 50 and 71.
+// read do (64 adapters of rank 64, top-8, 4096 -> 14336, tail and bucketed, 1 token 62 and 87, 30 tokens 82 and 95, 64 124 and 102).
+// Layers whose projection the bucketed sequence would split along K too (whole K tiles, 512 inputs and more, up to 32704 outputs), with
+// rank 8, 16 or 32 and up to 640 rows of Wcat, take the tail whatever they read: 28 adapters of rank 16, top-8, 64 tokens, bucketed
+// and tail 512 -> 28672 39.0 and 37.3, 4096 -> 32704 105 and 83; 17 of rank 32 4096 -> 32704 32 tokens 101 and 79, 64 107 and 103, but
+// 512 -> 32704 38.6 and 41.5, 44 and 63.  Wider ones lose more: 17 of rank 32, 64 tokens, 512 -> 65536 53 and 114.
 bool decode_fused_applies(int T, int d_in, int d_out, int N, int r, int k, bool bf16) {
     if (!bf16 || T > 64 || !gemm_decode_ok(d_in)) return false;
-    return ((r == 8 || r == 16 || r == 32) && prep_wcat_rows(N, r) <= kWcatMaxRows) || expand_by_rows_applies(64, d_in, d_out, r, k);
+    const bool split_too = d_in % 64 == 0 && d_in >= 512 && d_out <= 32704;
+    return (split_too && (r == 8 || r == 16 || r == 32) && prep_wcat_rows(N, r) <= kWcatMaxRows) ||
+           expand_by_rows_applies(64, d_in, d_out, r, k);
 }
 
 // Mid-sized batches whose 128 x 128 output tiles would leave most CUs idle (a few hundred tokens): the base
@@ -62,8 +65,9 @@ int dense_midsplit_splits(int T, int d_in, int d_out, int N, int r, int k, bool 
     // at T = 65, 36.1 against 60.1 at T = 512, 45.6 against 48.7 at T = 704, 47.6 against 48.8 at T = 768 for
     // 4096 -> 4096; 43.3 against 47.6 at T = 160 for 4096 -> 14336; 107 against 131 at T = 704 for 14336 -> 4096)
     // Above 640 rows of Wcat the bucketed sequence is the other choice: 64 adapters of rank 32, top-4, 4096 -> 4096 T = 65 29.2
-    // against 60.5, 200 36.6 against 61.7, 512 58.2 against 63.6; 14336 -> 4096 top-8 T = 300 123 against 170; but not with two
-    // workgroups per CU (4096 -> 14336 T = 65 91.0 against 84.9, 128 143 against 95.7).
+    // against 60.5, 200 36.6 against 61.7, 512 58.2 against 63.6; 14336 -> 4096 top-8 T = 300 123 against 170.  Two workgroups
+    // per CU, which lost while every XCD read all of B (4096 -> 14336 T = 65 91.0 against 84.9, 128 143 against 95.7; now 59 and 78
+    // against 82 and 92, top-8 76 and 108 against 84 and 94), are not taken.
     const int CR = prep_wcat_rows(N, r);
     if (!bf16 || T <= 64 || !gemm_multi_ok(T, d_in, CR) || !gemm_multi_ok(T, d_in, d_out)) return 0;
     const int col_tiles = ceil_div(d_out, 128) + ceil_div(CR, 128), fit = gemm_multi_fit(T, d_in, d_out);

@@ -128,10 +128,12 @@ def test_the_size_of_a_workspace_never_falls(d_in, d_out, N, r):
 
 @pytest.mark.parametrize("d_in,d_out,N,r,k,two_launches", [
     (4096, 14336, 64, 64, 8, False), (4096, 7704, 64, 64, 8, True), (4096, 7720, 64, 64, 8, False), (4096, 14336, 64, 32, 8, True),
-    (512, 28672, 28, 16, 8, True), (512, 65536, 17, 32, 8, True), (512, 65536, 7, 64, 7, False), (1024, 32704, 20, 20, 8, False)])
+    (512, 28672, 28, 16, 8, True), (512, 32704, 17, 32, 8, True), (512, 32712, 17, 32, 8, False), (512, 65536, 17, 32, 8, False),
+    (448, 28672, 28, 16, 8, False), (520, 28672, 28, 16, 8, False), (4096, 40960, 28, 8, 2, True), (512, 65536, 7, 64, 7, False),
+    (1024, 32704, 20, 20, 8, False)])
 def test_every_decode_batch_takes_the_same_sequence(d_in, d_out, N, r, k, two_launches):
     """The sequences add a token's logits in different orders: which of them runs does not depend on the tokens beside it.
-    With ranks 8, 16 and 32 of up to 640 rows of Wcat it is always the one of two launches, whatever the outputs."""
+    With ranks 8, 16 and 32 of up to 640 rows of Wcat it is the one of two launches for every layer that splits its projection anyway."""
     for T in range(1, 65):
         regs = {n: w for n, _, _, w in m.workspace_regions(T, d_in, d_out, N, r, k, "bf16", True)}
         assert (regs["gpart"] > 0) == two_launches and (regs["partials"] > 0) != two_launches, T
