@@ -753,7 +753,7 @@ int group_mid_splits(const int* d_out, const bool* packed, int G, int T, int d_i
     // With many rows of B per token the tail does not make up for a second round of tiles as long as all of K: 64 adapters, 4096 -> 14336
     // twice (260 column tiles), in two launches and member by member, top-8 of rank 32 65 tokens 175 and 169, 80 187 and 173; top-4
     // 80 136 and 172, 128 159 and 188; top-2 of rank 64 128 171 and 230.
-    if (k * r > 128 && col_tiles > 256) return 0;
+    if (cat_rows > kWcatMaxRows && k * r > 128 && col_tiles > 256) return 0;
     S = gemm_multi_splits(T, col_tiles, S, nk, rows);
     return S < 1 ? 1 : S;
 }
